@@ -26,8 +26,10 @@ on this chip, one with vector operands only at 2.5).
 The dynamic LDS segment starts at byte 0 (the kernel has no static LDS), so no base is added.
 
 Operation word: x = kind | a<<8 | b<<16 | c<<24, y = arg.  For a unitary, arg is the index of its
-matrix in execution order, so consecutive unitaries read consecutive 32-byte matrices and the
-next one can be prefetched (the table is padded by one entry for the last prefetch).
+matrix in execution order, so consecutive unitaries read consecutive 32-byte entries and the
+next one can be prefetched (the table is padded by one entry for the last prefetch).  An entry is
+either the eight floats of the matrix (c = 1) or the matrix without a scalar factor as a rotation
+between two phases (c = 0; see rot_pair), whose seventh word picks one of 16 instruction sequences.
 
 Fixed scalar registers (declared as clobbers; the text below names them s52..s56 and s68..s99,
 _renumbered() packs them into s36..s72, which leaves the compiler enough of the 96 scalar registers
@@ -62,7 +64,8 @@ def u_pair(a, b, variant="g"):
     operand issues at 4.2 cycles per wavefront on this chip, one with vector operands only at 2.5.
     Four interleaved chains; the last step of each overwrites an input that is dead by then.
     Variants leave out the products with
-    imaginary parts that are stored as exact zeros: "g" none (16 instructions), "a" m00i (14),
+    imaginary parts that are exact zeros: "g" none (16 instructions; the one the interpreter uses, for the
+    last unitary of a group and for shifted matrices), "a" m00i (14),
     "r" m00i and m01i (first row real, 12), "c" m00i and m10i (first column real, 12)."""
     ra, ia, rb, ib = "%%[r%d]" % a, "%%[i%d]" % a, "%%[r%d]" % b, "%%[i%d]" % b
     t = ["%[t0]", "%[t1]", "%[t2]", "%[t3]"]
@@ -103,6 +106,59 @@ def u_pair(a, b, variant="g"):
         fma(ra, "-%[m3]", ib, t[0]), fma(ia, "%[m2]", ib, t[1]),
         fma(rb, "-%[m7]", ib, t[2]), fma(ib, "%[m6]", ib, t[3]),
     ]
+
+
+# Forms of a factored unitary: which phases it has, and its core.
+FORMS = ("none", "before", "after", "both")
+CORES = ("c+", "c-", "s+", "s-")
+ROT_LENGTH = {"none": 6, "before": 7, "after": 7, "both": 10}
+
+
+def rot_pair(a, b, form, core):
+    """A unitary without its scalar factor, on the pair p (target bit 0) and q (target bit 1):
+    diag(1, e^iB) core diag(1, e^iA) with |A|, |B| <= pi/2.  The cores are the real rotations divided by
+    their larger entry,
+      c+- : p' = p + x q,     q' = y p +- q          s+- : p' = x p -+ q,    q' = p + y q,     |x|, |y| <= 1,
+    so each of the four real results takes one multiply-add.  A phase turns (re, im) of q by three shears
+    re += t im, im += s re, re += t im with t = -tan(A/2), s = sin A, in place.  4 + 3 (+ 3)
+    instructions where the matrix product takes 12 (14): the unitaries are 80 % of a pass's vector
+    instructions, and vector issue bounds the passes.
+    Entry: m0, m1 = t, s of A; m2, m3 = x, y; m4, m5 = t, s of B."""
+    ra, ia, rb, ib = "%%[r%d]" % a, "%%[i%d]" % a, "%%[r%d]" % b, "%%[i%d]" % b
+    t0, t1 = "%[t0]", "%[t1]"
+    m = ["%%[m%d]" % k for k in range(6)]
+    neg = lambda r: "-" + r
+
+    def fma(d, f, v, acc):
+        if d == acc:
+            return "v_fmac_f32 %s, %s, %s" % (d, f, v)
+        return "v_fma_f32 %s, %s, %s, %s" % (d, f, v, acc)
+
+    minus = core[1] == "-"
+    out = []
+    if form == "none":                     # q' waits in temporaries until p' has read q
+        qr, qi, nr, ni = rb, ib, t0, t1
+    elif form == "before":                 # the turned q sits in temporaries, q' goes to its place
+        out += [fma(t0, m[0], ib, rb), fma(t1, m[1], t0, ib), fma(t0, m[0], t1, t0)]
+        qr, qi, nr, ni = t0, t1, rb, ib
+    elif form == "after":                  # q' in temporaries, the shears bring it home
+        qr, qi, nr, ni = rb, ib, t0, t1
+    else:
+        out += [fma(t0, m[0], ib, rb), fma(t1, m[1], t0, ib), fma(t0, m[0], t1, t0)]
+        qr, qi, nr, ni = t0, t1, rb, ib
+    if core[0] == "c":
+        out += [fma(nr, m[3], ra, neg(qr) if minus else qr), fma(ni, m[3], ia, neg(qi) if minus else qi),
+                fma(ra, m[2], qr, ra), fma(ia, m[2], qi, ia)]
+    else:
+        out += [fma(nr, m[3], qr, ra), fma(ni, m[3], qi, ia),
+                fma(ra, m[2], ra, qr if minus else neg(qr)), fma(ia, m[2], ia, qi if minus else neg(qi))]
+    if form == "none":
+        out += ["v_mov_b32 %s, %s" % (rb, t0), "v_mov_b32 %s, %s" % (ib, t1)]
+    elif form == "after":
+        out += [fma(rb, m[4], t1, t0), fma(ib, m[5], rb, t1), fma(rb, m[4], ib, rb)]
+    elif form == "both":
+        out += [fma(rb, m[4], ib, rb), fma(ib, m[5], rb, ib), fma(rb, m[4], ib, rb)]
+    return out
 
 
 CHAIN_FORM = "move"     # "swap": every cycle by v_swap_b32
@@ -203,7 +259,7 @@ def gen(planes=2, perlane=False):
     # s[72:79] holds the matrix of the stream with index s56 (-1: none), s[70:71] its address; the
     # multiply sequences read vector copies, so the buffer is free for the next matrix of the stream
     # as soon as the copies are made.  Every scalar instruction here competes with the vector ones
-    # for issue slots, hence the short common path: two compares, the variant and bit dispatch.
+    # for issue slots, hence the short common path: three tests and one computed jump.
     emit(ALIGN)
     emit(lab("u") + ":")
     if perlane:
@@ -216,24 +272,47 @@ def gen(planes=2, perlane=False):
     emit("s_cmp_eq_u32 s81, s56")
     emit("s_cbranch_scc0 " + lab("uld"))
     emit(lab("uhave") + ":")
-    # pick the multiply sequence from the zeros the matrix builder stored
-    emit("s_cmp_lg_u32 s73, 0")
+    emit("s_bitcmp1_b32 s80, 24")                 # c: the entry is the matrix itself
     emit("s_cbranch_scc1 " + lab("ug"))
-    emit("s_cmp_eq_u32 s75, 0")
-    emit("s_cbranch_scc1 " + lab("ur"))
-    emit("s_cmp_eq_u32 s77, 0")
-    emit("s_cbranch_scc1 " + lab("uc"))
-    for variant in "argc":
-        emit(ALIGN)
-        emit(lab("u" + variant) + ":")
-        # the multiply sequences read vector registers only: stage the entries this variant uses
-        used = sorted({int(m) for ln in u_pair(0, 1, variant) for m in re.findall(r"%\[m(\d)\]", ln)})
-        for k in used:
-            emit("v_mov_b32 %%[m%d], s%d" % (k, 72 + k))
-        emit("s_add_u32 s70, s70, 32")            # prefetch the next matrix of the stream
+    # factored: jump through a table of branches, 4 * (4 * sequence + register bit) bytes into it
+    emit("s_lshl_b32 s84, s83, 2")
+    emit("s_add_u32 s84, s84, s78")
+    emit("s_add_u32 s84, s84, 12")                # the three instructions before the table
+    emit("s_getpc_b64 s[86:87]")
+    emit("s_add_u32 s86, s86, s84")
+    emit("s_addc_u32 s87, s87, 0")
+    emit("s_setpc_b64 s[86:87]")
+    for form in FORMS:
+        for core in range(len(CORES)):
+            for j in range(R):
+                emit("s_branch " + lab("r%s%d%d" % (form, core, j)))
+
+    def stream_next():
+        emit("s_add_u32 s70, s70, 32")            # prefetch the next entry of the stream
         emit("s_addc_u32 s71, s71, 0")
         emit("s_add_u32 s56, s56, 1")
         emit("s_load_dwordx8 s[72:79], s[70:71], 0x0")
+
+    for form in FORMS:
+        for core, name in enumerate(CORES):
+            used = sorted({int(m) for ln in rot_pair(0, 1, form, name) for m in re.findall(r"%\[m(\d)\]", ln)})
+            for j in range(R):
+                emit(ALIGN)
+                emit(lab("r%s%d%d" % (form, core, j)) + ":")
+                for k in used:                    # the sequences read vector registers only
+                    emit("v_mov_b32 %%[m%d], s%d" % (k, 72 + k))
+                stream_next()
+                prefetch_next_word()
+                for i in range(NR):
+                    if not i & (1 << j):
+                        L.extend(rot_pair(i, i | (1 << j), form, name))
+                emit("s_branch " + lab("next"))
+    for variant in "g":
+        emit(ALIGN)
+        emit(lab("u" + variant) + ":")
+        for k in range(8):
+            emit("v_mov_b32 %%[m%d], s%d" % (k, 72 + k))
+        stream_next()
         if variant == "g":
             emit(lab("ugj") + ":")                # the shifted matrix of a gradient row joins here
         prefetch_next_word()

@@ -242,6 +242,8 @@ struct Prepared {
     const CachedPlan* cp = nullptr;  // null: one-gate-per-launch path
     float* mats = nullptr;
     int mat_stride = 0;              // matrices per sample in a per-sample table; 0: those of the circuit run
+    const int* exec_of = nullptr;    // gradient: for the shifted matrices
+    const double* scale = nullptr;   // gradient: the table's scalars (null: a plain table)
 };
 
 size_t mats_table_bytes(const qsv_circuit& c, int n, int64_t samples) {
@@ -249,60 +251,51 @@ size_t mats_table_bytes(const qsv_circuit& c, int n, int64_t samples) {
     return align_up(((size_t)(c.reupload ? samples : 1) * c.n_layers * n + 1) * 32);
 }
 
-// the matrix table followed by the builder's side buffer
+// the matrix table followed by its scale table
 size_t mats_bytes(const qsv_circuit& c, int n, int64_t samples) {
-    return mats_table_bytes(c, n, samples) + align_up(build_mats_side_bytes(to_dev(c, n), samples));
+    return mats_table_bytes(c, n, samples) + align_up(mat_scale_bytes(to_dev(c, n), samples));
+}
+
+// layered: the layers of c run one by one as one-layer circuits (`run` = c with n_layers = 1): the plan
+// is the one-layer circuit's, and the matrices of all layers are built by one launch, every layer's in
+// that plan's order; layer l then runs with layer_of(prepared, l).  Otherwise run = c.
+qsv_status prepare(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& run, bool layered, int64_t rows, int inverse,
+                   int grad, const float* params, const float* feats, int64_t samples, float* mats, Prepared* out,
+                   int defer) {
+    const int n = ctx->n;
+    const bool has_u = (c.reupload + c.n_rot) > 0 && c.n_layers > 0;
+    out->mats = mats;
+    out->cp = nullptr;
+    out->mat_stride = layered ? c.n_layers * n : 0;
+    const int* order = nullptr;
+    int plain = 1;
+    if (!(ctx->opt_naive || n < kRegBits)) {
+        qsv_status st = get_plan(ctx, run, rows, inverse, grad, &out->cp, defer);
+        if (st != QSV_OK) return st;
+        order = reinterpret_cast<const int*>(ctx->ws + out->cp->order_off);
+        out->exec_of = reinterpret_cast<const int*>(ctx->ws + out->cp->execof_off);
+        // rows that share a tile and differ in their matrices read them per lane, as matrices
+        plain = n < out->cp->plan.tile && (c.reupload || grad) ? 1 : 0;
+    }
+    if (!has_u) return QSV_OK;
+    double* scale = grad && !plain
+        ? reinterpret_cast<double*>(reinterpret_cast<char*>(mats) + mats_table_bytes(c, n, samples)) : nullptr;
+    out->scale = scale;
+    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0, plain,
+                                   mats, scale, ctx->stream),
+            "build matrices");
+    return QSV_OK;
 }
 
 qsv_status prepare_circuit(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad,
                            const float* params, const float* feats, int64_t samples, float* mats,
                            Prepared* out, int defer = 0) {
-    const int n = ctx->n;
-    const bool has_u = (c.reupload + c.n_rot) > 0 && c.n_layers > 0;
-    out->mats = mats;
-    out->cp = nullptr;
-    const int* order = nullptr;
-    const int* exec_of = nullptr;
-    if (!(ctx->opt_naive || n < kRegBits)) {
-        qsv_status st = get_plan(ctx, c, rows, inverse, grad, &out->cp, defer);
-        if (st != QSV_OK) return st;
-        order = reinterpret_cast<const int*>(ctx->ws + out->cp->order_off);
-        exec_of = reinterpret_cast<const int*>(ctx->ws + out->cp->execof_off);
-    }
-    if (has_u) {
-        double* side = reinterpret_cast<double*>(reinterpret_cast<char*>(mats) + mats_table_bytes(c, n, samples));
-        QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, exec_of, mats, side,
-                                       ctx->stream),
-                "build matrices");
-    }
-    return QSV_OK;
+    return prepare(ctx, c, c, false, rows, inverse, grad, params, feats, samples, mats, out, defer);
 }
 
-// The same for the layers of c run one by one as one-layer circuits (`one` = c with n_layers = 1):
-// the plan is the one-layer circuit's, and the matrices of all layers are built by one launch, every
-// layer's in that plan's order; layer l then runs with layer_of(prepared, l).
 qsv_status prepare_layers(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& one, int64_t rows, int inverse,
                           const float* params, const float* feats, int64_t samples, float* mats, Prepared* out) {
-    const int n = ctx->n;
-    const bool has_u = (c.reupload + c.n_rot) > 0 && c.n_layers > 0;
-    out->mats = mats;
-    out->cp = nullptr;
-    out->mat_stride = c.n_layers * n;
-    const int* order = nullptr;
-    const int* exec_of = nullptr;
-    if (!(ctx->opt_naive || n < kRegBits)) {
-        qsv_status st = get_plan(ctx, one, rows, inverse, 0, &out->cp);
-        if (st != QSV_OK) return st;
-        order = reinterpret_cast<const int*>(ctx->ws + out->cp->order_off);
-        exec_of = reinterpret_cast<const int*>(ctx->ws + out->cp->execof_off);
-    }
-    if (has_u) {
-        double* side = reinterpret_cast<double*>(reinterpret_cast<char*>(mats) + mats_table_bytes(c, n, samples));
-        QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, exec_of, mats, side,
-                                       ctx->stream, order ? n : 0),
-                "build matrices");
-    }
-    return QSV_OK;
+    return prepare(ctx, c, one, true, rows, inverse, 0, params, feats, samples, mats, out, 0);
 }
 
 inline Prepared layer_of(const Prepared& all, int l, int n) {
@@ -1034,7 +1027,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
             Prepared pr;
             st = prepare_circuit(ctx, tail, chunk, 0, 1, p_l, feats_dev, B, mats, &pr);
             if (st != QSV_OK) return st;
-            QSV_HIP(ctx, launch_build_shifted(cd1, p_l, feats_dev, B, ovr, ctx->stream), "build shifted");
+            QSV_HIP(ctx, launch_build_shifted(cd1, p_l, feats_dev, B, pr.exec_of, pr.scale, tail.n_layers * n, ovr, ctx->stream), "build shifted");
             const int64_t circuits_l = B * per_l;
             for (int64_t row0 = 0; row0 < circuits_l; row0 += chunk) {
                 const int64_t rows = (circuits_l - row0) < chunk ? (circuits_l - row0) : chunk;
@@ -1066,7 +1059,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     st = prepare_circuit(ctx, *c, chunk, 0, 1, params_dev, feats_dev, B, mats, &pr);
     if (st != QSV_OK) return st;
     if (P > 0)
-        QSV_HIP(ctx, launch_build_shifted(cd, params_dev, feats_dev, B, ovr, ctx->stream), "build shifted");
+        QSV_HIP(ctx, launch_build_shifted(cd, params_dev, feats_dev, B, pr.exec_of, pr.scale, L * n, ovr, ctx->stream), "build shifted");
     for (int64_t row0 = 0; row0 < circuits; row0 += chunk) {
         const int64_t rows = (circuits - row0) < chunk ? (circuits - row0) : chunk;
         RowMap rm;

@@ -45,7 +45,8 @@ struct PassArgs {
     int rev;             // workgroups take the tiles in descending order (see run_circuit)
     int prio;            // wavefronts raise their issue priority while they compute addresses and issue the
                          // tile's loads, and again for its stores (the gates run at the base priority)
-    const float* mats;   // [samples if rowdep][n_mats][8], matrices in execution order
+    const float* mats;   // [samples if rowdep][n_mats][8], unitaries in execution order: factored in groups,
+                         // or plain matrices when several rows share a tile (n < tile) and differ in them
     const int* exec_of;  // [n_mats]: (layer * n + qubit) -> execution-order index
     const float* ovr;    // gradient: [samples if rowdep][2P][8] shifted matrices
     uint64_t total;      // valid extended indices = rows * 2^n
@@ -70,22 +71,23 @@ hipError_t launch_naive_u(float2* state, int64_t rows, int n, int q, const float
 hipError_t launch_naive_cnot(float2* state, int64_t rows, int n, int ctrl, int tgt, hipStream_t st);
 hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_t st);
 
-// fused per-(layer, qubit) matrices; out: [samples if reupload][n_layers*n][8] floats.  order
-// (device, [n_layers*n], may be NULL = natural order) gives the (layer*n + qubit) id stored at
-// each position of a sample's table, exec_of (device, same length, NULL with order) its inverse.
-// period = n: the two tables have n entries, describe a one-layer circuit and repeat for every layer
-// (the table of the whole circuit as the tables of its layers, run one by one, back to back).
-hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats,
-                             int64_t samples, int inverse, const int* order, const int* exec_of, float* out,
-                             double* side, hipStream_t st, int period = 0);
-// bytes of the side buffer launch_build_mats needs (phase factors and the last qubit's matrices in double)
-inline size_t build_mats_side_bytes(const CircDev& c, int64_t samples) {
-    const size_t tables = (size_t)(c.reupload ? samples : 1);
-    return tables * (size_t)c.n_layers * ((size_t)c.n * 16 + 64);
+// fused per-(layer, qubit) unitaries; out: [samples if reupload][n_layers*n][8] floats.  order
+// (device, [n_layers*n], NULL = natural order) gives the (layer*n + qubit) id stored at each position of
+// a sample's table.  period = n: the order table has n entries, describes a one-layer circuit and
+// repeats for every layer (the table of the whole circuit as the tables of its layers, run one by one,
+// back to back).  plain = 1: every entry is the matrix; 0: factored in groups (see kMatGroup), as the
+// interpreter of the fused pass reads them.  scale (NULL: not wanted): [tables][n_layers*n] complex doubles.
+hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
+                             const int* order, int period, int plain, float* out, double* scale, hipStream_t st);
+// bytes of the scale table
+inline size_t mat_scale_bytes(const CircDev& c, int64_t samples) {
+    return (size_t)(c.reupload ? samples : 1) * (size_t)c.n_layers * (size_t)c.n * 16;
 }
-// shifted matrices for the parameter-shift rule; out: [samples if reupload][2P][8]
-hipError_t launch_build_shifted(const CircDev& c, const float* params, const float* feats,
-                                int64_t samples, float* out, hipStream_t st);
+// shifted matrices for the parameter-shift rule; out: [samples if reupload][2P][8].  They replace entries of a
+// table of `per` entries per sample with that scale table (NULL: a plain one); exec_of: position in
+// it of (layer*n + qubit)
+hipError_t launch_build_shifted(const CircDev& c, const float* params, const float* feats, int64_t samples,
+                                const int* exec_of, const double* scale, int per, float* out, hipStream_t st);
 
 // encoding
 hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* partial, int nblk,

@@ -544,55 +544,80 @@ __device__ M2 fused_raw(const CircDev& c, const float* params, const float* feat
     return u;
 }
 
-// Phase bookkeeping.  Within one layer the single-qubit unitaries act on different qubits, so a
-// scalar factor may move freely between them.  Every matrix but the one of the last qubit is
-// stored as W = conj(p) U with p = m00 / |m00|, which makes m00 real (and, for the common
-// rotation sequences, a whole row or column real: the interpreter tests the stored zeros and
-// picks a shorter multiply sequence).  The last qubit's matrix takes the product of the removed
-// factors, so the layer as a whole, and hence the state, is unchanged.
-struct Ph { double r, i; };
+struct Cx { double r, i; };
 
-__device__ __forceinline__ Ph phase_of(const M2& u) {
-    const double mag = hypot(u.r[0], u.i[0]);
-    if (mag < 1e-6) return {1.0, 0.0};
-    return {u.r[0] / mag, u.i[0] / mag};
-}
+__device__ __forceinline__ Cx mul_c(Cx a, Cx b) { return {a.r * b.r - a.i * b.i, a.r * b.i + a.i * b.r}; }
 
-__device__ __forceinline__ void scale_m(M2& u, double pr, double pi) {  // u *= (pr + i pi)
+__device__ __forceinline__ void scale_m(M2& u, Cx f) {  // u *= f
     for (int k = 0; k < 4; ++k) {
-        const double a = u.r[k], b = u.i[k];
-        u.r[k] = a * pr - b * pi;
-        u.i[k] = a * pi + b * pr;
+        const Cx v = mul_c({u.r[k], u.i[k]}, f);
+        u.r[k] = v.r;
+        u.i[k] = v.i;
     }
 }
 
-__device__ __forceinline__ void strip_phase(M2& u) {
-    const Ph p = phase_of(u);
-    if (p.r == 1.0 && p.i == 0.0) return;
-    const double mag = hypot(u.r[0], u.i[0]);
-    scale_m(u, p.r, -p.i);
-    u.r[0] = mag; u.i[0] = 0.0;
+__device__ __forceinline__ void store_m(const M2& u, float* out8) {
+    float4* o = reinterpret_cast<float4*>(out8);
+    o[0] = make_float4((float)u.r[0], (float)u.i[0], (float)u.r[1], (float)u.i[1]);
+    o[1] = make_float4((float)u.r[2], (float)u.i[2], (float)u.r[3], (float)u.i[3]);
 }
 
-// Product of the factors removed from qubits 0..n-2 of layer l.
-__device__ Ph layer_phase(const CircDev& c, const float* params, const float* feats, u64 sample,
-                          int l, int inverse) {
-    Ph acc = {1.0, 0.0};
-    for (int q = 0; q + 1 < c.n; ++q) {
-        const Ph p = phase_of(fused_raw(c, params, feats, sample, l, q, -1, 0.0, inverse));
-        const double r = acc.r * p.r - acc.i * p.i;
-        acc.i = acc.r * p.i + acc.i * p.r;
-        acc.r = r;
+// The turn by the unit number p, |angle| <= pi/2 after its sign went into `sigma`, as three shears:
+// t = -tan(angle/2), s = sin(angle).  s is taken from the rounded t, so that the three rounded shears stay
+// a rotation as nearly as floats allow.  A phase that vanishes by structure comes out as rounding
+// noise of a few 1e-17 and is dropped.  Returns whether there is a phase.
+__device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) {
+    *sigma = 1.0;
+    if (p.r < 0.0) { *sigma = -1.0; p.r = -p.r; p.i = -p.i; }
+    *t = 0.f;
+    *s = 0.f;
+    if (fabs(p.i) < 1e-14) return false;
+    *t = (float)(-p.i / (1.0 + p.r));
+    const double td = (double)*t;
+    *s = (float)(-2.0 * td / (1.0 + td * td));
+    return true;
+}
+
+// u (unitary with determinant 1) = g * diag(1, e^iB) core diag(1, e^iA), the core being the real rotation
+// divided by its larger entry: see rot_pair in gen_gate_asm.py, which lists the entry's fields and
+// applies it.  g is taken from the rounded quotient, so a rounded entry times g has orthogonal columns of
+// length 1 up to double precision.  inverse: the entry of the conjugate transpose, with the same rounded
+// numbers: a reverse-mode gradient compares states taken forward and back, and an angle that differs
+// between the two by its rounding shows in it undiminished (measured: 1e-5 instead of 3e-6).
+__device__ __forceinline__ Cx factor_m(const M2& u, int inverse, float* out8) {
+    const double a = hypot(u.r[0], u.i[0]), b = hypot(u.r[2], u.i[2]);
+    Cx ea = {1.0, 0.0}, eb = {1.0, 0.0};              // phases of the first column
+    if (a != 0.0) ea = {u.r[0] / a, u.i[0] / a};
+    if (b != 0.0) eb = {u.r[2] / b, u.i[2] / b};
+    if (a == 0.0) ea = {eb.r, -eb.i};                 // free: leave no phase in front
+    if (b == 0.0) eb = {ea.r, -ea.i};
+    const Cx ab = mul_c(ea, eb);
+    double s1, s2;
+    float e[6];
+    const bool before = shears({ab.r, -ab.i}, &s1, &e[0], &e[1]);
+    const bool after = shears(mul_c(eb, {ea.r, -ea.i}), &s2, &e[4], &e[5]);
+    const bool c_core = !(a < b);                     // also the way of a NaN
+    const float q = (float)(c_core ? b / a : a / b);
+    e[2] = (c_core ? s1 < 0.0 : s2 > 0.0) ? q : -q;   // c: -s1 q, s: s2 q
+    e[3] = (c_core ? s2 : s1) > 0.0 ? q : -q;         // c: s2 q, s: s1 q
+    const bool minus = s1 * s2 < 0.0;
+    const double len = rsqrt(1.0 + (double)q * (double)q) * (c_core ? 1.0 : s2);
+    Cx g = {ea.r * len, ea.i * len};
+    int form = (after ? 2 : 0) + (before ? 1 : 0);
+    float4* o = reinterpret_cast<float4*>(out8);
+    const int core = (c_core ? 0 : 2) + (minus ? 1 : 0);
+    if (!inverse) {
+        o[0] = make_float4(e[0], e[1], e[2], e[3]);
+        o[1] = make_float4(e[4], e[5], __int_as_float((form * 4 + core) * 16), 0.f);
+        return g;
     }
-    return acc;
-}
-
-__device__ __forceinline__ void store_m(M2& u, float* out8) {
-    // imaginary parts that vanish by structure come out as rounding noise of a few 1e-17:
-    // store them as exact zeros so that the fast paths apply
-    for (int k = 0; k < 4; ++k)
-        if (fabs(u.i[k]) < 1e-14) u.i[k] = 0.0;
-    for (int k = 0; k < 4; ++k) { out8[2 * k] = (float)u.r[k]; out8[2 * k + 1] = (float)u.i[k]; }
+    // the phases change sign and places; the core is transposed: c swaps x and y, s (divided by its
+    // upper right entry again, which leaves a factor -+1) keeps them up to that sign
+    form = (before ? 2 : 0) + (after ? 1 : 0);
+    const float f = c_core ? 1.f : (minus ? 1.f : -1.f);
+    o[0] = make_float4(-e[4], -e[5], c_core ? e[3] : f * e[2], c_core ? e[2] : f * e[3]);
+    o[1] = make_float4(-e[0], -e[1], __int_as_float((form * 4 + core) * 16), 0.f);
+    return {g.r * (double)f, -g.i * (double)f};
 }
 
 // Entry pos of an order table.  period > 0: the table has `period` entries and describes one layer;
@@ -601,76 +626,62 @@ __device__ __forceinline__ int ordered(const int* table, int period, int pos) {
     return period > 0 ? (pos / period) * period + table[pos % period] : table[pos];
 }
 
-// Two steps, so that every thread does the same amount of work.  Step 1, one thread per matrix:
-// build it, and for every qubit but the last store it without its phase factor and note the factor;
-// the last qubit's matrix is kept in double.  Step 2, one thread per (sample, layer): multiply the
-// last qubit's matrix by the product of the layer's factors and store it.
-// side: [tables][L*n] factors (2 doubles each), then [tables][L] matrices (8 doubles each).
+// One thread per unitary, one wavefront per group of kMatGroup consecutive ones (a layer's unitaries when
+// period > 0): all but the one with the highest id are stored factored, and their scalars, multiplied up
+// across the wavefront, go into that one, which is stored as a matrix.  plain = 1: every entry is the matrix
+// itself (tables that are read per lane, and the one-gate-per-launch path).
+// scale (may be NULL): what a matrix that replaces entry pos has to be multiplied by.
+// One launch where the factors used to be collected by a second one (10 us to 5 us before a circuit).
 __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* params, const float* feats,
-                                                    u64 count, int inverse, const int* order, int period,
-                                                    float* out, double* side) {
-    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= count) return;
-    const u64 per = (u64)c.n_layers * c.n;
-    const u64 sample = idx / per;
-    const int pos = (int)(idx % per);
-    const int lq = order ? ordered(order, period, pos) : pos;
-    const int l = lq / c.n, q = lq % c.n;
-    M2 u = fused_raw(c, params, feats, sample, l, q, -1, 0.0, inverse);
-    if (q + 1 < c.n) {
-        const Ph p = phase_of(u);
-        double* ps = side + (sample * per + (u64)lq) * 2;
-        ps[0] = p.r; ps[1] = p.i;
-        strip_phase(u);
-        store_m(u, out + idx * 8);
-    } else {
-        const u64 tables = count / per;
-        double* ms = side + tables * per * 2 + (sample * c.n_layers + (u64)l) * 8;
-        for (int k = 0; k < 4; ++k) { ms[2 * k] = u.r[k]; ms[2 * k + 1] = u.i[k]; }
-    }
-}
-
-// One table shared by the whole batch and few qubits: one launch in which the thread of a layer's
-// last qubit recomputes that layer's factors itself.
-__global__ __launch_bounds__(256) void k_build_mats_shared(CircDev c, const float* params, u64 count,
-                                                           int inverse, const int* order, int period, float* out) {
-    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= count) return;
-    const int lq = order ? ordered(order, period, (int)idx) : (int)idx;
-    const int l = lq / c.n, q = lq % c.n;
-    M2 u = fused_raw(c, params, nullptr, 0, l, q, -1, 0.0, inverse);
-    if (q + 1 < c.n) strip_phase(u);
-    else { const Ph p = layer_phase(c, params, nullptr, 0, l, inverse); scale_m(u, p.r, p.i); }
-    store_m(u, out + idx * 8);
-}
-
-__global__ __launch_bounds__(256) void k_build_mats_last(CircDev c, u64 tables, const int* exec_of, int period,
-                                                         float* out, const double* side) {
-    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= tables * c.n_layers) return;
-    const u64 per = (u64)c.n_layers * c.n;
-    const u64 sample = idx / c.n_layers;
-    const int l = (int)(idx % c.n_layers);
-    Ph acc = {1.0, 0.0};
-    for (int q = 0; q + 1 < c.n; ++q) {      // same order of multiplication as layer_phase
-        const double* ps = side + (sample * per + (u64)l * c.n + q) * 2;
-        const double r = acc.r * ps[0] - acc.i * ps[1];
-        acc.i = acc.r * ps[1] + acc.i * ps[0];
-        acc.r = r;
-    }
-    const double* ms = side + tables * per * 2 + idx * 8;
+                                                    u64 groups, int inverse, const int* order, int period,
+                                                    int plain, float* out, double* scale) {
+    static_assert(kMatGroup == 64, "a wavefront is a group");
+    const u64 gi = (u64)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (gi >= groups) return;
+    const int lane = threadIdx.x & 63;
+    const int per = c.n_layers * c.n, seg = period > 0 ? period : per;
+    const int per_seg = (seg + kMatGroup - 1) / kMatGroup, per_table = per_seg * (per / seg);
+    const u64 sample = gi / (u64)per_table;
+    const int gt = (int)(gi % (u64)per_table);
+    const int in_seg = (gt % per_seg) * kMatGroup + lane;
+    const int pos = (gt / per_seg) * seg + in_seg;
+    const bool live = in_seg < seg;
+    const int lq = !live ? -1 : order ? ordered(order, period, pos) : pos;
+    int top = lq;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) top = max(top, __shfl_xor(top, d, 64));
+    const bool whole = plain || lq == top;
+    Cx g = {1.0, 0.0};
     M2 u;
-    for (int k = 0; k < 4; ++k) { u.r[k] = ms[2 * k]; u.i[k] = ms[2 * k + 1]; }
-    scale_m(u, acc.r, acc.i);
-    const int lq = l * c.n + c.n - 1;
-    const u64 pos = exec_of ? (u64)ordered(exec_of, period, lq) : (u64)lq;
-    store_m(u, out + (sample * per + pos) * 8);
+    float* o = out + (sample * (u64)per + (u64)pos) * 8;
+    if (live) {
+        u = fused_raw(c, params, feats, sample, lq / c.n, lq % c.n, -1, 0.0, whole ? inverse : 0);
+        if (!whole) g = factor_m(u, inverse, o);
+    }
+    Cx f = g;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const Cx other = {__shfl_xor(f.r, d, 64), __shfl_xor(f.i, d, 64)};
+        f = (lane & d) ? mul_c(other, f) : mul_c(f, other);   // the same product in every lane
+    }
+    if (!live) return;
+    if (whole) {
+        scale_m(u, f);
+        store_m(u, o);
+    } else {
+        const double m2 = g.r * g.r + g.i * g.i;
+        f = {g.r / m2, -g.i / m2};
+    }
+    if (scale) {
+        scale[(sample * (u64)per + (u64)pos) * 2] = f.r;
+        scale[(sample * (u64)per + (u64)pos) * 2 + 1] = f.i;
+    }
 }
 
-// Matrices with one angle shifted by +-pi/2 (parameter-shift rule), consistent with the phase
-// bookkeeping of the unshifted table they are substituted into.
-__global__ __launch_bounds__(256) void k_build_shifted(CircDev c, const float* params,
-                                                       const float* feats, u64 count, float* out) {
+// Matrices with one angle shifted by +-pi/2 (parameter-shift rule), each multiplied by what the entry it
+// replaces asks for (scale: [tables][per] as k_build_mats wrote it, NULL with a plain table).
+__global__ __launch_bounds__(256) void k_build_shifted(CircDev c, const float* params, const float* feats, u64 count,
+                                                       const int* exec_of, const double* scale, int per, float* out) {
     const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
     if (idx >= count) return;
     const int slots = c.reupload + c.n_rot;
@@ -683,12 +694,9 @@ __global__ __launch_bounds__(256) void k_build_shifted(CircDev c, const float* p
     const int l = p / (c.n * slots);
     const double shift = (v & 1) ? -1.57079632679489661923 : 1.57079632679489661923;
     M2 u = fused_raw(c, params, feats, sample, l, q, sl, shift, 0);
-    if (q + 1 < c.n) {
-        const Ph ph = phase_of(fused_raw(c, params, feats, sample, l, q, -1, 0.0, 0));
-        scale_m(u, ph.r, -ph.i);
-    } else {
-        const Ph ph = layer_phase(c, params, feats, sample, l, 0);
-        scale_m(u, ph.r, ph.i);
+    if (scale) {
+        const double* f = scale + (sample * (u64)per + (u64)exec_of[l * c.n + q]) * 2;
+        scale_m(u, {f[0], f[1]});
     }
     store_m(u, out + idx * 8);
 }
@@ -2242,35 +2250,27 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats,
-                             int64_t samples, int inverse, const int* order, const int* exec_of, float* out,
-                             double* side, hipStream_t st, int period) {
+hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
+                             const int* order, int period, int plain, float* out, double* scale, hipStream_t st) {
     if (period < 0 || (period > 0 && period != c.n)) return hipErrorInvalidValue;
     const u64 tables = (u64)(c.reupload ? samples : 1);
-    const u64 count = tables * c.n_layers * c.n;
-    if (count == 0) return hipSuccess;
-    if ((order == nullptr) != (exec_of == nullptr)) return hipErrorInvalidValue;
-    if (!c.reupload && c.n <= 8) {   // few qubits: the serial factor loop is shorter than a second launch
-        hipLaunchKernelGGL(k_build_mats_shared, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params,
-                           count, inverse, order, period, out);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params, feats,
-                       count, inverse, order, period, out, side);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_build_mats_last, dim3(blocks_for(tables * c.n_layers, 256)), dim3(256), 0, st, c,
-                       tables, exec_of, period, out, side);
+    const u64 per = (u64)c.n_layers * c.n;
+    if (tables * per == 0) return hipSuccess;
+    const u64 seg = period > 0 ? (u64)period : per;
+    const u64 groups = tables * (per / seg) * ((seg + kMatGroup - 1) / kMatGroup);
+    hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(groups, 4)), dim3(256), 0, st, c, params, feats, groups, inverse,
+                       order, period, plain, out, scale);
     return hipGetLastError();
 }
 
-hipError_t launch_build_shifted(const CircDev& c, const float* params, const float* feats,
-                                int64_t samples, float* out, hipStream_t st) {
+hipError_t launch_build_shifted(const CircDev& c, const float* params, const float* feats, int64_t samples,
+                                const int* exec_of, const double* scale, int per, float* out, hipStream_t st) {
     const u64 two_p = 2ull * c.n_layers * c.slots() * c.n;
     const u64 count = (u64)(c.reupload ? samples : 1) * two_p;
     if (count == 0) return hipSuccess;
+    if (scale && !exec_of) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_build_shifted, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params,
-                       feats, count, out);
+                       feats, count, exec_of, scale, per, out);
     return hipGetLastError();
 }
 

@@ -549,6 +549,10 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
         if (ne == 0) { p.complete = false; break; }  // cannot happen: the first pending gate always fits some window
         while (first < G.size() && done[first]) ++first;
     }
+    std::vector<int32_t> top((p.mat_order.size() + kMatGroup - 1) / kMatGroup, -1);   // per group: the highest id
+    for (size_t k = 0; k < p.mat_order.size(); ++k) top[k / kMatGroup] = std::max(top[k / kMatGroup], p.mat_order[k]);
+    for (Op& o : p.ops)
+        if (o.kind == OP_U && p.mat_order[o.arg] == top[o.arg / kMatGroup]) o.c = 1;
     return p;
 }
 

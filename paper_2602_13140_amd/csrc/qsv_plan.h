@@ -28,7 +28,8 @@ enum OpKind : uint8_t {
                     // barrier between writes and reads; c = 1 if a barrier is needed before the
                     // writes (an earlier exchange of this pass may still be read by other wavefronts)
     OP_U = 3,       // a = register bit j, b = 1 if the matrix depends on the state row,
-                    // arg = index of the matrix in execution order (see Plan::mat_order)
+                    // arg = index of the matrix in execution order (see Plan::mat_order), c = 1 if it holds
+                    // the scalars of its group (see kMatGroup): its table entry is the matrix itself
     OP_CX_REG = 4,  // a = target register bit, b = control register bit
     OP_CX_DYN = 5,  // a = target register bit, b = control index bit (extended index),
                     // c = 1 if the control bit is the same for a whole wavefront
@@ -50,6 +51,15 @@ enum OpKind : uint8_t {
     OP_CX_DEFER = 11 // never part of an operation list: a CNOT that the pass's index map carries (see
                     // Plan::defers); a = target qubit, b = control qubit, arg = the control's bit set
 };
+
+// Unitaries are stored without a scalar factor (complex, of modulus between 1/sqrt 2 and 1), which makes
+// them cheaper to apply.  Scalars commute with everything, so the product of the factors taken out of
+// a group of consecutive unitaries (in execution order) goes into one of the group, the one with the
+// highest layer * n + qubit: in a one-layer circuit the last qubit's, in either direction, so that
+// a layer and its inverse are rounded alike.  Inside a group amplitudes are off by at most sqrt 2 per
+// unitary: with 64 of them by less than 2^32 either way, so what has a finite probability (|a| < 2^64)
+// stays finite, and what has one that floats can hold (|a| > 2^-75) stays normal.
+constexpr int kMatGroup = 64;
 
 struct Op {
     uint8_t kind, a, b, c;

@@ -179,3 +179,49 @@ def test_chain_swaps_equal_the_cnots_one_after_the_other():
                     want[i], want[j] = want[j], want[i]
         assert [regs["%%[r%d]" % k] - 100 for k in range(16)] == want, (direction, first, count)
         assert [regs["%%[i%d]" % k] - 200 for k in range(16)] == want
+
+
+@pytest.mark.parametrize("form", g.FORMS)
+@pytest.mark.parametrize("core", g.CORES)
+def test_factored_unitary_sequences(form, core):
+    """Every sequence equals phase * core * phase on a pair, in as many instructions as stated."""
+    import numpy as np
+    r = np.random.Generator(np.random.PCG64(6))
+    first, last = r.uniform(-np.pi / 2, np.pi / 2, 2)
+    first = first if form in ("before", "both") else 0.0
+    last = last if form in ("after", "both") else 0.0
+    x, y = r.uniform(-1, 1, 2)
+    sign = -1.0 if core[1] == "-" else 1.0
+    m = [-np.tan(first / 2), np.sin(first), x, y, -np.tan(last / 2), np.sin(last)]
+    k = np.array([[1, x], [y, sign]] if core[0] == "c" else [[x, -sign], [1, y]], dtype=complex)
+    want = np.diag([1, np.exp(1j * last)]) @ k @ np.diag([1, np.exp(1j * first)])
+    a = r.standard_normal(2) + 1j * r.standard_normal(2)
+    regs = {"%[r3]": a[0].real, "%[i3]": a[0].imag, "%[r7]": a[1].real, "%[i7]": a[1].imag}
+    regs.update({"%%[m%d]" % i: v for i, v in enumerate(m)})
+    lines = g.rot_pair(3, 7, form, core)
+    assert len(lines) == g.ROT_LENGTH[form]
+    val = lambda tok: -regs[tok[1:]] if tok.startswith("-") else regs[tok]
+    for ln in lines:
+        op, rest = ln.split(" ", 1)
+        t = [s.strip() for s in rest.split(",")]
+        if op == "v_mov_b32":
+            regs[t[0]] = val(t[1])
+        elif op == "v_fmac_f32":
+            assert "-" not in rest
+            regs[t[0]] = val(t[1]) * val(t[2]) + regs[t[0]]
+        else:
+            assert op == "v_fma_f32"
+            regs[t[0]] = val(t[1]) * val(t[2]) + val(t[3])
+    got = np.array([regs["%[r3]"] + 1j * regs["%[i3]"], regs["%[r7]"] + 1j * regs["%[i7]"]])
+    assert np.allclose(got, want @ a, atol=1e-13)
+
+
+@PLANES
+def test_jump_table_of_the_factored_unitaries(planes):
+    """The computed jump lands 12 bytes (three instructions) behind its s_getpc plus 4 bytes per entry; the
+    entries are branches in the order (form, core, register bit) that the table entries number."""
+    lines = code_lines(planes)
+    at = lines.index("s_getpc_b64 s[58:59]")
+    assert [ln.split()[0] for ln in lines[at + 1:at + 4]] == ["s_add_u32", "s_addc_u32", "s_setpc_b64"]
+    want = ["s_branch L_r%s%d%d_%%=" % (f, c, j) for f in g.FORMS for c in range(4) for j in range(4)]
+    assert lines[at + 4:at + 4 + 64] == want

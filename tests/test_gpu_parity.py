@@ -904,3 +904,34 @@ def test_reverse_mode_with_every_amount_of_workspace(oracle, extra_states):
     assert np.abs(gg - gref).max() <= 1e-4
     assert np.linalg.norm(gg - gref) <= 1e-3 * np.linalg.norm(gref) + 1e-7
     ctx.close()
+
+
+# ------------------------------------------------------------------ factored unitaries
+@pytest.mark.parametrize("n,B,L,rot,ent,reup,tile", [
+    (4, 3, 3, (RY, RZ), RING, 0, 10), (9, 5, 4, (RX, RY, RZ), LADDER, 0, 11), (9, 3, 2, (RY,), RING, 1, 10),
+    (10, 2, 8, (RY, RZ), RING, 0, 10), (11, 3, 6, (RZ, RX), LADDER, 1, 0), (13, 2, 5, (RX, RY, RZ), RING, 0, 0),
+    (13, 2, 5, (RZ,), NONE, 0, 0), (14, 1, 9, (RY, RZ), NONE, 0, 0), (12, 1, 6, (RY,), NONE, 0, 10)])
+@pytest.mark.parametrize("inverse", [0, 1])
+def test_unitaries_at_special_angles(oracle, n, B, L, rot, ent, reup, tile, inverse):
+    """Angles at multiples of pi/4 and next to them: entries that vanish, equal moduli (the largest growth
+    inside a group, all of them at pi/2 in the last rows), every sign of both phases; 64 unitaries and
+    more, so that groups end inside and between passes.  The tolerance is that of float sums: a
+    few roundings of 6e-8 per gate."""
+    spec = wl.CircuitSpec(L, rot, ent, reup)
+    g = rng(n * 31 + L)
+    P = spec.num_params(n)
+    k = g.integers(-8, 9, P)
+    p = (k * (np.pi / 4) + g.choice([0.0, 0.0, 1e-7, -1e-4], P)).astype(np.float32)
+    p[P // 2:] = np.where(g.random(P - P // 2) < 0.8, np.float32(np.pi / 2), p[P // 2:])
+    x = g.standard_normal((B, 1 << n)).astype(np.float32)
+    feats = np.where(g.random((B, n)) < 0.5, 1.0, g.standard_normal((B, n))).astype(np.float32)
+    ref, _ = oracle.amp_encode(x, n)
+    oracle.apply_layers(ref, ocirc(oracle, spec), p, feats if reup else None, inverse)
+    ctx = gu.make_ctx(n, B, tile=tile)
+    ctx.qsv_set_option("small_apply", 0)
+    ctx.qsv_amp_encode(gu.dev(x))
+    ctx.qsv_apply_layers(qb.circuit_from_spec(spec), gu.dev(p), gu.dev(feats) if reup else None, inverse)
+    got = gu.state_np(ctx)
+    ctx.close()
+    rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert rel <= 6e-8 * 3 * np.sqrt(L * n * 2), rel
