@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqsv.so")
 SOURCES = ["qsv_api.cpp", "qsv_plan.cpp", "qsv_kernels.hip"]
-HEADERS = ["qsv_plan.h", "qsv_kernels.h", "gen_gate_asm.py", os.path.join(ROOT, "include", "qsv.h")]
+HEADERS = ["qsv_plan.h", "qsv_lower.h", "qsv_kernels.h", "gen_gate_asm.py", os.path.join(ROOT, "include", "qsv.h")]
 
 
 def hipcc():

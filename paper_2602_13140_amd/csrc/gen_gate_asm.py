@@ -681,6 +681,267 @@ def _renumbered(line):
     return re.sub(r"\bs(\d+)\b", lambda m: "s%d" % new(m.group(1)), line)
 
 
+# ==================================================================================================
+# The direct interpreter: the form of the block for tiles of one state row (see k_pass_direct).
+#
+# Measured with eight wavefronts per SIMD: a vector instruction on vector registers takes 2.1 to 2.4
+# cycles of its SIMD, one with a scalar source 4, v_swap_b32 8, a scalar instruction 4 (beside the vector
+# ones, up to one for two of them).  The interpreter above spends 28 scalar instructions on a
+# unitary of 56 to 80 vector ones, 20 to 40 on a gate of 8 to 16, and 95 vector instructions on a
+# transpose that only moves data; a shift-rule pass issued 0.6 scalar instructions per vector one.  Here
+#   - an operation word holds the offset of its code (low half; the host knows where every
+#     sequence starts) and its argument (high half): a wait, two additions and a jump per operation,
+#   - the table entries of the unitaries are read strictly in order, so there is no index to compare, and
+#     an entry holds the offset of its sequence,
+#   - every register layout has its own transpose code, with the elements at immediate offsets: element tau
+#     of the plane sits at tau + 2 (tau >> 5), which is additive over disjoint bits, so an element's
+#     address is the lane's part plus a constant.  The two words of padding per 32 keep 32 consecutive
+#     lanes on 32 banks in every layout but 0 (there two lanes share a bank),
+#   - exchanges of registers are moves (three of 2.1 cycles) instead of swaps.
+#
+# Fixed scalar registers:
+#   s[36:37] address of the block's first instruction (code offsets count from it)
+#   s[38:39] operation list   s40 byte offset of the next word   s[42:43] the word (code, argument)
+#   s[44:45] matrix table     s41 byte offset of the next entry   s[48:55] the next entry
+#   s[56:63] shifted matrix of a gradient row
+#   s[64:65], s[66:67] jump targets   s[68:69] saved exec   s70 argument of a transpose
+DIRECT_FIRST, DIRECT_LAST = 36, 70
+LAYOUTS = 11                                     # register runs at tile bits 0..10
+U_STRIDE = 576                                   # bytes from one register bit's code of a unitary to the next one's
+X_DELTA = LAYOUTS * 256                          # bytes from a layout's code for real to that for imaginary parts
+CZ_RUNGS = 3                                     # rungs between neighbouring register bits
+OVERRIDE_NONE = 0xffffffff
+
+
+def padded(tau):
+    return tau + 2 * (tau >> 5)
+
+
+def size_of(line):
+    """Bytes of one of the instructions used here."""
+    op = line.split()[0]
+    if op.startswith(("v_fma_", "ds_", "s_load_")) or op in ("v_lshl_or_b32", "v_lshl_add_u32", "v_bcnt_u32_b32"):
+        return 8
+    if op.startswith("v_mov_b32_dpp"):
+        return 8
+    literal = re.search(r"(?:^|[ ,])(0x[0-9a-f]+|\d+)\s*(?:,|$)", line.split(None, 1)[1]) if " " in line else None
+    if literal and not op.startswith(("s_waitcnt", "s_cbranch", "s_branch", "s_bitcmp")) and int(literal.group(1), 0) > 64:
+        return 8
+    return 4
+
+
+def move_pairs(pairs):
+    """Exchanges register elements: three moves through a temporary each."""
+    out = []
+    for a, b in pairs:
+        for part, tmp in (("r", "%[t0]"), ("i", "%[t1]")):
+            ra, rb = "%%[%s%d]" % (part, a), "%%[%s%d]" % (part, b)
+            out += ["v_mov_b32 %s, %s" % (tmp, ra), "v_mov_b32 %s, %s" % (ra, rb), "v_mov_b32 %s, %s" % (rb, tmp)]
+    return out
+
+
+def chain_moves(direction, first, count):
+    """chain_swaps with its exchanges of two as moves as well."""
+    out = []
+    for ln in chain_swaps(direction, first, count):
+        m = re.match(r"v_swap_b32 (%\[[ri]\d+\]), (%\[[ri]\d+\])", ln)
+        if m:
+            out += ["v_mov_b32 %%[t0], %s" % m.group(1), "v_mov_b32 %s, %s" % m.groups(),
+                    "v_mov_b32 %s, %%[t0]" % m.group(2)]
+        else:
+            out.append(ln)
+    return out
+
+
+def cz_elements(mask):
+    """Register elements whose sign the rungs of mask (bit j: between register bits j and j + 1) flip."""
+    return [k for k in range(NR) if bin(k & (k >> 1) & mask).count("1") & 1]
+
+
+NEXT_WORD = ["s_add_u32 s40, s40, 8", "s_load_dwordx2 s[42:43], s[38:39], s40"]
+NEXT_ENTRY = ["s_add_u32 s41, s41, 32", "s_load_dwordx8 s[48:55], s[44:45], s41"]
+DISPATCH = ["s_waitcnt lgkmcnt(0)",              # the next word and entry have landed, and what LDS owes
+            "s_add_u32 s64, s36, s42", "s_addc_u32 s65, s37, 0", "s_setpc_b64 s[64:65]"]
+
+
+def direct_handlers():
+    """[(name, lines)] in the order of the text; a line that ends in ':' is a local label."""
+    H = []
+
+    def flips(elems):
+        return ["v_xor_b32 %%[%s%d], 0x80000000, %%[%s%d]" % (p, k, p, k) for k in elems for p in "ri"]
+
+    # unitaries: the stub adds the register bit's part to the offset that the entry holds; _S looks for the
+    # shifted matrix of a gradient row first
+    for j in range(R):
+        go = (["s_add_u32 s54, s54, %d" % (j * U_STRIDE)] if j else []) + [
+            "s_add_u32 s64, s36, s54", "s_addc_u32 s65, s37, 0", "s_setpc_b64 s[64:65]"]
+        H.append(("U%d" % j, go))
+        H.append(("US%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc1 L_dovr%d_%%=" % j] + go))
+    for j in range(R):
+        pairs = [(i, i | (1 << j)) for i in range(NR) if not i & (1 << j)]
+        body = [ln for a, b in pairs for ln in u_pair(a, b, "g")]
+        H.append(("G%d" % j, ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in range(8)] + ["L_dgj%d_%%=:" % j] +
+                  NEXT_ENTRY + NEXT_WORD + body + DISPATCH))
+        H.append(("GS%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc0 L_dG%d_%%=" % j, "L_dovr%d_%%=:" % j,
+                               "s_load_dwordx8 s[56:63], %[ovr], 0x0", "s_waitcnt lgkmcnt(0)"] +
+                  ["v_mov_b32 %%[m%d], s%d" % (k, 56 + k) for k in range(8)] + ["s_branch L_dgj%d_%%=" % j]))
+    # CNOTs: inside the register run, chains of them, control elsewhere (a mask of the lane's index bits: one
+    # bit, or the parity of several), target behind a lane bit
+    for jt in range(R):
+        for jc in range(R):
+            if jt != jc:
+                H.append(("X%d%d" % (jt, jc), NEXT_WORD + move_pairs(
+                    [(i, i | (1 << jt)) for i in range(NR) if (i >> jc) & 1 and not (i >> jt) & 1]) + DISPATCH))
+    for k, chain in enumerate(CX_CHAINS):
+        H.append(("C%d" % k, NEXT_WORD + chain_moves(*chain) + DISPATCH))
+    for j in range(R):
+        swap = move_pairs([(i, i | (1 << j)) for i in range(NR) if not (i >> j) & 1])
+        for name, cond in (("D", []), ("P", ["v_bcnt_u32_b32 %[tc], %[tc], 0", "v_and_b32 %[tc], 1, %[tc]"])):
+            done = "L_d%s%dx_%%=" % (name, j)
+            H.append(("%s%d" % (name, j), ["v_and_b32 %[tc], s43, %[e0]"] + cond + NEXT_WORD +
+                      ["v_cmp_ne_u32 vcc, 0, %[tc]", "s_and_saveexec_b64 s[68:69], vcc", "s_cbranch_execz " + done] +
+                      swap + [done + ":", "s_mov_b64 exec, s[68:69]"] + DISPATCH))
+    for j in range(R):
+        high = [k for k in range(NR) if (k >> j) & 1]
+        for b, perm in ((0, "[1,0,3,2]"), (1, "[2,3,0,1]")):
+            H.append(("N%d%d" % (j, b), NEXT_WORD + [
+                "v_mov_b32_dpp %%[%s%d], %%[%s%d] quad_perm:%s row_mask:0xf bank_mask:0xf" % (p, k, p, k, perm)
+                for k in high for p in "ri"] + DISPATCH))
+        H.append(("N%d" % j, ["v_xor_b32 %[tc], s43, %[thr]", "v_and_b32 %[tc], 63, %[tc]",
+                              "v_lshlrev_b32 %[tc], 2, %[tc]"] + NEXT_WORD +
+                  ["ds_bpermute_b32 %%[%s%d], %%[tc], %%[%s%d]" % (p, k, p, k) for k in high for p in "ri"] + DISPATCH))
+    # CZ rungs: inside the run (any set of the three), one end in it, none
+    for mask in range(1, 1 << CZ_RUNGS):
+        H.append(("ZR%d" % mask, NEXT_WORD + flips(cz_elements(mask)) + DISPATCH))
+    for j in range(R):
+        H.append(("ZM%d" % j, ["v_and_b32 %[tc], s43, %[e0]"] + NEXT_WORD +
+                  ["v_cmp_ne_u32 vcc, 0, %[tc]", "s_and_saveexec_b64 s[68:69], vcc", "s_cbranch_execz L_dZM%dx_%%=" % j] +
+                  flips([k for k in range(NR) if (k >> j) & 1]) + ["L_dZM%dx_%%=:" % j, "s_mov_b64 exec, s[68:69]"] +
+                  DISPATCH))
+    H.append(("ZL", ["v_lshrrev_b32 %[tc], 1, %[e0]", "v_and_b32 %[tc], %[tc], %[e0]", "v_and_b32 %[tc], s43, %[tc]",
+                     "v_bcnt_u32_b32 %[tc], %[tc], 0", "v_and_b32 %[tc], 1, %[tc]"] + NEXT_WORD +
+              ["v_cmp_ne_u32 vcc, 0, %[tc]", "s_and_saveexec_b64 s[68:69], vcc", "s_cbranch_execz L_dZLx_%="] +
+              flips(range(NR)) + ["L_dZLx_%=:", "s_mov_b64 exec, s[68:69]"] + DISPATCH))
+    H.append(("END", ["s_branch L_dexit_%="]))
+    # transposes: W<s> writes the real parts in layout s and goes on to the target layout's R code (argument: its
+    # offset / 64, bit 16: the exchange crosses wavefronts, bit 17: barrier before the writes); that reads
+    # them and comes back to W<s>'s imaginary half, and so on
+    def cross(name):
+        return ["s_bitcmp1_b32 s70, 16", "s_cbranch_scc0 " + name, "s_waitcnt lgkmcnt(0)", "s_barrier", name + ":"]
+
+    def at(s, k):
+        return 4 * padded(k << s)
+
+    for half, part in enumerate("ri"):
+        for s in range(LAYOUTS):
+            w = ["ds_write_b32 %%[ldsb], %%[%s%d] offset:%d" % (part, k, at(s, k)) for k in range(NR)]
+            if half == 0:
+                H.append(("W%d" % s, ["s_mov_b32 s70, s43"] + NEXT_WORD +
+                          ["s_bitcmp1_b32 s70, 17", "s_cbranch_scc0 L_dW%db_%%=" % s, "s_barrier", "L_dW%db_%%=:" % s] + w +
+                          ["s_and_b32 s66, s70, 0xffff", "s_lshl_b32 s66, s66, 6", "s_add_u32 s66, s36, s66",
+                           "s_addc_u32 s67, s37, 0", "s_add_u32 s64, s36, @WI%d" % s, "s_addc_u32 s65, s37, 0",
+                           "s_setpc_b64 s[66:67]"]))
+            else:
+                H.append(("WI%d" % s, cross("L_dWI%db_%%=" % s) + w +
+                          ["s_add_u32 s66, s66, %d" % X_DELTA, "s_addc_u32 s67, s67, 0", "s_setpc_b64 s[66:67]"]))
+    for half, part in enumerate("ri"):
+        for s in range(LAYOUTS):
+            r = ["ds_read_b32 %%[%s%d], %%[ldsb] offset:%d" % (part, k, at(s, k)) for k in range(NR)]
+            if half:
+                H.append(("RI%d" % s, cross("L_dRI%db_%%=" % s) +
+                          [ln.replace("[ldsb]", "[ldsn]") for ln in r] + ["v_mov_b32 %[ldsb], %[ldsn]"] + DISPATCH))
+            else:
+                H.append(("R%d" % s, lane_address(s) + cross("L_dR%db_%%=" % s) +
+                          [ln.replace("[ldsb]", "[ldsn]") for ln in r] + ["s_setpc_b64 s[64:65]"]))
+    return H
+
+
+def lane_address(s):
+    """The lane's part of its elements' LDS byte address in layout s, and its index e0."""
+    out = ["v_lshrrev_b32 %%[t0], %d, %%[thr]" % s, "v_and_b32 %%[t1], %d, %%[thr]" % ((1 << s) - 1),
+           "v_lshl_or_b32 %%[t0], %%[t0], %d, %%[t1]" % (s + R),             # tau of the lane's element 0
+           "v_lshrrev_b32 %[t1], 5, %[t0]", "v_lshl_add_u32 %[t1], %[t1], 1, %[t0]",
+           "v_lshlrev_b32 %[ldsn], 2, %[t1]"]
+    return out + ["v_lshrrev_b32 %[t1], %[c], %[t0]", "v_and_b32 %[t2], %[cmask], %[t0]",
+                  "v_lshlrev_b32 %[t1], %[w], %[t1]", "v_or_b32 %[t2], %[tb], %[t2]", "v_or_b32 %[e0], %[t1], %[t2]"]
+
+
+def direct_layout():
+    """({name: byte offset}, first free offset): unitaries' sequences first, at fixed strides."""
+    off, pos = {}, 64 * 2                        # the block's own start takes two lines
+    for form in FORMS:
+        for core in range(len(CORES)):
+            off["F%s%d" % (form, core)] = pos
+            pos += U_STRIDE * R
+    group = {"W": 0, "R": 0}
+    for name, lines in direct_handlers():
+        m = re.fullmatch(r"(W|R)(I?)(\d+)", name)
+        if m:                                    # 256-byte places: W, WI, R, RI by layout
+            if not group["W"]:
+                pos = (pos + 255) // 256 * 256
+                group["W"], group["R"] = pos, pos + 2 * X_DELTA
+                pos += 4 * X_DELTA
+            off[name] = group[m.group(1)] + (X_DELTA if m.group(2) else 0) + 256 * int(m.group(3))
+            continue
+        off[name] = pos
+        pos += (sum(size_of(ln) for ln in lines if not ln.endswith(":")) + 63) // 64 * 64
+    return off, pos
+
+
+def gen_direct():
+    off, end = direct_layout()
+    L = [".p2align 6", "L_dbase_%=:",
+         "s_getpc_b64 s[36:37]", "s_sub_u32 s36, s36, 4", "s_subb_u32 s37, s37, 0",
+         "s_mov_b64 s[38:39], %[ops]", "s_mov_b64 s[44:45], %[mats]", "s_mov_b32 s40, 0", "s_mov_b32 s41, %[first]",
+         "s_load_dwordx2 s[42:43], s[38:39], 0x0", "s_load_dwordx8 s[48:55], s[44:45], s41"] + DISPATCH
+    bodies = []
+    for form in FORMS:
+        for core, name in enumerate(CORES):
+            used = sorted({int(m) for ln in rot_pair(0, 1, form, name) for m in re.findall(r"%\[m(\d)\]", ln)})
+            for j in range(R):
+                body = ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in used] + NEXT_ENTRY + NEXT_WORD
+                for i in range(NR):
+                    if not i & (1 << j):
+                        body += rot_pair(i, i | (1 << j), form, name)
+                bodies.append((off["F%s%d" % (form, core)] + j * U_STRIDE, "F%s%d%d" % (form, core, j), body + DISPATCH))
+    for name, lines in direct_handlers():
+        bodies.append((off[name], name, [re.sub(r"@(\w+)", lambda m: str(off[m.group(1)]), ln) for ln in lines]))
+    for pos, name, lines in sorted(bodies):
+        L.append(".org L_dbase_%%=+%d, 0" % pos)
+        L.append("L_d%s_%%=:" % name)
+        L += lines
+    L.append(".org L_dbase_%%=+%d, 0" % end)
+    L.append("L_dexit_%=:")
+    return L
+
+
+def direct_constants():
+    """C++ constants the host needs to write operation words and the matrix builder to write entries."""
+    off, _ = direct_layout()
+    rows = lambda names: ", ".join(str(off[n]) for n in names)
+    j4 = range(R)
+    return [
+        "namespace qsv { namespace direct {",
+        "// byte offsets of the code of each operation in the block (see gen_direct in the generator)",
+        "constexpr unsigned kU[4] = {%s}, kUShift[4] = {%s};" % (rows("U%d" % j for j in j4), rows("US%d" % j for j in j4)),
+        "constexpr unsigned kG[4] = {%s}, kGShift[4] = {%s};" % (rows("G%d" % j for j in j4), rows("GS%d" % j for j in j4)),
+        "constexpr unsigned kCx[4][4] = {%s};   // [target][control]" % ", ".join(
+            "{%s}" % ", ".join(str(off.get("X%d%d" % (t, c), 0)) for c in j4) for t in j4),
+        "constexpr unsigned kChain[%d] = {%s};" % (len(CX_CHAINS), rows("C%d" % k for k in range(len(CX_CHAINS)))),
+        "constexpr unsigned kCxBit[4] = {%s}, kCxParity[4] = {%s};" % (rows("D%d" % j for j in j4), rows("P%d" % j for j in j4)),
+        "constexpr unsigned kCxQuad[4][2] = {%s}, kCxLane[4] = {%s};" % (
+            ", ".join("{%s}" % rows("N%d%d" % (j, b) for b in (0, 1)) for j in j4), rows("N%d" % j for j in j4)),
+        "constexpr unsigned kCz[8] = {0, %s}, kCzMix[4] = {%s}, kCzLane = %d, kEnd = %d;" % (
+            rows("ZR%d" % m for m in range(1, 8)), rows("ZM%d" % j for j in j4), off["ZL"], off["END"]),
+        "constexpr unsigned kWrite[%d] = {%s};" % (LAYOUTS, rows("W%d" % s for s in range(LAYOUTS))),
+        "constexpr unsigned kRead[%d] = {%s};" % (LAYOUTS, rows("R%d" % s for s in range(LAYOUTS))),
+        "constexpr unsigned kSeq0 = %d, kSeqStride = %d;   // code of a factored unitary: kSeq0 + sequence * kSeqStride" % (
+            off["Fnone0"], U_STRIDE * R),
+        "} }",
+    ]
+
+
 def render():
     out = ["// Generated by gen_gate_asm.py -- do not edit by hand.",
            "// Inline-assembly gate interpreter of the fused pass kernel; see the generator for the",
@@ -694,6 +955,13 @@ def render():
             for ln in gen(planes, perlane):
                 out.append('    "%s\\n\\t" \\' % ln)
             out.append('    ""')
+    out.append("#define QSV_GATE_DIRECT_ASM \\")
+    for ln in gen_direct():
+        out.append('    "%s\\n\\t" \\' % ln)
+    out.append('    ""')
+    regs = ", ".join('"s%d"' % i for i in range(DIRECT_FIRST, DIRECT_LAST + 1))
+    out.append("#define QSV_GATE_DIRECT_CLOBBERS %s, \"vcc\", \"scc\", \"memory\"" % regs)
+    out += direct_constants()
     regs = ", ".join('"s%d"' % i for i in range(FIRST_SGPR, LAST_SGPR + 1))
     out.append("#define QSV_GATE_LOOP_CLOBBERS %s, \"vcc\", \"scc\", \"memory\"" % regs)
     return "\n".join(out) + "\n"

@@ -10,6 +10,7 @@
 
 #include "qsv.h"
 #include "qsv_kernels.h"
+#include "qsv_lower.h"
 #include "qsv_plan.h"
 
 using namespace qsv;
@@ -43,6 +44,8 @@ struct CachedPlan {
     qsv_circuit c;
     int inverse, tile, grad, low;   // tile: the resolved tile size (the default depends on the rows)
     int defer = 0;                  // planned with deferred CNOTs (index maps)
+    int direct = 0;                 // for the direct interpreter: `low_ops` is uploaded in place of plan.ops
+    DirectPlan low_ops;
     size_t maps_off = 0;            // uint32[plan.maps.size()]: the index maps of its passes
     Plan plan;
     bool resident = false;          // its arrays are in the ops region right now
@@ -162,10 +165,12 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
                     const CachedPlan** out, int defer = 0) {
     int tile = ctx->opt_tile > 0 ? ctx->opt_tile : default_tile(ctx->n, rows);
     tile = std::max(kMinTile, std::min(kMaxTile, tile));
+    // tiles of one row through one LDS plane (tiles of 2^14 have no other way): see kDirectMaxQubits
+    const int direct = ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile) ? 1 : 0;
     CachedPlan* hit = nullptr;
     for (CachedPlan& cp : ctx->cache)
         if (cp.inverse == inverse && cp.tile == tile && cp.grad == grad && cp.low == ctx->opt_low &&
-            cp.defer == defer && same_circuit(cp.c, c)) {
+            cp.defer == defer && cp.direct == direct && same_circuit(cp.c, c)) {
             hit = &cp;
             break;
         }
@@ -181,8 +186,11 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         cp.grad = grad;
         cp.low = ctx->opt_low;
         cp.defer = defer;
+        cp.direct = direct;
         cp.plan = build_plan(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
         if (!cp.plan.complete) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: pass planner failed");
+        if (direct && !lower_plan(cp.plan, grad != 0, &cp.low_ops))
+            return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: lowering the pass plan failed");
         const size_t nm = cp.plan.mat_order.size();
         cp.exec_of.assign(nm, 0);
         for (size_t k = 0; k < nm; ++k) cp.exec_of[cp.plan.mat_order[k]] = (int32_t)k;
@@ -213,8 +221,10 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
                                     hipMemcpyHostToDevice, ctx->stream),
                 "upload index maps");
     if (!cp.plan.ops.empty())
-        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.dev_off, cp.plan.ops.data(),
-                                    cp.plan.ops.size() * sizeof(Op), hipMemcpyHostToDevice, ctx->stream),
+        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.dev_off,
+                                    cp.direct ? (const void*)cp.low_ops.ops.data() : (const void*)cp.plan.ops.data(),
+                                    (cp.direct ? cp.low_ops.ops.size() : cp.plan.ops.size()) * sizeof(Op),
+                                    hipMemcpyHostToDevice, ctx->stream),
                 "upload plan");
     if (nm) {
         QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.order_off, cp.plan.mat_order.data(), nm * sizeof(int32_t),
@@ -268,20 +278,21 @@ qsv_status prepare(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& run, b
     out->cp = nullptr;
     out->mat_stride = layered ? c.n_layers * n : 0;
     const int* order = nullptr;
-    int plain = 1;
+    MatForm form = MatForm::plain;
     if (!(ctx->opt_naive || n < kRegBits)) {
         qsv_status st = get_plan(ctx, run, rows, inverse, grad, &out->cp, defer);
         if (st != QSV_OK) return st;
         order = reinterpret_cast<const int*>(ctx->ws + out->cp->order_off);
         out->exec_of = reinterpret_cast<const int*>(ctx->ws + out->cp->execof_off);
         // rows that share a tile and differ in their matrices read them per lane, as matrices
-        plain = n < out->cp->plan.tile && (c.reupload || grad) ? 1 : 0;
+        if (!(n < out->cp->plan.tile && (c.reupload || grad)))
+            form = out->cp->direct ? MatForm::direct : MatForm::factored;
     }
     if (!has_u) return QSV_OK;
-    double* scale = grad && !plain
+    double* scale = grad && form != MatForm::plain
         ? reinterpret_cast<double*>(reinterpret_cast<char*>(mats) + mats_table_bytes(c, n, samples)) : nullptr;
     out->scale = scale;
-    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0, plain,
+    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0, form,
                                    mats, scale, ctx->stream),
             "build matrices");
     return QSV_OK;
@@ -361,8 +372,6 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
     const CachedPlan* cp = pr.cp;
     if (!cp->resident) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: the plan was dropped from the plan buffer before use");
     const Plan& pl = cp->plan;
-    const int ext = n + ceil_log2_i64(rows);
-    const uint64_t n_tiles = ext > pl.tile ? (1ull << (ext - pl.tile)) : 1ull;
     const Op* dev_ops = reinterpret_cast<const Op*>(ctx->ws + cp->dev_off);
     const bool z_in_pass = zs && n >= pl.tile && !pl.passes.empty();
     // Two rows or more: the rows go through the passes as two halves on two streams.  The halves
@@ -387,9 +396,11 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         join.on = true;
     }
     auto tiles_of = [&](int64_t r) -> uint64_t {
+        if (cp->direct) return (uint64_t)r << (n - pl.tile);
         const int e = n + ceil_log2_i64(r);
         return e > pl.tile ? (1ull << (e - pl.tile)) : 1ull;
     };
+    const int planes = cp->direct ? 1 : ctx->opt_planes;
     const int waves_per_group = std::max(1, (1 << (pl.tile - kRegBits)) / 64);
     // Which passes change buffers: those with an index map must; when their number is odd, one pass
     // without a map changes too (any pass may), so that the last one writes into `state`.  A plan in
@@ -418,7 +429,7 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         a.zout = (last && z_in_pass) ? zs->zpart : nullptr;
         a.zq = zs ? zs->q : 0;
         a.nostore = a.zout ? 1 : 0;
-        a.ops = dev_ops + ps.op_begin;
+        a.ops = dev_ops + (cp->direct ? cp->low_ops.passes[pi].begin : ps.op_begin);
         a.mats = mats;
         a.exec_of = reinterpret_cast<const int*>(ctx->ws + cp->execof_off);
         a.ovr = ovr;
@@ -432,7 +443,16 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         a.n_mats = n_mats;
         a.rowdep = c.reupload;
         a.rm = rm;
-        QSV_HIP(ctx, launch_pass(pl.tile, ctx->opt_planes, a, split ? tiles_of(rows_a) : n_tiles, ctx->stream), "fused pass");
+        a.direct = cp->direct;
+        a.s_in = a.s_out = a.first_mat = 0;
+        a.g_sample0 = (unsigned)(rm.row0 / rm.per);
+        a.g_rem0 = (unsigned)(rm.row0 % rm.per);
+        if (cp->direct) {
+            a.s_in = cp->low_ops.passes[pi].s_in;
+            a.s_out = cp->low_ops.passes[pi].s_out;
+            a.first_mat = cp->low_ops.passes[pi].first_mat;
+        }
+        QSV_HIP(ctx, launch_pass(pl.tile, planes, a, tiles_of(rows_a), ctx->stream), "fused pass");
         if (!split) continue;
         // second half: rows rows_a .. rows - 1.  With a gradient row map the kernel works with global
         // row numbers (row0 moves); otherwise a row's matrices and start state are found relative to
@@ -443,12 +463,14 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         b.total = (uint64_t)rows_b << n;
         if (rm.grad) {
             b.rm.row0 = rm.row0 + rows_a;
+            b.g_sample0 = (unsigned)(b.rm.row0 / rm.per);
+            b.g_rem0 = (unsigned)(b.rm.row0 % rm.per);
         } else {
             if (b.src) b.src = b.src + ((uint64_t)rows_a << n);
             if (c.reupload && b.mats) b.mats = b.mats + (uint64_t)rows_a * (uint64_t)n_mats * 8;
         }
         if (b.zout) b.zout = b.zout + (uint64_t)rows_a * ((uint64_t)1 << (n - pl.tile)) * (uint64_t)waves_per_group;
-        QSV_HIP(ctx, launch_pass(pl.tile, ctx->opt_planes, b, tiles_of(rows_b), ctx->side), "fused pass");
+        QSV_HIP(ctx, launch_pass(pl.tile, planes, b, tiles_of(rows_b), ctx->side), "fused pass");
     }
     if (split) {       // what follows on the caller's stream sees both halves
         join.on = false;
@@ -527,7 +549,7 @@ qsv_status qsv_create(qsv_ctx** out, int n_qubits, int batch, int device, void* 
         return QSV_ERR_WORKSPACE;
     }
     hipError_t e = hipSetDevice(device);
-    if (e == hipSuccess) e = set_pass_attributes();
+    if (e == hipSuccess) e = set_pass_attributes(device);
     if (e != hipSuccess) {
         g_create_error = std::string("HIP initialisation failed: ") + hipGetErrorString(e);
         return QSV_ERR_HIP;
@@ -1344,8 +1366,14 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
         ops.push_back({OP_XPOSE, (uint8_t)((i & 1) ? sio : (sio ? 0 : smax)), 0, 0, 0});
     ops.push_back({OP_END, 0, 0, 0, 0});
     set_transpose_barriers(ops);
+    // a window over qubits alone goes through the kernel that the circuits use
+    DirectPlan low;
+    const bool direct = n >= tile && n <= kDirectMaxQubits && window_start + tile - low_bits <= n &&
+                        (ctx->opt_planes == 1 || tile == kMaxTile) && lower_pass(ops.data(), (int)ops.size(), false, &low);
     // a small synchronous upload: this is a measurement aid, not part of the hot path
-    QSV_HIP(ctx, hipMemcpyAsync(dev, ops.data(), ops.size() * sizeof(Op), hipMemcpyHostToDevice, ctx->stream),
+    const void* list = direct ? (const void*)low.ops.data() : (const void*)ops.data();
+    QSV_HIP(ctx, hipMemcpyAsync(dev, list, (direct ? low.ops.size() : ops.size()) * sizeof(Op), hipMemcpyHostToDevice,
+                                ctx->stream),
             "upload probe");
     QSV_HIP(ctx, hipStreamSynchronize(ctx->stream), "upload probe");
     PassArgs a;
@@ -1358,7 +1386,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     a.rev = (ctx->opt_rev >= 0 ? ctx->opt_rev : ((((uint64_t)ctx->batch << n) * 8) >= kNtStoreBytes ? 1 : 0))
                 ? (ctx->probe_count++ & 1) : 0;
     a.ops = dev;
-    a.mats = nullptr;
+    a.mats = reinterpret_cast<const float*>(dev);   // no unitaries, but the first table entry is fetched unseen
     a.exec_of = nullptr;
     a.ovr = nullptr;
     a.total = (uint64_t)ctx->batch << n;
@@ -1367,8 +1395,13 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     a.n_mats = 0;
     a.rowdep = 0;
     a.rm = plain_rows(n);
-    const uint64_t n_tiles = ext > tile ? (1ull << (ext - tile)) : 1ull;
-    QSV_HIP(ctx, launch_pass(tile, ctx->opt_planes, a, n_tiles, ctx->stream), "probe pass");
+    a.direct = direct;
+    a.s_in = direct ? low.passes[0].s_in : 0;
+    a.s_out = direct ? low.passes[0].s_out : 0;
+    a.first_mat = 0;
+    a.g_sample0 = a.g_rem0 = 0;
+    const uint64_t n_tiles = direct ? (uint64_t)ctx->batch << (n - tile) : ext > tile ? (1ull << (ext - tile)) : 1ull;
+    QSV_HIP(ctx, launch_pass(tile, direct ? 1 : ctx->opt_planes, a, n_tiles, ctx->stream), "probe pass");
     return QSV_OK;
 }
 

@@ -37,7 +37,7 @@ struct PassArgs {
                          // the tile at the end of the pass) has bit j set is written to the index with the
                          // bits imap[j] flipped: deferred CNOTs (needs n > tile and n <= 28)
     const float2* src;   // not NULL: tiles are read from src[sample of the row] instead of in (needs n >= tile)
-    const Op* ops;
+    const void* ops;     // Op list of the pass (direct: DirectOp)
     double* zout;        // not NULL: the pass also writes <Z_zq> partials [tile][wavefront] (needs n >= tile)
     int zq;
     int nostore;         // with zout: the state is not written back
@@ -54,15 +54,23 @@ struct PassArgs {
     int n_mats;
     int rowdep;          // matrices differ per sample
     RowMap rm;
+    // direct = 1: ops is a list of DirectOp (see qsv_lower.h) and the fields below are set
+    int direct;
+    int s_in, s_out;     // register layouts in which the tile is loaded and stored
+    int first_mat;       // index of the pass's first unitary
+    unsigned g_sample0, g_rem0;   // gradient rows: rm.row0 / rm.per and rm.row0 % rm.per
 };
 
+// k_pass_direct takes states of n >= tile qubits (a tile lies in one row), at most this many (a row is at most
+// 2^31 bytes), through one LDS plane; k_pass takes the rest: several rows in a tile, 29 and 30 qubits, two planes.
+constexpr int kDirectMaxQubits = 28;
 hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles, hipStream_t st);
 
 // Address, on the current device (which must be `device`), of the library's fixed scratch array of
 // kStaticScratchBytes bytes (256-byte aligned).  Looked up once per device; allocates nothing.
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
 hipError_t static_scratch(int device, void** ptr);
-hipError_t set_pass_attributes();
+hipError_t set_pass_attributes(int device);   // the current device, which must be `device`
 
 // one-gate-per-launch kernels (fallback for n < 4 and cross-check path)
 hipError_t launch_naive_u(float2* state, int64_t rows, int n, int q, const float* mats,
@@ -75,10 +83,11 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
 // (device, [n_layers*n], NULL = natural order) gives the (layer*n + qubit) id stored at each position of
 // a sample's table.  period = n: the order table has n entries, describes a one-layer circuit and
 // repeats for every layer (the table of the whole circuit as the tables of its layers, run one by one,
-// back to back).  plain = 1: every entry is the matrix; 0: factored in groups (see kMatGroup), as the
-// interpreter of the fused pass reads them.  scale (NULL: not wanted): [tables][n_layers*n] complex doubles.
+// back to back).  plain: every entry is the matrix; else factored in groups (see kMatGroup), as the
+// interpreters of the fused pass read them.  scale (NULL: not wanted): [tables][n_layers*n] complex doubles.
+enum class MatForm { plain, factored, direct };   // direct: factored, for the direct interpreter
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
-                             const int* order, int period, int plain, float* out, double* scale, hipStream_t st);
+                             const int* order, int period, MatForm form, float* out, double* scale, hipStream_t st);
 // bytes of the scale table
 inline size_t mat_scale_bytes(const CircDev& c, int64_t samples) {
     return (size_t)(c.reupload ? samples : 1) * (size_t)c.n_layers * (size_t)c.n * 16;

@@ -150,6 +150,10 @@ __device__ __forceinline__ unsigned to_sgpr(unsigned v) {
     return r;
 }
 
+__device__ __forceinline__ u64 uni64(u64 v) {
+    return ((u64)to_sgpr((unsigned)(v >> 32)) << 32) | to_sgpr((unsigned)v);
+}
+
 // The 16 amplitudes of a lane live in 32 separately named scalars (vr0..vr15, vi0..vi15): as an
 // array the compiler turns them into one 16-wide vector value and copies the whole tuple around
 // the asm block.  QSV_16 applies a statement macro to every index.
@@ -442,6 +446,148 @@ void k_pass(const PassArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
+// The same pass for tiles of one state row (n >= T, n <= 28): the form that almost every launch takes.
+// What a row's tiles have in common (register layouts of the load and the store, the row's sample, the
+// first table entry) comes from the host or is worked out once per wavefront with 32-bit numbers; a row is
+// one buffer of at most 2^31 bytes, so an element's address is the lane's byte offset plus one scalar
+// offset; and the gates run in the direct interpreter (see gen_gate_asm.py).
+// Bound by the issue of vector and scalar instructions together with memory.  Measured against k_pass on the
+// same plans, alternating the two: 16 qubits x 256 shift-rule gradient 120 -> 102 ms, 26 qubits x 30 layers
+// 12.1 -> 11.4 ms, 20 qubits x 32 autoencoder 5.95 -> 5.83 ms, one 19-qubit state 114 -> 88 us.
+template <int T>
+__global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(96)))
+void k_pass_direct(const PassArgs a) {
+    extern __shared__ float lds[];
+    if (a.prio) __builtin_amdgcn_s_setprio(3);
+    if ((unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)lds != 0) return;   // cannot happen; LDS addresses rely on it
+    const unsigned thr = threadIdx.x;
+    const unsigned tile = a.rev ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+    const unsigned nb = (unsigned)(a.n - T), row = tile >> nb, tr = tile & ((1u << nb) - 1u);
+    const unsigned c = (unsigned)a.c, w = (unsigned)a.w, cmask = (1u << c) - 1u;
+    const unsigned base = ((tr & ((1u << (w - c)) - 1u)) << c) | ((tr >> (w - c)) << (w + T - c));
+    auto expand = [&](unsigned tau) -> unsigned { return (tau & cmask) | ((tau >> c) << w); };
+    auto lane_tau = [&](unsigned s) -> unsigned { return ((thr >> s) << (s + R)) | (thr & ((1u << s) - 1u)); };
+    unsigned sample = row;
+    const float* ovr = a.ovr;
+    int ovr_at = -1;                               // table position of the row's shifted matrix
+    if (a.rm.grad) {
+        const unsigned local = a.g_rem0 + row;
+        sample = a.g_sample0 + local / (unsigned)a.rm.per;
+        const unsigned v = local % (unsigned)a.rm.per;
+        if (v < (unsigned)a.rm.two_p) {
+            const unsigned p = v >> 1;
+            ovr_at = a.exec_of[p / (unsigned)a.rm.slots_n * (unsigned)a.n + p % (unsigned)a.n];
+            ovr += ((a.rowdep ? (u64)sample * (unsigned)a.rm.two_p : 0) + v) * 8;
+        }
+    }
+    const float* mats = a.mats + (a.rowdep ? (u64)sample * (unsigned)a.n_mats * 8 : 0);
+    const int row_bytes = (int)(8u << a.n);        // the resource's size (unsigned to the hardware): one row
+    typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
+    // deferred CNOTs: lane j of every half wavefront holds the map's entry of index bit j
+    unsigned im = 0;
+    if (a.imap && (thr & 31u) < (unsigned)a.n) im = a.imap[thr & 31u];
+    QSV_16(QSV_DECL)
+    const unsigned s_in = (unsigned)a.s_in, s_out = (unsigned)a.s_out;
+    const unsigned tau0 = lane_tau(s_in);
+    unsigned e0 = expand(tau0);
+    {
+        const float2* in = a.src ? a.src + ((u64)sample << a.n) : a.in + ((u64)row << a.n);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)in, 0, row_bytes, 0x00020000);
+        const unsigned st0 = expand(1u << s_in) * 8u, st1 = expand(2u << s_in) * 8u, st2 = expand(4u << s_in) * 8u,
+                       st3 = expand(8u << s_in) * 8u;
+        const int voff = (int)(e0 * 8u);
+        unsigned so = base * 8u - st0;
+#define QSV_LD(k, bit, sign) { so = so sign st##bit; \
+            const u32x2v v = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, (int)so, 0)); \
+            vr##k = __uint_as_float(v.x); vi##k = __uint_as_float(v.y); }
+        QSV_16G(QSV_LD)
+#undef QSV_LD
+    }
+    if (a.prio) __builtin_amdgcn_s_setprio(0);
+    // where the amplitudes go: byte offset of the lane's element 0 in its row, and what register bits add
+    unsigned out_off = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
+    if (a.imap) {
+        // the map is linear over XOR: (tile's part) ^ (lane's part) ^ (register element's part)
+        unsigned et = (base >> (thr & 31u)) & 1u ? im : 0u;
+#pragma unroll
+        for (int d = 16; d > 0; d >>= 1) et ^= __shfl_xor(et, d, 32);
+        auto entry = [&](unsigned b) -> unsigned {   // of the index bit behind tile bit b
+            return (unsigned)__builtin_amdgcn_readlane((int)im, (int)(b < c ? b : b - c + w));
+        };
+#pragma unroll
+        for (unsigned i = 0; i < T - R; ++i) {       // thread bit i is tile bit i or i + 4
+            const unsigned m = entry(i < s_out ? i : i + R);
+            et ^= (thr >> i) & 1u ? m : 0u;
+        }
+        out_off = et * 8u;
+        x0 = entry(s_out) * 8u; x1 = entry(s_out + 1) * 8u; x2 = entry(s_out + 2) * 8u; x3 = entry(s_out + 3) * 8u;
+    }
+    {
+        unsigned ldsb = (tau0 + 2u * (tau0 >> 5)) * 4u, ldsn;
+        e0 |= base;
+        float t0, t1, t2, t3, tc, m0, m1, m2, m3, m4, m5, m6, m7;
+        const u64 ops = (u64)(uintptr_t)a.ops, mat = (u64)(uintptr_t)mats, ov = (u64)(uintptr_t)ovr;
+        asm volatile(QSV_GATE_DIRECT_ASM
+                     : QSV_16(QSV_RV)[t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [tc] "=&v"(tc),
+                       [m0] "=&v"(m0), [m1] "=&v"(m1), [m2] "=&v"(m2), [m3] "=&v"(m3), [m4] "=&v"(m4), [m5] "=&v"(m5),
+                       [m6] "=&v"(m6), [m7] "=&v"(m7), [ldsb] "+v"(ldsb), [ldsn] "=&v"(ldsn), [e0] "+v"(e0)
+                     : [thr] "v"(thr), [ops] "s"(uni64(ops)), [mats] "s"(uni64(mat)), [ovr] "s"(uni64(ov)),
+                       [ovrid] "s"(to_sgpr((unsigned)ovr_at)), [first] "s"(to_sgpr((unsigned)a.first_mat * 32u)),
+                       [c] "s"(to_sgpr(c)), [w] "s"(to_sgpr(w)), [cmask] "s"(to_sgpr(cmask)), [tb] "s"(to_sgpr(base))
+                     : QSV_GATE_DIRECT_CLOBBERS);
+    }
+    const unsigned lane_out = expand(lane_tau(s_out));
+    if (a.zout) {
+        // last pass of a gradient row: see k_pass
+        const int zq = a.zq;
+        float acc = 0.f;
+#define QSV_Z(k) { const float p = vr##k * vr##k + vi##k * vi##k; \
+                   acc += (expand((unsigned)k << s_out) >> zq) & 1u ? -p : p; }
+        QSV_16(QSV_Z)
+#undef QSV_Z
+        if (((base | lane_out) >> zq) & 1u) acc = -acc;
+        const double tot = wave_sum((double)acc);
+        if ((thr & 63u) == 0) a.zout[(u64)tile * (blockDim.x >> 6) + (thr >> 6)] = tot;
+        if (a.nostore) return;
+    }
+    if (a.prio) __builtin_amdgcn_s_setprio(3);
+    const __amdgpu_buffer_rsrc_t ro =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(a.state + ((u64)row << a.n)), 0, row_bytes, 0x00020000);
+#define QSV_PUT(k, off, so, aux) { u32x2v v; v.x = __float_as_uint(vr##k); v.y = __float_as_uint(vi##k); \
+            __builtin_amdgcn_raw_buffer_store_b64(v, ro, (int)(off), (int)(so), aux); }
+    if (a.imap) {
+        unsigned off = out_off ^ x0;
+#define QSV_ST(k, bit, sign) { off ^= x##bit; QSV_PUT(k, off, 0, AUX) }
+        if (a.nt_store) {
+#define AUX 2
+            QSV_16G(QSV_ST)
+#undef AUX
+        } else {
+#define AUX 0
+            QSV_16G(QSV_ST)
+#undef AUX
+        }
+#undef QSV_ST
+    } else {
+        const unsigned st0 = expand(1u << s_out) * 8u, st1 = expand(2u << s_out) * 8u, st2 = expand(4u << s_out) * 8u,
+                       st3 = expand(8u << s_out) * 8u;
+        unsigned so = base * 8u - st0;
+#define QSV_ST(k, bit, sign) { so = so sign st##bit; QSV_PUT(k, lane_out * 8u, so, AUX) }
+        if (a.nt_store) {
+#define AUX 2
+            QSV_16G(QSV_ST)
+#undef AUX
+        } else {
+#define AUX 0
+            QSV_16G(QSV_ST)
+#undef AUX
+        }
+#undef QSV_ST
+    }
+#undef QSV_PUT
+}
+
+// ------------------------------------------------------------------------------------------
 // One-gate-per-launch kernels.
 __global__ __launch_bounds__(256) void k_naive_u(float2* state, u64 pairs, int n, int q,
                                                  const float* mats, const float* ovr, int mat_id,
@@ -563,18 +709,30 @@ __device__ __forceinline__ void store_m(const M2& u, float* out8) {
 }
 
 // The turn by the unit number p, |angle| <= pi/2 after its sign went into `sigma`, as three shears:
-// t = -tan(angle/2), s = sin(angle).  s is taken from the rounded t, so that the three rounded shears stay
-// a rotation as nearly as floats allow.  A phase that vanishes by structure comes out as rounding
+// t = -tan(angle/2), s = sin(angle).  A phase that vanishes by structure comes out as rounding
 // noise of a few 1e-17 and is dropped.  Returns whether there is a phase.
+// The shears of a rounded pair (t, s) multiply to a turn by a slightly different angle and a small
+// stretch.  The angle's error acts on all amplitudes alike and shows in a gradient; the stretch
+// averages out.  So s is chosen for the angle (where it has a lever on it), and of three neighbouring
+// t the one that serves best is taken: 1.2e-8 rms instead of 2.0e-8, what rounding cos and sin gives.
 __device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) {
     *sigma = 1.0;
     if (p.r < 0.0) { *sigma = -1.0; p.r = -p.r; p.i = -p.i; }
     *t = 0.f;
     *s = 0.f;
     if (fabs(p.i) < 1e-14) return false;
-    *t = (float)(-p.i / (1.0 + p.r));
-    const double td = (double)*t;
-    *s = (float)(-2.0 * td / (1.0 + td * td));
+    const int bits = __float_as_int((float)(-p.i / (1.0 + p.r)));
+    double best = 1e300;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const float tf = __int_as_float(bits + (d == 2 ? -1 : d));
+        const double td = (double)tf, t2 = td * td;
+        const float sf = (float)(t2 < 0.5625 ? 2.0 * (p.i + td) / (1.0 - t2) : -2.0 * td / (1.0 + t2));
+        const double sd = (double)sf, low = 2.0 * td + t2 * sd;
+        const double angle = 0.5 * (sd - low) * p.r - (1.0 + td * sd) * p.i, stretch = sd + low;
+        const double cost = angle * angle + 0.04 * stretch * stretch;
+        if (d == 0 || cost < best) { best = cost; *t = tf; *s = sf; }
+    }
     return true;
 }
 
@@ -584,7 +742,7 @@ __device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) 
 // length 1 up to double precision.  inverse: the entry of the conjugate transpose, with the same rounded
 // numbers: a reverse-mode gradient compares states taken forward and back, and an angle that differs
 // between the two by its rounding shows in it undiminished (measured: 1e-5 instead of 3e-6).
-__device__ __forceinline__ Cx factor_m(const M2& u, int inverse, float* out8) {
+__device__ __forceinline__ Cx factor_m(const M2& u, int inverse, int seq0, int seq_stride, float* out8) {
     const double a = hypot(u.r[0], u.i[0]), b = hypot(u.r[2], u.i[2]);
     Cx ea = {1.0, 0.0}, eb = {1.0, 0.0};              // phases of the first column
     if (a != 0.0) ea = {u.r[0] / a, u.i[0] / a};
@@ -608,7 +766,7 @@ __device__ __forceinline__ Cx factor_m(const M2& u, int inverse, float* out8) {
     const int core = (c_core ? 0 : 2) + (minus ? 1 : 0);
     if (!inverse) {
         o[0] = make_float4(e[0], e[1], e[2], e[3]);
-        o[1] = make_float4(e[4], e[5], __int_as_float((form * 4 + core) * 16), 0.f);
+        o[1] = make_float4(e[4], e[5], __int_as_float(seq0 + (form * 4 + core) * seq_stride), 0.f);
         return g;
     }
     // the phases change sign and places; the core is transposed: c swaps x and y, s (divided by its
@@ -616,7 +774,7 @@ __device__ __forceinline__ Cx factor_m(const M2& u, int inverse, float* out8) {
     form = (before ? 2 : 0) + (after ? 1 : 0);
     const float f = c_core ? 1.f : (minus ? 1.f : -1.f);
     o[0] = make_float4(-e[4], -e[5], c_core ? e[3] : f * e[2], c_core ? e[2] : f * e[3]);
-    o[1] = make_float4(-e[0], -e[1], __int_as_float((form * 4 + core) * 16), 0.f);
+    o[1] = make_float4(-e[0], -e[1], __int_as_float(seq0 + (form * 4 + core) * seq_stride), 0.f);
     return {g.r * (double)f, -g.i * (double)f};
 }
 
@@ -634,7 +792,7 @@ __device__ __forceinline__ int ordered(const int* table, int period, int pos) {
 // One launch where the factors used to be collected by a second one (10 us to 5 us before a circuit).
 __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* params, const float* feats,
                                                     u64 groups, int inverse, const int* order, int period,
-                                                    int plain, float* out, double* scale) {
+                                                    int plain, int seq0, int seq_stride, float* out, double* scale) {
     static_assert(kMatGroup == 64, "a wavefront is a group");
     const u64 gi = (u64)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (gi >= groups) return;
@@ -656,7 +814,7 @@ __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* para
     float* o = out + (sample * (u64)per + (u64)pos) * 8;
     if (live) {
         u = fused_raw(c, params, feats, sample, lq / c.n, lq % c.n, -1, 0.0, whole ? inverse : 0);
-        if (!whole) g = factor_m(u, inverse, o);
+        if (!whole) g = factor_m(u, inverse, seq0, seq_stride, o);
     }
     Cx f = g;
 #pragma unroll
@@ -2194,10 +2352,21 @@ static hipError_t set_attr_for() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// the two variants that use 64 KiB of dynamic LDS
-hipError_t set_pass_attributes() {
-    const hipError_t e = set_attr_for<13, 2>();
-    return e != hipSuccess ? e : set_attr_for<14, 1>();
+constexpr int direct_lds_bytes(int tile) { return ((1 << tile) + (1 << (tile - 4))) * 4; }   // two words of padding per 32
+
+// the variants that use 64 KiB of dynamic LDS and more; once per device
+hipError_t set_pass_attributes(int device) {
+    static std::mutex mu;
+    static bool done[64] = {};
+    std::lock_guard<std::mutex> lock(mu);
+    if (device >= 0 && device < 64 && done[device]) return hipSuccess;
+    hipError_t e = set_attr_for<13, 2>();
+    if (e == hipSuccess) e = set_attr_for<14, 1>();
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, direct_lds_bytes(14));
+    if (e == hipSuccess && device >= 0 && device < 64) done[device] = true;
+    return e;
 }
 
 template <int T, int PLANES>
@@ -2212,6 +2381,22 @@ hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles
     if (planes != 1 && planes != 2) return hipErrorInvalidValue;
     if (tile == 14) planes = 1;   // the largest tile exists with one plane only
     const dim3 grid((unsigned)n_tiles);
+    if (a.direct) {
+        if (a.n < tile || a.n > kDirectMaxQubits || planes != 1 || a.w + tile - a.c > a.n || a.s_in < 0 || a.s_out < 0 ||
+            a.s_in > tile - R || a.s_out > tile - R)
+            return hipErrorInvalidValue;
+        const dim3 block(1u << (tile - R));
+        const size_t bytes = (size_t)direct_lds_bytes(tile);
+        switch (tile) {
+            case 10: hipLaunchKernelGGL(k_pass_direct<10>, grid, block, bytes, st, a); break;
+            case 11: hipLaunchKernelGGL(k_pass_direct<11>, grid, block, bytes, st, a); break;
+            case 12: hipLaunchKernelGGL(k_pass_direct<12>, grid, block, bytes, st, a); break;
+            case 13: hipLaunchKernelGGL(k_pass_direct<13>, grid, block, bytes, st, a); break;
+            case 14: hipLaunchKernelGGL(k_pass_direct<14>, grid, block, bytes, st, a); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (tile * 2 + planes - 1) {
         case 20: launch_pass_t<10, 1>(a, grid, st); break;
         case 21: launch_pass_t<10, 2>(a, grid, st); break;
@@ -2251,7 +2436,7 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
 }
 
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
-                             const int* order, int period, int plain, float* out, double* scale, hipStream_t st) {
+                             const int* order, int period, MatForm form, float* out, double* scale, hipStream_t st) {
     if (period < 0 || (period > 0 && period != c.n)) return hipErrorInvalidValue;
     const u64 tables = (u64)(c.reupload ? samples : 1);
     const u64 per = (u64)c.n_layers * c.n;
@@ -2259,7 +2444,8 @@ hipError_t launch_build_mats(const CircDev& c, const float* params, const float*
     const u64 seg = period > 0 ? (u64)period : per;
     const u64 groups = tables * (per / seg) * ((seg + kMatGroup - 1) / kMatGroup);
     hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(groups, 4)), dim3(256), 0, st, c, params, feats, groups, inverse,
-                       order, period, plain, out, scale);
+                       order, period, form == MatForm::plain ? 1 : 0, form == MatForm::direct ? (int)direct::kSeq0 : 0,
+                       form == MatForm::direct ? (int)direct::kSeqStride : 16, out, scale);
     return hipGetLastError();
 }
 
