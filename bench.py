@@ -62,7 +62,8 @@ def parse_args():
 
 
 def n_passes(qb, circ, n, batch, inverse, tile, defer=False):
-    text = qb.qsv_plan_describe(circ, n, batch, inverse, tile | (0x100 if defer else 0))
+    # 0x100: with deferred CNOTs, 0x200: the inverse as the mirror of the circuit's own plan, as the library runs it
+    text = qb.qsv_plan_describe(circ, n, batch, inverse, tile | (0x300 if defer else 0))
     return sum(1 for ln in text.split("\n") if ln.startswith("P "))
 
 

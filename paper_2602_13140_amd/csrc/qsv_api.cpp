@@ -19,10 +19,11 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr size_t kOpsRegion = 4u << 20;  // persistent: uploaded pass programs
-// Launches whose rows hold at least this many bytes store their tiles nontemporally: the chip's
-// last-level cache is 256 MiB, and measured on a 512 MiB state such stores are 4 % faster, on a
-// 256 MiB state 3 % slower.
+// Passes that go through at least this many bytes store their tiles nontemporally: the chip's last-level
+// cache is 256 MiB.  Measured with two buffers in turn: 2 x 256 MiB (20 qubits x 32) 1206 -> 1140 us, 2 x 512 MiB
+// (26 qubits) 3663 -> 3451 us; 2 x 128 MiB (24 qubits) 761 -> 849 us.
 constexpr uint64_t kNtStoreBytes = 384ull << 20;
+constexpr uint64_t kSplitBytes = 32ull << 20;    // see run_circuit
 constexpr int kChunkBits = 12;
 constexpr int kMaxBatch = 1 << 24;
 constexpr int64_t kMaxAmplitudes = (int64_t)1 << 36;
@@ -163,7 +164,7 @@ bool same_circuit(const qsv_circuit& a, const qsv_circuit& b) {
 // behind every kernel that read the old contents, so nothing waits on the host.
 qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad,
                     const CachedPlan** out, int defer = 0) {
-    int tile = ctx->opt_tile > 0 ? ctx->opt_tile : default_tile(ctx->n, rows);
+    int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer ? defer_tile(ctx->n, rows) : default_tile(ctx->n, rows);
     tile = std::max(kMinTile, std::min(kMaxTile, tile));
     // tiles of one row through one LDS plane (tiles of 2^14 have no other way): see kDirectMaxQubits
     const int direct = ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile) ? 1 : 0;
@@ -187,7 +188,18 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         cp.low = ctx->opt_low;
         cp.defer = defer;
         cp.direct = direct;
-        cp.plan = build_plan(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
+        if (inverse && defer && direct) {
+            // the mirror of the circuit's own plan, which an autoencoder has built already
+            const CachedPlan* fwd = nullptr;
+            for (const CachedPlan& o : ctx->cache)
+                if (!o.inverse && o.tile == tile && o.grad == grad && o.low == ctx->opt_low && o.defer && o.direct &&
+                    same_circuit(o.c, c))
+                    fwd = &o;
+            cp.plan = mirror_plan(fwd ? fwd->plan
+                                      : build_plan(c, ctx->n, rows, false, tile, grad != 0, ctx->opt_low, true));
+        } else {
+            cp.plan = build_plan(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
+        }
         if (!cp.plan.complete) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: pass planner failed");
         if (direct && !lower_plan(cp.plan, grad != 0, &cp.low_ops))
             return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: lowering the pass plan failed");
@@ -254,6 +266,7 @@ struct Prepared {
     int mat_stride = 0;              // matrices per sample in a per-sample table; 0: those of the circuit run
     const int* exec_of = nullptr;    // gradient: for the shifted matrices
     const double* scale = nullptr;   // gradient: the table's scalars (null: a plain table)
+    MatForm form = MatForm::plain;   // of the table
 };
 
 size_t mats_table_bytes(const qsv_circuit& c, int n, int64_t samples) {
@@ -278,7 +291,8 @@ qsv_status prepare(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& run, b
     out->cp = nullptr;
     out->mat_stride = layered ? c.n_layers * n : 0;
     const int* order = nullptr;
-    MatForm form = MatForm::plain;
+    MatForm& form = out->form;
+    form = MatForm::plain;
     if (!(ctx->opt_naive || n < kRegBits)) {
         qsv_status st = get_plan(ctx, run, rows, inverse, grad, &out->cp, defer);
         if (st != QSV_OK) return st;
@@ -377,11 +391,12 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
     // Two rows or more: the rows go through the passes as two halves on two streams.  The halves
     // never meet (a tile lies inside one row when n > tile, and the geometry of the passes does not
     // depend on the number of rows), and each one's launch gaps and tails are covered by the
-    // other's kernels: measured 7-13 % off the whole sequence from 16 to 256 MiB, 3.5 % at 384 and
-    // 512 MiB, 1.2 % at 1 GiB.
+    // other's kernels.  Measured, 10 layers of a ring: 16 qubits x 64 rows 169 -> 157 us, 20 x 16 726 -> 601 us,
+    // 24 x 4 3394 -> 3293 us; below 32 MiB the second launch of every pass costs more than that: 16 x 16
+    // 115 -> 124 us, 14 x 16 89 -> 105 us.
     const uint64_t state_bytes = ((uint64_t)rows << n) * 8;
-    const bool split = rows >= 2 && n > pl.tile && pl.passes.size() >= 2 &&
-                       ctx->opt_split != 0 && !ctx->forked;
+    const bool split = rows >= 2 && n > pl.tile && pl.passes.size() >= 2 && !ctx->forked &&
+                       (ctx->opt_split >= 0 ? ctx->opt_split == 1 : state_bytes >= kSplitBytes);
     const int64_t rows_a = split ? rows / 2 : rows, rows_b = rows - rows_a;
     struct Join {      // the second stream always rejoins the caller's, also when a launch fails
         qsv_ctx* c; bool on;
@@ -413,6 +428,7 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         for (size_t pi = 0; pi < pl.passes.size(); ++pi)
             if (pl.passes[pi].map_begin < 0) { extra_switch = pi; break; }
     float2* cur = state;
+    const uint64_t touched = n_mapped ? 2 * state_bytes : state_bytes;   // what the passes go through in turn
     bool first = true;
     for (size_t pi = 0; pi < pl.passes.size(); ++pi) {
         const Pass& ps = pl.passes[pi];
@@ -434,16 +450,18 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         a.exec_of = reinterpret_cast<const int*>(ctx->ws + cp->execof_off);
         a.ovr = ovr;
         a.total = (uint64_t)rows_a << n;
-        a.nt_store = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : (state_bytes >= kNtStoreBytes ? 1 : 0);
+        a.nt_store = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : (touched >= kNtStoreBytes ? 1 : 0);
         // Every other pass walks the tiles downwards, so that it starts with what the pass before
-        // wrote last and may still find in the memory-side cache (256 MiB).
-        a.rev = (ctx->opt_rev >= 0 ? ctx->opt_rev : (state_bytes >= kNtStoreBytes ? 1 : 0)) ? (int)(pi & 1) : 0;
+        // wrote last and may still find in a cache (measured, two buffers of 32 to 256 MiB: 16 qubits
+        // x 64 175 -> 166 us, 24 qubits 828 -> 761 us; no size at which it costs anything).
+        a.rev = ctx->opt_rev != 0 ? (int)(pi & 1) : 0;
         a.prio = ctx->opt_prio;
         a.n = n; a.c = ps.c; a.w = ps.w;
         a.n_mats = n_mats;
         a.rowdep = c.reupload;
         a.rm = rm;
         a.direct = cp->direct;
+        a.gather = pl.gather ? 1 : 0;
         a.s_in = a.s_out = a.first_mat = 0;
         a.g_sample0 = (unsigned)(rm.row0 / rm.per);
         a.g_rem0 = (unsigned)(rm.row0 % rm.per);
@@ -723,7 +741,7 @@ qsv_status qsv_apply_layers(qsv_ctx* ctx, const qsv_circuit* c, const float* par
     int defer = 0;
     if (ctx->opt_defer != 0 && c->entangler == QSV_ENT_CNOT_RING && ctx->n <= 28 && !ctx->opt_naive &&
         ar.remaining() >= align_up(state_bytes)) {
-        int tile = ctx->opt_tile > 0 ? ctx->opt_tile : default_tile(ctx->n, ctx->batch);
+        int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer_tile(ctx->n, ctx->batch);
         if (ctx->n > tile) {
             pong = (float2*)ar.take(state_bytes);
             defer = pong ? 1 : 0;
@@ -1247,8 +1265,8 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
             if (st != QSV_OK) return st;
             const float2* psi0 = keep ? ck(l, b0) : sc.S;
             const float2* lam0 = keep ? sc.S : sc.S + amps;
-            QSV_HIP(ctx, launch_adj_layer(psi0, lam0, keep ? 1 : 2, n, bc, sc.tp, cd, l, params_dev, feats_dev, b0, P, f,
-                                          ctx->stream),
+            QSV_HIP(ctx, launch_adj_layer(psi0, lam0, keep ? 1 : 2, n, bc, sc.tp, cd, l, params_dev, feats_dev, b0, P,
+                                          back.mats, back.exec_of, back.form, f, ctx->stream),
                     "adjoint layer");
         }
         return QSV_OK;
@@ -1396,6 +1414,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     a.rowdep = 0;
     a.rm = plain_rows(n);
     a.direct = direct;
+    a.gather = 0;
     a.s_in = direct ? low.passes[0].s_in : 0;
     a.s_out = direct ? low.passes[0].s_out : 0;
     a.first_mat = 0;

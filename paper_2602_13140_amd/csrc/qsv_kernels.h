@@ -56,6 +56,8 @@ struct PassArgs {
     RowMap rm;
     // direct = 1: ops is a list of DirectOp (see qsv_lower.h) and the fields below are set
     int direct;
+    int gather;          // the amplitudes are read through imap (position p from the index it maps to) and written
+                         // where they sit
     int s_in, s_out;     // register layouts in which the tile is loaded and stored
     int first_mat;       // index of the pass's first unitary
     unsigned g_sample0, g_rem0;   // gradient rows: rm.row0 / rm.per and rm.row0 % rm.per
@@ -194,6 +196,8 @@ hipError_t launch_pauli(const float2* state, int64_t rows, int n, uint64_t xmask
 // 1/n sum (z-y)^2 into f[.][2P] and coef = 2/n (z-y).
 // launch_adj_init: lambda = O psi for the rows of A; paired = 1 writes (psi, lambda) into rows 2r, 2r+1
 // of S, paired = 0 writes lambda alone into row r.
+// back: the inverse circuit's table, every layer's unitaries in the order of a one-layer plan (exec_of: position
+// of a qubit's; NULL: natural order).
 // launch_adj_layer: for row pairs (psi0 + rstride r 2^n, lam0 + rstride r 2^n), both taken back to the
 // start of `layer`, the derivatives with respect to that layer's angles, written into f[sample][2p],
 // f[sample][2p+1] as (g, -g).  partial: row_pairs * n * (adj_trans_blocks(n) + 1) * 8 doubles.
@@ -211,7 +215,7 @@ int adj_trans_blocks(int n);
 hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride, int n, int64_t row_pairs,
                             double* partial, const CircDev& c,
                             int layer, const float* params, const float* feats, int64_t sample0, int64_t P,
-                            double* f, hipStream_t st);
+                            const float* back, const int* exec_of, MatForm form, double* f, hipStream_t st);
 
 // gradient assembly from f[B][2P+1] (double)
 hipError_t launch_grad_finish(const double* f, int64_t B, int64_t P, const CircDev& c, const float* feats,

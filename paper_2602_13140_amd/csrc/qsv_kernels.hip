@@ -454,8 +454,11 @@ void k_pass(const PassArgs a) {
 // Bound by the issue of vector and scalar instructions together with memory.  Measured against k_pass on the
 // same plans, alternating the two: 16 qubits x 256 shift-rule gradient 120 -> 102 ms, 26 qubits x 30 layers
 // 12.1 -> 11.4 ms, 20 qubits x 32 autoencoder 5.95 -> 5.83 ms, one 19-qubit state 114 -> 88 us.
-template <int T>
-__global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(96)))
+// Eight wavefronts per SIMD: at most 64 vector registers (a workgroup of a 2^13 tile is eight wavefronts, and
+// a CU that holds three of them instead of four took 6 % longer).
+// GATHER: the variant for passes that read through an index map.
+template <int T, bool GATHER>
+__global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(96), amdgpu_waves_per_eu(8, 8)))
 void k_pass_direct(const PassArgs a) {
     extern __shared__ float lds[];
     if (a.prio) __builtin_amdgcn_s_setprio(3);
@@ -490,24 +493,11 @@ void k_pass_direct(const PassArgs a) {
     const unsigned s_in = (unsigned)a.s_in, s_out = (unsigned)a.s_out;
     const unsigned tau0 = lane_tau(s_in);
     unsigned e0 = expand(tau0);
-    {
-        const float2* in = a.src ? a.src + ((u64)sample << a.n) : a.in + ((u64)row << a.n);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)in, 0, row_bytes, 0x00020000);
-        const unsigned st0 = expand(1u << s_in) * 8u, st1 = expand(2u << s_in) * 8u, st2 = expand(4u << s_in) * 8u,
-                       st3 = expand(8u << s_in) * 8u;
-        const int voff = (int)(e0 * 8u);
-        unsigned so = base * 8u - st0;
-#define QSV_LD(k, bit, sign) { so = so sign st##bit; \
-            const u32x2v v = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, (int)so, 0)); \
-            vr##k = __uint_as_float(v.x); vi##k = __uint_as_float(v.y); }
-        QSV_16G(QSV_LD)
-#undef QSV_LD
-    }
-    if (a.prio) __builtin_amdgcn_s_setprio(0);
-    // where the amplitudes go: byte offset of the lane's element 0 in its row, and what register bits add
-    unsigned out_off = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
-    if (a.imap) {
-        // the map is linear over XOR: (tile's part) ^ (lane's part) ^ (register element's part)
+    // Deferred CNOTs: position p of a tile belongs at the index that is the XOR of the map's entries over p's
+    // set bits, (tile's part) ^ (lane's part) ^ (register element's part).  Byte offset of the lane's element 0
+    // in its row in layout s, and what the register bits flip in it.
+    unsigned map_off = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
+    auto follow_map = [&](unsigned s) {
         unsigned et = (base >> (thr & 31u)) & 1u ? im : 0u;
 #pragma unroll
         for (int d = 16; d > 0; d >>= 1) et ^= __shfl_xor(et, d, 32);
@@ -516,12 +506,38 @@ void k_pass_direct(const PassArgs a) {
         };
 #pragma unroll
         for (unsigned i = 0; i < T - R; ++i) {       // thread bit i is tile bit i or i + 4
-            const unsigned m = entry(i < s_out ? i : i + R);
+            const unsigned m = entry(i < s ? i : i + R);
             et ^= (thr >> i) & 1u ? m : 0u;
         }
-        out_off = et * 8u;
-        x0 = entry(s_out) * 8u; x1 = entry(s_out + 1) * 8u; x2 = entry(s_out + 2) * 8u; x3 = entry(s_out + 3) * 8u;
+        map_off = et * 8u;
+        x0 = entry(s) * 8u; x1 = entry(s + 1) * 8u; x2 = entry(s + 2) * 8u; x3 = entry(s + 3) * 8u;
+    };
+    {
+        const float2* in = a.src ? a.src + ((u64)sample << a.n) : a.in + ((u64)row << a.n);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)in, 0, row_bytes, 0x00020000);
+#define QSV_GET(k, off, so) { const u32x2v v = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(off), (int)(so), 0)); \
+            vr##k = __uint_as_float(v.x); vi##k = __uint_as_float(v.y); }
+        if constexpr (GATHER) {
+            follow_map(s_in);
+            unsigned off = map_off ^ x0;
+            // the empty asm keeps the offsets in one register, one after the other
+#define QSV_LD(k, bit, sign) { off ^= x##bit; asm volatile("" : "+v"(off)); QSV_GET(k, off, 0) }
+            QSV_16G(QSV_LD)
+#undef QSV_LD
+        } else {
+            const unsigned st0 = expand(1u << s_in) * 8u, st1 = expand(2u << s_in) * 8u, st2 = expand(4u << s_in) * 8u,
+                           st3 = expand(8u << s_in) * 8u;
+            const unsigned voff = e0 * 8u;
+            unsigned so = base * 8u - st0;
+#define QSV_LD(k, bit, sign) { so = so sign st##bit; QSV_GET(k, voff, so) }
+            QSV_16G(QSV_LD)
+#undef QSV_LD
+        }
+#undef QSV_GET
     }
+    if (a.prio) __builtin_amdgcn_s_setprio(0);
+    const bool scatter = !GATHER && a.imap;
+    if (scatter) follow_map(s_out);                  // while the tile is on its way
     {
         unsigned ldsb = (tau0 + 2u * (tau0 >> 5)) * 4u, ldsn;
         e0 |= base;
@@ -555,8 +571,8 @@ void k_pass_direct(const PassArgs a) {
         __builtin_amdgcn_make_buffer_rsrc((void*)(a.state + ((u64)row << a.n)), 0, row_bytes, 0x00020000);
 #define QSV_PUT(k, off, so, aux) { u32x2v v; v.x = __float_as_uint(vr##k); v.y = __float_as_uint(vi##k); \
             __builtin_amdgcn_raw_buffer_store_b64(v, ro, (int)(off), (int)(so), aux); }
-    if (a.imap) {
-        unsigned off = out_off ^ x0;
+    if (scatter) {
+        unsigned off = map_off ^ x0;
 #define QSV_ST(k, bit, sign) { off ^= x##bit; QSV_PUT(k, off, 0, AUX) }
         if (a.nt_store) {
 #define AUX 2
@@ -665,11 +681,11 @@ __device__ __forceinline__ M2 mul_m(const M2& a, const M2& b) {  // a * b
 }
 
 // U(l,q) for one sample: slots applied in order (re-upload RX first), i.e. U = R_last ... R_first.
-// shift_slot >= 0 adds shift to that slot's angle.
-__device__ M2 fused_raw(const CircDev& c, const float* params, const float* feats, u64 sample, int l,
-                        int q, int shift_slot, double shift, int inverse) {
-    M2 u;
-    for (int k = 0; k < 4; ++k) { u.r[k] = (k == 0 || k == 3) ? 1.0 : 0.0; u.i[k] = 0.0; }
+// shift_slot >= 0 adds shift to that slot's angle.  All factors have the form [[a, -conj b], [b, conj a]], so
+// only the first column is multiplied up.
+__device__ __forceinline__ M2 fused_raw(const CircDev& c, const float* params, const float* feats, u64 sample, int l,
+                                        int q, int shift_slot, double shift, int inverse) {
+    double ar = 1.0, ai = 0.0, br = 0.0, bi = 0.0;
     const int slots = c.reupload + c.n_rot;
     for (int sl = 0; sl < slots; ++sl) {
         double t = (double)params[((u64)l * slots + sl) * c.n + q];
@@ -677,16 +693,24 @@ __device__ M2 fused_raw(const CircDev& c, const float* params, const float* feat
         if (c.reupload && sl == 0) { t *= (double)feats[sample * c.n + q]; axis = QSV_RX; }
         else axis = c.rot[sl - c.reupload];
         if (sl == shift_slot) t += shift;
-        u = mul_m(rot_m(axis, t), u);
+        double s, co;
+        sincos(0.5 * t, &s, &co);
+        const double a0 = ar, a1 = ai, b0 = br, b1 = bi;
+        if (axis == QSV_RX) {
+            ar = co * a0 + s * b1; ai = co * a1 - s * b0;
+            br = co * b0 + s * a1; bi = co * b1 - s * a0;
+        } else if (axis == QSV_RY) {
+            ar = co * a0 - s * b0; ai = co * a1 - s * b1;
+            br = co * b0 + s * a0; bi = co * b1 + s * a1;
+        } else {
+            ar = co * a0 + s * a1; ai = co * a1 - s * a0;
+            br = co * b0 - s * b1; bi = co * b1 + s * b0;
+        }
     }
-    if (inverse) {  // conjugate transpose
-        M2 d;
-        d.r[0] = u.r[0]; d.i[0] = -u.i[0];
-        d.r[1] = u.r[2]; d.i[1] = -u.i[2];
-        d.r[2] = u.r[1]; d.i[2] = -u.i[1];
-        d.r[3] = u.r[3]; d.i[3] = -u.i[3];
-        u = d;
-    }
+    if (inverse) { ai = -ai; br = -br; bi = -bi; }   // conjugate transpose
+    M2 u;
+    u.r[0] = ar; u.i[0] = ai; u.r[1] = -br; u.i[1] = bi;
+    u.r[2] = br; u.i[2] = bi; u.r[3] = ar; u.i[3] = -ai;
     return u;
 }
 
@@ -712,9 +736,9 @@ __device__ __forceinline__ void store_m(const M2& u, float* out8) {
 // t = -tan(angle/2), s = sin(angle).  A phase that vanishes by structure comes out as rounding
 // noise of a few 1e-17 and is dropped.  Returns whether there is a phase.
 // The shears of a rounded pair (t, s) multiply to a turn by a slightly different angle and a small
-// stretch.  The angle's error acts on all amplitudes alike and shows in a gradient; the stretch
-// averages out.  So s is chosen for the angle (where it has a lever on it), and of three neighbouring
-// t the one that serves best is taken: 1.2e-8 rms instead of 2.0e-8, what rounding cos and sin gives.
+// stretch, which acts on every amplitude like one more rounding: of three neighbouring t, each with the s
+// that belongs to it, the one with the smallest is taken (rms stretch 1.5e-8 instead of 2.0e-8 at
+// an angle off by 2.8e-8; the angle's error is a perturbation of a parameter and counts for less).
 __device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) {
     *sigma = 1.0;
     if (p.r < 0.0) { *sigma = -1.0; p.r = -p.r; p.i = -p.i; }
@@ -727,10 +751,10 @@ __device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) 
     for (int d = 0; d < 3; ++d) {
         const float tf = __int_as_float(bits + (d == 2 ? -1 : d));
         const double td = (double)tf, t2 = td * td;
-        const float sf = (float)(t2 < 0.5625 ? 2.0 * (p.i + td) / (1.0 - t2) : -2.0 * td / (1.0 + t2));
+        const float sf = (float)(-2.0 * td / (1.0 + t2));
         const double sd = (double)sf, low = 2.0 * td + t2 * sd;
         const double angle = 0.5 * (sd - low) * p.r - (1.0 + td * sd) * p.i, stretch = sd + low;
-        const double cost = angle * angle + 0.04 * stretch * stretch;
+        const double cost = 0.16 * angle * angle + stretch * stretch;
         if (d == 0 || cost < best) { best = cost; *t = tf; *s = sf; }
     }
     return true;
@@ -743,7 +767,7 @@ __device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) 
 // numbers: a reverse-mode gradient compares states taken forward and back, and an angle that differs
 // between the two by its rounding shows in it undiminished (measured: 1e-5 instead of 3e-6).
 __device__ __forceinline__ Cx factor_m(const M2& u, int inverse, int seq0, int seq_stride, float* out8) {
-    const double a = hypot(u.r[0], u.i[0]), b = hypot(u.r[2], u.i[2]);
+    const double a = sqrt(u.r[0] * u.r[0] + u.i[0] * u.i[0]), b = sqrt(u.r[2] * u.r[2] + u.i[2] * u.i[2]);
     Cx ea = {1.0, 0.0}, eb = {1.0, 0.0};              // phases of the first column
     if (a != 0.0) ea = {u.r[0] / a, u.i[0] / a};
     if (b != 0.0) eb = {u.r[2] / b, u.i[2] / b};
@@ -776,6 +800,29 @@ __device__ __forceinline__ Cx factor_m(const M2& u, int inverse, int seq0, int s
     o[0] = make_float4(-e[4], -e[5], c_core ? e[3] : f * e[2], c_core ? e[2] : f * e[3]);
     o[1] = make_float4(-e[0], -e[1], __int_as_float(seq0 + (form * 4 + core) * seq_stride), 0.f);
     return {g.r * (double)f, -g.i * (double)f};
+}
+
+// The matrix of a table entry as the interpreter applies it, scaled to columns of length 1.
+__device__ __forceinline__ M2 entry_m(const float* e, bool whole, int seq0, int seq_stride) {
+    M2 u;
+    if (whole) {
+        for (int k = 0; k < 4; ++k) { u.r[k] = (double)e[2 * k]; u.i[k] = (double)e[2 * k + 1]; }
+    } else {
+        const int core = ((__float_as_int(e[6]) - seq0) / seq_stride) & 3;
+        const double sigma = (core & 1) ? -1.0 : 1.0, x = (double)e[2], y = (double)e[3];
+        auto turn = [](double t, double s) -> Cx { return {1.0 + t * s, 0.5 * (s - 2.0 * t - t * t * s)}; };
+        const Cx z1 = turn((double)e[0], (double)e[1]), z2 = turn((double)e[4], (double)e[5]);
+        const bool cc = core < 2;
+        const double m00 = cc ? 1.0 : x, m01 = cc ? x : -sigma, m10 = cc ? y : 1.0, m11 = cc ? sigma : y;
+        const Cx z12 = mul_c(z1, z2);
+        u.r[0] = m00; u.i[0] = 0.0;
+        u.r[1] = m01 * z1.r; u.i[1] = m01 * z1.i;
+        u.r[2] = m10 * z2.r; u.i[2] = m10 * z2.i;
+        u.r[3] = m11 * z12.r; u.i[3] = m11 * z12.i;
+    }
+    const double len = rsqrt(u.r[0] * u.r[0] + u.i[0] * u.i[0] + u.r[2] * u.r[2] + u.i[2] * u.i[2]);
+    for (int k = 0; k < 4; ++k) { u.r[k] *= len; u.i[k] *= len; }
+    return u;
 }
 
 // Entry pos of an order table.  period > 0: the table has `period` entries and describes one layer;
@@ -1854,14 +1901,17 @@ __global__ __launch_bounds__(256) void k_trans_finish(const double* partial, int
     }
 }
 
-// Gradients of one layer from the transition matrices: thread = (row pair, slot, qubit).  With
-// W = R_{s-1} ... R_0 (the slots before s on that qubit) the derivative with respect to the angle of
-// slot s is 2 Re sum_ab Bt[a][b] M[a][b], Bt = W^dagger (-i/2 P_s) W.  Written as f+ = g, f- = -g so
-// that the same finishing kernels as for the shift rule apply (they halve the difference and
-// multiply re-upload weights by the feature).
+// Gradients of one layer from the transition matrices: thread = (row pair, slot, qubit).  With U the
+// qubit's unitary and V = R_last ... R_{s+1} its slots after s, the derivative with respect to the angle of
+// slot s is 2 Re sum_ab Bt[a][b] M[a][b], Bt = U^dagger V (-i/2 P_s) V^dagger U.  U^dagger is taken from the
+// table that lambda came back through, as rounded as it is there: a derivative that vanishes because the
+// rest of the circuit commutes with P_s then vanishes here too, up to the sums' rounding.
+// Written as f+ = g, f- = -g so that the same finishing kernels as for the shift rule apply (they halve the
+// difference and multiply re-upload weights by the feature).
 __global__ __launch_bounds__(256) void k_adj_layer(const double* partial, int nblk, CircDev c, int layer,
                                                    const float* params, const float* feats, u64 sample0,
-                                                   u64 pairs_rows, u64 P, double* f) {
+                                                   u64 pairs_rows, u64 P, const float* back, const int* exec_of,
+                                                   int plain, int seq0, int seq_stride, double* f) {
     const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
     const int slots = c.reupload + c.n_rot;
     const u64 per = (u64)slots * c.n;
@@ -1874,27 +1924,30 @@ __global__ __launch_bounds__(256) void k_adj_layer(const double* partial, int nb
     const double* pp = partial + ((r * c.n + q) * (u64)nblk) * 8;
     for (int b = 0; b < nblk; ++b)
         for (int j = 0; j < 8; ++j) M[j] += pp[(u64)b * 8 + j];
-    M2 w;
-    for (int k = 0; k < 4; ++k) { w.r[k] = (k == 0 || k == 3) ? 1.0 : 0.0; w.i[k] = 0.0; }
-    int axis = QSV_RX;
-    for (int sl = 0; sl <= s; ++sl) {
-        double t = (double)params[((u64)layer * slots + sl) * c.n + q];
-        if (c.reupload && sl == 0) { t *= (double)feats[sample * c.n + q]; axis = QSV_RX; }
-        else axis = c.rot[sl - c.reupload];
-        if (sl < s) w = mul_m(rot_m(axis, t), w);
-    }
+    const u64 entry = (c.reupload ? sample * (u64)c.n_layers * c.n : 0) + (u64)layer * c.n + (exec_of ? exec_of[q] : q);
+    M2 w = entry_m(back + entry * 8, plain || q + 1 == c.n, seq0, seq_stride);   // U^dagger, then times V
+    auto axis_of = [&](int sl) { return c.reupload && sl == 0 ? (int)QSV_RX : c.rot[sl - c.reupload]; };
+    for (int sl = slots - 1; sl > s; --sl)          // never the re-upload slot
+        w = mul_m(w, rot_m(axis_of(sl), (double)params[((u64)layer * slots + sl) * c.n + q]));
+    const int axis = axis_of(s);
     // G = -i/2 P for the axis of slot s
     M2 g;
     for (int k = 0; k < 4; ++k) { g.r[k] = 0.0; g.i[k] = 0.0; }
     if (axis == QSV_RX) { g.i[1] = -0.5; g.i[2] = -0.5; }
     else if (axis == QSV_RY) { g.r[1] = -0.5; g.r[2] = 0.5; }
     else { g.i[0] = -0.5; g.i[3] = 0.5; }
-    M2 wd;   // W^dagger
+    M2 wd;   // its conjugate transpose
     wd.r[0] = w.r[0]; wd.i[0] = -w.i[0]; wd.r[1] = w.r[2]; wd.i[1] = -w.i[2];
     wd.r[2] = w.r[1]; wd.i[2] = -w.i[1]; wd.r[3] = w.r[3]; wd.i[3] = -w.i[3];
-    const M2 bt = mul_m(wd, mul_m(g, w));
+    const M2 bt = mul_m(w, mul_m(g, wd));
     double acc = 0.0;
     for (int k = 0; k < 4; ++k) acc += bt.r[k] * M[2 * k] - bt.i[k] * M[2 * k + 1];
+    // The RZ rotations that end the last layer are followed by an entangler, which permutes or signs basis
+    // states, and a diagonal observable: their derivative is exactly zero (what was summed is rounding, about
+    // 1e-9 a sample, and an optimiser that divides by a gradient's size makes steps of it).
+    bool vanishes = layer + 1 == c.n_layers;
+    for (int sl = s; sl < slots; ++sl) vanishes = vanishes && axis_of(sl) == QSV_RZ;
+    if (vanishes) acc *= 0.0;
     const u64 p = ((u64)layer * slots + s) * c.n + q;
     double* fb = f + sample * (2 * P + 1);
     fb[2 * p] = 2.0 * acc;
@@ -2363,7 +2416,10 @@ hipError_t set_pass_attributes(int device) {
     hipError_t e = set_attr_for<13, 2>();
     if (e == hipSuccess) e = set_attr_for<14, 1>();
     if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, direct_lds_bytes(14));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, direct_lds_bytes(14));
     if (e == hipSuccess && device >= 0 && device < 64) done[device] = true;
     return e;
@@ -2381,18 +2437,19 @@ hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles
     if (planes != 1 && planes != 2) return hipErrorInvalidValue;
     if (tile == 14) planes = 1;   // the largest tile exists with one plane only
     const dim3 grid((unsigned)n_tiles);
+    if (!a.direct && a.gather) return hipErrorInvalidValue;
     if (a.direct) {
         if (a.n < tile || a.n > kDirectMaxQubits || planes != 1 || a.w + tile - a.c > a.n || a.s_in < 0 || a.s_out < 0 ||
             a.s_in > tile - R || a.s_out > tile - R)
             return hipErrorInvalidValue;
         const dim3 block(1u << (tile - R));
         const size_t bytes = (size_t)direct_lds_bytes(tile);
-        switch (tile) {
-            case 10: hipLaunchKernelGGL(k_pass_direct<10>, grid, block, bytes, st, a); break;
-            case 11: hipLaunchKernelGGL(k_pass_direct<11>, grid, block, bytes, st, a); break;
-            case 12: hipLaunchKernelGGL(k_pass_direct<12>, grid, block, bytes, st, a); break;
-            case 13: hipLaunchKernelGGL(k_pass_direct<13>, grid, block, bytes, st, a); break;
-            case 14: hipLaunchKernelGGL(k_pass_direct<14>, grid, block, bytes, st, a); break;
+        switch (a.imap && a.gather ? -tile : tile) {
+#define QSV_DIRECT(T)                                                                         \
+    case T: hipLaunchKernelGGL((k_pass_direct<T, false>), grid, block, bytes, st, a); break;  \
+    case -T: hipLaunchKernelGGL((k_pass_direct<T, true>), grid, block, bytes, st, a); break;
+            QSV_DIRECT(10) QSV_DIRECT(11) QSV_DIRECT(12) QSV_DIRECT(13) QSV_DIRECT(14)
+#undef QSV_DIRECT
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -2435,6 +2492,10 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
     return hipGetLastError();
 }
 
+// how a factored entry names its instruction sequence
+inline int seq_first(MatForm f) { return f == MatForm::direct ? (int)direct::kSeq0 : 0; }
+inline int seq_step(MatForm f) { return f == MatForm::direct ? (int)direct::kSeqStride : 16; }
+
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
                              const int* order, int period, MatForm form, float* out, double* scale, hipStream_t st) {
     if (period < 0 || (period > 0 && period != c.n)) return hipErrorInvalidValue;
@@ -2444,8 +2505,7 @@ hipError_t launch_build_mats(const CircDev& c, const float* params, const float*
     const u64 seg = period > 0 ? (u64)period : per;
     const u64 groups = tables * (per / seg) * ((seg + kMatGroup - 1) / kMatGroup);
     hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(groups, 4)), dim3(256), 0, st, c, params, feats, groups, inverse,
-                       order, period, form == MatForm::plain ? 1 : 0, form == MatForm::direct ? (int)direct::kSeq0 : 0,
-                       form == MatForm::direct ? (int)direct::kSeqStride : 16, out, scale);
+                       order, period, form == MatForm::plain ? 1 : 0, seq_first(form), seq_step(form), out, scale);
     return hipGetLastError();
 }
 
@@ -2722,7 +2782,7 @@ int adj_trans_blocks(int n) { return n < 12 ? 1 : 4 * trans_groups(n); }
 hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride, int n, int64_t row_pairs,
                             double* partial, const CircDev& c,
                             int layer, const float* params, const float* feats, int64_t sample0, int64_t P,
-                            double* f, hipStream_t st) {
+                            const float* back, const int* exec_of, MatForm form, double* f, hipStream_t st) {
     if (row_pairs < 1 || row_pairs > 65535) return hipErrorInvalidValue;
     int nblk;
     if (n < 12) {
@@ -2778,7 +2838,8 @@ hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride,
         nblk = 1;
     }
     hipLaunchKernelGGL(k_adj_layer, dim3(blocks_for(jobs, 256)), dim3(256), 0, st, sums, nblk, c, layer,
-                       params, feats, (u64)sample0, (u64)row_pairs, (u64)P, f);
+                       params, feats, (u64)sample0, (u64)row_pairs, (u64)P, back, exec_of, form == MatForm::plain ? 1 : 0,
+                       seq_first(form), seq_step(form), f);
     return hipGetLastError();
 }
 

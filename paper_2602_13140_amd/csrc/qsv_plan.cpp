@@ -38,8 +38,9 @@ struct Geom {
 struct Weights { int u, cx, cz; };
 constexpr Weights kClassicWeights{2, 16, 1}, kDeferWeights{8, 8, 1};
 // The geometry of a pass is chosen by what it and the best pass after it complete together; the
-// second level is only tried for the kLookTop best first passes.
-constexpr int kLookTop = 6;
+// second level is only tried for the best few first passes: fewer change the number of passes with tiles
+// of 2^12 (26 qubits x 20 layers: 34 with six, 36 with three), not with larger ones.
+constexpr int look_top(int tile) { return tile <= 12 ? 6 : 3; }
 constexpr size_t kScanLimit = 8192;
 constexpr int kMinRoundGates = 2;
 
@@ -422,6 +423,14 @@ void merge_cx_chains(std::vector<Op>& ops, size_t begin) {
     ops.swap(out);
 }
 
+// Marks the unitary of every group that holds the group's scalars (see kMatGroup).
+void mark_groups(Plan& p) {
+    std::vector<int32_t> top((p.mat_order.size() + kMatGroup - 1) / kMatGroup, -1);   // per group: the highest id
+    for (size_t k = 0; k < p.mat_order.size(); ++k) top[k / kMatGroup] = std::max(top[k / kMatGroup], p.mat_order[k]);
+    for (Op& o : p.ops)
+        if (o.kind == OP_U && p.mat_order[o.arg] == top[o.arg / kMatGroup]) o.c = 1;
+}
+
 int ceil_log2(int64_t v) {
     int b = 0;
     while (((int64_t)1 << b) < v) ++b;
@@ -451,8 +460,26 @@ int default_tile(int n, int64_t batch) {
     // 2^12 amplitudes per tile measured best for large states.  For 10 or 11 qubits a tile is one
     // state row instead: matrices are then uniform per tile (no per-lane matrix path), and a batch
     // gives four times (twice) as many workgroups to spread over the compute units.
-    const int t = std::max(kMinTile, std::min(12, ext));
+    // For 13 qubits a tile is one row too: then nothing leaves the chip between the gates (10 layers on 37
+    // rows 70 against 85 us, on 2048 rows 300 against 366 us).  At 14 the larger tile's barriers cost more.
+    const int t = std::max(kMinTile, std::min(n == 13 ? 13 : 12, ext));
     return (n < t && n >= kMinTile) ? n : t;
+}
+
+int defer_tile(int n, int64_t batch) {
+    // A tile of 2^13 costs up to 7 % more per pass than one of 2^12 (barriers over eight wavefronts), so
+    // it pays where it saves more passes than that, and where passes are what counts (states of 32 MiB
+    // and more).  By the number of qubits the passes of 20 layers are, 2^12 / 2^13: 17: 14/15, 18: 17/16,
+    // 19: 21/15, 20: 21/18, 21: 25/22, 22: 25/26, 23: 25/25, 24: 30/30, 25: 30/30, 26: 34/32, and of 10 layers
+    // 26: 17/16, 27: 20/16, 28: 21/18.  Measured, 10 layers: 20 qubits x 32 1207 -> 1140 us, 26 qubits
+    // 3683 -> 3451 us, 27 qubits 8.6 -> 6.9 ms; 22 qubits x 8 1268 -> 1465 us, 18 qubits x 16 178 -> 178 us.
+    // States of at most 2^19 amplitudes leave most of the chip idle: twice the workgroups are worth
+    // more than passes (16 qubits 95 -> 88 us, 14 qubits x 16 89 -> 79 us; 2^20 amplitudes 128 -> 134 us).
+    const int64_t amps = batch << n;
+    const int t = default_tile(n, batch);
+    if (t != 12) return t;
+    if (amps >= ((int64_t)1 << 22) && ((n >= 19 && n <= 21) || n >= 26)) return 13;
+    return n > 13 && amps <= ((int64_t)1 << 19) ? 11 : 12;
 }
 
 Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int tile_log2, bool grad,
@@ -504,7 +531,7 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
             // two passes ahead (deferral makes the one-pass score short-sighted: a pass that defers a
             // long stretch of the chain scores well and leaves little for the next one)
             int best = -1;
-            for (size_t ci = 0; ci < cands.size() && (int)ci < kLookTop; ++ci) {
+            for (size_t ci = 0; ci < cands.size() && (int)ci < look_top(t); ++ci) {
                 std::vector<uint8_t> tmp(done);
                 int ne = 0;
                 run_pass(cands[ci].g, n, G, tmp, first, rowdep, defer, nullptr, nullptr, nullptr, &ne, nullptr);
@@ -549,10 +576,55 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
         if (ne == 0) { p.complete = false; break; }  // cannot happen: the first pending gate always fits some window
         while (first < G.size() && done[first]) ++first;
     }
-    std::vector<int32_t> top((p.mat_order.size() + kMatGroup - 1) / kMatGroup, -1);   // per group: the highest id
-    for (size_t k = 0; k < p.mat_order.size(); ++k) top[k / kMatGroup] = std::max(top[k / kMatGroup], p.mat_order[k]);
-    for (Op& o : p.ops)
-        if (o.kind == OP_U && p.mat_order[o.arg] == top[o.arg / kMatGroup]) o.c = 1;
+    mark_groups(p);
+    return p;
+}
+
+Plan mirror_plan(const Plan& f) {
+    Plan p;
+    p.n = f.n;
+    p.ext_bits = f.ext_bits;
+    p.tile = f.tile;
+    p.n_mats = f.n_mats;
+    p.row_dependent = f.row_dependent;
+    p.complete = f.complete;
+    p.deferring = f.deferring;
+    p.gather = true;
+    p.maps = f.maps;
+    p.mat_order.assign(f.mat_order.rbegin(), f.mat_order.rend());
+    const int32_t last = (int32_t)f.mat_order.size() - 1;
+    for (size_t k = f.passes.size(); k-- > 0;) {
+        const Pass& a = f.passes[k];
+        Pass b = a;
+        b.op_begin = (int)p.ops.size();
+        b.defer_begin = b.defer_count = 0;
+        std::vector<int> layout(a.op_count);             // register layout before each operation
+        int s = 0;
+        for (int i = 0; i < a.op_count; ++i) {
+            layout[i] = s;
+            const Op& o = f.ops[a.op_begin + i];
+            if (o.kind == OP_LOAD || o.kind == OP_XPOSE) s = o.a;
+        }
+        p.ops.push_back({OP_LOAD, (uint8_t)s, 0, 0, 0});
+        for (int i = a.op_count; i-- > 0;) {
+            Op o = f.ops[a.op_begin + i];
+            if (o.kind == OP_LOAD || o.kind == OP_END) continue;
+            if (o.kind == OP_XPOSE) o.a = (uint8_t)layout[i];
+            else if (o.kind == OP_U) { o.arg = last - o.arg; o.c = 0; }
+            else if (o.kind == OP_CX_CHAIN) {            // its gates backwards: another of the six chains
+                static const int other[6] = {1, 0, 5, 4, 3, 2};
+                o.a = (uint8_t)(o.c ? o.a - (o.b - 1) : o.a + (o.b - 1));
+                o.c ^= 1;
+                o.arg = other[o.arg];
+            }
+            p.ops.push_back(o);
+        }
+        p.ops.push_back({OP_END, 0, 0, 0, 0});
+        mark_transposes(p.ops, (size_t)b.op_begin);
+        b.op_count = (int)p.ops.size() - b.op_begin;
+        p.passes.push_back(b);
+    }
+    mark_groups(p);
     return p;
 }
 
@@ -609,9 +681,12 @@ extern "C" int64_t qsv_plan_describe(const qsv_circuit* c, int n_qubits, int bat
     using namespace qsv;
     if (!check_circuit(c, n_qubits, nullptr) || batch < 1) return -1;
     const bool defer = (tile_log2 & 0x100) != 0;     // flag bit: the plan with deferred CNOTs
+    const bool mirror = defer && inverse && (tile_log2 & 0x200) != 0;   // flag bit: as the mirror of the circuit's
     tile_log2 &= 0xff;
+    if (defer && tile_log2 == 0) tile_log2 = defer_tile(n_qubits, batch);
     if (tile_log2 != 0 && (tile_log2 < kMinTile || tile_log2 > kMaxTile)) return -1;
-    const Plan p = build_plan(*c, n_qubits, batch, inverse != 0, tile_log2, false, 0, defer);
+    Plan p = build_plan(*c, n_qubits, batch, inverse != 0 && !mirror, tile_log2, false, 0, defer);
+    if (mirror) p = mirror_plan(p);
     const std::string s = describe_plan(p);
     if (buf && buf_bytes > 0) {
         const size_t ncopy = s.size() < (size_t)buf_bytes - 1 ? s.size() : (size_t)buf_bytes - 1;

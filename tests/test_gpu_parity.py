@@ -935,3 +935,51 @@ def test_unitaries_at_special_angles(oracle, n, B, L, rot, ent, reup, tile, inve
     ctx.close()
     rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
     assert rel <= 6e-8 * 3 * np.sqrt(L * n * 2), rel
+
+
+# ------------------------------------------------------------------ choice of tile, mirrored plans
+@pytest.mark.parametrize("n,B,L", [(13, 5, 3), (14, 1, 4), (14, 33, 3), (16, 7, 5), (16, 9, 3), (19, 8, 3), (20, 4, 2),
+                                   (21, 2, 3), (22, 1, 3)])
+def test_ring_circuit_and_its_inverse_at_the_bounds_of_the_tile_rule(n, B, L):
+    """Tiles of 2^11, 2^12 and 2^13 by size, one or two streams, the inverse as the mirrored plan that reads
+    through index maps: against one gate per launch on the GPU.  2 L (3 n) gates of a few roundings
+    of 6e-8 each."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, (RX, RY, RZ), RING)
+    g = rng(77 + n)
+    p = gu.dev(g.uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32))
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, B)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    start = torch.randn(ctx.state.shape, generator=gen, device="cuda") * 2.0 ** (-n / 2)
+    res = {}
+    for naive in (1, 0):
+        ctx.qsv_set_option("naive", naive)
+        for inverse in (0, 1):
+            ctx.state.copy_(start)
+            ctx.qsv_apply_layers(circ, p, None, inverse)
+            res[naive, inverse] = ctx.state.clone()
+    torch.cuda.synchronize()
+    for inverse in (0, 1):
+        a, b = res[0, inverse].double(), res[1, inverse].double()
+        assert ((a - b).norm() / b.norm()).item() <= 6e-8 * 3 * np.sqrt(L * n * 4)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,rot,ent", [(5, (RY, RZ), RING), (11, (RX, RZ), LADDER), (13, (RX, RY, RZ), RING)])
+def test_reverse_mode_gradient_of_the_last_phases_is_zero(oracle, n, rot, ent):
+    """RZ rotations that end the last layer commute with the entangler's effect on a diagonal observable."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(2, rot, ent)
+    g = rng(n)
+    x = g.standard_normal((3, 1 << n)).astype(np.float32)
+    p = g.uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32)
+    ctx = gu.make_ctx(n, 3)
+    loss = torch.zeros(3, device="cuda")
+    grad = torch.zeros((3, spec.num_params(n)), device="cuda")
+    ctx.qsv_adjoint_grad(qb.circuit_from_spec(spec), gu.dev(x), gu.dev(p), None, 1, loss, grad)
+    got = grad.cpu().numpy()
+    assert np.all(got[:, -n:] == 0.0)
+    lref, gref = oracle.param_shift_grad(x, n, ocirc(oracle, spec), p, None, 1)
+    assert np.abs(got - gref).max() <= 1e-5
+    ctx.close()

@@ -349,3 +349,35 @@ def test_plan_replay_random_circuits(oracle, n, rows, L, rot, ent, reup, tile, i
     per_layer = (n if (reup + len(rot)) else 0) + ent_gates
     assert n_gates == L * per_layer
     assert np.allclose(out, ref, atol=1e-12)
+
+
+MIRROR = 0x200      # flag bit, with DEFER and inverse: the plan as the mirror of the circuit's own
+
+
+@pytest.mark.parametrize("n,L,rot,tile", DEFER_CASES + [(19, 2, (RY, RZ), 0)])
+def test_mirrored_plan_replays_to_the_oracle(oracle, n, L, rot, tile):
+    """The inverse circuit's plan as the mirror of the circuit's plan: every pass with a map reads position p
+    from the index that p maps to, applies its operations and writes positions as they are."""
+    g = np.random.Generator(np.random.PCG64(9100 + 17 * n + L))
+    circ = qb.make_circuit(L, list(rot), RING, 0)
+    params = g.uniform(0, 2 * np.pi, qb.qsv_num_params(circ, n)).astype(np.float32)
+    ref, _ = oracle.amp_encode(g.standard_normal((1, 1 << n)).astype(np.float32), n)
+    st = ref.copy()
+    oracle.apply_layers(ref, oracle.make_circuit(L, list(rot), RING, 0), params, None, inverse=True)
+    batch = 8 if tile == 0 else 1
+    forward = qb.qsv_plan_describe(circ, n, batch, 0, tile | DEFER).strip().split("\n")
+    lines = qb.qsv_plan_describe(circ, n, batch, 1, tile | DEFER | MIRROR).strip().split("\n")
+    assert len(lines) == len(forward)
+    for line in lines[1:]:
+        toks = line.split()
+        maps = [t for t in toks if t[0] == "M"]
+        if maps:
+            imap = [int(x, 16) for x in maps[0][1:].split(",")]
+            k = np.arange(1 << n)
+            src = np.zeros(1 << n, dtype=np.int64)
+            for j in range(n):
+                src ^= np.where((k >> j) & 1, imap[j], 0)
+            st = st[:, src]
+        one = lines[0] + "\n" + " ".join(t for t in toks if t[0] != "M") + "\n"
+        st, _, _ = replay(one, n, 1, L, rot, RING, 0, params.astype(np.float64), None, 1, st)
+    assert np.allclose(st, ref, atol=1e-12)
