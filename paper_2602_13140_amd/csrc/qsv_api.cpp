@@ -833,7 +833,9 @@ static qsv_status measure_impl(qsv_ctx* ctx, const qsv_measure_req* req, Arena& 
             if ((st = bind_device(ctx)) != QSV_OK) return st;
             unsigned long long* cum = (unsigned long long*)ar.take((size_t)B * chunk_blocks(n) * 8);
             if (!cum) return ws_fail(ctx, ar, "qsv_measure(SAMPLE)");
-            QSV_HIP(ctx, launch_sample(ctx->state, B, n, req->uniforms_dev, req->shots, cum,
+            // finer sums where the scratch has room for them: they save the draws most of their reading
+            unsigned long long* sub = (unsigned long long*)ar.take((size_t)B * chunk_blocks(n) * 16 * 8);
+            QSV_HIP(ctx, launch_sample(ctx->state, B, n, req->uniforms_dev, req->shots, cum, sub,
                                        (long long*)req->out_dev, ctx->stream),
                     "sample");
             return QSV_OK;

@@ -146,9 +146,9 @@ hipError_t launch_encode_write(const float* x, int64_t dim, int n, int64_t rows,
 
 // measurement
 hipError_t launch_probs(const float2* state, uint64_t total, float* out, hipStream_t st);
-// partial: [rows][nblk][13] doubles; nblk = max(1, 2^n / 4096)
+// partial: rows * max(1, 2^n / 4096) * 13 doubles or fewer; the finishing kernels take the same rows and n
 hipError_t launch_expz_block(const float2* state, int64_t rows, int n, double* partial, hipStream_t st);
-// rows of at most 4096 amplitudes: <Z_q> of every qubit (q_only < 0) or of q_only in one launch, same bits as block + finish
+// rows of at most 4096 amplitudes: <Z_q> of every qubit (q_only < 0) or of q_only in one launch
 hipError_t launch_expz_small(const float2* state, int64_t rows, int n, int q_only, float* out_f, hipStream_t st);
 hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,
                               double* out_d, hipStream_t st);
@@ -181,9 +181,10 @@ hipError_t launch_reset_sum(const double* Frow, int64_t per, int64_t B, float* o
 // finite-shot <Z_q> from samples [rows][shots] -> out [rows][n]
 hipError_t launch_shot_expz(const long long* samples, int64_t shots, int64_t rows, int n, float* out,
                             hipStream_t st);
-// sampling: bsum/cum are uint64 [rows][nblk], nblk = max(1, 2^n / 4096)
+// sampling: bsum/cum are uint64 [rows][nblk], nblk = max(1, 2^n / 4096); sub (NULL: do without, same samples)
+// uint64 [rows][nblk][16]
 hipError_t launch_sample(const float2* state, int64_t rows, int n, const double* uniforms, int64_t shots,
-                         unsigned long long* cum, long long* out, hipStream_t st);
+                         unsigned long long* cum, unsigned long long* sub, long long* out, hipStream_t st);
 
 // <P> of a Pauli string (X on xmask, Y on ymask, Z on zmask) per row; partial: rows * blocks * 2 doubles
 hipError_t launch_pauli(const float2* state, int64_t rows, int n, uint64_t xmask, uint64_t ymask,

@@ -983,3 +983,89 @@ def test_reverse_mode_gradient_of_the_last_phases_is_zero(oracle, n, rot, ent):
     lref, gref = oracle.param_shift_grad(x, n, ocirc(oracle, spec), p, None, 1)
     assert np.abs(got - gref).max() <= 1e-5
     ctx.close()
+
+
+# ------------------------------------------------------------------ measurement kernels by size
+@pytest.mark.parametrize("n,B", [(1, 5), (2, 3), (6, 9), (7, 4), (11, 130), (12, 3), (12, 2049), (13, 1), (13, 2000),
+                                 (15, 700), (16, 600), (17, 1024), (20, 17)])
+def test_expz_at_every_grouping(n, B):
+    """Rows of a wavefront, of a block, and blocks of 1 to 16 chunks, against double sums; the probabilities'
+    own rounding is 6e-8 relative."""
+    torch = gu.torch_cuda()
+    ctx = gu.make_ctx(n, B)
+    gen = torch.Generator(device="cuda").manual_seed(n + B)
+    ctx.state.normal_(generator=gen).mul_(2.0 ** (-n / 2 - 0.5))
+    z = torch.full((B, n), -7.0, device="cuda")
+    one = torch.full((B,), -7.0, device="cuda")
+    ctx.qsv_measure(qb.QSV_M_EXPZ_ALL, z)
+    ctx.qsv_measure(qb.QSV_M_EXPZ_ONE, one, qubit=n - 1)
+    p = ctx.state.double().square().sum(2)
+    tot = p.sum(1).max().item()
+    for q in range(n):
+        v = p.view(B, -1, 2, 1 << q).sum(3)
+        ref = (v[:, :, 0] - v[:, :, 1]).sum(1)
+        assert (z[:, q].double() - ref).abs().max().item() <= 2e-7 * tot, q
+    assert torch.equal(one, z[:, n - 1])
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,B,shots", [(1, 3, 5), (5, 2, 64), (12, 2, 129), (13, 3, 600), (14, 1, 5000), (18, 2, 1000)])
+def test_sampling_and_shot_means_by_size(n, B, shots):
+    """Draws against the integer rule in Python, one shot in 37; shot means against whole-number sums."""
+    torch = gu.torch_cuda()
+    ctx = gu.make_ctx(n, B)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    ctx.state.normal_(generator=gen).mul_(2.0 ** (-n / 2))
+    ctx.state[0, : (1 << n) // 2] = 0                      # empty chunks in front
+    u = torch.rand((B, shots), generator=gen, device="cuda", dtype=torch.float64)
+    s = torch.full((B, shots), -9, device="cuda", dtype=torch.int64)
+    probs = torch.zeros((B, 1 << n), device="cuda")
+    z = torch.zeros((B, n), device="cuda")
+    ctx.qsv_measure(qb.QSV_M_PROBS, probs)
+    ctx.qsv_measure(qb.QSV_M_SAMPLE, s, uniforms=u)
+    ctx.qsv_shot_expz(s, z)
+    w = np.floor(probs.cpu().numpy().astype(np.float64) * 2.0 ** 60).astype(np.uint64)
+    cum = np.cumsum(w, axis=1, dtype=np.uint64)
+    got, un = s.cpu().numpy(), u.cpu().numpy()
+    for b in range(B):
+        for i in list(range(0, shots, 37)) + [shots - 1]:
+            t = (int(np.floor(un[b, i] * 2.0 ** 53)) * int(cum[b, -1])) >> 53
+            assert got[b, i] == int(np.searchsorted(cum[b], np.uint64(t), side="right")), (b, i)
+    for q in range(n):
+        bits = (got >> q) & 1
+        ref = ((shots - 2.0 * bits.sum(1)) / shots).astype(np.float32)
+        assert np.array_equal(z.cpu().numpy()[:, q], ref)
+    ctx.close()
+
+
+def test_sampling_without_room_for_the_finer_sums():
+    """The fixed scratch array holds the block sums of 32768 chunks but not their 16 parts each: same draws."""
+    torch = gu.torch_cuda()
+    n, B, shots = 13, 16384, 3
+    ctx = gu.make_ctx(n, B)
+    ctx.state.normal_().mul_(2.0 ** (-n / 2))
+    u = torch.rand((B, shots), device="cuda", dtype=torch.float64)
+    a = torch.zeros((B, shots), device="cuda", dtype=torch.int64)
+    b = torch.ones((B, shots), device="cuda", dtype=torch.int64)
+    ctx.qsv_measure(qb.QSV_M_SAMPLE, a, uniforms=u)
+    ctx.qsv_measure_static(qb.QSV_M_SAMPLE, b, uniforms=u)
+    assert torch.equal(a, b)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,B,dim,shift", [(13, 2, 8192, 0), (13, 2, 8192, 1), (14, 3, 12289, 0), (15, 1, 20480, 1)])
+def test_fidelity_rows_that_start_anywhere(n, B, dim, shift):
+    """Rows of x on 8 bytes and off them (an odd dim, a pointer into the middle of a buffer)."""
+    torch = gu.torch_cuda()
+    ctx = gu.make_ctx(n, B)
+    ctx.state.normal_().mul_(2.0 ** (-n / 2))
+    buf = torch.randn(B * dim + shift, device="cuda")
+    x = buf[shift:].view(B, dim)
+    out = torch.zeros(B, device="cuda")
+    ctx.qsv_measure(qb.QSV_M_FIDELITY, out, x=x)
+    xd = x.double()
+    s = ctx.state.double()[:, :dim]
+    ref = (xd * s[:, :, 0]).sum(1).square() + (xd * s[:, :, 1]).sum(1).square()
+    ref = ref / xd.square().sum(1)
+    assert ((out.double() - ref).abs() <= 1e-6 * ref + 1e-12).all()
+    ctx.close()
