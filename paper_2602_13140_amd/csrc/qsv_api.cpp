@@ -721,7 +721,7 @@ qsv_status qsv_apply_layers(qsv_ctx* ctx, const qsv_circuit* c, const float* par
     // States small enough that launches cost more than arithmetic: the whole call in one launch, gates in
     // registers and lane exchanges (the kernel of qsv_forward_small, started from the state).
     if (ctx->opt_small_apply != 0 && ctx->n <= kSmallMaxQubits && ctx->opt_tile == 0 && !ctx->opt_naive &&
-        ((int64_t)ctx->batch << ctx->n) <= kSmallApplyAmplitudes) {
+        ((int64_t)ctx->batch << ctx->n) <= small_apply_amplitudes(ctx->n)) {
         const CircDev cd = to_dev(*c, ctx->n);
         const int regs = ctx->opt_small_regs ? ctx->opt_small_regs : small_choose_regs(cd, ctx->batch);
         if (regs != 0 && ctx->n - regs <= 8 && small_mats_per_group(cd, regs) <= kSmallMats) {

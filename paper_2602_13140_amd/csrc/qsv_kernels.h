@@ -112,7 +112,10 @@ hipError_t launch_encode_small(const float* x, int64_t samples, int64_t dim, int
 // fewer than 6 of them a wavefront holds 2^(6 - bits) samples.  A workgroup keeps the matrices of its
 // samples in LDS (at most kSmallMats).
 constexpr int kSmallMaxQubits = 10;
-constexpr int64_t kSmallApplyAmplitudes = (int64_t)1 << 21;   // batch * 2^n up to which one launch beats the fused passes
+// batch * 2^n up to which one launch beats the fused passes.  With 10 qubits the pass kernel has a tile per row
+// and takes the lead earlier (1024 rows, 6 layers: 32 against 36 us; 2048 rows: 49 against 41, 20 layers 186
+// against 91).
+constexpr int64_t small_apply_amplitudes(int n) { return (int64_t)1 << (n == 10 ? 20 : 21); }
 constexpr int kSmallMats = 512;   // matrices a workgroup keeps in LDS (16 KiB)
 inline int small_rows_per_group(int n, int regs) {
     const int tb = n > regs ? n - regs : 0;

@@ -653,9 +653,43 @@ __global__ __launch_bounds__(256) void k_naive_cz_ladder(float2* state, u64 tota
 // Fused per-(layer, qubit) matrices, computed in double and rounded once to float.
 struct M2 { double r[4], i[4]; };  // row-major 2x2: [0]=m00 [1]=m01 [2]=m10 [3]=m11
 
+// Sine and cosine in double.  Angles of up to 2^16 (any in use) are brought to |r| <= pi/4 by subtracting a multiple of
+// pi/2 held as the sum of two doubles, and the Taylor series up to r^17 and r^16 leave less than 1e-17: the
+// error is a few 1e-17, and the results are rounded to floats.
+__device__ __forceinline__ void sincos_angle(double x, double* s, double* c) {
+    if (!(fabs(x) <= 65536.0)) {                   // also infinities and NaN
+        sincos(x, s, c);
+        return;
+    }
+    const double k = rint(x * 0.6366197723675814);
+    const double r = fma(-k, 6.123233995736766e-17, fma(-k, 1.5707963267948966, x));
+    const double r2 = r * r;
+    double sp = 2.8114572543455206e-15, cp = 4.779477332387385e-14;
+    sp = fma(sp, r2, -7.647163731819816e-13);
+    sp = fma(sp, r2, 1.6059043836821613e-10);
+    sp = fma(sp, r2, -2.505210838544172e-08);
+    sp = fma(sp, r2, 2.7557319223985893e-06);
+    sp = fma(sp, r2, -0.0001984126984126984);
+    sp = fma(sp, r2, 0.008333333333333333);
+    sp = fma(sp, r2, -0.16666666666666666);
+    cp = fma(cp, r2, -1.1470745597729725e-11);
+    cp = fma(cp, r2, 2.08767569878681e-09);
+    cp = fma(cp, r2, -2.755731922398589e-07);
+    cp = fma(cp, r2, 2.48015873015873e-05);
+    cp = fma(cp, r2, -0.001388888888888889);
+    cp = fma(cp, r2, 0.041666666666666664);
+    cp = fma(cp, r2, -0.5);
+    sp = fma(r * r2, sp, r);
+    cp = fma(cp, r2, 1.0);
+    const int q = (int)k;
+    const double a = (q & 1) ? cp : sp, b = (q & 1) ? sp : cp;
+    *s = (q & 2) ? -a : a;
+    *c = ((q + 1) & 2) ? -b : b;
+}
+
 __device__ __forceinline__ M2 rot_m(int axis, double t) {
     double s, c;
-    sincos(0.5 * t, &s, &c);
+    sincos_angle(0.5 * t, &s, &c);
     M2 m;
     for (int k = 0; k < 4; ++k) { m.r[k] = 0.0; m.i[k] = 0.0; }
     if (axis == QSV_RX) { m.r[0] = c; m.i[1] = -s; m.i[2] = -s; m.r[3] = c; }
@@ -680,6 +714,22 @@ __device__ __forceinline__ M2 mul_m(const M2& a, const M2& b) {  // a * b
     return o;
 }
 
+// (a, b) = first column of R(axis, t) U from that of U; s, co = sin, cos of t / 2
+__device__ __forceinline__ void rotate_column(int axis, double s, double co, double& ar, double& ai, double& br,
+                                              double& bi) {
+    const double a0 = ar, a1 = ai, b0 = br, b1 = bi;
+    if (axis == QSV_RX) {
+        ar = co * a0 + s * b1; ai = co * a1 - s * b0;
+        br = co * b0 + s * a1; bi = co * b1 - s * a0;
+    } else if (axis == QSV_RY) {
+        ar = co * a0 - s * b0; ai = co * a1 - s * b1;
+        br = co * b0 + s * a0; bi = co * b1 + s * a1;
+    } else {
+        ar = co * a0 + s * a1; ai = co * a1 - s * a0;
+        br = co * b0 - s * b1; bi = co * b1 + s * b0;
+    }
+}
+
 // U(l,q) for one sample: slots applied in order (re-upload RX first), i.e. U = R_last ... R_first.
 // shift_slot >= 0 adds shift to that slot's angle.  All factors have the form [[a, -conj b], [b, conj a]], so
 // only the first column is multiplied up.
@@ -694,18 +744,8 @@ __device__ __forceinline__ M2 fused_raw(const CircDev& c, const float* params, c
         else axis = c.rot[sl - c.reupload];
         if (sl == shift_slot) t += shift;
         double s, co;
-        sincos(0.5 * t, &s, &co);
-        const double a0 = ar, a1 = ai, b0 = br, b1 = bi;
-        if (axis == QSV_RX) {
-            ar = co * a0 + s * b1; ai = co * a1 - s * b0;
-            br = co * b0 + s * a1; bi = co * b1 - s * a0;
-        } else if (axis == QSV_RY) {
-            ar = co * a0 - s * b0; ai = co * a1 - s * b1;
-            br = co * b0 + s * a0; bi = co * b1 + s * a1;
-        } else {
-            ar = co * a0 + s * a1; ai = co * a1 - s * a0;
-            br = co * b0 - s * b1; bi = co * b1 + s * b0;
-        }
+        sincos_angle(0.5 * t, &s, &co);
+        rotate_column(axis, s, co, ar, ai, br, bi);
     }
     if (inverse) { ai = -ai; br = -br; bi = -bi; }   // conjugate transpose
     M2 u;
@@ -2237,10 +2277,9 @@ __device__ __forceinline__ void small_cx_to_reg0(Amps<R>& a, bool ctrl) {  // co
 // permutation of the threads (src_f / src_r: the thread each one reads from), done by
 // ds_bpermute inside a wavefront and through LDS across wavefronts; the closing one swaps register
 // pairs in the threads whose top index bit is set.
-template <int R>
-__device__ __forceinline__ void small_ring(Amps<R>& a, int n, int tid, int tb, bool reverse, int src_f, int src_r,
-                                           Xchg& x) {
-    constexpr int NR = 1 << R;
+template <int R, int N>
+__device__ __forceinline__ void small_ring(Amps<R>& a, int tid, bool reverse, int src_f, int src_r, Xchg& x) {
+    constexpr int NR = 1 << R, n = N, tb = N > R ? N - R : 0;
     auto wrap = [&]() {
         if (n > R) small_cx_to_reg0<R>(a, (tid >> (tb - 1)) & 1);
         else if (n == 2) small_cx_rr<R, 1, 0>(a);
@@ -2285,9 +2324,9 @@ __device__ __forceinline__ void small_ring(Amps<R>& a, int n, int tid, int tb, b
 
 // CZ on qubits q and q + 1 for q = 0..n-2 (the gates commute, so the order does not matter): the
 // sign of an amplitude changes once for every pair of neighbouring set bits of its index.
-template <int R>
-__device__ __forceinline__ void small_cz_ladder(Amps<R>& a, int n, int ti) {
-    const int mask = (1 << (n - 1)) - 1;           // pairs (q, q + 1) for q = 0..n-2
+template <int R, int N>
+__device__ __forceinline__ void small_cz_ladder(Amps<R>& a, int ti) {
+    constexpr int mask = (1 << (N - 1)) - 1;           // pairs (q, q + 1) for q = 0..n-2
 #pragma unroll
     for (int k = 0; k < (1 << R); ++k) {
         const int idx = (ti << R) | k;
@@ -2311,64 +2350,102 @@ struct SmallArgs {
     float* out;            // probabilities [batch][2^n] or expectations [batch][n]
     float* norm_out;       // [batch] or NULL
     int mat_floats;        // LDS floats set aside for the workgroup's matrices (a multiple of 8)
+    int rows;              // samples per workgroup: at most what its lanes have room for
 };
 
-// dynamic LDS: [64] doubles for sums across wavefronts, the workgroup's matrices, then the exchange buffers
-template <int R>
+// Fused matrices of the samples first..first+rows_m-1 into LDS.  The angles and features come to LDS first, all
+// loads at once (read where they were needed, every matrix waited for them).  Neighbouring threads take the rotations of one matrix, a sine and cosine in double each, and
+// multiply up what they found.
+template <int N>
+__device__ __forceinline__ void small_build(const CircDev& c, const float* params, const float* feats, int64_t first,
+                                            int64_t batch, int rows_m, int tid, float* mats, float* stage) {
+    const int slots = c.reupload + c.n_rot, L = c.n_layers, n_par = L * slots * N, n_feat = c.reupload ? rows_m * N : 0;
+    const int64_t feat0 = first * N, feat_end = batch * N;
+    for (int i = tid; i < n_par; i += (int)blockDim.x) stage[i] = params[i];
+    for (int i = tid; i < n_feat; i += (int)blockDim.x) stage[n_par + i] = feat0 + i < feat_end ? feats[feat0 + i] : 0.f;
+    __syncthreads();
+    const int lg = slots > 2 ? 2 : slots - 1, count = (rows_m * L * N) << lg;
+    const int end = (count + (int)blockDim.x - 1) / (int)blockDim.x * (int)blockDim.x;
+    const float inv_l = 1.f / (float)L;
+    for (int i = tid; i < end; i += (int)blockDim.x) {       // every lane takes part in the exchanges
+        const int m = (i < count ? i : 0) >> lg, sl = i & ((1 << lg) - 1);
+        const int rl = m / N, q = m % N;
+        const int r = (int)(((float)rl + 0.5f) * inv_l), l = rl - r * L;      // rl < 2^9: exact
+        double sn = 0.0, co = 1.0;
+        if (sl < slots) {
+            double t = (double)stage[(l * slots + sl) * N + q];
+            if (c.reupload && sl == 0) t *= (double)stage[n_par + r * N + q];
+            sincos_angle(0.5 * t, &sn, &co);
+        }
+        double ar = 1.0, ai = 0.0, br = 0.0, bi = 0.0;
+        const int lane0 = (tid & 63) & ~((1 << lg) - 1);
+        for (int k = 0; k < slots; ++k) {
+            const double ks = __shfl(sn, lane0 + k, 64), kc = __shfl(co, lane0 + k, 64);
+            rotate_column(c.reupload && k == 0 ? (int)QSV_RX : c.rot[k - c.reupload], ks, kc, ar, ai, br, bi);
+        }
+        if (sl == 0 && i < count) {
+            float4* o = reinterpret_cast<float4*>(mats + (size_t)m * 8);
+            o[0] = make_float4((float)ar, (float)ai, (float)-br, (float)bi);
+            o[1] = make_float4((float)br, (float)bi, (float)ar, (float)-ai);
+        }
+    }
+}
+
+// dynamic LDS: [64] doubles for sums across wavefronts, the workgroup's matrices, then the exchange buffers (which
+// hold the angles and features while the matrices are built)
+// The number of qubits is a template argument: with it at run time every gate stood behind a branch, which kept
+// the matrices' loads and the exchanges of neighbouring gates from overlapping.
+template <int R, int N>
 __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
     constexpr int NR = 1 << R;
     extern __shared__ __align__(16) unsigned char small_lds[];
     double* red = reinterpret_cast<double*>(small_lds);
     float* mats = reinterpret_cast<float*>(small_lds + 64 * sizeof(double));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = a.c.n, L = a.c.n_layers;
-    const int tb = n > R ? n - R : 0;            // index bits held by the thread number
-    const int lb = tb < 6 ? tb : 6;              // of which inside the wavefront
-    const int n_waves = (int)blockDim.x >> 6;    // 2^(tb - 6) when tb > 6, else 1
-    const int rows_g = 64 >> lb;                 // samples per workgroup (1 when tb >= 6)
+    constexpr int n = N;
+    const int L = a.c.n_layers;
+    constexpr int tb = n > R ? n - R : 0;        // index bits held by the thread number
+    constexpr int lb = tb < 6 ? tb : 6;          // of which inside the wavefront
+    constexpr int n_waves = tb > 6 ? 1 << (tb - 6) : 1;
+    constexpr int rows_g = 64 >> lb;             // samples per workgroup (1 when tb >= 6)
     const int r_in = tb < 6 ? lane >> tb : 0;
     const int ti = tid & ((1 << tb) - 1);
     Xchg xc;
     xc.buf = mats + a.mat_floats;
     xc.threads = (int)blockDim.x;
     xc.cur = 0;
-    const int64_t first = (int64_t)blockIdx.x * rows_g;
+    const int64_t first = (int64_t)blockIdx.x * a.rows;
     const int64_t sample = first + r_in;
-    const bool live = sample < a.batch;
+    const bool live = r_in < a.rows && sample < a.batch;
     const int per = L * n;
     const bool has_u = a.c.reupload + a.c.n_rot > 0;
-    if (has_u) {
-        const int rows_m = a.c.reupload ? rows_g : 1;
-        for (int i = tid; i < rows_m * per; i += (int)blockDim.x) {
-            const int r = i / per, lq = i % per;
-            const int64_t s = first + r < a.batch ? first + r : a.batch - 1;
-            const M2 u = fused_raw(a.c, a.params, a.feats, (u64)s, lq / n, lq % n, -1, 0.0, 0);
-            float* o = mats + (size_t)i * 8;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) { o[2 * k] = (float)u.r[k]; o[2 * k + 1] = (float)u.i[k]; }
-        }
-    }
-    // amplitude encoding: x / ||x||, the norm in double (or the amplitudes the state already holds)
+    // what the circuit starts from is on its way while the matrices are built
     Amps<R> A;
+    const bool inside = live && ((int64_t)ti << R) < ((int64_t)1 << n);
     if (a.from_state) {
         const float2* srow = a.state + ((live ? sample : 0) << n) + ((int64_t)ti << R);
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             const int64_t idx = ((int64_t)ti << R) | k;
-            const float2 v = (live && idx < ((int64_t)1 << n)) ? srow[k] : make_float2(0.f, 0.f);
+            const float2 v = (inside && idx < ((int64_t)1 << n)) ? srow[k] : make_float2(0.f, 0.f);
             A.re[k] = v.x; A.im[k] = v.y;
         }
     } else {
         const float* xb = a.x + (live ? sample : 0) * a.dim;
-        float xv[NR];
-        double ss = 0.0;
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             const int64_t idx = ((int64_t)ti << R) | k;
-            const float v = (live && idx < a.dim) ? xb[idx] : 0.f;
-            xv[k] = v;
-            ss += (double)v * (double)v;
+            A.re[k] = (live && idx < a.dim) ? xb[idx] : 0.f;
+            A.im[k] = 0.f;
         }
+    }
+    if (has_u)
+        small_build<N>(a.c, a.params, a.feats, first, a.batch, a.c.reupload ? a.rows : 1, tid, mats, xc.buf);
+    // amplitude encoding: x / ||x||, the norm in double
+    if (!a.from_state) {
+        double ss = 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) ss += (double)A.re[k] * (double)A.re[k];
 #pragma unroll
         for (int b = 0; b < 6; ++b)
             if (b < lb) ss += __shfl_xor(ss, 1 << b, 64);
@@ -2381,11 +2458,11 @@ __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
         const double nrm = sqrt(ss);
         const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
 #pragma unroll
-        for (int k = 0; k < NR; ++k) { A.re[k] = (float)((double)xv[k] * inv); A.im[k] = 0.f; }
+        for (int k = 0; k < NR; ++k) A.re[k] = (float)((double)A.re[k] * inv);
         if (a.norm_out && live && ti == 0) a.norm_out[sample] = (float)nrm;
     }
     __syncthreads();                             // the matrices are in LDS; red[] may be written again
-    const float* mrow = mats + (size_t)(a.c.reupload ? r_in * per : 0) * 8;
+    const float* mrow = mats + (size_t)(a.c.reupload && live ? r_in * per : 0) * 8;
     // Thread permutations of the ring's CNOTs between thread bits (qubits R..n-1): an amplitude in
     // thread j moves to C(j), so afterwards thread j holds what thread C_first(...C_last(j)) held.
     int src_f = tid, src_r = tid;
@@ -2398,8 +2475,8 @@ __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
             const int l = pass ? L - 1 - ll : ll;
             for (int stage = 0; stage < 2; ++stage) {
                 if ((stage == 0) == (pass == 1)) {
-                    if (a.entangler == QSV_ENT_CNOT_RING) small_ring<R>(A, n, tid, tb, pass != 0, src_f, src_r, xc);
-                    else if (a.entangler == QSV_ENT_CZ_LADDER) small_cz_ladder<R>(A, n, ti);
+                    if (a.entangler == QSV_ENT_CNOT_RING) small_ring<R, N>(A, tid, pass != 0, src_f, src_r, xc);
+                    else if (a.entangler == QSV_ENT_CZ_LADDER) small_cz_ladder<R, N>(A, ti);
                 } else if (has_u) {
                     const float* ml = mrow + (size_t)l * n * 8;
                     auto load_m = [&](int q, float* m) {
@@ -2415,7 +2492,7 @@ __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
                     };
                     float m[8];
 #define QSV_SMALL_U(Q)                                                      \
-    if (n > Q) {                                                            \
+    if constexpr (n > Q) {                                                  \
         load_m(Q, m);                                                       \
         if constexpr (Q < R) small_u_reg<R, Q>(A, m);                       \
         else if constexpr (Q - R < 8) small_u_thr<R, Q - R>(A, m, tid, xc); \
@@ -2693,18 +2770,32 @@ hipError_t launch_forward_small(int regs, const float* x, int64_t dim, int64_t b
     a.x = x; a.dim = dim; a.batch = batch; a.c = c; a.entangler = entangler; a.params = params; a.feats = feats;
     a.pass_first = pass_first; a.pass_last = pass_last; a.from_state = x ? 0 : 1; a.kind = kind;
     a.state = state; a.out = out; a.norm_out = norm_out;
-    const int64_t blocks = (batch + rows_g - 1) / rows_g;
+    // Per-sample matrices are most of such a launch's work (a wavefront of 16 samples builds them for 18 us, 4 qubits,
+    // 6 layers), so while the chip has wavefronts to spare (eight per CU) the samples spread over them.
+    a.rows = rows_g;
+    if (c.reupload && rows_g > 1) {
+        const int64_t spread = (batch + 2047) / 2048;
+        if (spread < rows_g) a.rows = (int)spread;
+    }
+    const int64_t blocks = (batch + a.rows - 1) / a.rows;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     // sums across wavefronts, the matrices (only as many as this circuit has: LDS per workgroup decides how
     // many workgroups a CU holds), and (several wavefronts per sample only) two exchange buffers
-    a.mat_floats = (int)small_mats_per_group(c, regs) * 8;
+    a.mat_floats = (int)(c.slots() ? (c.reupload ? a.rows : 1) * c.n_layers * c.n : 0) * 8;
     size_t lds = 64 * sizeof(double) + (size_t)a.mat_floats * sizeof(float);
-    if (threads > 64) lds += 2 * (size_t)(2 << regs) * threads * sizeof(float);
+    const size_t stage = a.mat_floats ? ((size_t)c.n_layers * c.slots() * c.n + (c.reupload ? (size_t)a.rows * c.n : 0)) * sizeof(float) : 0;
+    const size_t exchange = threads > 64 ? 2 * (size_t)(2 << regs) * threads * sizeof(float) : 0;
+    lds += stage > exchange ? stage : exchange;
     const dim3 grid((unsigned)blocks), block(threads);
-    switch (regs) {
-        case 2: hipLaunchKernelGGL(k_forward_small<2>, grid, block, lds, st, a); break;
-        case 3: hipLaunchKernelGGL(k_forward_small<3>, grid, block, lds, st, a); break;
-        default: hipLaunchKernelGGL(k_forward_small<4>, grid, block, lds, st, a); break;
+    switch (regs * 16 + c.n) {
+#define QSV_SMALL(R, N) \
+    case R * 16 + N: hipLaunchKernelGGL((k_forward_small<R, N>), grid, block, lds, st, a); break;
+#define QSV_SMALL_ALL(R) QSV_SMALL(R, 1) QSV_SMALL(R, 2) QSV_SMALL(R, 3) QSV_SMALL(R, 4) QSV_SMALL(R, 5) QSV_SMALL(R, 6) \
+                         QSV_SMALL(R, 7) QSV_SMALL(R, 8) QSV_SMALL(R, 9) QSV_SMALL(R, 10)
+        QSV_SMALL_ALL(2) QSV_SMALL_ALL(3) QSV_SMALL_ALL(4)
+#undef QSV_SMALL_ALL
+#undef QSV_SMALL
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

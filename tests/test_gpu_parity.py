@@ -1069,3 +1069,27 @@ def test_fidelity_rows_that_start_anywhere(n, B, dim, shift):
     ref = ref / xd.square().sum(1)
     assert ((out.double() - ref).abs() <= 1e-6 * ref + 1e-12).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("n,B,L,reup", [(2, 3, 4, 1), (4, 70, 8, 1), (4, 2500, 2, 1), (5, 2049, 3, 1), (8, 3, 6, 1), (9, 5, 4, 0),
+                                        (3, 40000, 2, 1)])
+def test_one_launch_with_every_number_of_samples_per_workgroup(oracle, n, B, L, reup):
+    """Re-uploading samples spread over one workgroup each up to 2048, more than one beyond; large angles take the
+    sine and cosine past the short reduction."""
+    spec = wl.CircuitSpec(L, (RY, RZ, RX), RING, reup)
+    g = rng(n * 7 + B)
+    p = g.uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32)
+    p[:: 5] = np.float32(3.0e5) * g.standard_normal(p[:: 5].shape).astype(np.float32)
+    x = g.standard_normal((B, 1 << n)).astype(np.float32)
+    f = g.standard_normal((B, n)).astype(np.float32)
+    ref, _ = oracle.amp_encode(x, n)
+    oracle.apply_layers(ref, ocirc(oracle, spec), p, f if reup else None)
+    z = oracle.expz_all(ref)
+    torch = gu.torch_cuda()
+    ctx = gu.make_ctx(n, B)
+    out = torch.zeros((B, n), device="cuda")
+    ctx.qsv_forward_small(gu.dev(x), qb.circuit_from_spec(spec), gu.dev(p), gu.dev(f) if reup else None, 0,
+                          qb.QSV_M_EXPZ_ALL, out)
+    assert np.abs(out.cpu().numpy() - z).max() <= 1e-5
+    assert np.abs(gu.state_np(ctx) - ref).max() <= 1e-5
+    ctx.close()
