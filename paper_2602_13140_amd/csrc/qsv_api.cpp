@@ -1158,6 +1158,25 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
     double* inv = (double*)ar.take((size_t)B * 8);
     double* f = (double*)ar.take((size_t)B * per * 8);
     if (!npart || !inv || !f) return ws_fail(ctx, ar, "qsv_adjoint_grad");
+
+    // Small states: the whole sweep in one launch, where the scratch has room for its sums.
+    if (ctx->opt_small_apply != 0 && n <= kSmallMaxQubits && P > 0 && ctx->opt_tile == 0 && !ctx->opt_naive &&
+        ctx->opt_grad_layered && ctx->opt_grad_chunk == 0 && (int64_t)c->n_layers * n <= kSmallMats) {
+        Arena sm = ar;       // what is taken here is given back if it does not fit
+        float* mats = (float*)sm.take(mats_table_bytes(*c, n, B));
+        double* sums = (double*)sm.take((size_t)B * c->n_layers * sweep_record_bytes(n));
+        if (mats && sums) {
+            QSV_HIP(ctx, launch_build_mats(cd, params_dev, feats_dev, B, 1, nullptr, 0, MatForm::plain, mats, nullptr, ctx->stream),
+                    "build matrices");
+            QSV_HIP(ctx, launch_sweep_small(x_dev, dim, B, cd, c->entangler, params_dev, mats, kind, obs_qubit, mask,
+                                            targets_dev, sums, f, ctx->stream),
+                    "small sweep");
+            QSV_HIP(ctx, launch_grad_finish(f, B, P, cd, feats_dev, loss_dev, grad_dev, mean_loss_dev, mean_grad_dev,
+                                            ctx->stream),
+                    "grad finish");
+            return QSV_OK;
+        }
+    }
     QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
 
     // Two ways to have psi at the start of every layer on the way back.  With room for L + 1 states per

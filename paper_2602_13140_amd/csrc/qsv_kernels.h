@@ -144,6 +144,12 @@ inline int small_choose_regs(const CircDev& c, int64_t batch) {
 hipError_t launch_forward_small(int regs, const float* x, int64_t dim, int64_t batch, const CircDev& c, int entangler,
                                 const float* params, const float* feats, int pass_first, int pass_last, int kind,
                                 float2* state, float* out, float* norm_out, hipStream_t st);
+// Reverse-mode gradient of a whole small batch (see k_sweep_small) into f[batch][2P+1]; back: the plain table of the
+// inverse circuit in natural order; sums: batch * n_layers * sweep_record_bytes(n) bytes.  At most kSmallMats unitaries.
+hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const CircDev& c, int entangler,
+                              const float* params, const float* back, int kind, int q, uint64_t mask, const float* targets,
+                              double* sums, double* f, hipStream_t st);
+inline size_t sweep_record_bytes(int n) { return (size_t)(n > 8 ? 1 << (n - 8) : 1) * 32 * 8; }
 hipError_t launch_encode_write(const float* x, int64_t dim, int n, int64_t rows, const double* inv_norm,
                                const RowMap& rm, float2* state, hipStream_t st);
 

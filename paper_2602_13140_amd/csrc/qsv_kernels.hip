@@ -2077,31 +2077,15 @@ __global__ __launch_bounds__(256) void k_trans_finish(const double* partial, int
     }
 }
 
-// Gradients of one layer from the transition matrices: thread = (row pair, slot, qubit).  With U the
-// qubit's unitary and V = R_last ... R_{s+1} its slots after s, the derivative with respect to the angle of
-// slot s is 2 Re sum_ab Bt[a][b] M[a][b], Bt = U^dagger V (-i/2 P_s) V^dagger U.  U^dagger is taken from the
+// Derivative with respect to the angle of slot s on qubit q of a layer, from the qubit's transition sums M at the
+// layer's start.  With U the qubit's unitary and V = R_last ... R_{s+1} its slots after s it is
+// 2 Re sum_ab Bt[a][b] M[a][b], Bt = U^dagger V (-i/2 P_s) V^dagger U.  U^dagger (ud) is taken from the
 // table that lambda came back through, as rounded as it is there: a derivative that vanishes because the
 // rest of the circuit commutes with P_s then vanishes here too, up to the sums' rounding.
-// Written as f+ = g, f- = -g so that the same finishing kernels as for the shift rule apply (they halve the
-// difference and multiply re-upload weights by the feature).
-__global__ __launch_bounds__(256) void k_adj_layer(const double* partial, int nblk, CircDev c, int layer,
-                                                   const float* params, const float* feats, u64 sample0,
-                                                   u64 pairs_rows, u64 P, const float* back, const int* exec_of,
-                                                   int plain, int seq0, int seq_stride, double* f) {
-    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ double adj_derivative(const double (&M)[8], const M2& ud, const CircDev& c, int layer, int s, int q,
+                                                 const float* params) {
     const int slots = c.reupload + c.n_rot;
-    const u64 per = (u64)slots * c.n;
-    if (idx >= pairs_rows * per) return;
-    const u64 r = idx / per;
-    const int s = (int)((idx % per) / c.n), q = (int)(idx % c.n);
-    const u64 sample = sample0 + r;
-    double M[8];
-    for (int j = 0; j < 8; ++j) M[j] = 0.0;
-    const double* pp = partial + ((r * c.n + q) * (u64)nblk) * 8;
-    for (int b = 0; b < nblk; ++b)
-        for (int j = 0; j < 8; ++j) M[j] += pp[(u64)b * 8 + j];
-    const u64 entry = (c.reupload ? sample * (u64)c.n_layers * c.n : 0) + (u64)layer * c.n + (exec_of ? exec_of[q] : q);
-    M2 w = entry_m(back + entry * 8, plain || q + 1 == c.n, seq0, seq_stride);   // U^dagger, then times V
+    M2 w = ud;                                       // then times V
     auto axis_of = [&](int sl) { return c.reupload && sl == 0 ? (int)QSV_RX : c.rot[sl - c.reupload]; };
     for (int sl = slots - 1; sl > s; --sl)          // never the re-upload slot
         w = mul_m(w, rot_m(axis_of(sl), (double)params[((u64)layer * slots + sl) * c.n + q]));
@@ -2124,10 +2108,61 @@ __global__ __launch_bounds__(256) void k_adj_layer(const double* partial, int nb
     bool vanishes = layer + 1 == c.n_layers;
     for (int sl = s; sl < slots; ++sl) vanishes = vanishes && axis_of(sl) == QSV_RZ;
     if (vanishes) acc *= 0.0;
+    return 2.0 * acc;
+}
+
+// Gradients of one layer: thread = (row pair, slot, qubit).  Written as f+ = g, f- = -g so that the same
+// finishing kernels as for the shift rule apply (they halve the difference and multiply re-upload weights
+// by the feature).
+__global__ __launch_bounds__(256) void k_adj_layer(const double* partial, int nblk, CircDev c, int layer,
+                                                   const float* params, u64 sample0, u64 pairs_rows, u64 P,
+                                                   const float* back, const int* exec_of, int plain, int seq0,
+                                                   int seq_stride, double* f) {
+    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
+    const int slots = c.reupload + c.n_rot;
+    const u64 per = (u64)slots * c.n;
+    if (idx >= pairs_rows * per) return;
+    const u64 r = idx / per;
+    const int s = (int)((idx % per) / c.n), q = (int)(idx % c.n);
+    const u64 sample = sample0 + r;
+    double M[8];
+    for (int j = 0; j < 8; ++j) M[j] = 0.0;
+    const double* pp = partial + ((r * c.n + q) * (u64)nblk) * 8;
+    for (int b = 0; b < nblk; ++b)
+        for (int j = 0; j < 8; ++j) M[j] += pp[(u64)b * 8 + j];
+    const u64 entry = (c.reupload ? sample * (u64)c.n_layers * c.n : 0) + (u64)layer * c.n + (exec_of ? exec_of[q] : q);
+    const double g = adj_derivative(M, entry_m(back + entry * 8, plain || q + 1 == c.n, seq0, seq_stride), c, layer, s, q,
+                                    params);
     const u64 p = ((u64)layer * slots + s) * c.n + q;
     double* fb = f + sample * (2 * P + 1);
-    fb[2 * p] = 2.0 * acc;
-    fb[2 * p + 1] = -2.0 * acc;
+    fb[2 * p] = g;
+    fb[2 * p + 1] = -g;
+}
+
+// The same for all layers of the samples that k_sweep_small took: thread = (sample, parameter); sums as that kernel
+// writes them.  back: the plain table of the inverse circuit in natural order.
+__global__ __launch_bounds__(256) void k_adj_all(const double* sums, int waves, CircDev c, const float* params, u64 rows,
+                                                 const float* back, double* f) {
+    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
+    const int slots = c.reupload + c.n_rot;
+    const u64 P = (u64)c.n_layers * slots * c.n;
+    if (idx >= rows * P) return;
+    const u64 sample = idx / P, p = idx % P;
+    const int q = (int)(p % c.n), s = (int)(p / c.n % slots), l = (int)(p / ((u64)c.n * slots));
+    const double* rec = sums + (sample * c.n_layers + l) * (u64)waves * 32;
+    double t = 0.0, m00 = 0.0, kre = 0.0, kim = 0.0;
+    for (int w = 0; w < waves; ++w) {
+        t += rec[w * 32];
+        m00 += rec[w * 32 + 1 + 3 * q];
+        kre += rec[w * 32 + 2 + 3 * q];
+        kim += rec[w * 32 + 3 + 3 * q];
+    }
+    const double M[8] = {0.0, m00, kre, kim, 0.0, 0.0, 0.0, t - m00};
+    const u64 entry = (c.reupload ? sample * (u64)c.n_layers * c.n : 0) + (u64)l * c.n + q;
+    const double g = adj_derivative(M, entry_m(back + entry * 8, true, 0, 1), c, l, s, q, params);
+    double* fb = f + sample * (2 * P + 1);
+    fb[2 * p] = g;
+    fb[2 * p + 1] = -g;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2596,6 +2631,263 @@ __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
     }
 }
 
+// Reverse-mode sweep of small states (at most 10 qubits) in one launch: encoding, circuit, loss, lambda = O psi, then
+// both states back through the layers, and at every layer's start the transition sums of all qubits, which are
+// all that leaves the chip.  The layout is that of k_forward_small.  Through the fused passes the same takes six
+// launches per layer, each of which reads and writes the states: 10 qubits x 1024 re-uploading 6 layers 355 -> 102 us,
+// 8 x 64 302 -> 39 us, 4 x 1 178 -> 24 us.
+struct SweepArgs {
+    const float* x;          // [batch][dim]
+    int64_t dim, batch;
+    CircDev c;
+    int entangler;
+    const float* back;       // plain table of the inverse circuit in natural order
+    int rows;                // samples per workgroup
+    int mat_floats;          // LDS floats of the workgroup's matrices
+    int kind, obs_qubit;     // as launch_adj_init
+    u64 mask;
+    const float* targets;    // kind 2: [batch][n]
+    double* f;               // [batch][2P + 1]: the loss goes to entry 2P
+    double* sums;            // [batch][L][wavefronts of a sample][32]: sum of d, then 3 per qubit (see k_adj_all)
+};
+
+// Sums 32 values over the lanes of a sample (2^LB of them, LB <= 6): in step b lanes that differ in bit b split the
+// values between them, so that a lane ends with 32 >> LB of them (at least one), number first..first + that - 1.
+template <int H>
+__device__ __forceinline__ void reduce_step(double (&v)[32], int mask) {   // H: half of the values still held
+    const bool up = threadIdx.x & mask;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const double lo = v[i], hi = v[i + H];
+        const double keep = up ? hi : lo, give = up ? lo : hi;
+        v[i] = keep + __shfl_xor(give, mask, 64);
+    }
+}
+
+template <int LB>
+__device__ __forceinline__ int reduce32(double (&v)[32]) {
+    const int lane = threadIdx.x & 63;
+    if constexpr (LB > 0) reduce_step<16>(v, 1);
+    if constexpr (LB > 1) reduce_step<8>(v, 2);
+    if constexpr (LB > 2) reduce_step<4>(v, 4);
+    if constexpr (LB > 3) reduce_step<2>(v, 8);
+    if constexpr (LB > 4) reduce_step<1>(v, 16);
+    if constexpr (LB > 5) v[0] += __shfl_xor(v[0], 32, 64);
+    int first = 0;
+#pragma unroll
+    for (int b = 0; b < (LB < 5 ? LB : 5); ++b) first += (lane >> b) & 1 ? 16 >> b : 0;
+    return first;
+}
+
+// the values that another thread of the sample holds for thread bit B
+template <int R, int B>
+__device__ __forceinline__ void small_partner(const Amps<R>& a, float* pr, float* pi, int tid, Xchg& x) {
+    if constexpr (B < 6) {
+        const int addr = ((tid & 63) ^ (1 << B)) << 2;
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) { pr[k] = lane_flip<B>(a.re[k], addr); pi[k] = lane_flip<B>(a.im[k], addr); }
+    } else {
+        xchg_through_lds<R>(a, pr, pi, x, tid, tid ^ (1 << B));
+    }
+}
+
+// Im M00, Re K, Im K of qubit Q (see trans_acc) from this thread's amplitudes; d = Im conj(lambda) psi, dsum its sum
+template <int R, int Q>
+__device__ __forceinline__ void small_trans(const Amps<R>& s, const Amps<R>& l, const float (&d)[1 << R], float dsum, int tid,
+                                            Xchg& x, float (&acc)[3]) {
+    acc[0] = acc[1] = acc[2] = 0.f;
+    if constexpr (Q < R) {
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) {
+            if (k & (1 << Q)) continue;
+            const int k1 = k | (1 << Q);
+            acc[0] += d[k];
+            acc[1] += (l.re[k] * s.re[k1] + l.im[k] * s.im[k1]) - (l.re[k1] * s.re[k] + l.im[k1] * s.im[k]);
+            acc[2] += (l.re[k] * s.im[k1] - l.im[k] * s.re[k1]) + (l.re[k1] * s.im[k] - l.im[k1] * s.re[k]);
+        }
+    } else {
+        float pr[1 << R], pi[1 << R];
+        small_partner<R, Q - R>(s, pr, pi, tid, x);
+        const bool bit = (tid >> (Q - R)) & 1;
+        float re = 0.f;
+#pragma unroll
+        for (int k = 0; k < (1 << R); ++k) {
+            re += l.re[k] * pr[k] + l.im[k] * pi[k];
+            acc[2] += l.re[k] * pi[k] - l.im[k] * pr[k];
+        }
+        acc[0] = bit ? 0.f : dsum;
+        acc[1] = bit ? -re : re;
+    }
+}
+
+template <int R, int N>
+__global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
+    constexpr int NR = 1 << R, n = N;
+    constexpr int tb = n > R ? n - R : 0, lb = tb < 6 ? tb : 6, n_waves = tb > 6 ? 1 << (tb - 6) : 1;
+    extern __shared__ __align__(16) unsigned char small_lds[];
+    double* red = reinterpret_cast<double*>(small_lds);
+    float* mats = reinterpret_cast<float*>(small_lds + 64 * sizeof(double));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int L = a.c.n_layers, per = L * n;
+    const int r_in = tb < 6 ? lane >> tb : 0;
+    const int ti = tid & ((1 << tb) - 1);
+    Xchg xc;
+    xc.buf = mats + a.mat_floats;
+    xc.threads = (int)blockDim.x;
+    xc.cur = 0;
+    const int64_t first = (int64_t)blockIdx.x * a.rows;
+    const int64_t sample = first + r_in;
+    const bool live = r_in < a.rows && sample < a.batch;
+    const u64 P = (u64)per * (a.c.reupload + a.c.n_rot);
+    Amps<R> S, La;
+    const float* xb = a.x + (live ? sample : 0) * a.dim;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        const int64_t idx = ((int64_t)ti << R) | k;
+        S.re[k] = (live && idx < a.dim) ? xb[idx] : 0.f;
+        S.im[k] = 0.f;
+    }
+    {
+        const int64_t rows_m = a.c.reupload ? (a.batch - first < a.rows ? a.batch - first : a.rows) : 1;
+        const float4* src = reinterpret_cast<const float4*>(a.back + (a.c.reupload ? first * per * 8 : 0));
+        float4* dst = reinterpret_cast<float4*>(mats);
+        for (int i = tid; i < (int)rows_m * per * 2; i += (int)blockDim.x) dst[i] = src[i];
+    }
+    auto sample_sum = [&](double v) -> double {      // over the threads of the sample
+#pragma unroll
+        for (int b = 0; b < 6; ++b)
+            if (b < lb) v += __shfl_xor(v, 1 << b, 64);
+        if constexpr (n_waves > 1) {
+            __syncthreads();
+            if (lane == 0) red[wave] = v;
+            __syncthreads();
+            v = 0.0;
+            for (int w = 0; w < n_waves; ++w) v += red[w];
+        }
+        return v;
+    };
+    {
+        double ss = 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) ss += (double)S.re[k] * (double)S.re[k];
+        const double nrm = sqrt(sample_sum(ss)), inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) S.re[k] = (float)((double)S.re[k] * inv);
+    }
+    __syncthreads();                                 // the matrices are in LDS
+    const float* mrow = mats + (size_t)(a.c.reupload && live ? r_in * per : 0) * 8;
+    int src_f = tid, src_r = tid;
+    for (int b = tb - 2; b >= 0; --b) src_f ^= ((src_f >> b) & 1) << (b + 1);
+    for (int b = 0; b + 1 < tb; ++b) src_r ^= ((src_r >> b) & 1) << (b + 1);
+    auto entangle = [&](Amps<R>& A, bool reverse) {
+        if (a.entangler == QSV_ENT_CNOT_RING) small_ring<R, N>(A, tid, reverse, src_f, src_r, xc);
+        else if (a.entangler == QSV_ENT_CZ_LADDER) small_cz_ladder<R, N>(A, ti);
+    };
+#define QSV_ALL_Q(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9)
+    for (int l = 0; l < L; ++l) {
+        const float* ml = mrow + (size_t)l * n * 8;
+        float m[8];
+#define QSV_FWD(Q)                                                                          \
+    if constexpr (n > Q) {                                                                  \
+        const float4 lo = *reinterpret_cast<const float4*>(ml + Q * 8);                     \
+        const float4 hi = *reinterpret_cast<const float4*>(ml + Q * 8 + 4);                 \
+        m[0] = lo.x; m[1] = -lo.y; m[2] = hi.x; m[3] = -hi.y;                               \
+        m[4] = lo.z; m[5] = -lo.w; m[6] = hi.z; m[7] = -hi.w;                               \
+        if constexpr (Q < R) small_u_reg<R, Q>(S, m);                                       \
+        else if constexpr (Q - R < 8) small_u_thr<R, Q - R>(S, m, tid, xc);                 \
+    }
+        QSV_ALL_Q(QSV_FWD)
+#undef QSV_FWD
+        entangle(S, false);
+    }
+    // the loss, and lambda = (diagonal weight) psi
+    double loss = 0.0, coef[N];
+    if (a.kind == 2) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            double z = 0.0;
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                const double p = (double)prob32(make_float2(S.re[k], S.im[k]));
+                z += ((((ti << R) | k) >> q) & 1) ? -p : p;
+            }
+            const double off = sample_sum(z) - (double)a.targets[(live ? sample : 0) * n + q];
+            loss += off * off;
+            coef[q] = 2.0 * off / n;
+        }
+        loss /= n;
+    } else {
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const unsigned idx = ((unsigned)ti << R) | k;
+            const double p = (double)prob32(make_float2(S.re[k], S.im[k]));
+            if (a.kind == 0) v += ((idx >> a.obs_qubit) & 1u) ? -p : p;
+            else v += (idx & (unsigned)a.mask) ? 0.0 : p;
+        }
+        v = sample_sum(v);
+        loss = a.kind == 0 ? v : 1.0 - v;
+    }
+    if (live && ti == 0) a.f[sample * (2 * P + 1) + 2 * P] = loss;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        const unsigned idx = ((unsigned)ti << R) | k;
+        float w;
+        if (a.kind == 0) w = ((idx >> a.obs_qubit) & 1u) ? -1.f : 1.f;
+        else if (a.kind == 1) w = (idx & (unsigned)a.mask) ? 0.f : -1.f;
+        else {
+            double wd = 0.0;
+#pragma unroll
+            for (int q = 0; q < N; ++q) wd += ((idx >> q) & 1u) ? -coef[q] : coef[q];
+            w = (float)wd;
+        }
+        La.re[k] = w * S.re[k];
+        La.im[k] = w * S.im[k];
+    }
+    for (int l = L - 1; l >= 0; --l) {
+        entangle(S, true);
+        entangle(La, true);
+        const float* ml = mrow + (size_t)l * n * 8;
+        float m[8];
+#define QSV_BACK(Q)                                                                         \
+    if constexpr (n > Q) {                                                                  \
+        const float4 lo = *reinterpret_cast<const float4*>(ml + Q * 8);                     \
+        const float4 hi = *reinterpret_cast<const float4*>(ml + Q * 8 + 4);                 \
+        m[0] = lo.x; m[1] = lo.y; m[2] = lo.z; m[3] = lo.w;                                 \
+        m[4] = hi.x; m[5] = hi.y; m[6] = hi.z; m[7] = hi.w;                                 \
+        if constexpr (Q < R) { small_u_reg<R, Q>(S, m); small_u_reg<R, Q>(La, m); }         \
+        else if constexpr (Q - R < 8) { small_u_thr<R, Q - R>(S, m, tid, xc); small_u_thr<R, Q - R>(La, m, tid, xc); } \
+    }
+        QSV_ALL_Q(QSV_BACK)
+#undef QSV_BACK
+        float d[NR], dsum = 0.f;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            d[k] = La.re[k] * S.im[k] - La.im[k] * S.re[k];
+            dsum += d[k];
+        }
+        double v[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = 0.0;
+        v[0] = (double)dsum;
+#define QSV_SUMS(Q)                                                                         \
+    if constexpr (n > Q) {                                                                  \
+        float acc[3];                                                                       \
+        small_trans<R, Q>(S, La, d, dsum, tid, xc, acc);                                    \
+        v[1 + 3 * Q] = (double)acc[0]; v[2 + 3 * Q] = (double)acc[1]; v[3 + 3 * Q] = (double)acc[2]; \
+    }
+        QSV_ALL_Q(QSV_SUMS)
+#undef QSV_SUMS
+        const int v0 = reduce32<lb>(v);
+        if (live && (lb < 6 || lane < 32)) {
+            double* rec = a.sums + ((sample * L + l) * n_waves + wave) * 32 + v0;
+#pragma unroll
+            for (int i = 0; i < (lb < 5 ? 32 >> lb : 1); ++i) rec[i] = v[i];
+        }
+    }
+#undef QSV_ALL_Q
+}
+
 inline unsigned blocks_for(u64 items, unsigned per) { return (unsigned)((items + per - 1) / per); }
 
 // grid of the reduction kernels: chunks in x, rows over y and z (see grid_row)
@@ -2797,6 +3089,44 @@ hipError_t launch_forward_small(int regs, const float* x, int64_t dim, int64_t b
 #undef QSV_SMALL
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const CircDev& c, int entangler,
+                              const float* params, const float* back, int kind, int q, uint64_t mask, const float* targets,
+                              double* sums, double* f, hipStream_t st) {
+    if (c.n < 1 || c.n > kSmallMaxQubits || batch < 1 || dim < 1 || dim > ((int64_t)1 << c.n)) return hipErrorInvalidValue;
+    if (c.slots() < 1 || c.n_layers < 1 || (int64_t)c.n_layers * c.n > kSmallMats) return hipErrorInvalidValue;
+    // four amplitudes per thread: eight and sixteen measured slower or the same at every batch (9 qubits x 64 47 / 59 /
+    // 89 us, 10 x 1024 102 / 101 / 108 us)
+    constexpr int regs = 2;
+    const int rows_g = small_rows_per_group(c.n, regs), per = c.n_layers * c.n;
+    const int tb = c.n > regs ? c.n - regs : 0;
+    const unsigned threads = tb > 6 ? 64u << (tb - 6) : 64u;
+    SweepArgs a;
+    a.x = x; a.dim = dim; a.batch = batch; a.c = c; a.entangler = entangler; a.back = back;
+    a.kind = kind; a.obs_qubit = q; a.mask = mask; a.targets = targets; a.f = f; a.sums = sums;
+    a.rows = rows_g;
+    if (c.reupload && a.rows > kSmallMats / per) a.rows = kSmallMats / per;
+    a.mat_floats = (c.reupload ? a.rows : 1) * per * 8;
+    const int64_t blocks = (batch + a.rows - 1) / a.rows;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    size_t lds = 64 * sizeof(double) + (size_t)a.mat_floats * sizeof(float);
+    if (threads > 64) lds += 2 * (size_t)(2 << regs) * threads * sizeof(float);
+    const dim3 grid((unsigned)blocks), block(threads);
+    switch (c.n) {
+#define QSV_SWEEP(N) \
+    case N: hipLaunchKernelGGL((k_sweep_small<regs, N>), grid, block, lds, st, a); break;
+        QSV_SWEEP(1) QSV_SWEEP(2) QSV_SWEEP(3) QSV_SWEEP(4) QSV_SWEEP(5) QSV_SWEEP(6) QSV_SWEEP(7) QSV_SWEEP(8) QSV_SWEEP(9)
+        QSV_SWEEP(10)
+#undef QSV_SWEEP
+        default: return hipErrorInvalidValue;
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const u64 jobs = (u64)batch * per * c.slots();
+    hipLaunchKernelGGL(k_adj_all, dim3(blocks_for(jobs, 256)), dim3(256), 0, st, sums, (int)(threads / 64), c, params, (u64)batch,
+                       back, f);
     return hipGetLastError();
 }
 
@@ -3076,7 +3406,7 @@ hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride,
         nblk = 1;
     }
     hipLaunchKernelGGL(k_adj_layer, dim3(blocks_for(jobs, 256)), dim3(256), 0, st, sums, nblk, c, layer,
-                       params, feats, (u64)sample0, (u64)row_pairs, (u64)P, back, exec_of, form == MatForm::plain ? 1 : 0,
+                       params, (u64)sample0, (u64)row_pairs, (u64)P, back, exec_of, form == MatForm::plain ? 1 : 0,
                        seq_first(form), seq_step(form), f);
     return hipGetLastError();
 }

@@ -1093,3 +1093,40 @@ def test_one_launch_with_every_number_of_samples_per_workgroup(oracle, n, B, L, 
     assert np.abs(out.cpu().numpy() - z).max() <= 1e-5
     assert np.abs(gu.state_np(ctx) - ref).max() <= 1e-5
     ctx.close()
+
+
+@pytest.mark.parametrize("n,B,L,rot,ent,reup", [
+    (1, 3, 2, (RY, RZ), RING, 0), (2, 70, 3, (RX,), LADDER, 1), (3, 5, 3, (RY, RZ), RING, 1), (4, 37, 128, (RY,), RING, 0),
+    (5, 33, 4, (RX, RY, RZ), LADDER, 1), (6, 9, 60, (RZ, RY), RING, 1), (7, 3, 5, (RY, RZ), RING, 0),
+    (8, 6, 3, (RX, RY, RZ), RING, 1), (9, 5, 4, (RY, RZ), LADDER, 0), (10, 3, 51, (RY,), RING, 0), (10, 7, 3, (RY, RZ), RING, 1),
+    (10, 2, 52, (RY,), RING, 0)])
+def test_small_reverse_mode_sweep_against_the_passes(n, B, L, rot, ent, reup):
+    """The one-launch sweep against the layer-by-layer sweep for the three observables: every number of qubits, ragged
+    groups of samples, the most unitaries it takes (512) and one layer more.  Both carry float rounding of
+    2 L n gates; the gradient's entries are sums of products of amplitudes."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, rot, ent, reup)
+    g = rng(31 * n + B)
+    P = spec.num_params(n)
+    x, p, f = (gu.dev(a.astype(np.float32)) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P),
+                                                      g.standard_normal((B, n))))
+    y = gu.dev(g.uniform(-1, 1, (B, n)).astype(np.float32))
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, B)
+    res = {}
+    for small in (1, 0):
+        ctx.qsv_set_option("small_apply", small)
+        for kind in (0, 1, 2):
+            loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+            if kind == 0:
+                ctx.qsv_adjoint_grad(circ, x, p, f if reup else None, n - 1, loss, grad)
+            else:
+                ctx.qsv_loss_grad(circ, x, p, f if reup else None, kind, loss, grad, mask=1 << (n // 2), targets=y)
+            res[small, kind] = (loss.clone(), grad.clone())
+    torch.cuda.synchronize()
+    for kind in (0, 1, 2):
+        (la, ga), (lb, gb) = res[1, kind], res[0, kind]
+        assert (la - lb).abs().max().item() <= 2e-7 * np.sqrt(L * n) * 4
+        scale = max(1e-3, gb.abs().max().item())
+        assert (ga - gb).abs().max().item() <= 2e-7 * np.sqrt(L * n) * 4 * max(1.0, scale)
+    ctx.close()
