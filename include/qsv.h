@@ -278,8 +278,8 @@ int64_t qsv_plan_describe(const qsv_circuit* c, int n_qubits, int batch, int inv
  * operation list) and must not be called while the stream is being captured. */
 qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int transposes);
 
-/* Testing/tuning knobs: tile_log2 in 10..14 (0 = default) forces the tile size of the fused pass
- * kernel (14 exists with one LDS plane only); defer_cnots = 1 / 0 lets qsv_apply_layers carry the
+/* Testing/tuning knobs: tile_log2 in 10..14 (0 = default: 11, 12 or 13 by the number of qubits and
+ * of amplitudes) forces the tile size of the fused pass kernel (14 exists with one LDS plane only); defer_cnots = 1 / 0 lets qsv_apply_layers carry the
  * CNOTs whose target qubit lies outside a pass's tile by the index the pass writes each amplitude to
  * (fewer passes over the state; such passes write a second buffer taken from the workspace), or keeps
  * every CNOT a register operation (-1, the default, defers whenever the circuit has a CNOT ring, more
@@ -296,13 +296,12 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
  * after the other, 2 through two planes at once; naive = 1 routes qsv_apply_layers through the
  * one-gate-per-launch kernels; grad_layered = 0 makes qsv_param_shift_grad run every shifted
  * circuit whole; nt_store = 1 / 0 forces nontemporal / ordinary tile stores in the fused pass (-1,
- * the default, chooses by the size of the state); reverse_passes = 1 / 0 makes every other fused
+ * the default, for passes that touch 384 MiB or more); reverse_passes = 1 / 0 makes every other fused
  * pass take its tiles from the last to the first, so that it starts with what the pass before it
- * wrote last, or not (-1, the default, chooses by the size of the state; the result does not
- * depend on it); split_streams = 1 / 0 sends the state rows through a sequence of fused passes as
+ * wrote last, or not (-1, the default, is 1; the result does not depend on it); split_streams = 1 / 0 sends the state rows through a sequence of fused passes as
  * two halves, the second on a stream of the library's own that forks from and rejoins the caller's
- * stream inside the call, or not (-1, the default, is 1; it takes at least two rows and more qubits
- * than the tile has index bits; the result does not depend on it);
+ * stream inside the call, or not (-1, the default, does so from 32 MiB of states; it takes at least two rows and more
+ * qubits than the tile has index bits; the result does not depend on it);
  * probe_layout in 0..9 (-1 = the highest) sets the register run qsv_probe_pass loads
  * and stores the tile in; grad_chunk_rows in 1..32768 (0 = as many as fit) caps the circuits per
  * launch of qsv_param_shift_grad.  Unknown names and values out of range return

@@ -208,9 +208,11 @@ hipError_t launch_pauli(const float2* state, int64_t rows, int n, uint64_t xmask
 // of S, paired = 0 writes lambda alone into row r.
 // back: the inverse circuit's table, every layer's unitaries in the order of a one-layer plan (exec_of: position
 // of a qubit's; NULL: natural order).
-// launch_adj_layer: for row pairs (psi0 + rstride r 2^n, lam0 + rstride r 2^n), both taken back to the
-// start of `layer`, the derivatives with respect to that layer's angles, written into f[sample][2p],
-// f[sample][2p+1] as (g, -g).  partial: row_pairs * n * (adj_trans_blocks(n) + 1) * 8 doubles.
+// launch_trans: the transition sums of the row pairs (psi0 + rstride r 2^n, lam0 + rstride r 2^n), both taken back to
+// the start of a layer: adj_trans_count(n, row_pairs) partials for each pair and qubit, 8 doubles each.
+// launch_adj_layers: from the partials of the layers layer0 .. layer0 + n_layers - 1, one layer's after the other's, the
+// derivatives with respect to their angles, written into f[sample][2p], f[sample][2p+1] as (g, -g).  partial has room
+// for n_layers * row_pairs * n * (adj_trans_blocks(n) + 1) * 8 doubles (the sums go behind the partials).
 hipError_t launch_adj_init(const float2* A, int n, int kind, int q, uint64_t mask, const double* coef,
                            int64_t rows, float2* S, int paired, hipStream_t st);
 hipError_t launch_trash_loss(const float2* A, int n, uint64_t mask, int64_t rows, int64_t sample0, int64_t P,
@@ -222,10 +224,12 @@ hipError_t launch_sgd(float* p, const float* g, int64_t count, double lr, hipStr
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t count, int64_t t, double lr,
                        double b1, double b2, double eps, hipStream_t st);
 int adj_trans_blocks(int n);
-hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride, int n, int64_t row_pairs,
-                            double* partial, const CircDev& c,
-                            int layer, const float* params, const float* feats, int64_t sample0, int64_t P,
-                            const float* back, const int* exec_of, MatForm form, double* f, hipStream_t st);
+int adj_trans_count(int n, int64_t row_pairs);
+hipError_t launch_trans(const float2* psi0, const float2* lam0, int rstride, int n, int64_t row_pairs, double* partial,
+                        hipStream_t st);
+hipError_t launch_adj_layers(double* partial, int64_t row_pairs, const CircDev& c, int layer0, int n_layers,
+                             const float* params, int64_t sample0, int64_t P, const float* back, const int* exec_of,
+                             MatForm form, double* f, hipStream_t st);
 
 // gradient assembly from f[B][2P+1] (double)
 hipError_t launch_grad_finish(const double* f, int64_t B, int64_t P, const CircDev& c, const float* feats,

@@ -1758,7 +1758,7 @@ __global__ __launch_bounds__(256) void k_mse_coef(const double* z, const float* 
 // anti-Hermitian Bt (Bt00, Bt11 imaginary, Bt10 = -conj(Bt01)), which equals
 // -2 (Im Bt00 Im M00 + Im Bt11 Im M11) + 2 Re(Bt01 K) with K = M01 - conj(M10).  So only Im M00,
 // Im M11 and K are summed; K is stored in the place of M01 and the other entries are zero, which lets
-// k_adj_layer use the plain formula.  Pair r is (psi0 + rstride r 2^n, lam0 + rstride r 2^n): the two
+// k_adj_layers use the plain formula.  Pair r is (psi0 + rstride r 2^n, lam0 + rstride r 2^n): the two
 // states interleaved in one buffer (lam0 = psi0 + 2^n, rstride 2) or in buffers of their own (rstride 1).
 __global__ __launch_bounds__(256) void k_trans_block(const float2* psi0, const float2* lam0, int rstride, int n,
                                                      u64 pairs, int nblk, double* partial) {
@@ -1804,7 +1804,7 @@ __global__ __launch_bounds__(256) void k_trans_block(const float2* psi0, const f
 // A workgroup covers `per_group` consecutive tiles of one row pair before it reduces its
 // accumulators, so the reduction is amortised.
 // partial: [(pair * n + qubit) * nblk + group * 4 + wavefront][8] (nblk = 4 * groups), the layout
-// k_trans_finish and k_adj_layer read.
+// k_trans_finish reads.
 
 // A pointer to global memory that is the same in every lane, moved to scalar registers so that loads
 // through it take the scalar-base + 32-bit lane offset form (no 64-bit address per lane).
@@ -2111,25 +2111,23 @@ __device__ __forceinline__ double adj_derivative(const double (&M)[8], const M2&
     return 2.0 * acc;
 }
 
-// Gradients of one layer: thread = (row pair, slot, qubit).  Written as f+ = g, f- = -g so that the same
-// finishing kernels as for the shift rule apply (they halve the difference and multiply re-upload weights
-// by the feature).
-__global__ __launch_bounds__(256) void k_adj_layer(const double* partial, int nblk, CircDev c, int layer,
-                                                   const float* params, u64 sample0, u64 pairs_rows, u64 P,
-                                                   const float* back, const int* exec_of, int plain, int seq0,
-                                                   int seq_stride, double* f) {
+// Gradients of the layers layer0 .. layer0 + n_layers - 1: thread = (layer, row pair, slot, qubit), sums in the order
+// [layer][row pair][qubit].  Written as f+ = g, f- = -g so that the same finishing kernels as for the shift rule apply
+// (they halve the difference and multiply re-upload weights by the feature).
+__global__ __launch_bounds__(256) void k_adj_layers(const double* sums, CircDev c, int layer0, int n_layers,
+                                                    const float* params, u64 sample0, u64 pairs_rows, u64 P,
+                                                    const float* back, const int* exec_of, int plain, int seq0,
+                                                    int seq_stride, double* f) {
     const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
     const int slots = c.reupload + c.n_rot;
     const u64 per = (u64)slots * c.n;
-    if (idx >= pairs_rows * per) return;
-    const u64 r = idx / per;
+    if (idx >= (u64)n_layers * pairs_rows * per) return;
+    const u64 lr = idx / per, r = lr % pairs_rows;      // lr: row of the sums
     const int s = (int)((idx % per) / c.n), q = (int)(idx % c.n);
+    const int layer = layer0 + (int)(lr / pairs_rows);
     const u64 sample = sample0 + r;
     double M[8];
-    for (int j = 0; j < 8; ++j) M[j] = 0.0;
-    const double* pp = partial + ((r * c.n + q) * (u64)nblk) * 8;
-    for (int b = 0; b < nblk; ++b)
-        for (int j = 0; j < 8; ++j) M[j] += pp[(u64)b * 8 + j];
+    for (int j = 0; j < 8; ++j) M[j] = sums[(lr * c.n + q) * 8 + j];
     const u64 entry = (c.reupload ? sample * (u64)c.n_layers * c.n : 0) + (u64)layer * c.n + (exec_of ? exec_of[q] : q);
     const double g = adj_derivative(M, entry_m(back + entry * 8, plain || q + 1 == c.n, seq0, seq_stride), c, layer, s, q,
                                     params);
@@ -3347,14 +3345,25 @@ static inline int trans_groups(int n) { return (1 << (n - 12)) / trans_tiles_per
 // upper bound of the partial entries per (row pair, qubit) of the transition sums
 int adj_trans_blocks(int n) { return n < 12 ? 1 : 4 * trans_groups(n); }
 
-hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride, int n, int64_t row_pairs,
-                            double* partial, const CircDev& c,
-                            int layer, const float* params, const float* feats, int64_t sample0, int64_t P,
-                            const float* back, const int* exec_of, MatForm form, double* f, hipStream_t st) {
+// A workgroup's first load and last sums overlap with nothing, so it takes as many tiles as still leaves two
+// workgroups per compute unit (never fewer than the buffer was sized for).
+static inline int trans_per_group(int n, int64_t row_pairs) {
+    const int tiles = 1 << (n - 12);
+    int per_group = trans_tiles_per_group(n);
+    while (per_group * 2 <= tiles && per_group < 32 && (int64_t)(tiles / (per_group * 2)) * row_pairs >= 512)
+        per_group *= 2;
+    return per_group;
+}
+// partial entries per (row pair, qubit): one per wavefront of a group of tiles
+int adj_trans_count(int n, int64_t row_pairs) {
+    return n < 12 ? adj_trans_blocks(n) : 4 * ((1 << (n - 12)) / trans_per_group(n, row_pairs));
+}
+
+hipError_t launch_trans(const float2* psi0, const float2* lam0, int rstride, int n, int64_t row_pairs, double* partial,
+                        hipStream_t st) {
     if (row_pairs < 1 || row_pairs > 65535) return hipErrorInvalidValue;
-    int nblk;
+    const int nblk = adj_trans_count(n, row_pairs);
     if (n < 12) {
-        nblk = adj_trans_blocks(n);
         hipLaunchKernelGGL(k_trans_block, dim3(nblk, n, (unsigned)row_pairs), dim3(256), 0, st, psi0, lam0, rstride,
                            n, (u64)1 << (n - 1), nblk, partial);
         hipError_t e = hipGetLastError();
@@ -3362,14 +3371,7 @@ hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride,
     } else {
         // qubits 0..11 from contiguous tiles, then 8 more per read from tiles whose window sits higher
         // (the last window ends at bit n and only its not yet covered qubits are taken)
-        // A workgroup's first load and last sums overlap with nothing, so it takes as many tiles as
-        // still leaves two workgroups per compute unit (never fewer than the buffer was sized for).
-        const int tiles = 1 << (n - 12);
-        int per_group = trans_tiles_per_group(n);
-        while (per_group * 2 <= tiles && per_group < 32 && (int64_t)(tiles / (per_group * 2)) * row_pairs >= 512)
-            per_group *= 2;
-        const int groups = tiles / per_group;
-        nblk = 4 * groups;                               // one partial per wavefront of a group
+        const int per_group = trans_per_group(n, row_pairs), groups = (1 << (n - 12)) / per_group;
         const dim3 grid(groups, (unsigned)row_pairs);
         hipLaunchKernelGGL((k_trans_wave<3>), grid, dim3(256), 0, st, psi0, lam0, rstride, n, 12, 12, 0, per_group,
                            nblk, partial);
@@ -3393,20 +3395,25 @@ hipError_t launch_adj_layer(const float2* psi0, const float2* lam0, int rstride,
             done = w + 8;
         }
     }
-    const u64 jobs = (u64)row_pairs * c.slots() * c.n;
+    return hipSuccess;
+}
+
+hipError_t launch_adj_layers(double* partial, int64_t row_pairs, const CircDev& c, int layer0, int n_layers,
+                             const float* params, int64_t sample0, int64_t P, const float* back, const int* exec_of,
+                             MatForm form, double* f, hipStream_t st) {
+    const u64 jobs = (u64)n_layers * row_pairs * c.slots() * c.n, sums_n = (u64)n_layers * row_pairs * c.n;
     if (jobs == 0) return hipSuccess;
+    const int nblk = adj_trans_count(c.n, row_pairs);
     const double* sums = partial;
     if (nblk > 1) {   // the summed matrices go behind the partials
-        double* M = partial + (u64)row_pairs * n * nblk * 8;
-        hipLaunchKernelGGL(k_trans_finish, dim3(blocks_for((u64)row_pairs * n, 4)), dim3(256), 0, st, partial,
-                           nblk, (u64)row_pairs * n, M);
+        double* M = partial + sums_n * nblk * 8;
+        hipLaunchKernelGGL(k_trans_finish, dim3(blocks_for(sums_n, 4)), dim3(256), 0, st, partial, nblk, sums_n, M);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         sums = M;
-        nblk = 1;
     }
-    hipLaunchKernelGGL(k_adj_layer, dim3(blocks_for(jobs, 256)), dim3(256), 0, st, sums, nblk, c, layer,
-                       params, (u64)sample0, (u64)row_pairs, (u64)P, back, exec_of, form == MatForm::plain ? 1 : 0,
+    hipLaunchKernelGGL(k_adj_layers, dim3(blocks_for(jobs, 256)), dim3(256), 0, st, sums, c, layer0, n_layers, params,
+                       (u64)sample0, (u64)row_pairs, (u64)P, back, exec_of, form == MatForm::plain ? 1 : 0,
                        seq_first(form), seq_step(form), f);
     return hipGetLastError();
 }

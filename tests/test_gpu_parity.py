@@ -1130,3 +1130,28 @@ def test_small_reverse_mode_sweep_against_the_passes(n, B, L, rot, ent, reup):
         scale = max(1e-3, gb.abs().max().item())
         assert (ga - gb).abs().max().item() <= 2e-7 * np.sqrt(L * n) * 4 * max(1.0, scale)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,L", [(11, 1000), (12, 400)])
+def test_adjoint_sums_of_all_layers_late_or_layer_by_layer(n, L):
+    """The derivatives of a chunk in one go or layer by layer, whichever the scratch has room for.  The sums of all
+    layers take 256 L n 64 bytes times 2 (11 qubits, one partial and the total) or 5 (12 qubits): 360 and 393 MB, more
+    than the smallest workspace has and less than 512 MiB above it; L + 1 states of every sample (over 3 GiB) fit
+    neither.  The sums are the same and added in the same order, so the bits have to be equal."""
+    torch = gu.torch_cuda()
+    B = 256
+    spec = wl.CircuitSpec(L, (RY,), RING, 0)
+    g = rng(n + L)
+    P = spec.num_params(n)
+    x = gu.dev(g.standard_normal((B, 1 << n)).astype(np.float32))
+    p = gu.dev(g.uniform(0, 2 * np.pi, P).astype(np.float32))
+    res = []
+    for extra in (0, 512 << 20):
+        ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_workspace_bytes(n, B) + extra)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+        ctx.qsv_adjoint_grad(qb.circuit_from_spec(spec), x, p, None, 1, loss, grad)
+        torch.cuda.synchronize()
+        res.append((loss, grad))
+        ctx.close()
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    assert bool((res[0][1].abs() <= 1.0).all())
