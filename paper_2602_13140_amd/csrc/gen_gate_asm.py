@@ -22,7 +22,7 @@ with off(k) the XOR of the offsets of k's set bits.  A layout is therefore descr
 offsets (those of elements 1, 2, 4, 8), kept in vector registers, and the elements are visited in
 Gray-code order, so that each address is the previous one XOR one of the four: one vector-only
 v_xor per element (a vector instruction with a scalar operand issues at 4.2 cycles per wavefront
-on this chip, one with vector operands only at 2.5).
+on this chip, one with vector operands only at 2.1 to 2.4).
 The dynamic LDS segment starts at byte 0 (the kernel has no static LDS), so no base is added.
 
 Operation word: x = kind | a<<8 | b<<16 | c<<24, y = arg.  For a unitary, arg is the index of its
@@ -61,7 +61,7 @@ GRAY_BIT = [0] + [(i & -i).bit_length() - 1 for i in range(1, NR)]   # bit that 
 def u_pair(a, b, variant="g"):
     """(r_a,i_a) has the target bit 0, (r_b,i_b) has it 1; matrix m0..m7 = vector copies of
     s88..s95 = (m00r, m00i, m01r, m01i, m10r, m10i, m11r, m11i): a vector instruction with a scalar
-    operand issues at 4.2 cycles per wavefront on this chip, one with vector operands only at 2.5.
+    operand issues at 4.2 cycles per wavefront on this chip, one with vector operands only at 2.1 to 2.4.
     Four interleaved chains; the last step of each overwrites an input that is dead by then.
     Variants leave out the products with
     imaginary parts that are exact zeros: "g" none (16 instructions; the one the interpreter uses, for the
@@ -166,7 +166,7 @@ CHAIN_FORM = "move"     # "swap": every cycle by v_swap_b32
 
 def chain_swaps(direction, first, count):
     """The chain's CNOTs (control c, target c + 1) as one permutation of the 16 register elements.  A cycle of
-    k elements takes k - 1 swaps (v_swap_b32, 8.2 cycles each) or k + 1 moves through a temporary (2.5
+    k elements takes k - 1 swaps (v_swap_b32, 8.2 cycles each) or k + 1 moves through a temporary (2.1 to 2.4
     cycles each): cycles of two are swapped, longer ones moved.  Measured on one box, alternating the two
     builds: moves take 0.8 % off the 26-qubit and 20-qubit configurations now that their passes are
     heavy (when the passes were lighter and waited for memory the same change cost 0.6 %)."""

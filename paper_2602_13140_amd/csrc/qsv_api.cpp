@@ -78,7 +78,7 @@ struct qsv_ctx {
     int opt_probe_layout = -1;  // probe pass: register run of the load and the store (-1: the highest)
     int64_t opt_grad_chunk = 0;
     int opt_split = -1;      // state rows of a launch sequence in two halves on two streams; -1: by state size
-    int opt_prio = 1;        // raised issue priority around a tile's loads and stores (measured: 2 % off configs 3 and 4)
+    int opt_prio = 1;        // raised issue priority around a tile's loads and stores (2 % off configs 3 and 4 with k_pass, none with k_pass_direct)
     int opt_small_apply = 1; // qsv_apply_layers runs states of at most 2^21 amplitudes on at most 10 qubits in one launch
     int opt_small_regs = 0;  // qsv_forward_small: amplitudes per thread = 2^this (2..4); 0: by batch size
     int opt_defer = -1;      // qsv_apply_layers defers CNOTs whose target lies outside a pass's tile; -1: when it can
@@ -455,7 +455,10 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         // wrote last and may still find in a cache (measured, two buffers of 32 to 256 MiB: 16 qubits
         // x 64 175 -> 166 us, 24 qubits 828 -> 761 us; no size at which it costs anything).
         a.rev = ctx->opt_rev != 0 ? (int)(pi & 1) : 0;
-        a.prio = ctx->opt_prio;
+        // Beside the other chunk of a reverse-mode sweep the passes share the chip with the transition sums, which a
+        // raised priority holds up.  Measured, raised / not: 20 qubits x 32 12350 / 11900 us, 22 x 16 10607 / 10378, 24 x 4
+        // 10700 / 10474, 18 x 64 1853 / 1838; 16 x 256, whose rows the caches hold, 2967 / 3010.
+        a.prio = ctx->opt_prio && !(ctx->forked && n >= 18);
         a.n = n; a.c = ps.c; a.w = ps.w;
         a.n_mats = n_mats;
         a.rowdep = c.reupload;
