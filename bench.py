@@ -26,7 +26,7 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per pass (config 3: a pair of launches) from rocprofv3 FETCH_SIZE / WRITE_SIZE, each scaled by what the same
 # counter reads for the load/store-only probe pass of known size (FETCH_SIZE x 2.000, WRITE_SIZE x
 # 1.000); the runs and their figures are in profiles/k_pass_hbm_traffic_counters.md.
-TRAFFIC_BYTES_PER_LAUNCH = {"c4": 1073974797, "c3": 537444482}
+TRAFFIC_BYTES_PER_LAUNCH = {"c4": 1074408323, "c3": 575414195}
 
 
 def parse_args():
@@ -168,7 +168,7 @@ def bench_c4(torch, qb, wl, args, apply_only=False):
         "updates_per_s": updates / (ms * 1e-3), "apply_updates_per_s": updates / (apply_ms * 1e-3),
         "pass_avg_ms": apply_ms / passes, "pass_bytes": 2 * state_bytes,
         "pass_gbs": 2 * state_bytes / (apply_ms / passes * 1e-3) / 1e9,
-        "unitary_flops": 13.0 * w.circuit.n_layers * n * (1 << n),
+        "unitary_flops": 10.0 * w.circuit.n_layers * n * (1 << n),
     }
     if apply_only:
         ctx.close()
@@ -530,7 +530,7 @@ def alu_view(head):
             "peak_without_packed_instructions": one_per_lane, "frac_without_packed_instructions": tf / one_per_lane,
             "note": "fp32 vector peak of the data sheet (reached with packed instructions only, which this build does not "
                     "use); with one FMA per lane and cycle the same units give 78.6 TFLOP/s; flops are those of the "
-                    "unitaries alone (26 per amplitude pair), about 87 % of the vector instructions of a pass"}
+                    "unitaries alone (a rotation and two phases: 10 multiply-adds, 20 flops, per amplitude pair)"}
 
 
 def main():
@@ -594,7 +594,7 @@ def main():
         "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": head["workload"], "tile_log2": args.tile, "passes": head["passes"],
                    "apply_ms": head["apply_ms"], "apply_updates_per_s": head["apply_updates_per_s"]},
-        "roofline": {"bound": "hbm", "kernel": "k_pass (fused gate pass)", "achieved": head["pass_gbs"],
+        "roofline": {"bound": "hbm", "kernel": "k_pass_direct (fused gate pass)", "achieved": head["pass_gbs"],
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": head["pass_gbs"] / HBM_PEAK_GBS,
                      "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(head["workload"][:2]),
                      "traffic_source": "rocprofv3 FETCH_SIZE / WRITE_SIZE of an earlier run of this command, scaled by "
@@ -602,8 +602,8 @@ def main():
                                        "not re-measured in this run",
                      "bytes_per_launch": head["pass_bytes"], "avg_launch_ms": head["pass_avg_ms"],
                      "launches_per_pass": head.get("launches_per_pass", 1),
-                     # the same launches against the vector-ALU roofline: a fused unitary is 26 flops per amplitude
-                     # pair (2 multiplies + 12 FMAs), CNOTs and transposes move data and count nothing
+                     # the same launches against the vector-ALU roofline: a fused unitary is 20 flops per amplitude
+                     # pair (10 FMAs), CNOTs and transposes move data and count nothing
                      "alu_view": alu_view(head)},
         "cpu_baseline": cpu,
         "others": dict(others, **{k: head[k] for k in ("pauli_string", "true_reset") if k in head}),
