@@ -47,6 +47,7 @@ struct CachedPlan {
     int defer = 0;                  // planned with deferred CNOTs (index maps)
     int direct = 0;                 // for the direct interpreter: `low_ops` is uploaded in place of plan.ops
     DirectPlan low_ops;
+    std::vector<unsigned> mates;   // of a mirrored plan's passes: PassArgs::mate
     size_t maps_off = 0;            // uint32[plan.maps.size()]: the index maps of its passes
     Plan plan;
     bool resident = false;          // its arrays are in the ops region right now
@@ -197,6 +198,7 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
                     fwd = &o;
             cp.plan = mirror_plan(fwd ? fwd->plan
                                       : build_plan(c, ctx->n, rows, false, tile, grad != 0, ctx->opt_low, true));
+            for (const Pass& ps : cp.plan.passes) cp.mates.push_back(line_mate(cp.plan, ps));
         } else {
             cp.plan = build_plan(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
         }
@@ -465,6 +467,7 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         a.rm = rm;
         a.direct = cp->direct;
         a.gather = pl.gather ? 1 : 0;
+        a.mate = a.gather && ps.map_begin >= 0 ? cp->mates[pi] : 0;
         a.s_in = a.s_out = a.first_mat = 0;
         a.g_sample0 = (unsigned)(rm.row0 / rm.per);
         a.g_rem0 = (unsigned)(rm.row0 % rm.per);

@@ -58,10 +58,22 @@ struct PassArgs {
     int direct;
     int gather;          // the amplitudes are read through imap (position p from the index it maps to) and written
                          // where they sit
+    unsigned mate;       // gather: the tile of a row that has the other halves of tile t's lines is t ^ mate (0: t itself)
     int s_in, s_out;     // register layouts in which the tile is loaded and stored
     int first_mat;       // index of the pass's first unitary
     unsigned g_sample0, g_rem0;   // gradient rows: rm.row0 / rm.per and rm.row0 % rm.per
 };
+
+// The tile of a row that workgroup b of the row takes: t and t ^ mate are eight apart (mate = 0: tile b).  b without bit
+// 3 numbers the pairs: it fills the tile's bits other than the lowest bit of mate.  Needs 16 tiles in a row.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline unsigned mate_order(unsigned b, unsigned mate) {
+    if (mate == 0) return b;
+    const unsigned pair = (b & 7u) | (b >> 4 << 3), below = (mate & (0u - mate)) - 1u;
+    return ((pair & below) | (pair & ~below) << 1) ^ ((b >> 3) & 1u ? mate : 0u);
+}
 
 // k_pass_direct takes states of n >= tile qubits (a tile lies in one row), at most this many (a row is at most
 // 2^31 bytes), through one LDS plane; k_pass takes the rest: several rows in a tile, 29 and 30 qubits, two planes.

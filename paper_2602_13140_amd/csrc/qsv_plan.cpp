@@ -455,6 +455,27 @@ bool check_circuit(const qsv_circuit* c, int n, std::string* why) {
     return true;
 }
 
+unsigned line_mate(const Plan& p, const Pass& ps) {
+    if (ps.map_begin < 0 || p.n - ps.t < 4) return 0;
+    // solve M d = bit 3 over GF(2), M's columns being the map's entries: eliminate with (entry, set of columns)
+    std::vector<std::pair<unsigned, unsigned>> rows;
+    auto reduce = [&](std::pair<unsigned, unsigned> v) {
+        for (const auto& r : rows)
+            if (v.first & (r.first & (0u - r.first))) { v.first ^= r.first; v.second ^= r.second; }
+        return v;
+    };
+    for (int j = 0; j < p.n; ++j) {
+        const auto v = reduce({p.maps[ps.map_begin + j], 1u << j});
+        if (v.first == 0) return 0;
+        rows.push_back(v);
+    }
+    const auto d = reduce({1u << 3, 0u});
+    if (d.first != 0) return 0;
+    const int window = ps.t - ps.c;
+    const unsigned low = (d.second >> ps.c) & ((1u << (ps.w - ps.c)) - 1u);
+    return low | (d.second >> (ps.w + window)) << (ps.w - ps.c);
+}
+
 int default_tile(int n, int64_t batch) {
     const int ext = n + ceil_log2(batch);
     // 2^12 amplitudes per tile measured best for large states.  For 10 or 11 qubits a tile is one

@@ -121,6 +121,10 @@ std::string describe_plan(const Plan& p);
 // OP_LOAD), as build_plan does for the passes it emits.
 void set_transpose_barriers(std::vector<Op>& ops);
 
+// In a pass that reads through its index map: the difference, as tiles of a row, between a position and the one that reads
+// the other half of its 128-byte line (index bit 3).  0: the same tile, no map, or fewer than 16 tiles in a row.
+unsigned line_mate(const Plan& p, const Pass& ps);
+
 int default_tile(int n, int64_t batch);
 
 // Tile size of a circuit that is planned with deferred CNOTs.

@@ -1155,3 +1155,25 @@ def test_adjoint_sums_of_all_layers_late_or_layer_by_layer(n, L):
         ctx.close()
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
     assert bool((res[0][1].abs() <= 1.0).all())
+
+
+@pytest.mark.parametrize("n,B,L", [(13, 3, 5), (14, 1, 4), (14, 5, 7), (16, 3, 8), (17, 2, 6), (19, 1, 4)])
+def test_mirrored_passes_whose_lines_are_shared_by_two_tiles(oracle, n, B, L):
+    """Workgroups of a reading pass are renumbered so that the two tiles that share its lines start together (from 16 tiles a
+    row on): every tile must still be taken once.  Tiles of 2^10: 8 (not renumbered), 16, 64, 128 and 512 a row.
+    Inverse circuit against the oracle; 4 (2 L n) roundings of 6e-8 on entries of size 2^(-n/2) stay far below 1e-5."""
+    spec = wl.CircuitSpec(L, (RY, RZ), RING, 0)
+    circ = qb.circuit_from_spec(spec)
+    maps = [ln.split(" M")[1].split(",") for ln in qb.qsv_plan_describe(circ, n, B, 1, 10 | 0x300).split("\n") if " M" in ln]
+    assert any(int(m[3], 16) != 8 for m in maps)     # the halves of a line (index bit 3) lie in two tiles
+    params = wl.draw_params(spec, n, 61 + n)
+    g = rng(n * B)
+    ref = g.standard_normal((B, 1 << n)) + 1j * g.standard_normal((B, 1 << n))
+    ref /= np.linalg.norm(ref, axis=1, keepdims=True)
+    ctx = gu.make_ctx(n, B, tile=10)
+    ctx.state.copy_(gu.dev(np.stack([ref.real, ref.imag], -1).astype(np.float32)).reshape(ctx.state.shape))
+    ctx.qsv_apply_layers(circ, gu.dev(params), None, 1)
+    got = gu.state_np(ctx).reshape(B, -1)
+    oracle.apply_layers(ref, ocirc(oracle, spec), params, inverse=True)
+    assert np.abs(got - ref).max() <= 1e-5
+    ctx.close()
