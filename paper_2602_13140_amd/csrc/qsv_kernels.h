@@ -6,6 +6,12 @@
 
 #include "qsv_plan.h"
 
+#ifdef __HIPCC__
+#define QSV_HD __host__ __device__
+#else
+#define QSV_HD
+#endif
+
 namespace qsv {
 
 // Circuit fields the device-side matrix builders need.
@@ -66,10 +72,7 @@ struct PassArgs {
 
 // The tile of a row that workgroup b of the row takes: t and t ^ mate are eight apart (mate = 0: tile b).  b without bit
 // 3 numbers the pairs: it fills the tile's bits other than the lowest bit of mate.  Needs 16 tiles in a row.
-#ifdef __HIPCC__
-__host__ __device__
-#endif
-inline unsigned mate_order(unsigned b, unsigned mate) {
+QSV_HD inline unsigned mate_order(unsigned b, unsigned mate) {
     if (mate == 0) return b;
     const unsigned pair = (b & 7u) | (b >> 4 << 3), below = (mate & (0u - mate)) - 1u;
     return ((pair & below) | (pair & ~below) << 1) ^ ((b >> 3) & 1u ? mate : 0u);
@@ -133,8 +136,12 @@ inline int small_rows_per_group(int n, int regs) {
     const int tb = n > regs ? n - regs : 0;
     return tb < 6 ? 64 >> tb : 1;
 }
+// Whether the circuit has any unitary: if so its angles and features are staged in LDS and its matrices built there.
+QSV_HD inline bool small_has_unitaries(const CircDev& c) { return c.n_layers > 0 && c.reupload + c.n_rot > 0; }
+QSV_HD inline int small_staged_angles(const CircDev& c) { return c.n_layers * (c.reupload + c.n_rot) * c.n; }
+QSV_HD inline int small_staged_features(const CircDev& c, int rows) { return c.reupload ? rows * c.n : 0; }
 inline int64_t small_mats_per_group(const CircDev& c, int regs) {
-    if (c.reupload + c.n_rot == 0) return 0;
+    if (!small_has_unitaries(c)) return 0;
     return (int64_t)(c.reupload ? small_rows_per_group(c.n, regs) : 1) * c.n_layers * c.n;
 }
 // Amplitudes per thread: the most that still gives the chip about four wavefronts per SIMD (4096), else the
@@ -150,6 +157,34 @@ inline int small_choose_regs(const CircDev& c, int64_t batch) {
         fallback = r;             // the smallest that fits so far
     }
     return fallback;
+}
+// What a launch of k_forward_small is made of.
+struct SmallShape {
+    int rows;            // samples per workgroup
+    unsigned threads;
+    int mat_floats;      // LDS floats of the workgroup's matrices (a multiple of 8)
+    size_t lds;          // dynamic LDS in bytes
+};
+inline SmallShape small_shape(const CircDev& c, int regs, int64_t batch) {
+    SmallShape s;
+    const int tb = c.n > regs ? c.n - regs : 0;
+    s.threads = tb > 6 ? 64u << (tb - 6) : 64u;
+    // Per-sample matrices are most of such a launch's work (a wavefront of 16 samples builds them for 18 us, 4 qubits,
+    // 6 layers), so while the chip has wavefronts to spare (eight per CU) the samples spread over them.
+    s.rows = small_rows_per_group(c.n, regs);
+    if (c.reupload && s.rows > 1) {
+        const int64_t spread = (batch + 2047) / 2048;
+        if (spread < s.rows) s.rows = (int)spread;
+    }
+    // sums across wavefronts, the matrices (only as many as this circuit has: LDS per workgroup decides how
+    // many workgroups a CU holds), and two exchange buffers (several wavefronts per sample only) that share
+    // their place with the staged angles and features
+    const bool has = small_has_unitaries(c);
+    s.mat_floats = has ? (c.reupload ? s.rows : 1) * c.n_layers * c.n * 8 : 0;
+    const size_t stage = has ? (size_t)(small_staged_angles(c) + small_staged_features(c, s.rows)) * sizeof(float) : 0;
+    const size_t exchange = s.threads > 64 ? 2 * (size_t)(2 << regs) * s.threads * sizeof(float) : 0;
+    s.lds = 64 * sizeof(double) + (size_t)s.mat_floats * sizeof(float) + (stage > exchange ? stage : exchange);
+    return s;
 }
 // x = NULL: start from the amplitudes in `state`; passes pass_first..pass_last (0 = the circuit, 1 = its inverse);
 // kind = 0: no measurement (the final state is always written)

@@ -2398,7 +2398,7 @@ struct SmallArgs {
 template <int N>
 __device__ __forceinline__ void small_build(const CircDev& c, const float* params, const float* feats, int64_t first,
                                             int64_t batch, int rows_m, int tid, float* mats, float* stage) {
-    const int slots = c.reupload + c.n_rot, L = c.n_layers, n_par = L * slots * N, n_feat = c.reupload ? rows_m * N : 0;
+    const int slots = c.reupload + c.n_rot, L = c.n_layers, n_par = small_staged_angles(c), n_feat = small_staged_features(c, rows_m);
     const int64_t feat0 = first * N, feat_end = batch * N;
     for (int i = tid; i < n_par; i += (int)blockDim.x) stage[i] = params[i];
     for (int i = tid; i < n_feat; i += (int)blockDim.x) stage[n_par + i] = feat0 + i < feat_end ? feats[feat0 + i] : 0.f;
@@ -2457,7 +2457,7 @@ __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
     const int64_t sample = first + r_in;
     const bool live = r_in < a.rows && sample < a.batch;
     const int per = L * n;
-    const bool has_u = a.c.reupload + a.c.n_rot > 0;
+    const bool has_u = small_has_unitaries(a.c);
     // what the circuit starts from is on its way while the matrices are built
     Amps<R> A;
     const bool inside = live && ((int64_t)ti << R) < ((int64_t)1 << n);
@@ -3059,33 +3059,19 @@ hipError_t launch_forward_small(int regs, const float* x, int64_t dim, int64_t b
     if (pass_first < 0 || pass_last > 1 || pass_first > pass_last || (kind != 0 && !out)) return hipErrorInvalidValue;
     if (regs < 2 || regs > 4 || c.n - regs > 8) return hipErrorInvalidValue;
     if (small_mats_per_group(c, regs) > kSmallMats) return hipErrorInvalidValue;
-    const int rows_g = small_rows_per_group(c.n, regs);
-    const int tb = c.n > regs ? c.n - regs : 0;
-    const unsigned threads = tb > 6 ? 64u << (tb - 6) : 64u;
+    const SmallShape shape = small_shape(c, regs, batch);
     SmallArgs a;
     a.x = x; a.dim = dim; a.batch = batch; a.c = c; a.entangler = entangler; a.params = params; a.feats = feats;
     a.pass_first = pass_first; a.pass_last = pass_last; a.from_state = x ? 0 : 1; a.kind = kind;
     a.state = state; a.out = out; a.norm_out = norm_out;
-    // Per-sample matrices are most of such a launch's work (a wavefront of 16 samples builds them for 18 us, 4 qubits,
-    // 6 layers), so while the chip has wavefronts to spare (eight per CU) the samples spread over them.
-    a.rows = rows_g;
-    if (c.reupload && rows_g > 1) {
-        const int64_t spread = (batch + 2047) / 2048;
-        if (spread < rows_g) a.rows = (int)spread;
-    }
+    a.rows = shape.rows;
+    a.mat_floats = shape.mat_floats;
     const int64_t blocks = (batch + a.rows - 1) / a.rows;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    // sums across wavefronts, the matrices (only as many as this circuit has: LDS per workgroup decides how
-    // many workgroups a CU holds), and (several wavefronts per sample only) two exchange buffers
-    a.mat_floats = (int)(c.slots() ? (c.reupload ? a.rows : 1) * c.n_layers * c.n : 0) * 8;
-    size_t lds = 64 * sizeof(double) + (size_t)a.mat_floats * sizeof(float);
-    const size_t stage = a.mat_floats ? ((size_t)c.n_layers * c.slots() * c.n + (c.reupload ? (size_t)a.rows * c.n : 0)) * sizeof(float) : 0;
-    const size_t exchange = threads > 64 ? 2 * (size_t)(2 << regs) * threads * sizeof(float) : 0;
-    lds += stage > exchange ? stage : exchange;
-    const dim3 grid((unsigned)blocks), block(threads);
+    const dim3 grid((unsigned)blocks), block(shape.threads);
     switch (regs * 16 + c.n) {
 #define QSV_SMALL(R, N) \
-    case R * 16 + N: hipLaunchKernelGGL((k_forward_small<R, N>), grid, block, lds, st, a); break;
+    case R * 16 + N: hipLaunchKernelGGL((k_forward_small<R, N>), grid, block, shape.lds, st, a); break;
 #define QSV_SMALL_ALL(R) QSV_SMALL(R, 1) QSV_SMALL(R, 2) QSV_SMALL(R, 3) QSV_SMALL(R, 4) QSV_SMALL(R, 5) QSV_SMALL(R, 6) \
                          QSV_SMALL(R, 7) QSV_SMALL(R, 8) QSV_SMALL(R, 9) QSV_SMALL(R, 10)
         QSV_SMALL_ALL(2) QSV_SMALL_ALL(3) QSV_SMALL_ALL(4)

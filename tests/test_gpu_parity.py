@@ -76,6 +76,7 @@ SMALL = [
     (15, 2, 2, (RX, RY, RZ), RING, 0), (16, 1, 3, (RY, RZ), LADDER, 0), (16, 3, 5, (RY, RZ), RING, 0),
     (17, 1, 6, (RX, RY, RZ), RING, 0),
     (5, 2, 0, (RY,), RING, 0),             # no layers: the state must come back unchanged
+    (5, 70, 0, (RY,), RING, 1),            # nor with features that no layer takes
 ]
 
 
@@ -608,6 +609,7 @@ SMALL_FUSED = [
     (9, 3, 512, 5, (RY, RZ), LADDER, 1),
     (10, 6, 1024, 6, (RY, RZ), RING, 1),           # config 1's shape at a small batch
     (10, 2, 777, 0, (RY,), RING, 0),               # no layers: encoding and measurement only
+    (4, 40, 16, 0, (RY, RZ), RING, 1), (10, 3, 1024, 0, (), LADDER, 1),      # and with features that no layer takes
     (10, 3, 1024, 3, (), NONE, 0),                 # no gates at all per layer
     (10, 1, 1024, 51, (RZ, RY, RX), RING, 0),      # 510 matrices: the most a wavefront keeps
 ]

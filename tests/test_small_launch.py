@@ -1,0 +1,67 @@
+"""Host arithmetic of the one-launch kernel (no GPU): what a workgroup writes into LDS stays inside what its launch
+asks for."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include "qsv_kernels.h"
+using namespace qsv;
+
+// Bytes a workgroup of k_forward_small touches: sums of 64 doubles, the matrices, and behind them first the staged
+// angles and features, later (several wavefronts) two exchange buffers.
+static size_t touched(const CircDev& c, const SmallShape& s, int regs) {
+    const size_t mats = 512 + (size_t)s.mat_floats * 4;
+    size_t end = mats;
+    if (small_has_unitaries(c)) {
+        const int rows = c.reupload ? s.rows : 1;
+        if ((size_t)rows * c.n_layers * c.n * 32 > (size_t)s.mat_floats * 4) return ~(size_t)0;
+        end = mats + (size_t)(small_staged_angles(c) + small_staged_features(c, rows)) * 4;
+    }
+    if (s.threads > 64 && mats + (size_t)2 * (2 << regs) * s.threads * 4 > end)
+        end = mats + (size_t)2 * (2 << regs) * s.threads * 4;
+    return end;
+}
+
+int main() {
+    int checked = 0, bad = 0;
+    const long long batches[] = {1, 3, 64, 2048, 2049, 5000, 100000};
+    for (int n = 1; n <= kSmallMaxQubits; ++n)
+        for (int regs = 2; regs <= 4; ++regs)
+            for (int layers = 0; layers <= 512; layers = layers < 4 ? layers + 1 : layers * 2)
+                for (int slots = 0; slots <= 4; ++slots)
+                    for (int reup = 0; reup <= 1 && reup <= slots && slots - reup <= 3; ++reup)
+                        for (long long batch : batches) {
+                            const CircDev c{n, layers, reup, slots - reup, {1, 2, 3}};
+                            if (n - regs > 8 || small_mats_per_group(c, regs) > kSmallMats) continue;
+                            const SmallShape s = small_shape(c, regs, batch);
+                            ++checked;
+                            // nothing is staged or built for a circuit without unitaries
+                            const bool has = layers > 0 && slots > 0;
+                            if (small_has_unitaries(c) != has || touched(c, s, regs) > s.lds || s.lds > 65536 || s.rows < 1) {
+                                ++bad;
+                                std::printf("n %d regs %d layers %d slots %d reupload %d batch %lld: touched %zu of %zu\n", n, regs,
+                                            layers, slots, reup, batch, touched(c, s, regs), s.lds);
+                            }
+                        }
+    std::printf("checked %d bad %d\n", checked, bad);
+    return bad || checked < 1000;
+}
+"""
+
+
+def test_lds_of_the_one_launch_kernel_holds_all_it_writes(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    src, exe = tmp_path / "small.cpp", str(tmp_path / "small")
+    src.write_text(PROGRAM)
+    subprocess.check_call(["g++", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           "-I", os.path.join(ROOT, "paper_2602_13140_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
+                           str(src), "-o", exe])
+    r = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout[-2000:]
