@@ -29,7 +29,7 @@ Operation word: x = kind | a<<8 | b<<16 | c<<24, y = arg.  For a unitary, arg is
 matrix in execution order, so consecutive unitaries read consecutive 32-byte entries and the
 next one can be prefetched (the table is padded by one entry for the last prefetch).  An entry is
 either the eight floats of the matrix (c = 1) or the matrix without a scalar factor as a rotation
-between two phases (c = 0; see rot_pair), whose seventh word picks one of 16 instruction sequences.
+between two phases (c = 0; see rot_pair), whose seventh word picks one of 28 instruction sequences.
 
 Fixed scalar registers (declared as clobbers; the text below names them s52..s56 and s68..s99,
 _renumbered() packs them into s36..s72, which leaves the compiler enough of the 96 scalar registers
@@ -108,29 +108,34 @@ def u_pair(a, b, variant="g"):
     ]
 
 
-# Forms of a factored unitary: which phases it has, and its core.
-FORMS = ("none", "before", "after", "both")
+# Forms of a factored unitary: which phases it has, and its core.  With both phases, A and B after the name say
+# that the one before or after the core has a quarter turn taken out of it.
+FORMS = ("none", "before", "after", "both", "bothA", "bothB", "bothAB")
 CORES = ("c+", "c-", "s+", "s-")
-ROT_LENGTH = {"none": 6, "before": 7, "after": 7, "both": 10}
+ROT_LENGTH = {"none": 6, "before": 7, "after": 7, "both": 10, "bothA": 10, "bothB": 10, "bothAB": 10}
 
 
 def rot_pair(a, b, form, core):
     """A unitary without its scalar factor, on the pair p (target bit 0) and q (target bit 1):
-    diag(1, e^iB) core diag(1, e^iA) with |A|, |B| <= pi/2.  The cores are the real rotations divided by
+    diag(1, e^iB) core diag(1, e^iA) with |A|, |B| <= pi/2 (both phases: diag(1, i^b e^iB) core diag(1, i^a e^iA) with
+    |A|, |B| <= pi/4 and a, b as the form says).  The cores are the real rotations divided by
     their larger entry,
       c+- : p' = p + x q,     q' = y p +- q          s+- : p' = x p -+ q,    q' = p + y q,     |x|, |y| <= 1,
     so each of the four real results takes one multiply-add.  A phase turns (re, im) of q by three shears
     re += t im, im += s re, re += t im with t = -tan(A/2), s = sin A, in place.  4 + 3 (+ 3)
     instructions where the matrix product takes 12 (14): the unitaries are 80 % of a pass's vector
     instructions, and vector issue bounds the passes.
+    The quarter turns cost no instruction (registers change names and signs).  Without them the larger t and s of
+    the larger angles, and the larger numbers between the shears, made unitaries with two phases round worse than the
+    matrix product: RX RY on 16 qubits, 20 layers 9.7e-7 against 8.1e-7 from 64 bits.
     Entry: m0, m1 = t, s of A; m2, m3 = x, y; m4, m5 = t, s of B."""
     ra, ia, rb, ib = "%%[r%d]" % a, "%%[i%d]" % a, "%%[r%d]" % b, "%%[i%d]" % b
     t0, t1 = "%[t0]", "%[t1]"
     m = ["%%[m%d]" % k for k in range(6)]
-    neg = lambda r: "-" + r
+    neg = lambda r: r[1:] if r[0] == "-" else "-" + r
 
     def fma(d, f, v, acc):
-        if d == acc:
+        if d == acc and "-" not in (f + v):
             return "v_fmac_f32 %s, %s, %s" % (d, f, v)
         return "v_fma_f32 %s, %s, %s, %s" % (d, f, v, acc)
 
@@ -146,17 +151,25 @@ def rot_pair(a, b, form, core):
     else:
         out += [fma(t0, m[0], ib, rb), fma(t1, m[1], t0, ib), fma(t0, m[0], t1, t0)]
         qr, qi, nr, ni = t0, t1, rb, ib
+        if "A" in form:                    # i q
+            qr, qi = neg(t1), t0
+        if "B" in form:                    # q' goes to the place of i q'
+            nr, ni = ib, neg(rb)
+
+    def to(d, f, v, acc):                  # d may be the negative of a register
+        return fma(d, f, v, acc) if d[0] != "-" else fma(d[1:], neg(f), v, neg(acc))
+
     if core[0] == "c":
-        out += [fma(nr, m[3], ra, neg(qr) if minus else qr), fma(ni, m[3], ia, neg(qi) if minus else qi),
+        out += [to(nr, m[3], ra, neg(qr) if minus else qr), to(ni, m[3], ia, neg(qi) if minus else qi),
                 fma(ra, m[2], qr, ra), fma(ia, m[2], qi, ia)]
     else:
-        out += [fma(nr, m[3], qr, ra), fma(ni, m[3], qi, ia),
+        out += [to(nr, m[3], qr, ra), to(ni, m[3], qi, ia),
                 fma(ra, m[2], ra, qr if minus else neg(qr)), fma(ia, m[2], ia, qi if minus else neg(qi))]
     if form == "none":
         out += ["v_mov_b32 %s, %s" % (rb, t0), "v_mov_b32 %s, %s" % (ib, t1)]
     elif form == "after":
         out += [fma(rb, m[4], t1, t0), fma(ib, m[5], rb, t1), fma(rb, m[4], ib, rb)]
-    elif form == "both":
+    elif form.startswith("both"):
         out += [fma(rb, m[4], ib, rb), fma(ib, m[5], rb, ib), fma(rb, m[4], ib, rb)]
     return out
 

@@ -778,40 +778,41 @@ __device__ __forceinline__ void store_m(const M2& u, float* out8) {
     o[1] = make_float4((float)u.r[2], (float)u.i[2], (float)u.r[3], (float)u.i[3]);
 }
 
-// The turn by the unit number p, |angle| <= pi/2 after its sign went into `sigma`, as three shears:
-// t = -tan(angle/2), s = sin(angle).  A phase that vanishes by structure comes out as rounding
-// noise of a few 1e-17 and is dropped.  Returns whether there is a phase.
+// The turn by the unit number p = i^quarter sigma e^(i angle) as three shears, t = -tan(angle/2), s = sin(angle):
+// |angle| <= pi/2, or <= pi/4 where a quarter turn may be taken out.  A phase that vanishes by structure comes out as
+// rounding noise of a few 1e-17 and is dropped.
 // The shears of a rounded pair (t, s) multiply to a turn by a slightly different angle and a small
-// stretch, which acts on every amplitude like one more rounding: of three neighbouring t, each with the s
-// that belongs to it, the one with the smallest is taken (rms stretch 1.5e-8 instead of 2.0e-8 at
-// an angle off by 2.8e-8; the angle's error is a perturbation of a parameter and counts for less).
-__device__ __forceinline__ bool shears(Cx p, double* sigma, float* t, float* s) {
+// stretch, about 1e-8 each; s is the one that belongs to the rounded t, which keeps the stretch to its rounding.
+__device__ __forceinline__ bool has_phase(Cx p) { return !(fabs(p.i) < 1e-14); }
+
+__device__ __forceinline__ void shears(Cx p, bool quarters, double* sigma, bool* quarter, float* t, float* s) {
+    *quarter = quarters && fabs(p.i) > fabs(p.r);
+    if (*quarter) p = {p.i, -p.r};
     *sigma = 1.0;
     if (p.r < 0.0) { *sigma = -1.0; p.r = -p.r; p.i = -p.i; }
     *t = 0.f;
     *s = 0.f;
-    if (fabs(p.i) < 1e-14) return false;
-    const int bits = __float_as_int((float)(-p.i / (1.0 + p.r)));
-    double best = 1e300;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const float tf = __int_as_float(bits + (d == 2 ? -1 : d));
-        const double td = (double)tf, t2 = td * td;
-        const float sf = (float)(-2.0 * td / (1.0 + t2));
-        const double sd = (double)sf, low = 2.0 * td + t2 * sd;
-        const double angle = 0.5 * (sd - low) * p.r - (1.0 + td * sd) * p.i, stretch = sd + low;
-        const double cost = 0.16 * angle * angle + stretch * stretch;
-        if (d == 0 || cost < best) { best = cost; *t = tf; *s = sf; }
-    }
-    return true;
+    if (!has_phase(p)) return;
+    *t = (float)(-p.i / (1.0 + p.r));
+    const double td = (double)*t;
+    *s = (float)(-2.0 * td / (1.0 + td * td));
 }
 
-// u (unitary with determinant 1) = g * diag(1, e^iB) core diag(1, e^iA), the core being the real rotation
+// What the three shears and the quarter turn multiply q by (as far as it is a number: see shears).
+__device__ __forceinline__ Cx turned(float t, float s, bool quarter) {
+    const double td = (double)t, sd = (double)s;
+    const Cx z = {1.0 + td * sd, 0.5 * (sd - 2.0 * td - td * td * sd)};
+    return quarter ? Cx{-z.i, z.r} : z;
+}
+
+// u (unitary with determinant 1) = g * diag(1, zB) core diag(1, zA), the core being the real rotation
 // divided by its larger entry: see rot_pair in gen_gate_asm.py, which lists the entry's fields and
-// applies it.  g is taken from the rounded quotient, so a rounded entry times g has orthogonal columns of
-// length 1 up to double precision.  inverse: the entry of the conjugate transpose, with the same rounded
+// applies it.  inverse: the entry of the conjugate transpose, with the same rounded
 // numbers: a reverse-mode gradient compares states taken forward and back, and an angle that differs
 // between the two by its rounding shows in it undiminished (measured: 1e-5 instead of 3e-6).
+// g brings the rounded entry nearest to u: the angles of zA and zB are off by about 2e-8, and half of such an angle
+// is a factor of the whole entry, which g takes back; the other half acts on p and q in opposite directions and is
+// less of an error by sqrt 2 than the whole angle on q.
 __device__ __forceinline__ Cx factor_m(const M2& u, int inverse, int seq0, int seq_stride, float* out8) {
     const double a = sqrt(u.r[0] * u.r[0] + u.i[0] * u.i[0]), b = sqrt(u.r[2] * u.r[2] + u.i[2] * u.i[2]);
     Cx ea = {1.0, 0.0}, eb = {1.0, 0.0};              // phases of the first column
@@ -819,33 +820,45 @@ __device__ __forceinline__ Cx factor_m(const M2& u, int inverse, int seq0, int s
     if (b != 0.0) eb = {u.r[2] / b, u.i[2] / b};
     if (a == 0.0) ea = {eb.r, -eb.i};                 // free: leave no phase in front
     if (b == 0.0) eb = {ea.r, -ea.i};
-    const Cx ab = mul_c(ea, eb);
-    double s1, s2;
-    float e[6];
-    const bool before = shears({ab.r, -ab.i}, &s1, &e[0], &e[1]);
-    const bool after = shears(mul_c(eb, {ea.r, -ea.i}), &s2, &e[4], &e[5]);
+    const Cx ab = mul_c(ea, eb), za = {ab.r, -ab.i}, zb = mul_c(eb, {ea.r, -ea.i});
+    bool before = has_phase(za), after = has_phase(zb);
+    const bool both = before && after;
+    double sa, sb;
+    bool qa, qb;
+    float ta, na, tb, nb;
+    shears(za, both, &sa, &qa, &ta, &na);
+    shears(zb, both, &sb, &qb, &tb, &nb);
+    float e[6] = {ta, na, 0.f, 0.f, tb, nb};
+    double turn = 1.0;                                // sign of the rotation's lower left entry
+    if (inverse) {                                    // the phases change places and signs: conj(i) = -i
+        e[0] = -tb; e[1] = -nb; e[4] = -ta; e[5] = -na;
+        const double other = qa ? -sa : sa;
+        sa = qb ? -sb : sb;
+        sb = other;
+        bool keep = qa; qa = qb; qb = keep;
+        keep = before; before = after; after = keep;
+        turn = -1.0;
+    }
     const bool c_core = !(a < b);                     // also the way of a NaN
     const float q = (float)(c_core ? b / a : a / b);
-    e[2] = (c_core ? s1 < 0.0 : s2 > 0.0) ? q : -q;   // c: -s1 q, s: s2 q
-    e[3] = (c_core ? s2 : s1) > 0.0 ? q : -q;         // c: s2 q, s: s1 q
-    const bool minus = s1 * s2 < 0.0;
-    const double len = rsqrt(1.0 + (double)q * (double)q) * (c_core ? 1.0 : s2);
-    Cx g = {ea.r * len, ea.i * len};
-    int form = (after ? 2 : 0) + (before ? 1 : 0);
+    // rotation (1, -turn q; turn q, 1) or (q, -turn; turn, q), with the signs of the phases, divided by the entry that is
+    // to be 1: 1 or sb turn
+    e[2] = (float)(c_core ? -sa * turn : sb * turn) * q;
+    e[3] = (float)(c_core ? sb * turn : sa * turn) * q;
+    const int form = both ? 3 + (qa ? 1 : 0) + (qb ? 2 : 0) : (after ? 2 : 0) + (before ? 1 : 0);
+    const int seq = form * 4 + (c_core ? 0 : 2) + (sa * sb < 0.0 ? 1 : 0);
     float4* o = reinterpret_cast<float4*>(out8);
-    const int core = (c_core ? 0 : 2) + (minus ? 1 : 0);
-    if (!inverse) {
-        o[0] = make_float4(e[0], e[1], e[2], e[3]);
-        o[1] = make_float4(e[4], e[5], __int_as_float(seq0 + (form * 4 + core) * seq_stride), 0.f);
-        return g;
-    }
-    // the phases change sign and places; the core is transposed: c swaps x and y, s (divided by its
-    // upper right entry again, which leaves a factor -+1) keeps them up to that sign
-    form = (before ? 2 : 0) + (after ? 1 : 0);
-    const float f = c_core ? 1.f : (minus ? 1.f : -1.f);
-    o[0] = make_float4(-e[4], -e[5], c_core ? e[3] : f * e[2], c_core ? e[2] : f * e[3]);
-    o[1] = make_float4(-e[0], -e[1], __int_as_float(seq0 + (form * 4 + core) * seq_stride), 0.f);
-    return {g.r * (double)f, -g.i * (double)f};
+    o[0] = make_float4(e[0], e[1], e[2], e[3]);
+    o[1] = make_float4(e[4], e[5], __int_as_float(seq0 + seq * seq_stride), 0.f);
+    // Of the entries that are to be u's (or its conjugate transpose's), two belong to the core's ones: x, and conj(x) or
+    // -conj(x).  Divided by their phases in the rounded entry they agree but for the errors of those: their mean, with
+    // the length that gives the entry columns of length 1.
+    const Cx z1 = turned(e[0], e[1], qa), z2 = turned(e[4], e[5], qb), z12 = mul_c(z1, z2);
+    const Cx x = c_core ? Cx{u.r[0], turn * u.i[0]} : Cx{turn * u.r[2], turn * u.i[2]};
+    const double sigma = sa * sb;
+    const Cx x1 = c_core ? x : mul_c({z2.r, -z2.i}, x), x2 = mul_c(c_core ? z12 : z1, x);   // the second's conjugate
+    const double big = c_core ? a : b, len = 0.5 * rsqrt((1.0 + (double)q * (double)q) * big * big);
+    return {len * (x1.r + sigma * x2.r), len * (x1.i - sigma * x2.i)};
 }
 
 // The matrix of a table entry as the interpreter applies it, scaled to columns of length 1.
@@ -854,12 +867,11 @@ __device__ __forceinline__ M2 entry_m(const float* e, bool whole, int seq0, int 
     if (whole) {
         for (int k = 0; k < 4; ++k) { u.r[k] = (double)e[2 * k]; u.i[k] = (double)e[2 * k + 1]; }
     } else {
-        const int core = ((__float_as_int(e[6]) - seq0) / seq_stride) & 3;
+        const int seq = (__float_as_int(e[6]) - seq0) / seq_stride, core = seq & 3, form = seq >> 2;
         const double sigma = (core & 1) ? -1.0 : 1.0, x = (double)e[2], y = (double)e[3];
-        auto turn = [](double t, double s) -> Cx { return {1.0 + t * s, 0.5 * (s - 2.0 * t - t * t * s)}; };
-        const Cx z1 = turn((double)e[0], (double)e[1]), z2 = turn((double)e[4], (double)e[5]);
-        const bool cc = core < 2;
-        const double m00 = cc ? 1.0 : x, m01 = cc ? x : -sigma, m10 = cc ? y : 1.0, m11 = cc ? sigma : y;
+        const Cx z1 = turned(e[0], e[1], form == 4 || form == 6), z2 = turned(e[4], e[5], form == 5 || form == 6);
+        const bool c_core = core < 2;
+        const double m00 = c_core ? 1.0 : x, m01 = c_core ? x : -sigma, m10 = c_core ? y : 1.0, m11 = c_core ? sigma : y;
         const Cx z12 = mul_c(z1, z2);
         u.r[0] = m00; u.i[0] = 0.0;
         u.r[1] = m01 * z1.r; u.i[1] = m01 * z1.i;

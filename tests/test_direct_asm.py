@@ -247,13 +247,14 @@ def gate(t, bit, m):
 
 def factored(r, form, core):
     """A random table entry of a sequence and its matrix."""
-    first = r.uniform(-np.pi / 2, np.pi / 2) if form in ("before", "both") else 0.0
-    last = r.uniform(-np.pi / 2, np.pi / 2) if form in ("after", "both") else 0.0
+    first = r.uniform(-np.pi / 2, np.pi / 2) if form.startswith(("before", "both")) else 0.0
+    last = r.uniform(-np.pi / 2, np.pi / 2) if form.startswith(("after", "both")) else 0.0
     x, y = r.uniform(-1, 1, 2)
     sign = -1.0 if g.CORES[core][1] == "-" else 1.0
     k = np.array([[1, x], [y, sign]] if g.CORES[core][0] == "c" else [[x, -sign], [1, y]], dtype=complex)
     e = [-np.tan(first / 2), np.sin(first), x, y, -np.tan(last / 2), np.sin(last), OFF["F%s%d" % (form, core)], 0.0]
-    return e, np.diag([1, np.exp(1j * last)]) @ k @ np.diag([1, np.exp(1j * first)])
+    zb, za = np.exp(1j * last) * (1j if "B" in form else 1), np.exp(1j * first) * (1j if "A" in form else 1)
+    return e, np.diag([1, zb]) @ k @ np.diag([1, za])
 
 
 @pytest.mark.parametrize("shifts", [0, 1])
