@@ -102,7 +102,8 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
 // repeats for every layer (the table of the whole circuit as the tables of its layers, run one by one,
 // back to back).  plain: every entry is the matrix; else factored in groups (see kMatGroup), as the
 // interpreters of the fused pass read them.  scale (NULL: not wanted): [tables][n_layers*n] complex doubles.
-enum class MatForm { plain, factored, direct };   // direct: factored, for the direct interpreter
+enum class MatForm { plain, factored, direct, phaseless };   // direct: factored, for the direct interpreter; phaseless:
+                                                             // matrices up to a phase, which a group's last one has
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
                              const int* order, int period, MatForm form, float* out, double* scale, hipStream_t st);
 // bytes of the scale table
@@ -191,11 +192,12 @@ inline SmallShape small_shape(const CircDev& c, int regs, int64_t batch) {
 hipError_t launch_forward_small(int regs, const float* x, int64_t dim, int64_t batch, const CircDev& c, int entangler,
                                 const float* params, const float* feats, int pass_first, int pass_last, int kind,
                                 float2* state, float* out, float* norm_out, hipStream_t st);
-// Reverse-mode gradient of a whole small batch (see k_sweep_small) into f[batch][2P+1]; back: the plain table of the
-// inverse circuit in natural order; sums: batch * n_layers * sweep_record_bytes(n) bytes.  At most kSmallMats unitaries.
+// Reverse-mode gradient of a whole small batch (see k_sweep_small) into f[batch][2P+1]; back: the phaseless table of the
+// inverse circuit in natural order; kept (NULL: do without): n_layers * batch * 2^n amplitudes; sums: batch * n_layers *
+// sweep_record_bytes(n) bytes.  At most kSmallMats unitaries.
 hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const CircDev& c, int entangler,
                               const float* params, const float* back, int kind, int q, uint64_t mask, const float* targets,
-                              double* sums, double* f, hipStream_t st);
+                              float2* kept, double* sums, double* f, hipStream_t st);
 inline size_t sweep_record_bytes(int n) { return (size_t)(n > 8 ? 1 << (n - 8) : 1) * 32 * 8; }
 hipError_t launch_encode_write(const float* x, int64_t dim, int n, int64_t rows, const double* inv_norm,
                                const RowMap& rm, float2* state, hipStream_t st);

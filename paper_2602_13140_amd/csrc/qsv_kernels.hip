@@ -891,13 +891,15 @@ __device__ __forceinline__ int ordered(const int* table, int period, int pos) {
 
 // One thread per unitary, one wavefront per group of kMatGroup consecutive ones (a layer's unitaries when
 // period > 0): all but the one with the highest id are stored factored, and their scalars, multiplied up
-// across the wavefront, go into that one, which is stored as a matrix.  plain = 1: every entry is the matrix
-// itself (tables that are read per lane, and the one-gate-per-launch path).
+// across the wavefront, go into that one, which is stored as a matrix.  kind = plain: every entry is the matrix
+// itself (tables that are read per lane, and the one-gate-per-launch path).  kind = phaseless: matrices in the factored
+// ones' place too, without the phase of their upper left entry; products with its imaginary part, an exact zero, round
+// nothing (gradients of the small sweep 2 to 4 % nearer to 64 bits).
 // scale (may be NULL): what a matrix that replaces entry pos has to be multiplied by.
 // One launch where the factors used to be collected by a second one (10 us to 5 us before a circuit).
 __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* params, const float* feats,
                                                     u64 groups, int inverse, const int* order, int period,
-                                                    int plain, int seq0, int seq_stride, float* out, double* scale) {
+                                                    MatForm kind, int seq0, int seq_stride, float* out, double* scale) {
     static_assert(kMatGroup == 64, "a wavefront is a group");
     const u64 gi = (u64)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (gi >= groups) return;
@@ -913,13 +915,21 @@ __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* para
     int top = lq;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) top = max(top, __shfl_xor(top, d, 64));
-    const bool whole = plain || lq == top;
+    const bool whole = kind == MatForm::plain || lq == top, matrix = whole || kind == MatForm::phaseless;
     Cx g = {1.0, 0.0};
     M2 u;
     float* o = out + (sample * (u64)per + (u64)pos) * 8;
     if (live) {
-        u = fused_raw(c, params, feats, sample, lq / c.n, lq % c.n, -1, 0.0, whole ? inverse : 0);
-        if (!whole) g = factor_m(u, inverse, seq0, seq_stride, o);
+        u = fused_raw(c, params, feats, sample, lq / c.n, lq % c.n, -1, 0.0, matrix ? inverse : 0);
+        if (!matrix) g = factor_m(u, inverse, seq0, seq_stride, o);
+        else if (!whole) {
+            const double a = sqrt(u.r[0] * u.r[0] + u.i[0] * u.i[0]);
+            if (a != 0.0) g = {u.r[0] / a, u.i[0] / a};
+            scale_m(u, {g.r, -g.i});
+            u.r[0] = a;
+            u.i[0] = 0.0;
+            store_m(u, o);
+        }
     }
     Cx f = g;
 #pragma unroll
@@ -2156,7 +2166,7 @@ __global__ __launch_bounds__(256) void k_adj_layers(const double* sums, CircDev 
 }
 
 // The same for all layers of the samples that k_sweep_small took: thread = (sample, parameter); sums as that kernel
-// writes them.  back: the plain table of the inverse circuit in natural order.
+// writes them.  back: the phaseless table of the inverse circuit in natural order.
 __global__ __launch_bounds__(256) void k_adj_all(const double* sums, int waves, CircDev c, const float* params, u64 rows,
                                                  const float* back, double* f) {
     const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
@@ -2648,22 +2658,26 @@ __global__ __launch_bounds__(256) void k_forward_small(SmallArgs a) {
 }
 
 // Reverse-mode sweep of small states (at most 10 qubits) in one launch: encoding, circuit, loss, lambda = O psi, then
-// both states back through the layers, and at every layer's start the transition sums of all qubits, which are
-// all that leaves the chip.  The layout is that of k_forward_small.  Through the fused passes the same takes six
-// launches per layer, each of which reads and writes the states: 10 qubits x 1024 re-uploading 6 layers 355 -> 102 us,
-// 8 x 64 302 -> 39 us, 4 x 1 178 -> 24 us.
+// lambda back through the layers, and at every layer's start the transition sums of all qubits, which are
+// what leaves the chip.  The layout is that of k_forward_small.  KEEP: psi is written at every layer's start on the way
+// forward and read on the way back (each thread its own amplitudes, while lambda's gates run); without room for that it
+// is taken back beside lambda, with a third more gates and the roundings of those (gradients 1.3 to 1.8 times as far from
+// 64 bits).  Bound by vector issue.  Through the fused passes the same takes six launches per layer, each of which reads
+// and writes the states.  Passes / taken back / kept: 10 qubits x 1024 re-uploading 6 layers 391 / 102 / 85 us, 8 x 64 319 / 39 /
+// 35 us, 4 x 1 176 / 23.4 / 21.5 us.
 struct SweepArgs {
     const float* x;          // [batch][dim]
     int64_t dim, batch;
     CircDev c;
     int entangler;
-    const float* back;       // plain table of the inverse circuit in natural order
+    const float* back;       // phaseless table of the inverse circuit in natural order
     int rows;                // samples per workgroup
     int mat_floats;          // LDS floats of the workgroup's matrices
     int kind, obs_qubit;     // as launch_adj_init
     u64 mask;
     const float* targets;    // kind 2: [batch][n]
     double* f;               // [batch][2P + 1]: the loss goes to entry 2P
+    float2* kept;            // KEEP: [L][batch][2^n], psi at the start of every layer
     double* sums;            // [batch][L][wavefronts of a sample][32]: sum of d, then 3 per qubit (see k_adj_all)
 };
 
@@ -2736,9 +2750,9 @@ __device__ __forceinline__ void small_trans(const Amps<R>& s, const Amps<R>& l, 
     }
 }
 
-template <int R, int N>
+template <int R, int N, bool KEEP>
 __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
-    constexpr int NR = 1 << R, n = N;
+    constexpr int NR = 1 << R, n = N, NV = N < R ? 1 << N : NR;     // NV of a thread's amplitudes exist
     constexpr int tb = n > R ? n - R : 0, lb = tb < 6 ? tb : 6, n_waves = tb > 6 ? 1 << (tb - 6) : 1;
     extern __shared__ __align__(16) unsigned char small_lds[];
     double* red = reinterpret_cast<double*>(small_lds);
@@ -2800,7 +2814,16 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
         else if (a.entangler == QSV_ENT_CZ_LADDER) small_cz_ladder<R, N>(A, ti);
     };
 #define QSV_ALL_Q(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9)
+    auto kept = [&](int l) -> float4* {
+        return reinterpret_cast<float4*>(a.kept + (((int64_t)l * a.batch + (live ? sample : 0)) << n) + ti * NV);
+    };
     for (int l = 0; l < L; ++l) {
+        if constexpr (KEEP) {
+            if (live) {
+#pragma unroll
+                for (int k = 0; k < NV; k += 2) kept(l)[k / 2] = make_float4(S.re[k], S.im[k], S.re[k + 1], S.im[k + 1]);
+            }
+        }
         const float* ml = mrow + (size_t)l * n * 8;
         float m[8];
 #define QSV_FWD(Q)                                                                          \
@@ -2861,7 +2884,15 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
         La.im[k] = w * S.im[k];
     }
     for (int l = L - 1; l >= 0; --l) {
-        entangle(S, true);
+        if constexpr (KEEP) {
+#pragma unroll
+            for (int k = 0; k < NV; k += 2) {
+                const float4 v = kept(l)[k / 2];
+                S.re[k] = v.x; S.im[k] = v.y; S.re[k + 1] = v.z; S.im[k + 1] = v.w;
+            }
+        } else {
+            entangle(S, true);
+        }
         entangle(La, true);
         const float* ml = mrow + (size_t)l * n * 8;
         float m[8];
@@ -2871,8 +2902,11 @@ __global__ __launch_bounds__(256) void k_sweep_small(SweepArgs a) {
         const float4 hi = *reinterpret_cast<const float4*>(ml + Q * 8 + 4);                 \
         m[0] = lo.x; m[1] = lo.y; m[2] = lo.z; m[3] = lo.w;                                 \
         m[4] = hi.x; m[5] = hi.y; m[6] = hi.z; m[7] = hi.w;                                 \
-        if constexpr (Q < R) { small_u_reg<R, Q>(S, m); small_u_reg<R, Q>(La, m); }         \
-        else if constexpr (Q - R < 8) { small_u_thr<R, Q - R>(S, m, tid, xc); small_u_thr<R, Q - R>(La, m, tid, xc); } \
+        if constexpr (Q < R) { if constexpr (!KEEP) small_u_reg<R, Q>(S, m); small_u_reg<R, Q>(La, m); } \
+        else if constexpr (Q - R < 8) {                                                     \
+            if constexpr (!KEEP) small_u_thr<R, Q - R>(S, m, tid, xc);                      \
+            small_u_thr<R, Q - R>(La, m, tid, xc);                                          \
+        }                                                                                   \
     }
         QSV_ALL_Q(QSV_BACK)
 #undef QSV_BACK
@@ -3026,7 +3060,7 @@ hipError_t launch_build_mats(const CircDev& c, const float* params, const float*
     const u64 seg = period > 0 ? (u64)period : per;
     const u64 groups = tables * (per / seg) * ((seg + kMatGroup - 1) / kMatGroup);
     hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(groups, 4)), dim3(256), 0, st, c, params, feats, groups, inverse,
-                       order, period, form == MatForm::plain ? 1 : 0, seq_first(form), seq_step(form), out, scale);
+                       order, period, form, seq_first(form), seq_step(form), out, scale);
     return hipGetLastError();
 }
 
@@ -3096,7 +3130,7 @@ hipError_t launch_forward_small(int regs, const float* x, int64_t dim, int64_t b
 
 hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const CircDev& c, int entangler,
                               const float* params, const float* back, int kind, int q, uint64_t mask, const float* targets,
-                              double* sums, double* f, hipStream_t st) {
+                              float2* kept, double* sums, double* f, hipStream_t st) {
     if (c.n < 1 || c.n > kSmallMaxQubits || batch < 1 || dim < 1 || dim > ((int64_t)1 << c.n)) return hipErrorInvalidValue;
     if (c.slots() < 1 || c.n_layers < 1 || (int64_t)c.n_layers * c.n > kSmallMats) return hipErrorInvalidValue;
     // four amplitudes per thread: eight and sixteen measured slower or the same at every batch (9 qubits x 64 47 / 59 /
@@ -3107,7 +3141,7 @@ hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const 
     const unsigned threads = tb > 6 ? 64u << (tb - 6) : 64u;
     SweepArgs a;
     a.x = x; a.dim = dim; a.batch = batch; a.c = c; a.entangler = entangler; a.back = back;
-    a.kind = kind; a.obs_qubit = q; a.mask = mask; a.targets = targets; a.f = f; a.sums = sums;
+    a.kind = kind; a.obs_qubit = q; a.mask = mask; a.targets = targets; a.f = f; a.kept = kept; a.sums = sums;
     a.rows = rows_g;
     if (c.reupload && a.rows > kSmallMats / per) a.rows = kSmallMats / per;
     a.mat_floats = (c.reupload ? a.rows : 1) * per * 8;
@@ -3116,9 +3150,10 @@ hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const 
     size_t lds = 64 * sizeof(double) + (size_t)a.mat_floats * sizeof(float);
     if (threads > 64) lds += 2 * (size_t)(2 << regs) * threads * sizeof(float);
     const dim3 grid((unsigned)blocks), block(threads);
-    switch (c.n) {
-#define QSV_SWEEP(N) \
-    case N: hipLaunchKernelGGL((k_sweep_small<regs, N>), grid, block, lds, st, a); break;
+    switch (kept ? -c.n : c.n) {
+#define QSV_SWEEP(N)                                                                                   \
+    case N: hipLaunchKernelGGL((k_sweep_small<regs, N, false>), grid, block, lds, st, a); break;       \
+    case -N: hipLaunchKernelGGL((k_sweep_small<regs, N, true>), grid, block, lds, st, a); break;
         QSV_SWEEP(1) QSV_SWEEP(2) QSV_SWEEP(3) QSV_SWEEP(4) QSV_SWEEP(5) QSV_SWEEP(6) QSV_SWEEP(7) QSV_SWEEP(8) QSV_SWEEP(9)
         QSV_SWEEP(10)
 #undef QSV_SWEEP

@@ -1205,3 +1205,58 @@ def test_factored_unitaries_round_no_worse_than_matrices(oracle, rot, reup, n, B
         err.append(np.linalg.norm(gu.state_np(ctx).reshape(B, -1) - ref))
         ctx.close()
     assert err[0] <= 1.05 * err[1]
+
+
+@pytest.mark.parametrize("n,B,L,rot,ent,reup", [(4, 128, 2, (RY, RZ), RING, 0), (5, 33, 12, (RX, RY, RZ), RING, 1), (8, 32, 6, (RY, RZ), RING, 1),
+                                                (9, 16, 8, (RX, RY), LADDER, 0), (10, 16, 6, (RY,), RING, 1)])
+def test_small_reverse_mode_sweep_is_as_near_to_64_bits_as_the_passes(oracle, n, B, L, rot, ent, reup):
+    """The one-launch sweep keeps psi of every layer as the layer-by-layer sweep does, so its gradient is as near to 64
+    bits but for the rounding of its unitaries: 2x2 matrices, where the passes' factored form rounds down to 0.8 times as much,
+    hence 1.25 (measured 0.95 to 1.16; with psi taken back beside lambda 1.30 to 1.82)."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, rot, ent, reup)
+    g = rng(77 * n + B)
+    P = spec.num_params(n)
+    x = g.standard_normal((B, 1 << n)).astype(np.float32)
+    p = g.uniform(0, 2 * np.pi, P).astype(np.float32)
+    f = g.standard_normal((B, n)).astype(np.float32)
+    y = g.uniform(-1, 1, (B, n)).astype(np.float32)
+    circ = qb.circuit_from_spec(spec)
+    _, ref = oracle.loss_grad(x, n, ocirc(oracle, spec), p, f if reup else None, kind=oracle.LOSS_MSE_Z, targets=y)
+    ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
+    err = []
+    for small in (1, 0):
+        ctx.qsv_set_option("small_apply", small)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+        ctx.qsv_loss_grad(circ, gu.dev(x), gu.dev(p), gu.dev(f) if reup else None, qb.QSV_LOSS_MSE_Z, loss, grad, targets=gu.dev(y))
+        torch.cuda.synchronize()
+        err.append(np.linalg.norm(grad.cpu().numpy() - ref))
+    ctx.close()
+    assert err[0] <= 1.25 * err[1]
+
+
+@pytest.mark.parametrize("n,B,L,reup", [(9, 3000, 56, 0), (10, 1000, 51, 0), (10, 1600, 40, 1)])
+def test_small_reverse_mode_sweep_with_and_without_room_for_the_states(n, B, L, reup):
+    """B L states do not fit into the smallest workspace (psi is taken back beside lambda), but do into the one for
+    gradients.  Same gradient up to the rounding of 3 L n gates on entries of at most 1."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, (RY,), RING, reup)
+    circ = qb.circuit_from_spec(spec)
+    need = 8 * B * L << n
+    sizes = qb.qsv_workspace_bytes(n, B), qb.qsv_grad_workspace_bytes(n, B, circ)
+    assert sizes[0] < need < sizes[1]
+    g = rng(n + L)
+    P = spec.num_params(n)
+    x, f = (gu.dev(g.standard_normal(s).astype(np.float32)) for s in ((B, 1 << n), (B, n)))
+    p = gu.dev(g.uniform(0, 2 * np.pi, P).astype(np.float32))
+    res = []
+    for size in sizes:
+        ctx = gu.make_ctx(n, B, ws_bytes=size)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+        ctx.qsv_adjoint_grad(circ, x, p, f if reup else None, 2, loss, grad)
+        torch.cuda.synchronize()
+        res.append((loss, grad))
+        ctx.close()
+    assert torch.equal(res[0][0], res[1][0])
+    d = (res[0][1] - res[1][1]).abs().max().item()
+    assert 0.0 < d <= 6e-8 * np.sqrt(3 * L * n) * 4
