@@ -165,7 +165,7 @@ bool same_circuit(const qsv_circuit& a, const qsv_circuit& b) {
 // behind every kernel that read the old contents, so nothing waits on the host.
 qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad,
                     const CachedPlan** out, int defer = 0) {
-    int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer ? defer_tile(ctx->n, rows) : default_tile(ctx->n, rows);
+    int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer ? defer_tile(ctx->n, rows, c.n_layers) : default_tile(ctx->n, rows);
     tile = std::max(kMinTile, std::min(kMaxTile, tile));
     // tiles of one row through one LDS plane (tiles of 2^14 have no other way): see kDirectMaxQubits
     const int direct = ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile) ? 1 : 0;
@@ -747,7 +747,7 @@ qsv_status qsv_apply_layers(qsv_ctx* ctx, const qsv_circuit* c, const float* par
     int defer = 0;
     if (ctx->opt_defer != 0 && c->entangler == QSV_ENT_CNOT_RING && ctx->n <= 28 && !ctx->opt_naive &&
         ar.remaining() >= align_up(state_bytes)) {
-        int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer_tile(ctx->n, ctx->batch);
+        int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer_tile(ctx->n, ctx->batch, c->n_layers);
         if (ctx->n > tile) {
             pong = (float2*)ar.take(state_bytes);
             defer = pong ? 1 : 0;

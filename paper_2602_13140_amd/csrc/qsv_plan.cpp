@@ -487,19 +487,26 @@ int default_tile(int n, int64_t batch) {
     return (n < t && n >= kMinTile) ? n : t;
 }
 
-int defer_tile(int n, int64_t batch) {
-    // A tile of 2^13 costs up to 7 % more per pass than one of 2^12 (barriers over eight wavefronts), so
-    // it pays where it saves more passes than that, and where passes are what counts (states of 32 MiB
-    // and more).  By the number of qubits the passes of 20 layers are, 2^12 / 2^13: 17: 14/15, 18: 17/16,
-    // 19: 21/15, 20: 21/18, 21: 25/22, 22: 25/26, 23: 25/25, 24: 30/30, 25: 30/30, 26: 34/32, and of 10 layers
-    // 26: 17/16, 27: 20/16, 28: 21/18.  Measured, 10 layers: 20 qubits x 32 1207 -> 1140 us, 26 qubits
-    // 3683 -> 3451 us, 27 qubits 8.6 -> 6.9 ms; 22 qubits x 8 1268 -> 1465 us, 18 qubits x 16 178 -> 178 us.
+int defer_tile(int n, int64_t batch, int layers) {
+    // A tile of 2^13 costs up to 11 % more per pass than one of 2^12 (barriers over eight wavefronts), so it pays where it
+    // saves a pass, and where passes are what counts (states of 32 MiB and more).  By the planner, for rings of 1 to 40
+    // layers, 2^13 needs fewer passes than 2^12: 19 and 20 qubits from 4 layers on (20 layers: 21/15 and 21/18 with 2^12 /
+    // 2^13; up to 3 layers and 20 x 8 the same number), 21 qubits (1 layer 3/2, 20: 25/21) but for 2 and 4 layers, 22
+    // qubits only with 1 layer (3/2; 20: 25/26), 23 and 25 qubits in turns (20: 25/26, 30/30), 24 qubits from 12
+    // layers on by about a fifteenth (20: 30/28; 1543 -> 1512 us: kept at 2^12), 26 qubits (20: 34/32) but for 1 layer (3/3), 2
+    // (4/5), 4 (8/8) and 8 (14/14), 27 and 28 qubits (10: 20/16, 21/18) but for 1 layer (3/3).
+    // Measured, 2^12 / 2^13: 20 qubits x 32, 10 layers 1207 / 1140 us; 20 x 32, 2 layers 285 / 300, 20 x 4, 3 layers 84 / 88,
+    // 21 x 16, 2 layers 306 / 303; 21 qubits, 1 layer 49 / 30; 22 x 8, 1 layer 257 / 193, 10 layers 1268 / 1465; 26 qubits, 1 layer
+    // 612 / 538, 2 layers 882 / 1024, 4 layers 1700 / 1750, 8 layers 2990 / 3053, 10 layers 3683 / 3451; 27 qubits, 10 layers 8.6 /
+    // 6.9 ms; 18 x 16, 10 layers 178 / 178 us.
     // States of at most 2^19 amplitudes leave most of the chip idle: twice the workgroups are worth
     // more than passes (16 qubits 95 -> 88 us, 14 qubits x 16 89 -> 79 us; 2^20 amplitudes 128 -> 134 us).
     const int64_t amps = batch << n;
     const int t = default_tile(n, batch);
     if (t != 12) return t;
-    if (amps >= ((int64_t)1 << 22) && ((n >= 19 && n <= 21) || n >= 26)) return 13;
+    if (layers == 1 && (n == 21 || n == 22)) return 13;
+    const bool fewer = (n >= 19 && n <= 21) || n >= 27 || (n == 26 && layers != 2 && layers != 4 && layers != 8);
+    if (amps >= ((int64_t)1 << 22) && fewer) return 13;
     return n > 13 && amps <= ((int64_t)1 << 19) ? 11 : 12;
 }
 
@@ -704,7 +711,7 @@ extern "C" int64_t qsv_plan_describe(const qsv_circuit* c, int n_qubits, int bat
     const bool defer = (tile_log2 & 0x100) != 0;     // flag bit: the plan with deferred CNOTs
     const bool mirror = defer && inverse && (tile_log2 & 0x200) != 0;   // flag bit: as the mirror of the circuit's
     tile_log2 &= 0xff;
-    if (defer && tile_log2 == 0) tile_log2 = defer_tile(n_qubits, batch);
+    if (defer && tile_log2 == 0) tile_log2 = defer_tile(n_qubits, batch, c->n_layers);
     if (tile_log2 != 0 && (tile_log2 < kMinTile || tile_log2 > kMaxTile)) return -1;
     Plan p = build_plan(*c, n_qubits, batch, inverse != 0 && !mirror, tile_log2, false, 0, defer);
     if (mirror) p = mirror_plan(p);

@@ -127,7 +127,7 @@ unsigned line_mate(const Plan& p, const Pass& ps);
 
 int default_tile(int n, int64_t batch);
 
-// Tile size of a circuit that is planned with deferred CNOTs.
-int defer_tile(int n, int64_t batch);
+// Tile size of a circuit of that many layers that is planned with deferred CNOTs.
+int defer_tile(int n, int64_t batch, int layers);
 
 }  // namespace qsv

@@ -941,7 +941,7 @@ def test_unitaries_at_special_angles(oracle, n, B, L, rot, ent, reup, tile, inve
 
 # ------------------------------------------------------------------ choice of tile, mirrored plans
 @pytest.mark.parametrize("n,B,L", [(13, 5, 3), (14, 1, 4), (14, 33, 3), (16, 7, 5), (16, 9, 3), (19, 8, 3), (20, 4, 2),
-                                   (21, 2, 3), (22, 1, 3)])
+                                   (21, 2, 3), (22, 1, 3), (21, 1, 1), (22, 2, 1)])
 def test_ring_circuit_and_its_inverse_at_the_bounds_of_the_tile_rule(n, B, L):
     """Tiles of 2^11, 2^12 and 2^13 by size, one or two streams, the inverse as the mirrored plan that reads
     through index maps: against one gate per launch on the GPU.  2 L (3 n) gates of a few roundings

@@ -381,3 +381,21 @@ def test_mirrored_plan_replays_to_the_oracle(oracle, n, L, rot, tile):
         one = lines[0] + "\n" + " ".join(t for t in toks if t[0] != "M") + "\n"
         st, _, _ = replay(one, n, 1, L, rot, RING, 0, params.astype(np.float64), None, 1, st)
     assert np.allclose(st, ref, atol=1e-12)
+
+
+@pytest.mark.parametrize("n", [18, 19, 20, 21, 22, 24, 26, 27, 28])
+def test_default_tile_never_costs_a_pass(n):
+    """The tile that a ring circuit gets by its number of qubits and layers takes no more passes than a tile of 2^12, and
+    from 26 qubits on none more than 2^13 either."""
+    def passes(L, batch, tile):
+        circ = qb.make_circuit(L, [RY, RZ], 1, 0)
+        return sum(ln.startswith("P ") for ln in qb.qsv_plan_describe(circ, n, batch, 0, tile | DEFER).split("\n"))
+
+    for L in (1, 2, 3, 4, 5, 8, 9):
+        for batch in (1, 8) if n < 24 else (1,):
+            if batch << n <= 1 << 19:
+                continue                             # tiles of 2^11 there, for the number of workgroups
+            got, p12, p13 = passes(L, batch, 0), passes(L, 1, 12), passes(L, 1, 13)
+            assert got <= p12, (L, batch)
+            if n >= 26:
+                assert got <= p13, (L, batch)
