@@ -455,8 +455,11 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         a.nt_store = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : (touched >= kNtStoreBytes ? 1 : 0);
         // Every other pass walks the tiles downwards, so that it starts with what the pass before
         // wrote last and may still find in a cache (measured, two buffers of 32 to 256 MiB: 16 qubits
-        // x 64 175 -> 166 us, 24 qubits 828 -> 761 us; no size at which it costs anything).
-        a.rev = ctx->opt_rev != 0 ? (int)(pi & 1) : 0;
+        // x 64 175 -> 166 us, 24 qubits 828 -> 761 us).  A pass without a map finds its tiles where they were: it keeps them
+        // on their XCDs, whose L2s hold 32 MiB together (ladders of 2 layers: 21 qubits 67 -> 52 us, 52 without any reversing;
+        // 22 qubits 63 -> 58).  Passes through a map read or write all over the row (kept on its XCD, 20 qubits x 4, 10
+        // layers back 211 -> 216 us).
+        a.rev = ctx->opt_rev != 0 && (pi & 1) ? (ps.map_begin < 0 ? 2 : 1) : 0;
         // Beside the other chunk of a reverse-mode sweep the passes share the chip with the transition sums, which a
         // raised priority holds up.  Measured, raised / not: 20 qubits x 32 12350 / 11900 us, 22 x 16 10607 / 10378, 24 x 4
         // 10700 / 10474, 18 x 64 1853 / 1838; 16 x 256, whose rows the caches hold, 2967 / 3010.

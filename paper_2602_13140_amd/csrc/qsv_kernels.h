@@ -48,7 +48,7 @@ struct PassArgs {
     int zq;
     int nostore;         // with zout: the state is not written back
     int nt_store;        // nontemporal tile stores (states much larger than the last-level cache)
-    int rev;             // workgroups take the tiles in descending order (see run_circuit)
+    int rev;             // workgroups take the tiles in descending order (see run_circuit and reversed_tile)
     int prio;            // wavefronts raise their issue priority while they compute addresses and issue the
                          // tile's loads, and again for its stores (the gates run at the base priority)
     const float* mats;   // [samples if rowdep][n_mats][8], unitaries in execution order: factored in groups,
@@ -69,6 +69,12 @@ struct PassArgs {
     int first_mat;       // index of the pass's first unitary
     unsigned g_sample0, g_rem0;   // gradient rows: rm.row0 / rm.per and rm.row0 % rm.per
 };
+
+// The tile that workgroup b of `tiles` takes in a pass that goes downwards.  Workgroups go to the eight XCDs in turn; with
+// rev = 2 eights of tiles change places and keep their order inside, so that a tile stays on its XCD.
+QSV_HD inline unsigned reversed_tile(unsigned b, unsigned tiles, int rev) {
+    return rev == 2 && (tiles & 7u) == 0 ? tiles - 8u - (b & ~7u) + (b & 7u) : tiles - 1u - b;
+}
 
 // The tile of a row that workgroup b of the row takes: t and t ^ mate are eight apart (mate = 0: tile b).  b without bit
 // 3 numbers the pairs: it fills the tile's bits other than the lowest bit of mate.  Needs 16 tiles in a row.

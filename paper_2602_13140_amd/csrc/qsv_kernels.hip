@@ -209,7 +209,7 @@ void k_pass(const PassArgs a) {
                   "with two planes the second plane is reached through the LDS offset fields");
     const unsigned lds_byte0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)lds;
     const unsigned thr = threadIdx.x;
-    const u64 tb = a.rev ? (u64)(gridDim.x - 1u - blockIdx.x) : (u64)blockIdx.x;
+    const u64 tb = a.rev ? (u64)reversed_tile(blockIdx.x, gridDim.x, a.rev) : (u64)blockIdx.x;
     const int c = a.c, w = a.w;
     const unsigned cmask = (1u << c) - 1u;
     const int wc = w - c;
@@ -468,7 +468,7 @@ void k_pass_direct(const PassArgs a) {
     if (a.prio) __builtin_amdgcn_s_setprio(3);
     if ((unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)lds != 0) return;   // cannot happen; LDS addresses rely on it
     const unsigned thr = threadIdx.x;
-    const unsigned tile = a.rev ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+    const unsigned tile = a.rev ? reversed_tile(blockIdx.x, gridDim.x, a.rev) : blockIdx.x;
     const unsigned nb = (unsigned)(a.n - T), row = tile >> nb;
     unsigned tr = tile & ((1u << nb) - 1u);
     if constexpr (GATHER) tr = mate_order(tr, a.mate);

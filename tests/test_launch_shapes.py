@@ -1,5 +1,5 @@
-"""Host arithmetic of the one-launch kernel (no GPU): what a workgroup writes into LDS stays inside what its launch
-asks for."""
+"""Host arithmetic of launches (no GPU): what a workgroup of the one-launch kernel writes into LDS stays inside what its
+launch asks for; workgroups of a pass that goes downwards take every tile once."""
 import os
 import shutil
 import subprocess
@@ -55,13 +55,41 @@ int main() {
 """
 
 
-def test_lds_of_the_one_launch_kernel_holds_all_it_writes(tmp_path):
+ORDER = r"""
+#include <cstdio>
+#include <vector>
+#include "qsv_kernels.h"
+using namespace qsv;
+int main() {
+    for (int rev = 1; rev <= 2; ++rev)
+        for (unsigned tiles = 1; tiles <= 300; ++tiles) {
+            std::vector<int> seen(tiles, 0);
+            for (unsigned b = 0; b < tiles; ++b) {
+                const unsigned t = reversed_tile(b, tiles, rev);
+                const bool on_its_xcd = rev == 1 || tiles % 8 != 0 || t % 8 == b % 8;
+                if (t >= tiles || seen[t]++ || !on_its_xcd) { std::printf("rev %d tiles %u b %u -> %u\n", rev, tiles, b, t); return 1; }
+            }
+        }
+    return 0;
+}
+"""
+
+
+def run(tmp_path, program):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
-    src, exe = tmp_path / "small.cpp", str(tmp_path / "small")
-    src.write_text(PROGRAM)
+    src, exe = tmp_path / "program.cpp", str(tmp_path / "program")
+    src.write_text(program)
     subprocess.check_call(["g++", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                            "-I", os.path.join(ROOT, "paper_2602_13140_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
                            str(src), "-o", exe])
     r = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[-2000:]
+
+
+def test_lds_of_the_one_launch_kernel_holds_all_it_writes(tmp_path):
+    run(tmp_path, PROGRAM)
+
+
+def test_a_pass_that_goes_downwards_takes_every_tile_once(tmp_path):
+    run(tmp_path, ORDER)
