@@ -842,8 +842,10 @@ static qsv_status measure_impl(qsv_ctx* ctx, const qsv_measure_req* req, Arena& 
             if ((st = bind_device(ctx)) != QSV_OK) return st;
             unsigned long long* cum = (unsigned long long*)ar.take((size_t)B * chunk_blocks(n) * 8);
             if (!cum) return ws_fail(ctx, ar, "qsv_measure(SAMPLE)");
-            // finer sums where the scratch has room for them: they save the draws most of their reading
-            unsigned long long* sub = (unsigned long long*)ar.take((size_t)B * chunk_blocks(n) * 16 * 8);
+            // Finer sums, of 256 amplitudes each, where the scratch has room for them: they save the draws most of their
+            // reading.  Up to 7 qubits the scan has only two steps at most, which are less than the search (64 rows x 1024
+            // shots, scan / sums: 4 qubits 24 / 33 us, 7 qubits 27 / 33; 8 qubits 34 / 33, 9 qubits 53 / 33).
+            unsigned long long* sub = n < 8 ? nullptr : (unsigned long long*)ar.take((size_t)B * chunk_blocks(n) * 16 * 8);
             QSV_HIP(ctx, launch_sample(ctx->state, B, n, req->uniforms_dev, req->shots, cum, sub,
                                        (long long*)req->out_dev, ctx->stream),
                     "sample");

@@ -1011,7 +1011,7 @@ def test_expz_at_every_grouping(n, B):
     ctx.close()
 
 
-@pytest.mark.parametrize("n,B,shots", [(1, 3, 5), (5, 2, 64), (12, 2, 129), (13, 3, 600), (14, 1, 5000), (18, 2, 1000)])
+@pytest.mark.parametrize("n,B,shots", [(1, 3, 5), (5, 2, 64), (7, 3, 100), (8, 3, 100), (12, 2, 129), (13, 3, 600), (14, 1, 5000), (18, 2, 1000)])
 def test_sampling_and_shot_means_by_size(n, B, shots):
     """Draws against the integer rule in Python, one shot in 37; shot means against whole-number sums."""
     torch = gu.torch_cuda()
