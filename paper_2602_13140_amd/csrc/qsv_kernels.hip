@@ -659,43 +659,9 @@ __global__ __launch_bounds__(256) void k_naive_cz_ladder(float2* state, u64 tota
 // Fused per-(layer, qubit) matrices, computed in double and rounded once to float.
 struct M2 { double r[4], i[4]; };  // row-major 2x2: [0]=m00 [1]=m01 [2]=m10 [3]=m11
 
-// Sine and cosine in double.  Angles of up to 2^16 (any in use) are brought to |r| <= pi/4 by subtracting a multiple of
-// pi/2 held as the sum of two doubles, and the Taylor series up to r^17 and r^16 leave less than 1e-17: the
-// error is a few 1e-17, and the results are rounded to floats.
-__device__ __forceinline__ void sincos_angle(double x, double* s, double* c) {
-    if (!(fabs(x) <= 65536.0)) {                   // also infinities and NaN
-        sincos(x, s, c);
-        return;
-    }
-    const double k = rint(x * 0.6366197723675814);
-    const double r = fma(-k, 6.123233995736766e-17, fma(-k, 1.5707963267948966, x));
-    const double r2 = r * r;
-    double sp = 2.8114572543455206e-15, cp = 4.779477332387385e-14;
-    sp = fma(sp, r2, -7.647163731819816e-13);
-    sp = fma(sp, r2, 1.6059043836821613e-10);
-    sp = fma(sp, r2, -2.505210838544172e-08);
-    sp = fma(sp, r2, 2.7557319223985893e-06);
-    sp = fma(sp, r2, -0.0001984126984126984);
-    sp = fma(sp, r2, 0.008333333333333333);
-    sp = fma(sp, r2, -0.16666666666666666);
-    cp = fma(cp, r2, -1.1470745597729725e-11);
-    cp = fma(cp, r2, 2.08767569878681e-09);
-    cp = fma(cp, r2, -2.755731922398589e-07);
-    cp = fma(cp, r2, 2.48015873015873e-05);
-    cp = fma(cp, r2, -0.001388888888888889);
-    cp = fma(cp, r2, 0.041666666666666664);
-    cp = fma(cp, r2, -0.5);
-    sp = fma(r * r2, sp, r);
-    cp = fma(cp, r2, 1.0);
-    const int q = (int)k;
-    const double a = (q & 1) ? cp : sp, b = (q & 1) ? sp : cp;
-    *s = (q & 2) ? -a : a;
-    *c = ((q + 1) & 2) ? -b : b;
-}
-
 __device__ __forceinline__ M2 rot_m(int axis, double t) {
     double s, c;
-    sincos_angle(0.5 * t, &s, &c);
+    sincos(0.5 * t, &s, &c);
     M2 m;
     for (int k = 0; k < 4; ++k) { m.r[k] = 0.0; m.i[k] = 0.0; }
     if (axis == QSV_RX) { m.r[0] = c; m.i[1] = -s; m.i[2] = -s; m.r[3] = c; }
@@ -750,7 +716,7 @@ __device__ __forceinline__ M2 fused_raw(const CircDev& c, const float* params, c
         else axis = c.rot[sl - c.reupload];
         if (sl == shift_slot) t += shift;
         double s, co;
-        sincos_angle(0.5 * t, &s, &co);
+        sincos(0.5 * t, &s, &co);
         rotate_column(axis, s, co, ar, ai, br, bi);
     }
     if (inverse) { ai = -ai; br = -br; bi = -bi; }   // conjugate transpose
@@ -2436,7 +2402,7 @@ __device__ __forceinline__ void small_build(const CircDev& c, const float* param
         if (sl < slots) {
             double t = (double)stage[(l * slots + sl) * N + q];
             if (c.reupload && sl == 0) t *= (double)stage[n_par + r * N + q];
-            sincos_angle(0.5 * t, &sn, &co);
+            sincos(0.5 * t, &sn, &co);
         }
         double ar = 1.0, ai = 0.0, br = 0.0, bi = 0.0;
         const int lane0 = (tid & 63) & ~((1 << lg) - 1);

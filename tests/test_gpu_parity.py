@@ -1076,8 +1076,8 @@ def test_fidelity_rows_that_start_anywhere(n, B, dim, shift):
 @pytest.mark.parametrize("n,B,L,reup", [(2, 3, 4, 1), (4, 70, 8, 1), (4, 2500, 2, 1), (5, 2049, 3, 1), (8, 3, 6, 1), (9, 5, 4, 0),
                                         (3, 40000, 2, 1)])
 def test_one_launch_with_every_number_of_samples_per_workgroup(oracle, n, B, L, reup):
-    """Re-uploading samples spread over one workgroup each up to 2048, more than one beyond; large angles take the
-    sine and cosine past the short reduction."""
+    """Re-uploading samples spread over one workgroup each up to 2048, more than one beyond; some angles are
+    large."""
     spec = wl.CircuitSpec(L, (RY, RZ, RX), RING, reup)
     g = rng(n * 7 + B)
     p = g.uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32)
