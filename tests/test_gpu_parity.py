@@ -1260,3 +1260,29 @@ def test_small_reverse_mode_sweep_with_and_without_room_for_the_states(n, B, L, 
     assert torch.equal(res[0][0], res[1][0])
     d = (res[0][1] - res[1][1]).abs().max().item()
     assert 0.0 < d <= 6e-8 * np.sqrt(3 * L * n) * 4
+
+
+@pytest.mark.parametrize("n,L,ent", [(27, 2, RING), (28, 2, RING), (28, 1, LADDER), (29, 1, LADDER)])
+def test_rows_at_the_largest_offsets(n, L, ent):
+    """The last sizes whose rows the 32-bit offsets of the direct pass kernel reach (28 qubits: a row of 2^31 bytes) and the
+    first that the general kernel takes: circuit and inverse against one gate per launch.  2 L (3 n) gates of a few
+    roundings of 6e-8 each on a state of norm 1."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, (RX, RY), ent)
+    p = gu.dev(rng(n).uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32))
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, 1)
+    for inverse in (0, 1):
+        res = []
+        for naive in (1, 0):
+            ctx.qsv_set_option("naive", naive)
+            ctx.state.normal_(generator=torch.Generator(device="cuda").manual_seed(n)).mul_(2.0 ** (-(n + 1) / 2))
+            ctx.qsv_apply_layers(circ, p, None, inverse)
+            res.append(ctx.state.clone())
+        diff = sum((a - b).double().square().sum().item() for a, b in zip(res[0].view(-1).split(1 << 26), res[1].view(-1).split(1 << 26)))
+        norm = sum(a.double().square().sum().item() for a in res[0].view(-1).split(1 << 26))
+        assert abs(norm - 1.0) <= 1e-3
+        assert np.sqrt(diff) <= 6e-8 * 4 * np.sqrt(2 * L * 3 * n), (inverse, np.sqrt(diff))
+        del res
+    ctx.close()
+    torch.cuda.empty_cache()
