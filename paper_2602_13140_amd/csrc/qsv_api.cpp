@@ -74,7 +74,7 @@ struct qsv_ctx {
     int opt_planes = 1;
     int opt_grad_layered = 1;
     int opt_nt_store = -1;   // -1: by state size
-    int opt_rev = -1;        // every other pass takes its tiles in descending order; -1: by state size
+    int opt_rev = -1;        // every other pass takes its tiles in descending order; -1: yes
     int probe_count = 0;
     int opt_probe_layout = -1;  // probe pass: register run of the load and the store (-1: the highest)
     int64_t opt_grad_chunk = 0;
@@ -1449,8 +1449,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     a.src = nullptr;
     a.zout = nullptr; a.zq = 0; a.nostore = 0;
     a.nt_store = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : ((((uint64_t)ctx->batch << n) * 8) >= kNtStoreBytes ? 1 : 0);
-    a.rev = (ctx->opt_rev >= 0 ? ctx->opt_rev : ((((uint64_t)ctx->batch << n) * 8) >= kNtStoreBytes ? 1 : 0))
-                ? (ctx->probe_count++ & 1) : 0;
+    a.rev = ctx->opt_rev != 0 && (ctx->probe_count++ & 1) ? 2 : 0;      // as run_circuit's passes without a map
     a.ops = dev;
     a.mats = reinterpret_cast<const float*>(dev);   // no unitaries, but the first table entry is fetched unseen
     a.exec_of = nullptr;
@@ -1463,6 +1462,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     a.rm = plain_rows(n);
     a.direct = direct;
     a.gather = 0;
+    a.mate = 0;
     a.s_in = direct ? low.passes[0].s_in : 0;
     a.s_out = direct ? low.passes[0].s_out : 0;
     a.first_mat = 0;
