@@ -278,9 +278,9 @@ int64_t qsv_plan_describe(const qsv_circuit* c, int n_qubits, int batch, int inv
  * operation list) and must not be called while the stream is being captured. */
 qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int transposes);
 
-/* Testing/tuning knobs: tile_log2 in 10..14 (0 = default: 11, 12 or 13 by the number of qubits and
- * of amplitudes) forces the tile size of the fused pass kernel (14 exists with one LDS plane only); defer_cnots = 1 / 0 lets qsv_apply_layers carry the
- * CNOTs whose target qubit lies outside a pass's tile by the index the pass writes each amplitude to
+/* Testing/tuning knobs: tile_log2 in 10..14 (0 = default: 11, 12 or 13 by the number of qubits, of layers and
+ * of amplitudes) forces the tile size of the fused pass kernel (14 exists with one LDS plane only);
+ * defer_cnots = 1 / 0 lets qsv_apply_layers carry the CNOTs whose target qubit lies outside a pass's tile by the index the pass writes each amplitude to
  * (fewer passes over the state; such passes write a second buffer taken from the workspace), or keeps
  * every CNOT a register operation (-1, the default, defers whenever the circuit has a CNOT ring, more
  * qubits than the tile has index bits, at most 28 of them, and the workspace has room for a copy of
@@ -290,10 +290,13 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
  * small_apply = 1 (default) / 0 lets qsv_apply_layers run states of at most 10 qubits and 2^21 amplitudes in
  * all (10 qubits: 2^20) in one launch with the gates in registers and lane exchanges (the kernel of qsv_forward_small, started
  * from the state; measured 1.6 to 4 times faster there than the fused passes, whose launches cost more than
- * their arithmetic on such states), or always takes the fused passes;
+ * their arithmetic on such states), or always takes the fused passes; with it qsv_adjoint_grad and
+ * qsv_loss_grad run circuits of at most 10 qubits and 512 unitaries (layers times qubits) in one launch too,
+ * unless tile_log2, naive, grad_layered = 0 or grad_chunk_rows is set or the workspace has no room for
+ * its matrices and sums (1 KiB at most per sample and layer);
  * small_regs = 2, 3 or 4 fixes the amplitudes per thread of qsv_forward_small at 4, 8 or 16 (0, the
- * default, takes the most that still gives the chip about four wavefronts per SIMD); low_bits in 4..10 (0 = default) forces the planner's minimum number of low index bits
- * per tile; lds_planes = 1 (default) moves real and imaginary parts through one LDS plane one
+ * default, takes the most that still gives the chip about four wavefronts per SIMD); low_bits in 3..10
+ * (0 = default) forces the planner's minimum number of low index bits per tile; lds_planes = 1 (default) moves real and imaginary parts through one LDS plane one
  * after the other, 2 through two planes at once; naive = 1 routes qsv_apply_layers through the
  * one-gate-per-launch kernels; grad_layered = 0 makes qsv_param_shift_grad run every shifted
  * circuit whole; nt_store = 1 / 0 forces nontemporal / ordinary tile stores in the fused pass (-1,

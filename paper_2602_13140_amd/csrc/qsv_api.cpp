@@ -80,7 +80,7 @@ struct qsv_ctx {
     int64_t opt_grad_chunk = 0;
     int opt_split = -1;      // state rows of a launch sequence in two halves on two streams; -1: by state size
     int opt_prio = 1;        // raised issue priority around a tile's loads and stores (2 % off configs 3 and 4 with k_pass, none with k_pass_direct)
-    int opt_small_apply = 1; // qsv_apply_layers runs states of at most 2^21 amplitudes on at most 10 qubits in one launch
+    int opt_small_apply = 1; // at most 10 qubits: qsv_apply_layers (up to small_apply_amplitudes) and reverse mode in one launch
     int opt_small_regs = 0;  // qsv_forward_small: amplitudes per thread = 2^this (2..4); 0: by batch size
     int opt_defer = -1;      // qsv_apply_layers defers CNOTs whose target lies outside a pass's tile; -1: when it can
     hipStream_t side = nullptr;          // second stream for that (default priority, non-blocking)
@@ -1240,7 +1240,8 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
     }
     // With room for the transition sums of all layers, adding them up and the derivatives are two launches for a whole
     // chunk instead of two short ones (6 to 8 us each, nothing of the same chunk runs beside them) for every layer:
-    // 16 qubits x 256, 10 layers 2948 -> 2865 us; 20 qubits x 32, 20 layers, bound by memory traffic, 12.4 ms either way.
+    // 16 qubits x 256, 10 layers 2948 -> 2865 us.  At 20 qubits x 32, 20 layers the two sets would take 210 MB, which a
+    // workspace of qsv_grad_workspace_bytes does not have left; with so much more 11.87 -> 11.83 ms (bound by traffic).
     bool late = L > 1 && P > 0;
     {
         Arena all = ar;     // what is taken here is given back if it does not fit

@@ -1136,10 +1136,11 @@ def test_small_reverse_mode_sweep_against_the_passes(n, B, L, rot, ent, reup):
 
 @pytest.mark.parametrize("n,L", [(11, 1000), (12, 400)])
 def test_adjoint_sums_of_all_layers_late_or_layer_by_layer(n, L):
-    """The derivatives of a chunk in one go or layer by layer, whichever the scratch has room for.  The sums of all
-    layers take 256 L n 64 bytes times 2 (11 qubits, one partial and the total) or 5 (12 qubits): 360 and 393 MB, more
-    than the smallest workspace has and less than 512 MiB above it; L + 1 states of every sample (over 3 GiB) fit
-    neither.  The sums are the same and added in the same order, so the bits have to be equal."""
+    """The derivatives of a chunk in one go or layer by layer, whichever the scratch has room for.  The sums are the same
+    and added in the same order, so the bits have to be equal.  Which of the two a workspace leads to follows from what
+    the call takes from it: the sums of all layers (L B n records of 64 bytes, times 2 with 11 qubits: one partial and the
+    total, times 5 with 12) do not fit into the smallest workspace, and do into the larger one beside all the rest;
+    the L + 1 states of every sample fit neither."""
     torch = gu.torch_cuda()
     B = 256
     spec = wl.CircuitSpec(L, (RY,), RING, 0)
@@ -1147,9 +1148,18 @@ def test_adjoint_sums_of_all_layers_late_or_layer_by_layer(n, L):
     P = spec.num_params(n)
     x = gu.dev(g.standard_normal((B, 1 << n)).astype(np.float32))
     p = gu.dev(g.uniform(0, 2 * np.pi, P).astype(np.float32))
+    sums = L * B * n * (2 if n == 11 else 5) * 64
+    plans = 4 << 20                                        # the workspace's first part, for the plans
+    rest = (B * (2 * P + 1) * 8                            # gradient values
+            + 3 * B * (8 << n)                             # the final states, psi and lambda
+            + 2 * 48 * (L * n + 1)                         # two tables of unitaries with their scalars
+            + sums // L + B * 16 * n                       # one layer's sums, <Z> values and coefficients
+            + B * 13 * 8 + (2 * B + 32) * 256)             # <Z> partials, norms, alignment
+    sizes = [qb.qsv_workspace_bytes(n, B) + extra for extra in (0, 512 << 20)]
+    assert sizes[0] - plans < sums and plans + rest + sums <= sizes[1] < B * (L + 1) * (8 << n)
     res = []
-    for extra in (0, 512 << 20):
-        ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_workspace_bytes(n, B) + extra)
+    for size in sizes:
+        ctx = gu.make_ctx(n, B, ws_bytes=size)
         loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
         ctx.qsv_adjoint_grad(qb.circuit_from_spec(spec), x, p, None, 1, loss, grad)
         torch.cuda.synchronize()
