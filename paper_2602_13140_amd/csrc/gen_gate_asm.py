@@ -58,49 +58,20 @@ GRAY = [i ^ (i >> 1) for i in range(NR)]        # element visited at step i
 GRAY_BIT = [0] + [(i & -i).bit_length() - 1 for i in range(1, NR)]   # bit that changes on entering step i
 
 
-def u_pair(a, b, variant="g"):
-    """(r_a,i_a) has the target bit 0, (r_b,i_b) has it 1; matrix m0..m7 = vector copies of
+def u_pair(a, b):
+    """The product of the pair with a whole matrix (the last unitary of a group, shifted matrices): (r_a,i_a) has the
+    target bit 0, (r_b,i_b) has it 1; m0..m7 = vector copies of
     s88..s95 = (m00r, m00i, m01r, m01i, m10r, m10i, m11r, m11i): a vector instruction with a scalar
     operand issues at 4.2 cycles per wavefront on this chip, one with vector operands only at 2.1 to 2.4.
-    Four interleaved chains; the last step of each overwrites an input that is dead by then.
-    Variants leave out the products with
-    imaginary parts that are exact zeros: "g" none (16 instructions; the one the interpreter uses, for the
-    last unitary of a group and for shifted matrices), "a" m00i (14),
-    "r" m00i and m01i (first row real, 12), "c" m00i and m10i (first column real, 12)."""
+    Four interleaved chains; the last step of each overwrites an input that is dead by then."""
     ra, ia, rb, ib = "%%[r%d]" % a, "%%[i%d]" % a, "%%[r%d]" % b, "%%[i%d]" % b
     t = ["%[t0]", "%[t1]", "%[t2]", "%[t3]"]
     mul = lambda d, m, x: "v_mul_f32 %s, %s, %s" % (d, m, x)
     fma = lambda d, m, x, acc: "v_fma_f32 %s, %s, %s, %s" % (d, m, x, acc)
-    if variant == "g":
-        return [
-            mul(t[0], "%[m0]", ra), mul(t[1], "%[m1]", ra), mul(t[2], "%[m4]", ra), mul(t[3], "%[m5]", ra),
-            fma(t[0], "-%[m1]", ia, t[0]), fma(t[1], "%[m0]", ia, t[1]),
-            fma(t[2], "-%[m5]", ia, t[2]), fma(t[3], "%[m4]", ia, t[3]),
-            fma(t[0], "%[m2]", rb, t[0]), fma(t[1], "%[m3]", rb, t[1]),
-            fma(t[2], "%[m6]", rb, t[2]), fma(t[3], "%[m7]", rb, t[3]),
-            fma(ra, "-%[m3]", ib, t[0]), fma(ia, "%[m2]", ib, t[1]),
-            fma(rb, "-%[m7]", ib, t[2]), fma(ib, "%[m6]", ib, t[3]),
-        ]
-    if variant == "a":
-        return [
-            mul(t[0], "%[m0]", ra), mul(t[1], "%[m0]", ia), mul(t[2], "%[m4]", ra), mul(t[3], "%[m5]", ra),
-            fma(t[2], "-%[m5]", ia, t[2]), fma(t[3], "%[m4]", ia, t[3]),
-            fma(t[0], "%[m2]", rb, t[0]), fma(t[1], "%[m3]", rb, t[1]),
-            fma(t[2], "%[m6]", rb, t[2]), fma(t[3], "%[m7]", rb, t[3]),
-            fma(ra, "-%[m3]", ib, t[0]), fma(ia, "%[m2]", ib, t[1]),
-            fma(rb, "-%[m7]", ib, t[2]), fma(ib, "%[m6]", ib, t[3]),
-        ]
-    if variant == "r":
-        return [
-            mul(t[0], "%[m0]", ra), mul(t[1], "%[m0]", ia), mul(t[2], "%[m4]", ra), mul(t[3], "%[m5]", ra),
-            fma(t[2], "-%[m5]", ia, t[2]), fma(t[3], "%[m4]", ia, t[3]),
-            fma(t[2], "%[m6]", rb, t[2]), fma(t[3], "%[m7]", rb, t[3]),
-            fma(ra, "%[m2]", rb, t[0]), fma(ia, "%[m2]", ib, t[1]),
-            fma(rb, "-%[m7]", ib, t[2]), fma(ib, "%[m6]", ib, t[3]),
-        ]
-    assert variant == "c"
     return [
-        mul(t[0], "%[m0]", ra), mul(t[1], "%[m0]", ia), mul(t[2], "%[m4]", ra), mul(t[3], "%[m4]", ia),
+        mul(t[0], "%[m0]", ra), mul(t[1], "%[m1]", ra), mul(t[2], "%[m4]", ra), mul(t[3], "%[m5]", ra),
+        fma(t[0], "-%[m1]", ia, t[0]), fma(t[1], "%[m0]", ia, t[1]),
+        fma(t[2], "-%[m5]", ia, t[2]), fma(t[3], "%[m4]", ia, t[3]),
         fma(t[0], "%[m2]", rb, t[0]), fma(t[1], "%[m3]", rb, t[1]),
         fma(t[2], "%[m6]", rb, t[2]), fma(t[3], "%[m7]", rb, t[3]),
         fma(ra, "-%[m3]", ib, t[0]), fma(ia, "%[m2]", ib, t[1]),
@@ -320,26 +291,23 @@ def gen(planes=2, perlane=False):
                     if not i & (1 << j):
                         L.extend(rot_pair(i, i | (1 << j), form, name))
                 emit("s_branch " + lab("next"))
-    for variant in "g":
+    emit(ALIGN)
+    emit(lab("ug") + ":")
+    for k in range(8):
+        emit("v_mov_b32 %%[m%d], s%d" % (k, 72 + k))
+    stream_next()
+    emit(lab("ugj") + ":")                        # the shifted matrix of a gradient row joins here
+    prefetch_next_word()
+    for j in range(R - 1):
+        emit("s_cmp_eq_u32 s83, %d" % j)
+        emit("s_cbranch_scc1 " + lab("ug%d" % j))
+    for j in reversed(range(R)):
         emit(ALIGN)
-        emit(lab("u" + variant) + ":")
-        for k in range(8):
-            emit("v_mov_b32 %%[m%d], s%d" % (k, 72 + k))
-        stream_next()
-        if variant == "g":
-            emit(lab("ugj") + ":")                # the shifted matrix of a gradient row joins here
-        prefetch_next_word()
-        for j in range(R - 1):
-            emit("s_cmp_eq_u32 s83, %d" % j)
-            emit("s_cbranch_scc1 " + lab("u%s%d" % (variant, j)))
-        for j in reversed(range(R)):
-            emit(ALIGN)
-            emit(lab("u%s%d" % (variant, j)) + ":")
-            for i in range(NR):
-                if i & (1 << j):
-                    continue
-                L.extend(u_pair(i, i | (1 << j), variant))
-            emit("s_branch " + lab("next"))
+        emit(lab("ug%d" % j) + ":")
+        for i in range(NR):
+            if not i & (1 << j):
+                L.extend(u_pair(i, i | (1 << j)))
+        emit("s_branch " + lab("next"))
     # not the prefetched one (first unitary of a tile, or the one after a shifted matrix): fetch it
     emit(lab("uld") + ":")
     emit("s_lshl_b32 s84, s81, 5")
@@ -793,7 +761,7 @@ def direct_handlers():
         H.append(("US%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc1 L_dovr%d_%%=" % j] + go))
     for j in range(R):
         pairs = [(i, i | (1 << j)) for i in range(NR) if not i & (1 << j)]
-        body = [ln for a, b in pairs for ln in u_pair(a, b, "g")]
+        body = [ln for a, b in pairs for ln in u_pair(a, b)]
         H.append(("G%d" % j, ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in range(8)] + ["L_dgj%d_%%=:" % j] +
                   NEXT_ENTRY + NEXT_WORD + body + DISPATCH))
         H.append(("GS%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc0 L_dG%d_%%=" % j, "L_dovr%d_%%=:" % j,

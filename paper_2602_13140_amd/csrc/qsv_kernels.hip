@@ -1534,6 +1534,8 @@ __global__ __launch_bounds__(256) void k_sample_blocksum(const float2* state, u6
         bsum[row * nblk + blockIdx.x] = tot;
     }
 }
+
+// In-place inclusive prefix sum of each row's block sums (one 1024-thread block per row).
 __global__ __launch_bounds__(1024) void k_sample_scan(u64* cum, int nblk) {
     __shared__ u64 sm[1024];
     u64* c = cum + (u64)blockIdx.x * nblk;
@@ -1555,8 +1557,8 @@ __global__ __launch_bounds__(1024) void k_sample_scan(u64* cum, int nblk) {
     for (int i = lo; i < hi; ++i) { run += c[i]; c[i] = run; }
 }
 
-// One wavefront per shot.
-__device__ __forceinline__ u64 scan_u64(u64 v, int width, int lane) {     // inclusive, over the first `width` lanes
+// Inclusive sums over the first `width` lanes.
+__device__ __forceinline__ u64 scan_u64(u64 v, int width, int lane) {
     for (int o = 1; o < width; o <<= 1) {
         const u64 up = __shfl_up(v, o, 64);
         if (lane >= o) v += up;
@@ -1564,7 +1566,7 @@ __device__ __forceinline__ u64 scan_u64(u64 v, int width, int lane) {     // inc
     return v;
 }
 
-// The block is found by a search with 64 probes at a time (two loads in turn for 4096 blocks instead of 12);
+// One wavefront per shot.  The block is found by a search with 64 probes at a time (two loads in turn for 4096 blocks instead of 12);
 // with sub the 256 amplitudes in question by its 16 sums, without it by scanning the block's 4096 (24 qubits,
 // 4096 shots: 51 -> 9 us).
 __global__ __launch_bounds__(256) void k_sample_draw(const float2* state, int n, int nblk, const u64* cum,
