@@ -988,7 +988,7 @@ def test_reverse_mode_gradient_of_the_last_phases_is_zero(oracle, n, rot, ent):
 
 
 # ------------------------------------------------------------------ measurement kernels by size
-@pytest.mark.parametrize("n,B", [(1, 5), (2, 3), (6, 9), (7, 4), (11, 130), (12, 3), (12, 2049), (13, 1), (13, 2000),
+@pytest.mark.parametrize("n,B", [(5, 1024), (5, 1025), (1, 5), (2, 3), (6, 9), (7, 4), (11, 130), (12, 3), (12, 2049), (13, 1), (13, 2000),
                                  (15, 700), (16, 600), (17, 1024), (20, 17)])
 def test_expz_at_every_grouping(n, B):
     """Rows of a wavefront, of a block, and blocks of 1 to 16 chunks, against double sums; the probabilities'
