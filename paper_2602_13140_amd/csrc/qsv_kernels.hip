@@ -1096,7 +1096,7 @@ __device__ __forceinline__ void expz_tree(const double (&p)[16], double& T, doub
 // A block takes 2^g consecutive chunks of 4096 amplitudes of a row, whose numbers' bits (index bits 12..12+g-1)
 // are signs of the chunks' totals.  partial: [row][13 + g][nblk] doubles: T, index bits 0..11, then those.
 // One chunk per block and one reduction per chunk: 40 us on 24 qubits and 21 us for the finishing kernel,
-// which walked over 104-byte records; with 2048 blocks left and the entries side by side 25 + 4 us.
+// which walked over 104-byte records; with 2048 blocks left and the entries side by side 24 + 10 us.
 __global__ __launch_bounds__(256) void k_expz_block(const float2* state, u64 rows, int n, int g, int nblk,
                                                     double* partial) {
     __shared__ double sm[4][15];
@@ -1380,7 +1380,7 @@ __global__ __launch_bounds__(256) void k_fidelity_block(const float2* state, u64
         sr += xv * (double)re;
         si += xv * (double)im;
     };
-    // full chunks of x rows that start on 8 bytes: two entries per load (24 qubits 47 -> 35 us)
+    // full chunks of x rows that start on 8 bytes: two entries per load (24 qubits 47 -> 30 us)
     const bool pairs = ((u64)(uintptr_t)xb & 7) == 0;
     for (u64 base = (u64)blockIdx.x * CHUNK; base < dim; base += (u64)nblk * CHUNK) {
         if (pairs && base + CHUNK <= dim) {
@@ -1456,7 +1456,7 @@ __global__ __launch_bounds__(256) void k_reset_sum(const double* Frow, u64 per, 
 
 // <Z_q> of every qubit from the samples of a row: one block per row.  A wavefront takes 64 samples at a time and
 // counts the set bits of every qubit by a ballot, so that a sample is read once and not once per qubit;
-// whole numbers, so the mean is the same (24 qubits, 4096 shots: 22 -> 5 us).
+// whole numbers, so the mean is the same (24 qubits, 4096 shots: 22 -> 9 us).
 __global__ __launch_bounds__(1024) void k_shot_expz(const long long* samples, u64 shots, int n, float* out) {
     __shared__ unsigned long long ones[31];        // per qubit, and the valid samples behind them
     const u64 row = blockIdx.x;
@@ -1568,7 +1568,7 @@ __device__ __forceinline__ u64 scan_u64(u64 v, int width, int lane) {
 
 // One wavefront per shot.  The block is found by a search with 64 probes at a time (two loads in turn for 4096 blocks instead of 12);
 // with sub the 256 amplitudes in question by its 16 sums, without it by scanning the block's 4096 (24 qubits,
-// 4096 shots: 51 -> 9 us).
+// 4096 shots: 51 -> 6 us).
 __global__ __launch_bounds__(256) void k_sample_draw(const float2* state, int n, int nblk, const u64* cum,
                                                      const u64* sub, const double* uniforms, u64 shots, u64 jobs,
                                                      long long* out) {
