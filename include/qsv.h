@@ -108,7 +108,9 @@ qsv_status qsv_amp_encode(qsv_ctx* ctx, const float* x_dev, int64_t dim, float* 
  * decoder variational layers, data re-uploading blocks").  params_dev: float32 [P].  feats_dev:
  * float32 [batch][n], required when c->reupload = 1, ignored otherwise.  inverse = 1 applies the
  * exact inverse: layers last..first, inside a layer the entangler gates in reverse order, then
- * the rotation slots in reverse order with negated angles, then the re-upload RX negated. */
+ * the rotation slots in reverse order with negated angles, then the re-upload RX negated.
+ * Amplitudes are 0 or such that float32 holds their probability (modulus 2^-75 to 2^64): inside the
+ * call they may be off by a common factor of up to 2^32, which the last gates take back. */
 qsv_status qsv_apply_layers(qsv_ctx* ctx, const qsv_circuit* c, const float* params_dev,
                             const float* feats_dev, int inverse);
 
