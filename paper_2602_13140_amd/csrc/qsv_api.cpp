@@ -2,9 +2,14 @@
 // Every numeric step runs in the HIP kernels; nothing here touches amplitudes on the host.
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <iterator>
+#include <list>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -158,6 +163,39 @@ bool same_circuit(const qsv_circuit& a, const qsv_circuit& b) {
     return true;
 }
 
+// build_plan's results, kept for the contexts of the whole process: planning depends on the circuit's shape and the sizes
+// only and takes longer than the call it is for (20 qubits, 20 layers 25 ms, 4.4 ms there and back; 26 qubits, 30 layers
+// 129 and 10.8 ms), and programs make several contexts for one circuit.  The latest kKeptPlans plans, and no more than
+// kKeptPlanBytes of operations, are held; any thread may ask.
+constexpr size_t kKeptPlans = 64, kKeptPlanBytes = (size_t)8 << 20;
+
+std::shared_ptr<const Plan> planned(const qsv_circuit& c, int n, int64_t rows, bool inverse, int tile, bool grad, int low,
+                                    bool defer) {
+    // of the circuit, what build_plan looks at; of the rows, the number of index bits
+    const std::array<int, 11> key = {c.n_layers, c.reupload, c.n_rot > 0, c.entangler, n, ceil_log2_i64(rows),
+                                     inverse,    tile,       grad,        low,         defer};
+    struct Kept { std::array<int, 11> key; std::shared_ptr<const Plan> plan; };
+    static std::mutex mu;
+    static std::list<Kept> kept;       // the latest first
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        for (auto it = kept.begin(); it != kept.end(); ++it)
+            if (it->key == key) {
+                kept.splice(kept.begin(), kept, it);
+                return it->plan;
+            }
+    }
+    auto plan = std::make_shared<const Plan>(build_plan(c, n, rows, inverse, tile, grad, low, defer));
+    std::lock_guard<std::mutex> lock(mu);
+    kept.push_front({key, plan});
+    size_t count = 0, bytes = 0;
+    for (auto it = kept.begin(); it != kept.end();) {
+        bytes += it->plan->ops.size() * sizeof(Op);
+        it = ++count > kKeptPlans || bytes > kKeptPlanBytes ? kept.erase(it) : std::next(it);
+    }
+    return plan;
+}
+
 // Finds or builds the plan and makes sure its arrays are resident in the ops region.  Uploads are
 // asynchronous copies on the context's stream from host arrays that live as long as the context.
 // When the region is full, every plan in it is dropped from the region (not from the host) and the
@@ -190,17 +228,11 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         cp.defer = defer;
         cp.direct = direct;
         if (inverse && defer && direct) {
-            // the mirror of the circuit's own plan, which an autoencoder has built already
-            const CachedPlan* fwd = nullptr;
-            for (const CachedPlan& o : ctx->cache)
-                if (!o.inverse && o.tile == tile && o.grad == grad && o.low == ctx->opt_low && o.defer && o.direct &&
-                    same_circuit(o.c, c))
-                    fwd = &o;
-            cp.plan = mirror_plan(fwd ? fwd->plan
-                                      : build_plan(c, ctx->n, rows, false, tile, grad != 0, ctx->opt_low, true));
+            // the mirror image of the circuit's own plan
+            cp.plan = mirror_plan(*planned(c, ctx->n, rows, false, tile, grad != 0, ctx->opt_low, true));
             for (const Pass& ps : cp.plan.passes) cp.mates.push_back(line_mate(cp.plan, ps));
         } else {
-            cp.plan = build_plan(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
+            cp.plan = *planned(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
         }
         if (!cp.plan.complete) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: pass planner failed");
         if (direct && !lower_plan(cp.plan, grad != 0, &cp.low_ops))

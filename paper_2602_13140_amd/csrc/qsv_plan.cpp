@@ -25,6 +25,17 @@ struct Gate {
     int32_t mat; // U: matrix id l*n + q
 };
 
+// The gates not executed yet.
+struct Pending {
+    std::vector<uint8_t> todo;
+    explicit Pending(size_t count) : todo(count, 1) {}
+    void clear(size_t i) { todo[i] = 0; }
+    size_t next(size_t i, size_t end) const {    // the first one from i on, at most `end`
+        while (i < end && !todo[i]) ++i;
+        return i;
+    }
+};
+
 struct Geom {
     int t, c, w;
     bool local(int q) const { return q < c || (q >= w && q < w + t - c); }
@@ -88,20 +99,22 @@ std::vector<Gate> lower(const qsv_circuit& c, int n, bool inverse) {
 struct VState {
     uint32_t v[32];
     uint32_t taint = 0;   // bits that occur in the set of another qubit
-    bool any = false;     // some set differs from {q}
     void reset(int n) {
         for (int q = 0; q < 32; ++q) v[q] = q < n ? (1u << q) : 0u;
         taint = 0;
-        any = false;
     }
     void retaint(int n) {
-        taint = 0;
-        any = false;
-        for (int q = 0; q < n; ++q) {
-            taint |= v[q] & ~(1u << q);
-            any = any || v[q] != (1u << q);
-        }
+        uint32_t t = 0;
+        for (int q = 0; q < n; ++q) t |= v[q] & ~(1u << q);
+        taint = t;
     }
+    // every set that holds bit t takes cm in as well, but qubit t's own
+    void fold(int n, int t, uint32_t cm) {
+        for (int q = 0; q < n; ++q)
+            if (q != t && ((v[q] >> t) & 1u)) v[q] ^= cm;
+        retaint(n);
+    }
+    bool any() const { return taint != 0; }   // some set differs from {q}: it holds q itself and then another bit too
 };
 
 enum ExecForm : uint8_t { F_PLAIN = 0, F_PARITY = 1, F_DEFER = 2, F_LANE = 3 };
@@ -120,70 +133,65 @@ constexpr uint32_t kLowMask = (1u << 3) - 1u;
 // One register round: which pending gates can run with the run at tile position s.
 // Appends them to exec (program order) and returns the score; *n_real receives the number of gates
 // that need the tile in this layout (everything but deferred CNOTs).  vs is updated as gates run.
-// Does not modify done.
-int scan_round(const Geom& gm, int s, int n, const std::vector<Gate>& G,
-               const std::vector<uint8_t>& done, size_t first, bool defer, VState& vs,
-               std::vector<Exec>* exec, int* n_real) {
-    uint64_t blk_any = 0, blk_diag = 0;
-    const uint64_t all = n >= 64 ? ~0ull : ((1ull << n) - 1);
+// diag: the circuit has CZ rungs, which run wherever their qubits sit.
+int scan_round(const Geom& gm, int s, int n, const std::vector<Gate>& G, const Pending& todo, size_t first, bool defer,
+               bool diag, VState& vs, std::vector<Exec>* exec, int* n_real) {
+    uint32_t blk_any = 0, blk_diag = 0;
     int score = 0, real = 0;
     const size_t end = std::min(G.size(), first + kScanLimit);
-    auto in_run = [&](int q) {
-        if (!gm.local(q)) return false;
-        const int p = gm.pos(q);
-        return p >= s && p < s + kRegBits;
-    };
-    uint32_t run_mask = 0;    // the qubits behind the register run
+    uint32_t run_mask = 0, local = 0;    // the qubits behind the register run, and behind the tile
     for (int q = 0; q < n; ++q)
-        if (in_run(q)) run_mask |= 1u << q;
+        if (gm.local(q)) {
+            local |= 1u << q;
+            const int p = gm.pos(q);
+            if (p >= s && p < s + kRegBits) run_mask |= 1u << q;
+        }
+    const uint32_t all = n >= 32 ? ~0u : (1u << n) - 1u;
+    // Every gate that can run has a free qubit among these: the run's, and what a deferred CNOT may have as its target.
+    const uint32_t wanted = diag ? all : run_mask | (defer ? all & ~local : 0u);
+    const Weights& wt = defer ? kDeferWeights : kClassicWeights;
     for (size_t i = first; i < end; ++i) {
-        if (done[i]) continue;
+        if (!todo.todo[i]) continue;
         const Gate& g = G[i];
-        uint64_t m = 1ull << g.q0;
-        if (g.kind != G_U) m |= 1ull << g.q1;
+        const uint32_t target = 1u << g.q0;
+        uint32_t m = target;
         bool can;
         Exec ex{(int)i, F_PLAIN, 0};
         if (g.kind == G_CZ) {
+            m |= 1u << g.q1;
             can = !(blk_any & m);
         } else if (g.kind == G_U) {
-            can = !((blk_any | blk_diag) & m) && in_run(g.q0) && !((vs.taint >> g.q0) & 1u);
+            can = !((blk_any | blk_diag) & m) && (run_mask & target) && !(vs.taint & target);
         } else {
             const int t = g.q0, c = g.q1;
-            const uint32_t cm = vs.v[c];
-            can = !((blk_any | blk_diag) & m) && !((cm >> t) & 1u);
+            const uint32_t ctrl = 1u << c, cm = vs.v[c];
+            m |= ctrl;
+            can = !((blk_any | blk_diag) & m) && !(cm & target);
             // control in the register run, target one of the lane's own index bits: the amplitudes with
             // the control set trade places with those of the partner lane (a cross-lane exchange, no
             // transpose); lane_bit >= 0 is the bit of the lane number behind the target
             int lane_bit = -1;
-            if (can && gm.local(t) && !in_run(t) && in_run(c) && cm == (1u << c)) {
+            if (can && (local & ~run_mask & target) && (run_mask & ctrl) && cm == ctrl) {
                 const int pp = gm.pos(t);
                 const int b = pp < s ? pp : pp - kRegBits;     // bit of the thread index
                 if (b < 6) lane_bit = b;
             }
             if (lane_bit >= 0) {
-                const bool others_hold_t = (vs.taint >> t) & 1u;
+                const bool others_hold_t = (vs.taint & target) != 0;
                 if (others_hold_t && (cm & kLowMask)) can = false;
-                if (can && others_hold_t) {
-                    for (int q = 0; q < n; ++q)
-                        if (q != t && ((vs.v[q] >> t) & 1u)) vs.v[q] ^= cm;
-                    vs.retaint(n);
-                }
+                if (can && others_hold_t) vs.fold(n, t, cm);
                 ex.form = F_LANE;
                 ex.mask = (uint32_t)lane_bit;
-            } else if (can && gm.local(t)) {
-                can = in_run(t);
-                if (can && cm != (1u << c)) {
+            } else if (can && (local & target)) {
+                can = (run_mask & target) != 0;
+                if (can && cm != ctrl) {
                     can = !(cm & run_mask);
                     ex.form = F_PARITY;
                     ex.mask = cm;
                 }
-                const bool others_hold_t = (vs.taint >> t) & 1u;
+                const bool others_hold_t = (vs.taint & target) != 0;
                 if (can && others_hold_t && (cm & kLowMask)) can = false;
-                if (can && others_hold_t) {
-                    for (int q = 0; q < n; ++q)
-                        if (q != t && ((vs.v[q] >> t) & 1u)) vs.v[q] ^= cm;
-                    vs.retaint(n);
-                }
+                if (can && others_hold_t) vs.fold(n, t, cm);
             } else if (can) {
                 can = defer && !(cm & kLowMask);
                 if (can) {
@@ -196,12 +204,11 @@ int scan_round(const Geom& gm, int s, int n, const std::vector<Gate>& G,
         }
         if (can) {
             if (exec) exec->push_back(ex);
-            const Weights& wt = defer ? kDeferWeights : kClassicWeights;
             score += g.kind == G_U ? wt.u : g.kind == G_CNOT ? wt.cx : wt.cz;
             if (ex.form != F_DEFER) ++real;
         } else {
             if (g.kind == G_CZ) blk_diag |= m; else blk_any |= m;
-            if (blk_any == all) break;
+            if ((blk_any & wanted) == wanted) break;
         }
     }
     if (n_real) *n_real = real;
@@ -275,11 +282,11 @@ void emit_round(const Geom& gm, int s, const std::vector<Gate>& G, const std::ve
     }
 }
 
-// Greedy rounds of one pass.  Marks executed gates in done; emits ops when ops != nullptr.
+// Greedy rounds of one pass.  Takes executed gates out of todo; emits ops when ops != nullptr.
 // Returns the pass score; *n_exec receives the number of gates executed; *vs_out the qubit sets at the
 // end of the pass (from which the caller derives the pass's index map).
-int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, std::vector<uint8_t>& done,
-             size_t first, bool rowdep, bool defer, std::vector<Op>* ops, std::vector<int32_t>* mat_order,
+int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, Pending& todo,
+             size_t first, bool rowdep, bool defer, bool diag, std::vector<Op>* ops, std::vector<int32_t>* mat_order,
              std::vector<Op>* defers, int* n_exec, VState* vs_out) {
     const int smax = gm.t - kRegBits;
     const int smin_io = std::min(kLowBits, smax);  // layouts with coalesced global access
@@ -291,10 +298,10 @@ int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, std::vector<uint
     vs.reset(n);
     std::vector<Exec> exec, best_exec;
     auto commit = [&](int s, const std::vector<Exec>& ex) {
-        for (const Exec& e : ex) done[e.gate] = 1;
+        for (const Exec& e : ex) todo.clear((size_t)e.gate);
         cnt += (int)ex.size();
         if (ops) emit_round(gm, s, G, ex, rowdep, ops, mat_order, defers);
-        while (first < G.size() && done[first]) ++first;
+        first = todo.next(first, G.size());
     };
     // first round: loaded straight from global memory
     int s = smax, best = 0;
@@ -303,7 +310,7 @@ int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, std::vector<uint
     for (int cand = smin_io; cand <= sgate; ++cand) {
         exec.clear();
         VState tv = vs;
-        const int sc = scan_round(gm, cand, n, G, done, first, defer, tv, &exec, nullptr);
+        const int sc = scan_round(gm, cand, n, G, todo, first, defer, diag, tv, &exec, nullptr);
         if (sc > best) { best = sc; s = cand; best_exec = exec; best_vs = tv; }
     }
     if (ops) ops->push_back({OP_LOAD, (uint8_t)s, 0, 0, 0});
@@ -319,7 +326,7 @@ int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, std::vector<uint
             exec.clear();
             VState tv = vs;
             int real = 0;
-            const int sc = scan_round(gm, cand, n, G, done, first, defer, tv, &exec, &real);
+            const int sc = scan_round(gm, cand, n, G, todo, first, defer, diag, tv, &exec, &real);
             // ties go to the later (higher) layout, which also stores coalesced
             if (sc > best || (sc == best && sc > 0 && cand >= smin_io)) {
                 best = sc; bs = cand; best_exec = exec; best_vs = tv; best_real = real;
@@ -337,7 +344,7 @@ int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, std::vector<uint
         if (!critical && best_real < kMinRoundGates) {
             // A transpose for one stray gate is not worth it, unless going on like this finishes
             // the whole circuit inside this pass (then it saves a pass over the state).
-            std::vector<uint8_t> tmp(done);
+            Pending tmp(todo);
             size_t f2 = first;
             int s2 = s;
             VState v2 = vs;
@@ -349,12 +356,12 @@ int run_pass(const Geom& gm, int n, const std::vector<Gate>& G, std::vector<uint
                     if (cand == s2) continue;
                     ex2.clear();
                     VState tv = v2;
-                    const int sc = scan_round(gm, cand, n, G, tmp, f2, defer, tv, &ex2, nullptr);
+                    const int sc = scan_round(gm, cand, n, G, tmp, f2, defer, diag, tv, &ex2, nullptr);
                     if (sc > b2) { b2 = sc; bs2 = cand; bex2 = ex2; bv2 = tv; }
                 }
                 if (bs2 < 0) break;
-                for (const Exec& e : bex2) tmp[e.gate] = 1;
-                while (f2 < G.size() && tmp[f2]) ++f2;
+                for (const Exec& e : bex2) tmp.clear((size_t)e.gate);
+                f2 = tmp.next(f2, G.size());
                 s2 = bs2;
                 v2 = bv2;
             }
@@ -527,8 +534,9 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
     p.deferring = defer;
 
     const std::vector<Gate> G = lower(c, n, inverse);
-    std::vector<uint8_t> done(G.size(), 0);
+    Pending todo(G.size());
     size_t first = 0;
+    const bool diag = c.entangler == QSV_ENT_CZ_LADDER;
     // fewest low bits of a tile: kLowBits unless the caller asks for another number (3 = 64-byte runs)
     const int cmin = std::min(min_low_bits > 0 ? std::max(3, min_low_bits) : kLowBits, t);
     // local set = low c bits + window of t-c bits at w; c >= 4 keeps 128-byte runs contiguous
@@ -544,15 +552,20 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
         }
     };
     struct Cand { Geom g; int score; };
-    std::vector<Cand> cands;
-    while (first < G.size()) {
-        cands.clear();
+    // every geometry's score as the next pass, in the order of all_geoms
+    auto scores = [&](const Pending& from, size_t at) {
+        std::vector<Cand> out;
+        Pending tmp(from);
         all_geoms([&](Geom gm) {
-            std::vector<uint8_t> tmp(done);
-            int ne = 0;
-            const int sc = run_pass(gm, n, G, tmp, first, rowdep, defer, nullptr, nullptr, nullptr, &ne, nullptr);
-            cands.push_back({gm, sc});
+            tmp = from;
+            out.push_back({gm, run_pass(gm, n, G, tmp, at, rowdep, defer, diag, nullptr, nullptr, nullptr, nullptr, nullptr)});
         });
+        return out;
+    };
+    std::vector<Cand> cands, after;    // after: the next pass's, if the look ahead has worked them out
+    while (first < G.size()) {
+        cands = after.empty() ? scores(todo, first) : after;
+        after.clear();
         std::stable_sort(cands.begin(), cands.end(), [](const Cand& a, const Cand& b) { return a.score > b.score; });
         Geom bestg = cands[0].g;
         if (defer && cands.size() > 1) {
@@ -560,21 +573,20 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
             // long stretch of the chain scores well and leaves little for the next one)
             int best = -1;
             for (size_t ci = 0; ci < cands.size() && (int)ci < look_top(t); ++ci) {
-                std::vector<uint8_t> tmp(done);
-                int ne = 0;
-                run_pass(cands[ci].g, n, G, tmp, first, rowdep, defer, nullptr, nullptr, nullptr, &ne, nullptr);
-                size_t f2 = first;
-                while (f2 < G.size() && tmp[f2]) ++f2;
+                Pending tmp(todo);
+                run_pass(cands[ci].g, n, G, tmp, first, rowdep, defer, diag, nullptr, nullptr, nullptr, nullptr, nullptr);
+                const size_t f2 = tmp.next(first, G.size());
                 int b2 = 0;
+                std::vector<Cand> seconds;
                 if (f2 >= G.size()) b2 = 1 << 24;             // finishes the circuit
                 else
-                    all_geoms([&](Geom g2) {
-                        std::vector<uint8_t> tmp2(tmp);
-                        int ne2 = 0;
-                        const int sc2 = run_pass(g2, n, G, tmp2, f2, rowdep, defer, nullptr, nullptr, nullptr, &ne2, nullptr);
-                        if (sc2 > b2) b2 = sc2;
-                    });
-                if (cands[ci].score + b2 > best) { best = cands[ci].score + b2; bestg = cands[ci].g; }
+                    seconds = scores(tmp, f2);
+                for (const Cand& second : seconds) b2 = std::max(b2, second.score);
+                if (cands[ci].score + b2 > best) {
+                    best = cands[ci].score + b2;
+                    bestg = cands[ci].g;
+                    after.swap(seconds);
+                }
             }
         }
         Pass ps;
@@ -583,13 +595,13 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
         int ne = 0;
         VState vs;
         ps.defer_begin = (int)p.defers.size();
-        run_pass(bestg, n, G, done, first, rowdep, defer, &p.ops, &p.mat_order, &p.defers, &ne, &vs);
+        run_pass(bestg, n, G, todo, first, rowdep, defer, diag, &p.ops, &p.mat_order, &p.defers, &ne, &vs);
         mark_transposes(p.ops, (size_t)ps.op_begin);
         merge_cx_chains(p.ops, (size_t)ps.op_begin);
         ps.op_count = (int)p.ops.size() - ps.op_begin;
         ps.defer_count = (int)p.defers.size() - ps.defer_begin;
         ps.n_gates = ne;
-        if (vs.any) {
+        if (vs.any()) {
             // index map of the pass: map[j] = the index bits that flip in an amplitude's destination
             // when bit j of its position is set = the qubits whose set holds j (always j itself)
             ps.map_begin = (int)p.maps.size();
@@ -602,7 +614,7 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
         }
         p.passes.push_back(ps);
         if (ne == 0) { p.complete = false; break; }  // cannot happen: the first pending gate always fits some window
-        while (first < G.size() && done[first]) ++first;
+        first = todo.next(first, G.size());
     }
     mark_groups(p);
     return p;
