@@ -230,8 +230,10 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
  * each layer the derivative with respect to an angle of slot s on qubit q is
  * 2 Re <lambda| W^dagger (-i/2 P_s) W |psi> on that qubit, W = the layer's earlier slots on it,
  * read off the 2x2 sums  M_q[a][b] = sum_rest conj(lambda[a, rest]) psi[b, rest].
- * Work: about 3 L layers and L n reductions per sample instead of 2 P circuits.  Uses the workspace
- * (three states per sample of a chunk); the context's state buffer is left untouched. */
+ * Work: about 3 L layers and L n reductions per sample instead of 2 P circuits.  Uses the workspace (at
+ * least three states per sample of a chunk; with room for the states between the passes of the circuit, which
+ * qsv_grad_workspace_bytes mostly has, the way back reads them and takes the sums as it goes, in a third to two thirds of the
+ * time); the context's state buffer is left untouched. */
 qsv_status qsv_adjoint_grad(qsv_ctx* ctx, const qsv_circuit* c, const float* x_dev, int64_t dim,
                             const float* params_dev, const float* feats_dev, int32_t obs_qubit,
                             float* loss_dev, float* grad_dev, float* mean_loss_dev,
@@ -293,7 +295,8 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
  * all (10 qubits: 2^20) in one launch with the gates in registers and lane exchanges (the kernel of qsv_forward_small, started
  * from the state; measured 1.6 to 4 times faster there than the fused passes, whose launches cost more than
  * their arithmetic on such states), or always takes the fused passes; with it qsv_adjoint_grad and
- * qsv_loss_grad run circuits of at most 10 qubits and 512 unitaries (layers times qubits) in one launch too,
+ * qsv_loss_grad run circuits of at most 10 qubits and 512 unitaries (layers times qubits) in one launch too (10 qubits
+ * without re-uploading: up to 2^20 amplitudes where the workspace has room for more),
  * unless tile_log2, naive, grad_layered = 0 or grad_chunk_rows is set or the workspace has no room for
  * its matrices and sums (1 KiB at most per sample and layer);
  * small_regs = 2, 3 or 4 fixes the amplitudes per thread of qsv_forward_small at 4, 8 or 16 (0, the
@@ -301,7 +304,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
  * (0 = default) forces the planner's minimum number of low index bits per tile; lds_planes = 1 (default) moves real and imaginary parts through one LDS plane one
  * after the other, 2 through two planes at once; naive = 1 routes qsv_apply_layers through the
  * one-gate-per-launch kernels; grad_layered = 0 makes qsv_param_shift_grad run every shifted
- * circuit whole; nt_store = 1 / 0 forces nontemporal / ordinary tile stores in the fused pass (-1,
+ * circuit whole and the reverse-mode calls take psi back beside lambda, a layer at a time; nt_store = 1 / 0 forces nontemporal / ordinary tile stores in the fused pass (-1,
  * the default, for passes that touch 384 MiB or more); reverse_passes = 1 / 0 makes every other fused
  * pass take its tiles from the last to the first, so that it starts with what the pass before it
  * wrote last, or not (-1, the default, is 1; the result does not depend on it); split_streams = 1 / 0 sends the state rows through a sequence of fused passes as

@@ -686,10 +686,26 @@ def _renumbered(line):
 #   s[44:45] matrix table     s41 byte offset of the next entry   s[48:55] the next entry
 #   s[56:63] shifted matrix of a gradient row
 #   s[64:65], s[66:67] jump targets   s[68:69] saved exec   s70 argument of a transpose
-DIRECT_FIRST, DIRECT_LAST = 36, 70
+#
+# The paired form (pair=True) is the same block for two states at once, psi in r, i and lambda in p, q: the reverse-mode
+# sweep takes both back through a pass and reads the transition sums off the registers between the gates (see
+# sum_handlers).  Every operation acts on psi first and then on lambda, with one fetch, one dispatch and one set of
+# numbers for both; a transpose moves four parts through the plane.  It has no whole or shifted matrices, keeps what waits
+# in t2, t3 and tc of the single form in registers that are free then (80 registers in all: six wavefronts per SIMD), and uses besides
+#   s[72:73] where the next record of sums goes   s[74:75] lanes 0, 16, 32 and 48
+DIRECT_FIRST, DIRECT_LAST, PAIR_LAST = 36, 70, 75
 LAYOUTS = 11                                     # register runs at tile bits 0..10
-U_STRIDE = 576                                   # bytes from one register bit's code of a unitary to the next one's
-X_DELTA = LAYOUTS * 256                          # bytes from a layout's code for real to that for imaginary parts
+
+
+def u_stride(pair):
+    """Bytes from one register bit's code of a unitary to the next one's."""
+    return 1088 if pair else 576
+
+
+X_DELTA = LAYOUTS * 256                          # bytes from a layout's code for one of a transpose's parts to the next one's
+PARTS = (("", "r"), ("I", "i"), ("L", "p"), ("LI", "q"))
+
+
 CZ_RUNGS = 3                                     # rungs between neighbouring register bits
 OVERRIDE_NONE = 0xffffffff
 
@@ -701,12 +717,12 @@ def padded(tau):
 def size_of(line):
     """Bytes of one of the instructions used here."""
     op = line.split()[0]
-    if op.startswith(("v_fma_", "ds_", "s_load_")) or op in ("v_lshl_or_b32", "v_lshl_add_u32", "v_bcnt_u32_b32"):
+    if op.startswith(("v_fma_", "ds_", "s_load_", "global_")) or op in ("v_lshl_or_b32", "v_lshl_add_u32", "v_bcnt_u32_b32"):
         return 8
-    if op.startswith("v_mov_b32_dpp"):
+    if op.endswith("_dpp"):
         return 8
     literal = re.search(r"(?:^|[ ,])(0x[0-9a-f]+|\d+)\s*(?:,|$)", line.split(None, 1)[1]) if " " in line else None
-    if literal and not op.startswith(("s_waitcnt", "s_cbranch", "s_branch", "s_bitcmp")) and int(literal.group(1), 0) > 64:
+    if literal and not op.startswith(("s_waitcnt", "s_cbranch", "s_branch", "s_bitcmp", "s_nop")) and int(literal.group(1), 0) > 64:
         return 8
     return 4
 
@@ -745,9 +761,84 @@ DISPATCH = ["s_waitcnt lgkmcnt(0)",              # the next word and entry have 
             "s_add_u32 s64, s36, s42", "s_addc_u32 s65, s37, 0", "s_setpc_b64 s[64:65]"]
 
 
-def direct_handlers():
+def of_lambda(lines):
+    """Lines that work on psi's registers, on lambda's."""
+    return [re.sub(r"%\[([ri])(\d+)\]", lambda m: "%%[%s%s]" % ("p" if m.group(1) == "r" else "q", m.group(2)), ln)
+            for ln in lines]
+
+
+AXES = "XYZ"
+
+
+def sum_terms(axis, a, b):
+    """Im <lambda| P |psi> of one pair, P the Pauli matrix of the axis, as (sign, lambda's, psi's register), the first
+    with a plus sign."""
+    ra, ia, rb, ib = ("%%[%s%d]" % (x, k) for k in (a, b) for x in "ri")
+    pa, qa, pb, qb = ("%%[%s%d]" % (x, k) for k in (a, b) for x in "pq")
+    return {"X": [(1, pa, ib), (-1, qa, rb), (1, pb, ia), (-1, qb, ra)],
+            "Y": [(1, pb, ra), (1, qb, ia), (-1, pa, rb), (-1, qa, ib)],
+            "Z": [(1, pa, ia), (-1, qa, ra), (-1, pb, ib), (1, qb, rb)]}[axis]
+
+
+def lane_sums(j, axes, accs):
+    """The sums of the lane's eight pairs of register bit j, one axis into each of accs: four multiply-adds a pair."""
+    out, fresh = [], set(accs)
+    for i in range(NR):
+        if not i & (1 << j):
+            for rank in range(4):
+                for axis, acc in zip(axes, accs):
+                    sign, x, y = sum_terms(axis, i, i | (1 << j))[rank]
+                    if acc in fresh:
+                        fresh.discard(acc)
+                        out.append("v_mul_f32 %s, %s, %s" % (acc, x, y))
+                    elif sign > 0:
+                        out.append("v_fmac_f32 %s, %s, %s" % (acc, x, y))
+                    else:
+                        out.append("v_fma_f32 %s, -%s, %s, %s" % (acc, x, y, acc))
+    return out
+
+
+def sum_handlers():
+    """Transition sums of the qubit behind register bit j, from which the derivatives with respect to its angles follow:
+    Im <lambda| P |psi> for the axes P that its unitary's rotations need.  B keeps one sum per lane for the S2 after the
+    unitary; S1, S2 and S3 add one, two and three up over the wavefront and write a record of four floats: [A A A A],
+    [A A B B] (A: its own axis, B: what was kept) and [X Z Y 0].
+    A unitary of one rotation R needs its axis, which commutes with it; of two, R1 R0, the axis of R1 before the inverse
+    unitary and that of R0 after it; of three, all axes after it.  So 4, 8 or 12 multiply-adds a pair beside the 8 to 20
+    of the two unitaries; adding up over the lanes takes 12 to 14 instructions: v_permlane32_swap and
+    v_permlane16_swap halve the lanes that hold a value by swapping it with another's (or its own copy's) half, four
+    row rotations add up the rest.  s_nop 1: what these instructions need after their source was written."""
+    H = []
+    m = ["%%[m%d]" % k for k in range(4)]
+
+    def swap(bits, a, b):
+        return ["s_nop 1", "v_permlane%d_swap_b32 %s, %s" % (bits, a, b), "v_add_f32 %s, %s, %s" % (a, a, b)]
+
+    rows = []
+    for k in (8, 4, 2, 1):
+        rows += ["s_nop 1", "v_add_f32_dpp %s, %s, %s row_ror:%d row_mask:0xf bank_mask:0xf" % (m[0], m[0], m[0], k)]
+    write = rows + ["v_lshrrev_b32 %[t0], 4, %[thr]", "v_lshlrev_b32 %[t0], 2, %[t0]", "s_mov_b64 exec, s[74:75]",
+                    "global_store_dword %[t0], " + m[0] + ", s[72:73]", "s_mov_b64 exec, -1",
+                    "s_add_u32 s72, s72, %[sstep]", "s_addc_u32 s73, s73, 0"]
+    twice = ["v_mov_b32 %s, %s" % (m[2], m[0])] + swap(16, m[0], m[2])      # both rows of a half from the row sums
+    for j in range(R):
+        for axis in AXES:
+            H.append(("B%d%s" % (j, axis), NEXT_WORD + lane_sums(j, axis, ["%[kept]"]) + DISPATCH))
+            own = lane_sums(j, axis, [m[0]])
+            H.append(("S1%d%s" % (j, axis), NEXT_WORD + own + ["v_mov_b32 %s, %s" % (m[1], m[0])] + swap(32, m[0], m[1]) +
+                      twice + write + DISPATCH))
+            H.append(("S2%d%s" % (j, axis), NEXT_WORD + own + swap(32, m[0], "%[kept]") + twice + write + DISPATCH))
+        H.append(("S3%d" % j, NEXT_WORD + lane_sums(j, AXES, m[:3]) + ["v_mov_b32 %s, 0" % m[3]] + swap(32, m[0], m[1]) +
+                  swap(32, m[2], m[3]) + swap(16, m[0], m[2]) + write + DISPATCH))
+    return H
+
+
+def direct_handlers(pair=False):
     """[(name, lines)] in the order of the text; a line that ends in ':' is a local label."""
     H = []
+
+    def states(lines):                           # what is done to psi, and the same to lambda
+        return lines + of_lambda(lines) if pair else lines
 
     def flips(elems):
         return ["v_xor_b32 %%[%s%d], 0x80000000, %%[%s%d]" % (p, k, p, k) for k in elems for p in "ri"]
@@ -755,29 +846,40 @@ def direct_handlers():
     # unitaries: the stub adds the register bit's part to the offset that the entry holds; _S looks for the
     # shifted matrix of a gradient row first
     for j in range(R):
-        go = (["s_add_u32 s54, s54, %d" % (j * U_STRIDE)] if j else []) + [
+        go = (["s_add_u32 s54, s54, %d" % (j * u_stride(pair))] if j else []) + [
             "s_add_u32 s64, s36, s54", "s_addc_u32 s65, s37, 0", "s_setpc_b64 s[64:65]"]
         H.append(("U%d" % j, go))
-        H.append(("US%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc1 L_dovr%d_%%=" % j] + go))
+        if not pair:
+            H.append(("US%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc1 L_dovr%d_%%=" % j] + go))
     for j in range(R):
         pairs = [(i, i | (1 << j)) for i in range(NR) if not i & (1 << j)]
         body = [ln for a, b in pairs for ln in u_pair(a, b)]
-        H.append(("G%d" % j, ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in range(8)] + ["L_dgj%d_%%=:" % j] +
-                  NEXT_ENTRY + NEXT_WORD + body + DISPATCH))
-        H.append(("GS%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc0 L_dG%d_%%=" % j, "L_dovr%d_%%=:" % j,
+        if not pair:
+            H.append(("G%d" % j, ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in range(8)] + ["L_dgj%d_%%=:" % j] +
+                      NEXT_ENTRY + NEXT_WORD + body + DISPATCH))
+            H.append(("GS%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc0 L_dG%d_%%=" % j, "L_dovr%d_%%=:" % j,
                                "s_load_dwordx8 s[56:63], %[ovr], 0x0", "s_waitcnt lgkmcnt(0)"] +
                   ["v_mov_b32 %%[m%d], s%d" % (k, 56 + k) for k in range(8)] + ["s_branch L_dgj%d_%%=" % j]))
+    # the scalar of a group by itself: 4 instructions an amplitude, as many as the whole matrix takes above the
+    # cheapest form; it rounds all amplitudes alike, where a rounded matrix changes the lengths of its two columns by
+    # different amounts, which shows in <Z> of the qubit in full (3e-8)
+    scaled = []
+    for k in range(NR):
+        r, i = "%%[r%d]" % k, "%%[i%d]" % k
+        scaled += ["v_mul_f32 %%[t0], %%[m1], %s" % i, "v_mul_f32 %%[t1], %%[m1], %s" % r,
+                   "v_fma_f32 %s, %%[m0], %s, -%%[t0]" % (r, r), "v_fma_f32 %s, %%[m0], %s, %%[t1]" % (i, i)]
+    H.append(("M", ["v_mov_b32 %[m0], s48", "v_mov_b32 %[m1], s49"] + NEXT_ENTRY + NEXT_WORD + states(scaled) + DISPATCH))
     # CNOTs: inside the register run, chains of them, control elsewhere (a mask of the lane's index bits: one
     # bit, or the parity of several), target behind a lane bit
     for jt in range(R):
         for jc in range(R):
             if jt != jc:
-                H.append(("X%d%d" % (jt, jc), NEXT_WORD + move_pairs(
-                    [(i, i | (1 << jt)) for i in range(NR) if (i >> jc) & 1 and not (i >> jt) & 1]) + DISPATCH))
+                H.append(("X%d%d" % (jt, jc), NEXT_WORD + states(move_pairs(
+                    [(i, i | (1 << jt)) for i in range(NR) if (i >> jc) & 1 and not (i >> jt) & 1])) + DISPATCH))
     for k, chain in enumerate(CX_CHAINS):
-        H.append(("C%d" % k, NEXT_WORD + chain_moves(*chain) + DISPATCH))
+        H.append(("C%d" % k, NEXT_WORD + states(chain_moves(*chain)) + DISPATCH))
     for j in range(R):
-        swap = move_pairs([(i, i | (1 << j)) for i in range(NR) if not (i >> j) & 1])
+        swap = states(move_pairs([(i, i | (1 << j)) for i in range(NR) if not (i >> j) & 1]))
         for name, cond in (("D", []), ("P", ["v_bcnt_u32_b32 %[tc], %[tc], 0", "v_and_b32 %[tc], 1, %[tc]"])):
             done = "L_d%s%dx_%%=" % (name, j)
             H.append(("%s%d" % (name, j), ["v_and_b32 %[tc], s43, %[e0]"] + cond + NEXT_WORD +
@@ -786,55 +888,61 @@ def direct_handlers():
     for j in range(R):
         high = [k for k in range(NR) if (k >> j) & 1]
         for b, perm in ((0, "[1,0,3,2]"), (1, "[2,3,0,1]")):
-            H.append(("N%d%d" % (j, b), NEXT_WORD + [
+            H.append(("N%d%d" % (j, b), NEXT_WORD + states([
                 "v_mov_b32_dpp %%[%s%d], %%[%s%d] quad_perm:%s row_mask:0xf bank_mask:0xf" % (p, k, p, k, perm)
-                for k in high for p in "ri"] + DISPATCH))
+                for k in high for p in "ri"]) + DISPATCH))
         H.append(("N%d" % j, ["v_xor_b32 %[tc], s43, %[thr]", "v_and_b32 %[tc], 63, %[tc]",
                               "v_lshlrev_b32 %[tc], 2, %[tc]"] + NEXT_WORD +
-                  ["ds_bpermute_b32 %%[%s%d], %%[tc], %%[%s%d]" % (p, k, p, k) for k in high for p in "ri"] + DISPATCH))
+                  states(["ds_bpermute_b32 %%[%s%d], %%[tc], %%[%s%d]" % (p, k, p, k) for k in high for p in "ri"]) + DISPATCH))
     # CZ rungs: inside the run (any set of the three), one end in it, none
     for mask in range(1, 1 << CZ_RUNGS):
-        H.append(("ZR%d" % mask, NEXT_WORD + flips(cz_elements(mask)) + DISPATCH))
+        H.append(("ZR%d" % mask, NEXT_WORD + states(flips(cz_elements(mask))) + DISPATCH))
     for j in range(R):
         H.append(("ZM%d" % j, ["v_and_b32 %[tc], s43, %[e0]"] + NEXT_WORD +
                   ["v_cmp_ne_u32 vcc, 0, %[tc]", "s_and_saveexec_b64 s[68:69], vcc", "s_cbranch_execz L_dZM%dx_%%=" % j] +
-                  flips([k for k in range(NR) if (k >> j) & 1]) + ["L_dZM%dx_%%=:" % j, "s_mov_b64 exec, s[68:69]"] +
+                  states(flips([k for k in range(NR) if (k >> j) & 1])) + ["L_dZM%dx_%%=:" % j, "s_mov_b64 exec, s[68:69]"] +
                   DISPATCH))
     H.append(("ZL", ["v_lshrrev_b32 %[tc], 1, %[e0]", "v_and_b32 %[tc], %[tc], %[e0]", "v_and_b32 %[tc], s43, %[tc]",
                      "v_bcnt_u32_b32 %[tc], %[tc], 0", "v_and_b32 %[tc], 1, %[tc]"] + NEXT_WORD +
               ["v_cmp_ne_u32 vcc, 0, %[tc]", "s_and_saveexec_b64 s[68:69], vcc", "s_cbranch_execz L_dZLx_%="] +
-              flips(range(NR)) + ["L_dZLx_%=:", "s_mov_b64 exec, s[68:69]"] + DISPATCH))
+              states(flips(range(NR))) + ["L_dZLx_%=:", "s_mov_b64 exec, s[68:69]"] + DISPATCH))
+    if pair:
+        H += sum_handlers()
     H.append(("END", ["s_branch L_dexit_%="]))
     # transposes: W<s> writes the real parts in layout s and goes on to the target layout's R code (argument: its
     # offset / 64, bit 16: the exchange crosses wavefronts, bit 17: barrier before the writes); that reads
-    # them and comes back to W<s>'s imaginary half, and so on
+    # them and comes back to W<s>'s imaginary half, and so on, in the paired form with lambda's parts after psi's
     def cross(name):
         return ["s_bitcmp1_b32 s70, 16", "s_cbranch_scc0 " + name, "s_waitcnt lgkmcnt(0)", "s_barrier", name + ":"]
 
     def at(s, k):
         return 4 * padded(k << s)
 
-    for half, part in enumerate("ri"):
+    parts = PARTS if pair else PARTS[:2]
+    delta = ["s_add_u32 s66, s66, %d" % X_DELTA, "s_addc_u32 s67, s67, 0"]
+    back = ["s_add_u32 s64, s64, %d" % X_DELTA, "s_addc_u32 s65, s65, 0"]
+    for nth, (sub, part) in enumerate(parts):
         for s in range(LAYOUTS):
             w = ["ds_write_b32 %%[ldsb], %%[%s%d] offset:%d" % (part, k, at(s, k)) for k in range(NR)]
-            if half == 0:
-                H.append(("W%d" % s, ["s_mov_b32 s70, s43"] + NEXT_WORD +
+            name = "W%s%d" % (sub, s)
+            if nth == 0:
+                H.append((name, ["s_mov_b32 s70, s43"] + NEXT_WORD +
                           ["s_bitcmp1_b32 s70, 17", "s_cbranch_scc0 L_dW%db_%%=" % s, "s_barrier", "L_dW%db_%%=:" % s] + w +
                           ["s_and_b32 s66, s70, 0xffff", "s_lshl_b32 s66, s66, 6", "s_add_u32 s66, s36, s66",
                            "s_addc_u32 s67, s37, 0", "s_add_u32 s64, s36, @WI%d" % s, "s_addc_u32 s65, s37, 0",
                            "s_setpc_b64 s[66:67]"]))
             else:
-                H.append(("WI%d" % s, cross("L_dWI%db_%%=" % s) + w +
-                          ["s_add_u32 s66, s66, %d" % X_DELTA, "s_addc_u32 s67, s67, 0", "s_setpc_b64 s[66:67]"]))
-    for half, part in enumerate("ri"):
+                H.append((name, cross("L_d%sb_%%=" % name) + w + delta + (back if nth + 1 < len(parts) else []) +
+                          ["s_setpc_b64 s[66:67]"]))
+    for nth, (sub, part) in enumerate(parts):
         for s in range(LAYOUTS):
-            r = ["ds_read_b32 %%[%s%d], %%[ldsb] offset:%d" % (part, k, at(s, k)) for k in range(NR)]
-            if half:
-                H.append(("RI%d" % s, cross("L_dRI%db_%%=" % s) +
-                          [ln.replace("[ldsb]", "[ldsn]") for ln in r] + ["v_mov_b32 %[ldsb], %[ldsn]"] + DISPATCH))
-            else:
-                H.append(("R%d" % s, lane_address(s) + cross("L_dR%db_%%=" % s) +
-                          [ln.replace("[ldsb]", "[ldsn]") for ln in r] + ["s_setpc_b64 s[64:65]"]))
+            name = "R%s%d" % (sub, s)
+            r = cross("L_d%sb_%%=" % name) + ["ds_read_b32 %%[%s%d], %%[ldsn] offset:%d" % (part, k, at(s, k)) for k in range(NR)]
+            if nth == 0:
+                r = lane_address(s) + r
+            H.append((name, r + (["v_mov_b32 %[ldsb], %[ldsn]"] + DISPATCH if nth + 1 == len(parts) else ["s_setpc_b64 s[64:65]"])))
+    if pair:
+        H = [(name, [ln.replace("%[t2]", "%[m0]").replace("%[tc]", "%[m1]") for ln in lines]) for name, lines in H]
     return H
 
 
@@ -848,45 +956,51 @@ def lane_address(s):
                   "v_lshlrev_b32 %[t1], %[w], %[t1]", "v_or_b32 %[t2], %[tb], %[t2]", "v_or_b32 %[e0], %[t1], %[t2]"]
 
 
-def direct_layout():
+def direct_layout(pair=False):
     """({name: byte offset}, first free offset): unitaries' sequences first, at fixed strides."""
-    off, pos = {}, 64 * 2                        # the block's own start takes two lines
+    off, pos = {}, 64 * (3 if pair else 2)       # the block's own start takes two or three lines
+    steps = 4 if pair else 2
     for form in FORMS:
         for core in range(len(CORES)):
             off["F%s%d" % (form, core)] = pos
-            pos += U_STRIDE * R
+            pos += u_stride(pair) * R
     group = {"W": 0, "R": 0}
-    for name, lines in direct_handlers():
-        m = re.fullmatch(r"(W|R)(I?)(\d+)", name)
-        if m:                                    # 256-byte places: W, WI, R, RI by layout
+    for name, lines in direct_handlers(pair):
+        m = re.fullmatch(r"(W|R)(L?I?)(\d+)", name)
+        if m:                                    # 256-byte places: W, WI, R, RI by layout, paired W, WI, WL, WLI, ...
             if not group["W"]:
                 pos = (pos + 255) // 256 * 256
-                group["W"], group["R"] = pos, pos + 2 * X_DELTA
-                pos += 4 * X_DELTA
-            off[name] = group[m.group(1)] + (X_DELTA if m.group(2) else 0) + 256 * int(m.group(3))
+                group["W"], group["R"] = pos, pos + steps * X_DELTA
+                pos += 2 * steps * X_DELTA
+            off[name] = group[m.group(1)] + [sub for sub, _ in PARTS].index(m.group(2)) * X_DELTA + 256 * int(m.group(3))
             continue
         off[name] = pos
         pos += (sum(size_of(ln) for ln in lines if not ln.endswith(":")) + 63) // 64 * 64
     return off, pos
 
 
-def gen_direct():
-    off, end = direct_layout()
+def gen_direct(pair=False):
+    off, end = direct_layout(pair)
     L = [".p2align 6", "L_dbase_%=:",
          "s_getpc_b64 s[36:37]", "s_sub_u32 s36, s36, 4", "s_subb_u32 s37, s37, 0",
          "s_mov_b64 s[38:39], %[ops]", "s_mov_b64 s[44:45], %[mats]", "s_mov_b32 s40, 0", "s_mov_b32 s41, %[first]",
-         "s_load_dwordx2 s[42:43], s[38:39], 0x0", "s_load_dwordx8 s[48:55], s[44:45], s41"] + DISPATCH
+         "s_load_dwordx2 s[42:43], s[38:39], 0x0", "s_load_dwordx8 s[48:55], s[44:45], s41"]
+    if pair:
+        L += ["s_mov_b64 s[72:73], %[sums]", "s_mov_b32 s74, 0x10001", "s_mov_b32 s75, 0x10001"]
+    L += DISPATCH
     bodies = []
     for form in FORMS:
         for core, name in enumerate(CORES):
             used = sorted({int(m) for ln in rot_pair(0, 1, form, name) for m in re.findall(r"%\[m(\d)\]", ln)})
             for j in range(R):
-                body = ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in used] + NEXT_ENTRY + NEXT_WORD
+                body = []
                 for i in range(NR):
                     if not i & (1 << j):
                         body += rot_pair(i, i | (1 << j), form, name)
-                bodies.append((off["F%s%d" % (form, core)] + j * U_STRIDE, "F%s%d%d" % (form, core, j), body + DISPATCH))
-    for name, lines in direct_handlers():
+                body = ["v_mov_b32 %%[m%d], s%d" % (k, 48 + k) for k in used] + NEXT_ENTRY + NEXT_WORD + body + (
+                    of_lambda(body) if pair else [])
+                bodies.append((off["F%s%d" % (form, core)] + j * u_stride(pair), "F%s%d%d" % (form, core, j), body + DISPATCH))
+    for name, lines in direct_handlers(pair):
         bodies.append((off[name], name, [re.sub(r"@(\w+)", lambda m: str(off[m.group(1)]), ln) for ln in lines]))
     for pos, name, lines in sorted(bodies):
         L.append(".org L_dbase_%%=+%d, 0" % pos)
@@ -897,30 +1011,35 @@ def gen_direct():
     return L
 
 
-def direct_constants():
+def direct_constants(pair=False):
     """C++ constants the host needs to write operation words and the matrix builder to write entries."""
-    off, _ = direct_layout()
+    off, _ = direct_layout(pair)
     rows = lambda names: ", ".join(str(off[n]) for n in names)
     j4 = range(R)
-    return [
-        "namespace qsv { namespace direct {",
+    c = [
+        "namespace qsv { struct %s {" % ("paired" if pair else "direct"),
         "// byte offsets of the code of each operation in the block (see gen_direct in the generator)",
-        "constexpr unsigned kU[4] = {%s}, kUShift[4] = {%s};" % (rows("U%d" % j for j in j4), rows("US%d" % j for j in j4)),
-        "constexpr unsigned kG[4] = {%s}, kGShift[4] = {%s};" % (rows("G%d" % j for j in j4), rows("GS%d" % j for j in j4)),
-        "constexpr unsigned kCx[4][4] = {%s};   // [target][control]" % ", ".join(
+        "static constexpr unsigned kU[4] = {%s};" % rows("U%d" % j for j in j4),
+        "static constexpr unsigned kG[4] = {%s}, kUShift[4] = {%s}, kGShift[4] = {%s};" % (
+            rows("G%d" % j for j in j4), rows("US%d" % j for j in j4), rows("GS%d" % j for j in j4)) if not pair else
+        "static constexpr unsigned kBefore[4][3] = {%s}, kSum1[4][3] = {%s}, kSum2[4][3] = {%s}, kSum3[4] = {%s};" % (
+            *(", ".join("{%s}" % rows("%s%d%s" % (k, j, x) for x in AXES) for j in j4) for k in ("B", "S1", "S2")),
+            rows("S3%d" % j for j in j4)),
+        "static constexpr unsigned kCx[4][4] = {%s};   // [target][control]" % ", ".join(
             "{%s}" % ", ".join(str(off.get("X%d%d" % (t, c), 0)) for c in j4) for t in j4),
-        "constexpr unsigned kChain[%d] = {%s};" % (len(CX_CHAINS), rows("C%d" % k for k in range(len(CX_CHAINS)))),
-        "constexpr unsigned kCxBit[4] = {%s}, kCxParity[4] = {%s};" % (rows("D%d" % j for j in j4), rows("P%d" % j for j in j4)),
-        "constexpr unsigned kCxQuad[4][2] = {%s}, kCxLane[4] = {%s};" % (
+        "static constexpr unsigned kChain[%d] = {%s};" % (len(CX_CHAINS), rows("C%d" % k for k in range(len(CX_CHAINS)))),
+        "static constexpr unsigned kCxBit[4] = {%s}, kCxParity[4] = {%s};" % (rows("D%d" % j for j in j4), rows("P%d" % j for j in j4)),
+        "static constexpr unsigned kCxQuad[4][2] = {%s}, kCxLane[4] = {%s};" % (
             ", ".join("{%s}" % rows("N%d%d" % (j, b) for b in (0, 1)) for j in j4), rows("N%d" % j for j in j4)),
-        "constexpr unsigned kCz[8] = {0, %s}, kCzMix[4] = {%s}, kCzLane = %d, kEnd = %d;" % (
-            rows("ZR%d" % m for m in range(1, 8)), rows("ZM%d" % j for j in j4), off["ZL"], off["END"]),
-        "constexpr unsigned kWrite[%d] = {%s};" % (LAYOUTS, rows("W%d" % s for s in range(LAYOUTS))),
-        "constexpr unsigned kRead[%d] = {%s};" % (LAYOUTS, rows("R%d" % s for s in range(LAYOUTS))),
-        "constexpr unsigned kSeq0 = %d, kSeqStride = %d;   // code of a factored unitary: kSeq0 + sequence * kSeqStride" % (
-            off["Fnone0"], U_STRIDE * R),
-        "} }",
+        "static constexpr unsigned kCz[8] = {0, %s}, kCzMix[4] = {%s}, kCzLane = %d, kScale = %d, kEnd = %d;" % (
+            rows("ZR%d" % m for m in range(1, 8)), rows("ZM%d" % j for j in j4), off["ZL"], off["M"], off["END"]),
+        "static constexpr unsigned kWrite[%d] = {%s};" % (LAYOUTS, rows("W%d" % s for s in range(LAYOUTS))),
+        "static constexpr unsigned kRead[%d] = {%s};" % (LAYOUTS, rows("R%d" % s for s in range(LAYOUTS))),
+        "static constexpr unsigned kSeq0 = %d, kSeqStride = %d;   // code of a factored unitary: kSeq0 + sequence * kSeqStride" % (
+            off["Fnone0"], u_stride(pair) * R),
+        "}; }",
     ]
+    return c
 
 
 def render():
@@ -936,13 +1055,14 @@ def render():
             for ln in gen(planes, perlane):
                 out.append('    "%s\\n\\t" \\' % ln)
             out.append('    ""')
-    out.append("#define QSV_GATE_DIRECT_ASM \\")
-    for ln in gen_direct():
-        out.append('    "%s\\n\\t" \\' % ln)
-    out.append('    ""')
-    regs = ", ".join('"s%d"' % i for i in range(DIRECT_FIRST, DIRECT_LAST + 1))
-    out.append("#define QSV_GATE_DIRECT_CLOBBERS %s, \"vcc\", \"scc\", \"memory\"" % regs)
-    out += direct_constants()
+    for pair, name, last in ((False, "DIRECT", DIRECT_LAST), (True, "PAIRED", PAIR_LAST)):
+        out.append("#define QSV_GATE_%s_ASM \\" % name)
+        for ln in gen_direct(pair):
+            out.append('    "%s\\n\\t" \\' % ln)
+        out.append('    ""')
+        regs = ", ".join('"s%d"' % i for i in range(DIRECT_FIRST, last + 1))
+        out.append("#define QSV_GATE_%s_CLOBBERS %s, \"vcc\", \"scc\", \"memory\"" % (name, regs))
+        out += direct_constants(pair)
     regs = ", ".join('"s%d"' % i for i in range(FIRST_SGPR, LAST_SGPR + 1))
     out.append("#define QSV_GATE_LOOP_CLOBBERS %s, \"vcc\", \"scc\", \"memory\"" % regs)
     return "\n".join(out) + "\n"

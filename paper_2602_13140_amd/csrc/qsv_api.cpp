@@ -51,6 +51,8 @@ struct CachedPlan {
     int inverse, tile, grad, low;   // tile: the resolved tile size (the default depends on the rows)
     int defer = 0;                  // planned with deferred CNOTs (index maps)
     int direct = 0;                 // for the direct interpreter: `low_ops` is uploaded in place of plan.ops
+    int sweep = 0;                  // of a fused reverse-mode sweep: groups end with their passes, the inverse is the
+                                    // circuit's mirror image for the paired interpreter
     DirectPlan low_ops;
     std::vector<unsigned> mates;   // of a mirrored plan's passes: PassArgs::mate
     size_t maps_off = 0;            // uint32[plan.maps.size()]: the index maps of its passes
@@ -58,7 +60,8 @@ struct CachedPlan {
     bool resident = false;          // its arrays are in the ops region right now
     size_t dev_off;     // byte offset of the ops inside the ops region
     size_t order_off;   // int32[n_mats]: execution order -> (layer*n + qubit)
-    size_t execof_off;  // int32[n_mats]: (layer*n + qubit) -> execution order
+    size_t execof_off;  // int32[n_mats]: (layer*n + qubit) -> execution order; sweep: execution order -> table entry
+    size_t groups_off = 0;          // int32[plan.groups.size()]
     std::vector<int32_t> exec_of;
 };
 
@@ -201,16 +204,20 @@ std::shared_ptr<const Plan> planned(const qsv_circuit& c, int n, int64_t rows, b
 // When the region is full, every plan in it is dropped from the region (not from the host) and the
 // region is filled again from its start: the copies that overwrite it are ordered, on the stream,
 // behind every kernel that read the old contents, so nothing waits on the host.
+int tile_of(const qsv_ctx* ctx, int64_t rows, int layers, int defer) {
+    const int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer ? defer_tile(ctx->n, rows, layers) : default_tile(ctx->n, rows);
+    return std::max(kMinTile, std::min(kMaxTile, tile));
+}
+
 qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad,
-                    const CachedPlan** out, int defer = 0) {
-    int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer ? defer_tile(ctx->n, rows, c.n_layers) : default_tile(ctx->n, rows);
-    tile = std::max(kMinTile, std::min(kMaxTile, tile));
+                    const CachedPlan** out, int defer = 0, int sweep = 0) {
+    const int tile = tile_of(ctx, rows, c.n_layers, defer);
     // tiles of one row through one LDS plane (tiles of 2^14 have no other way): see kDirectMaxQubits
     const int direct = ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile) ? 1 : 0;
     CachedPlan* hit = nullptr;
     for (CachedPlan& cp : ctx->cache)
         if (cp.inverse == inverse && cp.tile == tile && cp.grad == grad && cp.low == ctx->opt_low &&
-            cp.defer == defer && cp.direct == direct && same_circuit(cp.c, c)) {
+            cp.defer == defer && cp.direct == direct && cp.sweep == sweep && same_circuit(cp.c, c)) {
             hit = &cp;
             break;
         }
@@ -227,28 +234,48 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         cp.low = ctx->opt_low;
         cp.defer = defer;
         cp.direct = direct;
-        if (inverse && defer && direct) {
-            // the mirror image of the circuit's own plan
-            cp.plan = mirror_plan(*planned(c, ctx->n, rows, false, tile, grad != 0, ctx->opt_low, true));
-            for (const Pass& ps : cp.plan.passes) cp.mates.push_back(line_mate(cp.plan, ps));
+        cp.sweep = sweep;
+        auto build = [&](bool inv) {
+            return planned(c, ctx->n, rows, inv, tile, grad != 0, ctx->opt_low, defer != 0);
+        };
+        if (direct && defer && inverse) {
+            cp.plan = mirror_plan(*build(false));      // the mirror image of the circuit's own plan
+        } else if (sweep && !defer && !inverse) {
+            // Without deferral either direction plans as well as the other.  The way back is planned and the way there
+            // is its mirror image: then the gates that an observable of a few qubits depends on come last, and what is
+            // rounded before them shows less in it (<Z_0> of a ladder of 10 layers, 16 qubits: 7.8e-7 from 64 bits, the
+            // other way round 9.6e-7, layer by layer 7.9e-7).
+            cp.plan = mirror_plan(*build(true));
         } else {
-            cp.plan = *planned(c, ctx->n, rows, inverse != 0, tile, grad != 0, ctx->opt_low, defer != 0);
+            cp.plan = *build(inverse != 0);
         }
+        if (cp.plan.gather)
+            for (const Pass& ps : cp.plan.passes) cp.mates.push_back(line_mate(cp.plan, ps));
+        else
+            cp.mates.assign(cp.plan.passes.size(), 0);
         if (!cp.plan.complete) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: pass planner failed");
-        if (direct && !lower_plan(cp.plan, grad != 0, &cp.low_ops))
+        if (sweep) group_by_passes(&cp.plan);
+        const SumAxes axes = sum_axes(c);
+        if (direct && !lower_plan(cp.plan, grad != 0, &cp.low_ops, sweep && inverse ? &axes : nullptr))
             return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: lowering the pass plan failed");
         const size_t nm = cp.plan.mat_order.size();
         cp.exec_of.assign(nm, 0);
-        for (size_t k = 0; k < nm; ++k) cp.exec_of[cp.plan.mat_order[k]] = (int32_t)k;
+        if (sweep) {
+            for (size_t g = 0; g + 1 < cp.plan.groups.size(); ++g)
+                for (int32_t k = cp.plan.groups[g]; k < cp.plan.groups[g + 1]; ++k) cp.exec_of[k] = k + (int32_t)g;
+        } else {
+            for (size_t k = 0; k < nm; ++k) cp.exec_of[cp.plan.mat_order[k]] = (int32_t)k;
+        }
         ctx->cache.push_back(std::move(cp));
         hit = &ctx->cache.back();
     }
     CachedPlan& cp = *hit;
     const size_t nm = cp.plan.mat_order.size();
-    const size_t ops_bytes = align_up(cp.plan.ops.size() * sizeof(Op) + sizeof(Op));
+    const size_t ops_bytes = align_up(std::max(cp.plan.ops.size(), cp.low_ops.ops.size()) * sizeof(Op) + sizeof(Op));
     const size_t tab_bytes = align_up(nm * sizeof(int32_t) + 4);
     const size_t map_bytes = align_up(cp.plan.maps.size() * sizeof(uint32_t) + 4);
-    const size_t bytes = ops_bytes + 2 * tab_bytes + map_bytes;
+    const size_t group_bytes = align_up(cp.plan.groups.size() * sizeof(int32_t) + 4);
+    const size_t bytes = ops_bytes + 2 * tab_bytes + map_bytes + group_bytes;
     if (bytes > kOpsRegion) return fail(ctx, QSV_ERR_UNSUPPORTED, "circuit too long for the plan buffer");
     if (ctx->ops_used + bytes > kOpsRegion) {
         // While a call has work on the second stream, kernels there may still read the region, and
@@ -262,6 +289,11 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
     cp.order_off = cp.dev_off + ops_bytes;
     cp.execof_off = cp.order_off + tab_bytes;
     cp.maps_off = cp.execof_off + tab_bytes;
+    cp.groups_off = cp.maps_off + map_bytes;
+    if (!cp.plan.groups.empty())
+        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.groups_off, cp.plan.groups.data(), cp.plan.groups.size() * sizeof(int32_t),
+                                    hipMemcpyHostToDevice, ctx->stream),
+                "upload groups");
     if (!cp.plan.maps.empty())
         QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.maps_off, cp.plan.maps.data(), cp.plan.maps.size() * sizeof(uint32_t),
                                     hipMemcpyHostToDevice, ctx->stream),
@@ -340,7 +372,7 @@ qsv_status prepare(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& run, b
     double* scale = grad && form != MatForm::plain
         ? reinterpret_cast<double*>(reinterpret_cast<char*>(mats) + mats_table_bytes(c, n, samples)) : nullptr;
     out->scale = scale;
-    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0, form,
+    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0, nullptr, 0, form,
                                    mats, scale, ctx->stream),
             "build matrices");
     return QSV_OK;
@@ -1165,8 +1197,216 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     return QSV_OK;
 }
 
-// Reverse-mode loss and gradient for a diagonal observable: kind 0 <Z_q>; 1 the loss 1 - P0(mask);
-// 2 the mean squared error of <Z_q> against targets [batch][n].
+// The chunks of a reverse-mode sweep alternate between the caller's stream and the context's second one; this forks the
+// second one off, and always joins it again.
+struct Fork {
+    qsv_ctx* c;
+    hipStream_t main;
+    bool on;
+    explicit Fork(qsv_ctx* ctx) : c(ctx), main(ctx->stream), on(false) {}
+    qsv_status begin() {
+        QSV_HIP(c, hipEventRecord(c->ev_fork, main), "fork");
+        QSV_HIP(c, hipStreamWaitEvent(c->side, c->ev_fork, 0), "fork");
+        on = true;
+        c->forked = true;
+        return QSV_OK;
+    }
+    // chunk i runs on stream i % 2 with scratch set i % 2 (stream order guards the reuse of a set)
+    int take(int64_t i) {
+        const int set = on ? (int)(i & 1) : 0;
+        c->stream = set ? c->side : main;
+        return set;
+    }
+    qsv_status join() {        // what follows sees both streams' work
+        c->stream = main;
+        if (!on) return QSV_OK;
+        on = false;
+        c->forked = false;
+        QSV_HIP(c, hipEventRecord(c->ev_join, c->side), "join");
+        QSV_HIP(c, hipStreamWaitEvent(main, c->ev_join, 0), "join");
+        return QSV_OK;
+    }
+    ~Fork() {
+        c->stream = main;
+        if (!on) return;
+        c->forked = false;
+        if (hipEventRecord(c->ev_join, c->side) == hipSuccess) (void)hipStreamWaitEvent(main, c->ev_join, 0);
+    }
+};
+
+// What reverse mode differentiates: kind 0 <Z_q>; 1 the loss 1 - P0(mask); 2 the mean squared error of <Z_q> against targets.
+struct Objective { int kind, q; uint64_t mask; const float* targets; };
+
+// The losses of rows 0 .. rows - 1 of A (samples sample0 + row) into f[sample][2P]; kind 2 also the coefficients of lambda.
+static qsv_status losses(qsv_ctx* ctx, const Objective& ob, const float2* A, int64_t rows, int64_t sample0, int64_t P,
+                         double* zpart, double* zall, double* coef, double* f) {
+    const int n = ctx->n;
+    if (ob.kind == 1) {
+        QSV_HIP(ctx, launch_trash_loss(A, n, ob.mask, rows, sample0, P, zpart, f, ctx->stream), "trash loss");
+        return QSV_OK;
+    }
+    QSV_HIP(ctx, launch_expz_block(A, rows, n, zpart, ctx->stream), "expz block");
+    if (ob.kind == 0) {
+        QSV_HIP(ctx, launch_expz_finish_scatter(zpart, rows, n, ob.q, f, Scatter{sample0, 1, 2 * P + 1, 2 * P}, ctx->stream),
+                "expz finish");
+        return QSV_OK;
+    }
+    QSV_HIP(ctx, launch_expz_finish(zpart, rows, n, -1, nullptr, zall, ctx->stream), "expz finish");
+    QSV_HIP(ctx, launch_mse_coef(zall, ob.targets, n, rows, sample0, P, coef, f, ctx->stream), "mse loss");
+    return QSV_OK;
+}
+
+// Reverse mode in the passes of the whole circuit's plan.  The forward run keeps the state after every pass; the mirrored
+// passes take lambda = O psi back, and with it, tile by tile, the kept psi of their end, and read the transition sums of
+// every unitary off the registers where it is undone.  So a sweep moves five states a pass (two there; psi and lambda in,
+// lambda out on the way back) of a plan with deferral, where the layers one by one move twelve each: 20 qubits x 32, 20
+// layers 18 passes, 24 GB instead of 64; a 16-qubit ladder of 10 layers 3 passes, 2 GB instead of 16.
+// *done = false: nothing was launched, the scratch has no room (or the options ask for another way).
+// f: [batch][2P+1]; inv: room for the norms; what is taken of ar is taken for good.
+static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objective& ob, const float* x_dev, int64_t dim,
+                              const float* params, const float* feats, double* npart, int nblk, double* inv, double* f,
+                              Arena& ar, bool* done) {
+    *done = false;
+    const int n = ctx->n, L = c.n_layers;
+    const int64_t B = ctx->batch, P = qsv_num_params(&c, n), per = (int64_t)L * n;
+    if (!ctx->opt_grad_layered || P < 1 || ctx->opt_naive || n < kMinTile || n > kDirectMaxQubits || ctx->opt_planes != 1)
+        return QSV_OK;
+    const int64_t most = ctx->opt_grad_chunk > 0 ? ctx->opt_grad_chunk : B;
+    int defer = ctx->opt_defer != 0 && c.entangler == QSV_ENT_CNOT_RING;
+    if (defer && n <= tile_of(ctx, B, L, 1)) defer = 0;
+    const int tile = tile_of(ctx, B, L, defer);
+    if (tile > kPairMaxTile || n < tile) return QSV_OK;
+    const size_t state_bytes = (size_t)8 << n;
+    const size_t sums_bytes = pair_sums_bytes(n, per), zbytes = (size_t)chunk_blocks(n) * 13 * 8;
+    auto sample_bytes = [&](size_t passes) {
+        return (passes + 1) * state_bytes + sums_bytes + zbytes + 2 * (size_t)n * 8;
+    };
+    // a table: the unitaries and at most as many groups' scalars, and one entry that is only prefetched
+    const size_t table_bytes = 2 * mats_table_bytes(c, n, B), corr_bytes = mat_scale_bytes(to_dev(c, n), B);
+    const size_t fixed = 2 * table_bytes + corr_bytes + 16 * kAlign;
+    // Two halves on two streams pay as in run_circuit: 20 qubits x 32, 20 layers 8.66 -> 8.24 ms, 16 x 256 1.25 -> 1.17, 22 x 2,
+    // 6 layers 0.98 -> 0.88; 18 x 4 296 -> 312 us, 16 x 16 357 -> 374, 13 x 37 163 -> 210, 11 x 64 135 -> 168.
+    const bool two = B >= 2 && !ctx->forked &&
+                     (ctx->opt_split >= 0 ? ctx->opt_split == 1 : (uint64_t)B * state_bytes >= kSplitBytes);
+    const int sets = two ? 2 : 1;
+    const int64_t half = std::min(most, two ? (B + 1) / 2 : B);
+    if (ar.remaining() < fixed + (size_t)sets * half * sample_bytes(1)) return QSV_OK;     // without planning for it
+    const CachedPlan *fp = nullptr, *bp = nullptr;
+    for (int k = 0; k < 2; ++k) {      // twice: should the second plan recycle the plan buffer, the first comes back
+        qsv_status st = get_plan(ctx, c, B, 0, 0, &fp, defer, 1);
+        if (st == QSV_OK) st = get_plan(ctx, c, B, 1, 0, &bp, defer, 1);
+        if (st != QSV_OK) return st;
+    }
+    const size_t passes = fp->plan.passes.size();
+    if (!fp->resident || !bp->resident || passes == 0 || ar.remaining() < fixed + (size_t)sets * half * sample_bytes(passes))
+        return QSV_OK;
+    int64_t chunk = std::min<int64_t>(half, 32768);
+    // the records of a unitary are at most 4 GiB
+    while (chunk > 1 && ((uint64_t)chunk << (n - 10)) * 16 > 0xffffffffull) chunk = (chunk + 1) / 2;
+
+    float* fmats = (float*)ar.take(table_bytes);
+    float* bmats = (float*)ar.take(table_bytes);
+    double* corr = (double*)ar.take(corr_bytes);
+    struct Scratch { float2* psi; float* sums; double *zpart, *zall, *coef; } scr[2];
+    for (int i = 0; i < sets; ++i) {
+        scr[i].psi = (float2*)ar.take((passes + 1) * (size_t)chunk * state_bytes);
+        scr[i].sums = (float*)ar.take((size_t)chunk * sums_bytes);
+        scr[i].zpart = (double*)ar.take((size_t)chunk * zbytes);
+        scr[i].zall = (double*)ar.take((size_t)chunk * n * 8);
+        scr[i].coef = (double*)ar.take((size_t)chunk * n * 8);
+        if (!scr[i].coef) return ws_fail(ctx, ar, "qsv_adjoint_grad");
+    }
+    *done = true;
+    const CircDev cd = to_dev(c, n);
+    auto table = [&](const CachedPlan* cp, int inverse, MatForm form, float* out, double* scale) -> qsv_status {
+        QSV_HIP(ctx, launch_build_mats(cd, params, feats, B, inverse, reinterpret_cast<const int*>(ctx->ws + cp->order_off), 0,
+                                       reinterpret_cast<const int*>(ctx->ws + cp->groups_off), (int)cp->plan.groups.size() - 1,
+                                       form, out, scale, ctx->stream),
+                "build matrices");
+        return QSV_OK;
+    };
+    QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
+    qsv_status st = table(fp, 0, MatForm::direct, fmats, nullptr);
+    if (st == QSV_OK) st = table(bp, 1, MatForm::paired, bmats, corr);
+    if (st != QSV_OK) return st;
+
+    const size_t amps = (size_t)1 << n;
+    const int groups = (int)fp->plan.groups.size() - 1;      // the mirror image has as many
+    auto run_chunk = [&](int64_t b0, int64_t rows, const Scratch& sc) -> qsv_status {
+        auto state = [&](size_t k) { return sc.psi + k * (size_t)chunk * amps; };   // 0: encoded; k: after pass k - 1
+        RowMap rm;
+        rm.grad = 1; rm.two_p = 0; rm.per = 1; rm.row0 = b0; rm.slots_n = 1; rm.n = n;
+        QSV_HIP(ctx, launch_encode_write(x_dev, dim, n, rows, inv, rm, state(0), ctx->stream), "encode rows");
+        const uint64_t touched = ((uint64_t)rows << n) * 16;
+        const int nt = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : (touched >= kNtStoreBytes ? 1 : 0);
+        for (size_t k = 0; k < passes; ++k) {
+            const Pass& ps = fp->plan.passes[k];
+            const DirectPass& low = fp->low_ops.passes[k];
+            PassArgs a{};
+            a.state = state(k + 1);
+            a.in = state(k);
+            a.imap = ps.map_begin >= 0 ? reinterpret_cast<const unsigned*>(ctx->ws + fp->maps_off) + ps.map_begin : nullptr;
+            a.ops = reinterpret_cast<const Op*>(ctx->ws + fp->dev_off) + low.begin;
+            a.mats = fmats;
+            a.total = (uint64_t)rows << n;
+            a.nt_store = nt;
+            a.rev = ctx->opt_rev != 0 && (k & 1) ? (ps.map_begin < 0 ? 2 : 1) : 0;
+            a.prio = 0;      // raised / not: 20 qubits x 32, 20 layers 8.24 / 7.88 ms, 22 x 2 877 / 839 us, below 18 no difference
+            a.n = n; a.c = ps.c; a.w = ps.w;
+            a.n_mats = (int)per + groups;
+            a.rowdep = c.reupload;
+            a.rm = rm;
+            a.direct = 1;
+            a.s_in = low.s_in; a.s_out = low.s_out; a.first_mat = low.first_mat;
+            a.g_sample0 = (unsigned)b0;
+            QSV_HIP(ctx, launch_pass(tile, 1, a, (uint64_t)rows << (n - tile), ctx->stream), "fused pass");
+        }
+        qsv_status s = losses(ctx, ob, state(passes), rows, b0, P, sc.zpart, sc.zall, sc.coef, f);
+        if (s != QSV_OK) return s;
+        // backwards: lambda changes between the encoded states' buffer and the last states', whose pass comes first
+        const float2* lam = nullptr;
+        for (size_t k = 0; k < passes; ++k) {
+            const Pass& ps = bp->plan.passes[k];
+            const DirectPass& low = bp->low_ops.passes[k];
+            PairArgs a{};
+            a.psi = state(passes - k);
+            a.lam_in = lam;
+            a.lam_out = k + 1 == passes ? nullptr : k & 1 ? state(passes) : state(0);
+            lam = a.lam_out;
+            a.imap = ps.map_begin >= 0 ? reinterpret_cast<const unsigned*>(ctx->ws + bp->maps_off) + ps.map_begin : nullptr;
+            a.ops = reinterpret_cast<const Op*>(ctx->ws + bp->dev_off) + low.begin;
+            a.mats = bmats;
+            a.sums = sc.sums;
+            a.sample0 = b0;
+            a.rows = rows;
+            a.n = n; a.c = ps.c; a.w = ps.w;
+            a.n_mats = (int)per + groups;
+            a.rowdep = c.reupload;
+            a.s_in = low.s_in; a.s_out = low.s_out; a.first_mat = low.first_mat; a.first_u = low.first_u;
+            a.mate = ps.map_begin >= 0 ? bp->mates[k] : 0;
+            // the forward run's last pass was number passes - 1: go on in turns
+            a.rev = ctx->opt_rev != 0 && ((passes + k) & 1) ? (ps.map_begin < 0 ? 2 : 1) : 0;
+            a.nt_store = nt;
+            a.kind = ob.kind; a.q = ob.q; a.mask = ob.mask; a.coef = sc.coef;
+            QSV_HIP(ctx, launch_pair_pass(tile, a, ctx->stream), "reverse pass");
+        }
+        QSV_HIP(ctx, launch_pair_finish(sc.sums, rows, cd, params, b0, P, reinterpret_cast<const int*>(ctx->ws + bp->order_off),
+                                        reinterpret_cast<const int*>(ctx->ws + bp->execof_off), bmats, (int)per + groups,
+                                        corr, f, ctx->stream),
+                "adjoint layers");
+        return QSV_OK;
+    };
+    Fork fork(ctx);
+    if (two && chunk < B && (st = fork.begin()) != QSV_OK) return st;
+    int64_t ci = 0;
+    for (int64_t b0 = 0; b0 < B; b0 += chunk, ++ci) {
+        st = run_chunk(b0, std::min(chunk, B - b0), scr[fork.take(ci)]);
+        if (st != QSV_OK) return st;
+    }
+    return fork.join();
+}
+
+// Reverse-mode loss and gradient for a diagonal observable (see Objective).
 static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* x_dev, int64_t dim,
                                const float* params_dev, const float* feats_dev, int kind, int32_t obs_qubit,
                                uint64_t mask, const float* targets_dev, float* loss_dev, float* grad_dev,
@@ -1214,6 +1454,22 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
     const size_t tables = mats_bytes(*c, n, B);
     const bool keep = ctx->opt_grad_layered && P > 0 &&
                       ar.remaining() >= align_up(ckpt_bytes) + state_bytes + small_bytes + 2 * tables + 2 * kAlign;
+    const Objective ob{kind, obs_qubit, mask, targets_dev};
+    auto fused = [&](bool* done) -> qsv_status {
+        Arena fs = ar;       // what is taken here is given back if it does not fit
+        qsv_status s = fused_sweep(ctx, *c, ob, x_dev, dim, params_dev, feats_dev, npart, nblk, inv, f, fs, done);
+        if (s != QSV_OK || !*done) return s;
+        QSV_HIP(ctx, launch_grad_finish(f, B, P, cd, feats_dev, loss_dev, grad_dev, mean_loss_dev, mean_grad_dev, ctx->stream),
+                "grad finish");
+        return QSV_OK;
+    };
+    bool done = false;
+    // 10 qubits have both: one launch is faster up to 1024 samples (512, 4 layers 45 against 84 us), passes beyond (4096, 6
+    // layers 306 / 230), but for re-uploading circuits, whose tables cost them as much (2048, 12 layers 326 / 318)
+    if (n >= kMinTile && !c->reupload && (B << n) > small_apply_amplitudes(kSmallMaxQubits)) {
+        st = fused(&done);
+        if (st != QSV_OK || done) return st;
+    }
     // Small states: the whole sweep in one launch, where the scratch has room for its sums.  It keeps psi too where there
     // is room: the gradient is then no further from 64 bits than layer by layer (psi taken back 1.2 to 1.6 times).
     if (ctx->opt_small_apply != 0 && n <= kSmallMaxQubits && P > 0 && ctx->opt_tile == 0 && !ctx->opt_naive &&
@@ -1223,7 +1479,7 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
         double* sums = (double*)sm.take((size_t)B * L * sweep_record_bytes(n));
         float2* kept = (float2*)sm.take((size_t)B * L * state_bytes);
         if (mats && sums && (kept || !keep)) {
-            QSV_HIP(ctx, launch_build_mats(cd, params_dev, feats_dev, B, 1, nullptr, 0, MatForm::phaseless, mats, nullptr,
+            QSV_HIP(ctx, launch_build_mats(cd, params_dev, feats_dev, B, 1, nullptr, 0, nullptr, 0, MatForm::phaseless, mats, nullptr,
                                            ctx->stream),
                     "build matrices");
             QSV_HIP(ctx, launch_sweep_small(x_dev, dim, B, cd, c->entangler, params_dev, mats, kind, obs_qubit, mask,
@@ -1235,6 +1491,8 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
             return QSV_OK;
         }
     }
+    st = fused(&done);
+    if (st != QSV_OK || done) return st;
     QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
     float2* ckpt = keep ? (float2*)ar.take(ckpt_bytes) : nullptr;
     if (keep && !ckpt) return ws_fail(ctx, ar, "qsv_adjoint_grad");
@@ -1312,19 +1570,8 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
             st = run_circuit(ctx, *c, pr, A, bc, 0, nullptr, rm1);
             if (st != QSV_OK) return st;
         }
-        // the loss of every sample of the chunk into f[sample][2P]
-        if (kind == 0) {
-            QSV_HIP(ctx, launch_expz_block(A, bc, n, sc.zpart, ctx->stream), "expz block");
-            QSV_HIP(ctx, launch_expz_finish_scatter(sc.zpart, bc, n, obs_qubit, f, Scatter{b0, 1, per, 2 * P},
-                                                    ctx->stream),
-                    "expz finish");
-        } else if (kind == 1) {
-            QSV_HIP(ctx, launch_trash_loss(A, n, mask, bc, b0, P, sc.zpart, f, ctx->stream), "trash loss");
-        } else {
-            QSV_HIP(ctx, launch_expz_block(A, bc, n, sc.zpart, ctx->stream), "expz block");
-            QSV_HIP(ctx, launch_expz_finish(sc.zpart, bc, n, -1, nullptr, sc.zall, ctx->stream), "expz finish");
-            QSV_HIP(ctx, launch_mse_coef(sc.zall, targets_dev, n, bc, b0, P, sc.coef, f, ctx->stream), "mse loss");
-        }
+        st = losses(ctx, ob, A, bc, b0, P, sc.zpart, sc.zall, sc.coef, f);
+        if (st != QSV_OK) return st;
         if (P == 0) return QSV_OK;
         // backward: lambda = O psi (and psi beside it unless its states were kept), taken back layer by layer
         QSV_HIP(ctx, launch_adj_init(A, n, kind, obs_qubit, mask, sc.coef, bc, sc.S, keep ? 0 : 1, ctx->stream),
@@ -1352,16 +1599,7 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
         }
         return QSV_OK;
     };
-    // chunk i runs on stream i % 2 with scratch set i % 2 (stream order guards the reuse of a set)
-    struct Fork {
-        qsv_ctx* c; hipStream_t main; bool on;
-        ~Fork() {
-            c->stream = main;
-            if (!on) return;
-            c->forked = false;
-            if (hipEventRecord(c->ev_join, c->side) == hipSuccess) (void)hipStreamWaitEvent(main, c->ev_join, 0);
-        }
-    } fork{ctx, ctx->stream, false};
+    Fork fork(ctx);
     if (two && chunk < B) {
         // Plans are uploaded on the stream that first asks for them: have the ones the chunks will use
         // in place before the second stream branches off (three calls: should the second one recycle
@@ -1375,26 +1613,15 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
                 if (st != QSV_OK) return st;
             }
         }
-        QSV_HIP(ctx, hipEventRecord(ctx->ev_fork, ctx->stream), "fork");
-        QSV_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0), "fork");
-        fork.on = true;
-        ctx->forked = true;
+        if ((st = fork.begin()) != QSV_OK) return st;
     }
     int64_t ci = 0;
     for (int64_t b0 = 0; b0 < B; b0 += chunk, ++ci) {
         const int64_t bc = (B - b0) < chunk ? (B - b0) : chunk;
-        const int set = fork.on ? (int)(ci & 1) : 0;
-        ctx->stream = set ? ctx->side : fork.main;
-        st = run_chunk(b0, bc, scr[set]);
+        st = run_chunk(b0, bc, scr[fork.take(ci)]);
         if (st != QSV_OK) return st;
     }
-    ctx->stream = fork.main;
-    if (fork.on) {        // the finishing kernel sees both streams' work
-        fork.on = false;
-        ctx->forked = false;
-        QSV_HIP(ctx, hipEventRecord(ctx->ev_join, ctx->side), "join");
-        QSV_HIP(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0), "join");
-    }
+    if ((st = fork.join()) != QSV_OK) return st;
     QSV_HIP(ctx, launch_grad_finish(f, B, P, cd, feats_dev, loss_dev, grad_dev, mean_loss_dev,
                                     mean_grad_dev, ctx->stream),
             "grad finish");

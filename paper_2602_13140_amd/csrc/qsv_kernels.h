@@ -89,6 +89,34 @@ QSV_HD inline unsigned mate_order(unsigned b, unsigned mate) {
 constexpr int kDirectMaxQubits = 28;
 hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles, hipStream_t st);
 
+// A mirrored pass on the states psi and lambda = O psi at once, with the transition sums of its unitaries: reverse mode.
+struct PairArgs {
+    const float2* psi;     // the circuit's states after the pass, [rows][2^n]; only read
+    const float2* lam_in;  // lambda after the pass; NULL: O psi, for the observable below (the circuit's last pass)
+    float2* lam_out;       // lambda before the pass; another buffer than lam_in if imap; NULL: not wanted
+    const unsigned* imap;  // as PassArgs::imap, read through
+    const void* ops;       // DirectOp list of the paired interpreter
+    const float* mats;     // [samples if rowdep][n_mats][8], paired
+    float* sums;           // [unitaries][rows][2^(n - 10)][4]: a record per unitary (execution order) and wavefront
+    int64_t sample0;       // row r belongs to sample sample0 + r
+    int64_t rows;
+    int n, c, w, n_mats, rowdep, s_in, s_out, first_mat, first_u;
+    unsigned mate;
+    int rev, nt_store;
+    int kind, q;           // observable, as launch_adj_init's
+    uint64_t mask;
+    const double* coef;
+};
+constexpr int kPairMaxTile = 13;
+hipError_t launch_pair_pass(int tile, const PairArgs& a, hipStream_t st);
+inline size_t pair_sums_bytes(int n, int64_t n_mats) { return (size_t)n_mats * ((size_t)16 << (n - 10)); }   // of a row
+// From the records of all unitaries, the derivatives with respect to the angles of the rows' samples, written into
+// f[sample][2p], f[sample][2p+1] as (g, -g).  order: (layer * n + qubit) by position; entry_of: its entry in the inverse
+// circuit's paired table back of n_mats entries; corr: the scale table.
+hipError_t launch_pair_finish(const float* sums, int64_t rows, const CircDev& c, const float* params, int64_t sample0,
+                              int64_t P, const int* order, const int* entry_of, const float* back, int n_mats,
+                              const double* corr, double* f, hipStream_t st);
+
 // Address, on the current device (which must be `device`), of the library's fixed scratch array of
 // kStaticScratchBytes bytes (256-byte aligned).  Looked up once per device; allocates nothing.
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
@@ -108,10 +136,15 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
 // repeats for every layer (the table of the whole circuit as the tables of its layers, run one by one,
 // back to back).  plain: every entry is the matrix; else factored in groups (see kMatGroup), as the
 // interpreters of the fused pass read them.  scale (NULL: not wanted): [tables][n_layers*n] complex doubles.
-enum class MatForm { plain, factored, direct, phaseless };   // direct: factored, for the direct interpreter; phaseless:
-                                                             // matrices up to a phase, which a group's last one has
+enum class MatForm { plain, factored, direct, paired, phaseless };   // direct, paired: factored, for those interpreters;
+                                                             // phaseless: matrices up to a phase, which a group's last one has
+// groups (device, NULL: every kMatGroup entries): the n_groups groups of a table with their scalars as entries of their own
+// (see Plan::groups; period = 0, form = direct or paired); a table then has n_layers*n + n_groups entries.
+// form = paired: scale (then [tables][n_layers*n][2] doubles by position) receives what sums of products of two states that
+// have come through the unitaries up to this one are to be multiplied by, and the same without this one.
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
-                             const int* order, int period, MatForm form, float* out, double* scale, hipStream_t st);
+                             const int* order, int period, const int* groups, int n_groups, MatForm form, float* out,
+                             double* scale, hipStream_t st);
 // bytes of the scale table
 inline size_t mat_scale_bytes(const CircDev& c, int64_t samples) {
     return (size_t)(c.reupload ? samples : 1) * (size_t)c.n_layers * (size_t)c.n * 16;

@@ -167,6 +167,8 @@ __device__ __forceinline__ u64 uni64(u64 v) {
                    X(12, 3, +) X(13, 0, +) X(15, 1, +) X(14, 0, -) X(10, 2, -) X(11, 0, +) X(9, 1, -) X(8, 0, -)
 #define QSV_DECL(k) float vr##k, vi##k;
 #define QSV_RV(k) [r##k] "+v"(vr##k), [i##k] "+v"(vi##k),
+#define QSV_DECL2(k) float lr##k, li##k;
+#define QSV_RV2(k) [p##k] "+v"(lr##k), [q##k] "+v"(li##k),
 
 // Byte offsets of register elements 1, 2, 4, 8 in layout s inside an LDS plane, as XORed onto the
 // lane's own address part: swz(k << s) * 4 with swz(x) = x ^ ((x >> 4) & 31).  swz is linear over
@@ -610,6 +612,137 @@ void k_pass_direct(const PassArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
+// A diagonal observable O, given by its weight w(k):
+//   kind 0: Z_q,             w = +1 / -1 by bit q
+//   kind 1: -P0(mask),       w = -1 where no bit of mask is set, else 0  (loss 1 - P0)
+//   kind 2: sum_q c[r][q] Z_q, w = sum_q c[r][q] (1 - 2 bit_q(k))        (chain rule of the squared error)
+struct AdjObs { int kind; int q; u64 mask; const double* coef; };
+
+__device__ __forceinline__ float adj_weight(const AdjObs& o, u64 r, u64 k, int n) {
+    if (o.kind == 0) return ((k >> o.q) & 1ull) ? -1.f : 1.f;
+    if (o.kind == 1) return (k & o.mask) ? 0.f : -1.f;
+    double w = 0.0;
+    const double* c = o.coef + r * n;
+#pragma unroll 1
+    for (int q = 0; q < n; ++q) w += ((k >> q) & 1ull) ? -c[q] : c[q];
+    return (float)w;
+}
+
+// A mirrored pass on two states at once: psi (read only) and lambda, in the paired interpreter, which takes the
+// transition sums of every unitary off the registers.  GATHER: through an index map, as in k_pass_direct.
+// Bound by vector issue (the sums and two unitaries take 3.3 times the instructions of one) and by how much of the
+// transposes and loads other wavefronts cover: a wavefront holds both tiles' parts, 64 registers of amplitudes in 77, so
+// that six fit a SIMD, and a workgroup one LDS plane.  With 84 registers and two planes (four wavefronts, half the
+// barriers of a transpose) 20 qubits x 32, 20 layers took 7.88 instead of 7.12 ms, 16 x 256, 10 layers 1.12 instead of 1.05.
+// Against layer by layer (psi of every layer kept, lambda taken back by k_pass_direct, the sums by two or three launches
+// that read both): 11.8 -> 7.1 ms and 2.83 -> 1.05 ms; 13 x 37, 5 re-uploading layers 500 -> 160 us, 18 x 4, 6 layers 584 ->
+// 300, 22 x 2, 6 layers 1428 -> 840.
+template <int T, bool GATHER>
+__global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(100), amdgpu_waves_per_eu(6, 6)))
+void k_pair_pass(const PairArgs a) {
+    extern __shared__ float lds[];
+    if ((unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)lds != 0) return;   // cannot happen; LDS addresses rely on it
+    const unsigned thr = threadIdx.x;
+    const unsigned tile = a.rev ? reversed_tile(blockIdx.x, gridDim.x, a.rev) : blockIdx.x;
+    const unsigned nb = (unsigned)(a.n - T), row = tile >> nb;
+    unsigned tr = tile & ((1u << nb) - 1u);
+    if constexpr (GATHER) tr = mate_order(tr, a.mate);
+    const unsigned c = (unsigned)a.c, w = (unsigned)a.w, cmask = (1u << c) - 1u;
+    const unsigned base = ((tr & ((1u << (w - c)) - 1u)) << c) | ((tr >> (w - c)) << (w + T - c));
+    auto expand = [&](unsigned tau) -> unsigned { return (tau & cmask) | ((tau >> c) << w); };
+    auto lane_tau = [&](unsigned s) -> unsigned { return ((thr >> s) << (s + R)) | (thr & ((1u << s) - 1u)); };
+    const float* mats = a.mats + (a.rowdep ? ((u64)a.sample0 + row) * (unsigned)a.n_mats * 8 : 0);
+    const int row_bytes = (int)(8u << a.n);        // the resources' size (unsigned to the hardware): one row
+    typedef unsigned u32x2v __attribute__((ext_vector_type(2)));
+    unsigned im = 0;
+    if constexpr (GATHER) { if ((thr & 31u) < (unsigned)a.n) im = a.imap[thr & 31u]; }
+    QSV_16(QSV_DECL)
+    QSV_16(QSV_DECL2)
+    const unsigned s_in = (unsigned)a.s_in, s_out = (unsigned)a.s_out;
+    const unsigned tau0 = lane_tau(s_in);
+    unsigned e0 = expand(tau0);
+    unsigned map_off = 0, x0 = 0, x1 = 0, x2 = 0, x3 = 0;
+    const float2* psi = a.psi + ((u64)row << a.n);
+    const float2* lam = a.lam_in ? a.lam_in + ((u64)row << a.n) : psi;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)psi, 0, row_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc((void*)lam, 0, row_bytes, 0x00020000);
+#define QSV_GETV(S, rsrc, k, off, so) { const u32x2v got = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(off), (int)(so), 0)); \
+        S##r##k = __uint_as_float(got.x); S##i##k = __uint_as_float(got.y); }
+    if constexpr (GATHER) {
+        unsigned et = (base >> (thr & 31u)) & 1u ? im : 0u;
+#pragma unroll
+        for (int d = 16; d > 0; d >>= 1) et ^= __shfl_xor(et, d, 32);
+        auto entry = [&](unsigned b) -> unsigned {   // of the index bit behind tile bit b
+            return (unsigned)__builtin_amdgcn_readlane((int)im, (int)(b < c ? b : b - c + w));
+        };
+#pragma unroll
+        for (unsigned i = 0; i < T - R; ++i) {       // thread bit i is tile bit i or i + 4
+            const unsigned m = entry(i < s_in ? i : i + R);
+            et ^= (thr >> i) & 1u ? m : 0u;
+        }
+        map_off = et * 8u;
+        x0 = entry(s_in) * 8u; x1 = entry(s_in + 1) * 8u; x2 = entry(s_in + 2) * 8u; x3 = entry(s_in + 3) * 8u;
+        unsigned off = map_off ^ x0;
+        // the empty asm keeps the offsets in one register, one after the other
+#define QSV_LD(k, bit, sign) { off ^= x##bit; asm volatile("" : "+v"(off)); QSV_GETV(v, rs, k, off, 0) QSV_GETV(l, rl, k, off, 0) }
+        QSV_16G(QSV_LD)
+#undef QSV_LD
+    } else {
+        x0 = expand(1u << s_in) * 8u; x1 = expand(2u << s_in) * 8u; x2 = expand(4u << s_in) * 8u; x3 = expand(8u << s_in) * 8u;
+        const unsigned voff = e0 * 8u;
+        unsigned so = base * 8u - x0;
+#define QSV_LD(k, bit, sign) { so = so sign x##bit; QSV_GETV(v, rs, k, voff, so) QSV_GETV(l, rl, k, voff, so) }
+        QSV_16G(QSV_LD)
+#undef QSV_LD
+        map_off = voff | base * 8u;
+    }
+#undef QSV_GETV
+    if (!a.lam_in) {                                 // lambda = O psi, at the indices the amplitudes were read from
+        const AdjObs o{a.kind, a.q, a.mask, a.coef};
+        unsigned off = map_off ^ x0;
+#define QSV_OBS(k, bit, sign) { off ^= x##bit; const float wk = adj_weight(o, row, off >> 3, a.n); lr##k = wk * vr##k; li##k = wk * vi##k; }
+        QSV_16G(QSV_OBS)
+#undef QSV_OBS
+    }
+    {
+        unsigned ldsb = (tau0 + 2u * (tau0 >> 5)) * 4u, ldsn;
+        e0 |= base;
+        float t0, t1, m0, m1, m2, m3, m4, m5, kept;
+        const u64 ops = (u64)(uintptr_t)a.ops, mat = (u64)(uintptr_t)mats;
+        // the pass's records: of a unitary, 16 bytes per wavefront in the order of the rows and tiles
+        const u64 waves = (u64)a.rows << (a.n - 10);
+        const u64 sums = (u64)(uintptr_t)(a.sums + ((u64)(unsigned)a.first_u * waves + (((u64)row << nb) + tr) * (blockDim.x >> 6)) * 4);
+        asm volatile(QSV_GATE_PAIRED_ASM
+                     : QSV_16(QSV_RV) QSV_16(QSV_RV2)[t0] "=&v"(t0), [t1] "=&v"(t1), [m0] "=&v"(m0), [m1] "=&v"(m1), [m2] "=&v"(m2),
+                       [m3] "=&v"(m3), [m4] "=&v"(m4), [m5] "=&v"(m5), [kept] "=&v"(kept), [ldsb] "+v"(ldsb), [ldsn] "=&v"(ldsn),
+                       [e0] "+v"(e0)
+                     : [thr] "v"(thr), [ops] "s"(uni64(ops)), [mats] "s"(uni64(mat)), [sums] "s"(uni64(sums)),
+                       [sstep] "s"(to_sgpr((unsigned)(waves * 16u))), [first] "s"(to_sgpr((unsigned)a.first_mat * 32u)),
+                       [c] "s"(to_sgpr(c)), [w] "s"(to_sgpr(w)), [cmask] "s"(to_sgpr(cmask)), [tb] "s"(to_sgpr(base))
+                     : QSV_GATE_PAIRED_CLOBBERS);
+    }
+    if (!a.lam_out) return;
+    const unsigned lane_out = expand(lane_tau(s_out));
+    const __amdgpu_buffer_rsrc_t ro =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(a.lam_out + ((u64)row << a.n)), 0, row_bytes, 0x00020000);
+    const unsigned st0 = expand(1u << s_out) * 8u, st1 = expand(2u << s_out) * 8u, st2 = expand(4u << s_out) * 8u,
+                   st3 = expand(8u << s_out) * 8u;
+    unsigned so = base * 8u - st0;
+#define QSV_ST(k, bit, sign) { so = so sign st##bit; u32x2v v; v.x = __float_as_uint(lr##k); v.y = __float_as_uint(li##k); \
+            __builtin_amdgcn_raw_buffer_store_b64(v, ro, (int)(lane_out * 8u), (int)so, AUX); }
+    if (a.nt_store) {
+#define AUX 2
+        QSV_16G(QSV_ST)
+#undef AUX
+    } else {
+#define AUX 0
+        QSV_16G(QSV_ST)
+#undef AUX
+    }
+#undef QSV_ST
+}
+
+// ------------------------------------------------------------------------------------------
 // One-gate-per-launch kernels.
 __global__ __launch_bounds__(256) void k_naive_u(float2* state, u64 pairs, int n, int q,
                                                  const float* mats, const float* ovr, int mat_id,
@@ -862,29 +995,33 @@ __device__ __forceinline__ int ordered(const int* table, int period, int pos) {
 // ones' place too, without the phase of their upper left entry; products with its imaginary part, an exact zero, round
 // nothing (gradients of the small sweep 2 to 4 % nearer to 64 bits).
 // scale (may be NULL): what a matrix that replaces entry pos has to be multiplied by.
+// starts: groups of their own sizes, whose scalars are an entry behind each (see Plan::groups).  kind = paired: scale
+// receives what sums over two states, both taken through the entries up to this one, are to be multiplied by (they lack
+// the scalars of the group's unitaries so far), and the same without this entry.
 // One launch where the factors used to be collected by a second one (10 us to 5 us before a circuit).
 __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* params, const float* feats,
                                                     u64 groups, int inverse, const int* order, int period,
+                                                    const int* starts, int n_starts,
                                                     MatForm kind, int seq0, int seq_stride, float* out, double* scale) {
     static_assert(kMatGroup == 64, "a wavefront is a group");
     const u64 gi = (u64)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (gi >= groups) return;
     const int lane = threadIdx.x & 63;
     const int per = c.n_layers * c.n, seg = period > 0 ? period : per;
-    const int per_seg = (seg + kMatGroup - 1) / kMatGroup, per_table = per_seg * (per / seg);
+    const int per_seg = (seg + kMatGroup - 1) / kMatGroup, per_table = starts ? n_starts : per_seg * (per / seg);
     const u64 sample = gi / (u64)per_table;
     const int gt = (int)(gi % (u64)per_table);
     const int in_seg = (gt % per_seg) * kMatGroup + lane;
-    const int pos = (gt / per_seg) * seg + in_seg;
-    const bool live = in_seg < seg;
+    const int pos = starts ? starts[gt] + lane : (gt / per_seg) * seg + in_seg;
+    const bool live = starts ? pos < starts[gt + 1] : in_seg < seg;
     const int lq = !live ? -1 : order ? ordered(order, period, pos) : pos;
     int top = lq;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) top = max(top, __shfl_xor(top, d, 64));
-    const bool whole = kind == MatForm::plain || lq == top, matrix = whole || kind == MatForm::phaseless;
+    const bool whole = !starts && (kind == MatForm::plain || lq == top), matrix = whole || kind == MatForm::phaseless;
     Cx g = {1.0, 0.0};
     M2 u;
-    float* o = out + (sample * (u64)per + (u64)pos) * 8;
+    float* o = out + (sample * (u64)(per + (starts ? n_starts : 0)) + (u64)(pos + (starts ? gt : 0))) * 8;
     if (live) {
         u = fused_raw(c, params, feats, sample, lq / c.n, lq % c.n, -1, 0.0, matrix ? inverse : 0);
         if (!matrix) g = factor_m(u, inverse, seq0, seq_stride, o);
@@ -902,6 +1039,27 @@ __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* para
     for (int d = 32; d > 0; d >>= 1) {
         const Cx other = {__shfl_xor(f.r, d, 64), __shfl_xor(f.i, d, 64)};
         f = (lane & d) ? mul_c(other, f) : mul_c(f, other);   // the same product in every lane
+    }
+    if (starts) {
+        if (live && pos + 1 == starts[gt + 1]) {
+            float4* own = reinterpret_cast<float4*>(o + 8);
+            own[0] = make_float4((float)f.r, (float)f.i, 0.f, 0.f);
+            own[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        if (kind != MatForm::paired) return;
+        const double own = g.r * g.r + g.i * g.i;
+        double up = own;                                 // of the entries up to this one
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const double before = __shfl_up(up, d, 64);
+            if (lane >= d) up *= before;
+        }
+        if (live) {
+            double* to = scale + (sample * (u64)per + (u64)pos) * 2;
+            to[0] = up;
+            to[1] = up / own;
+        }
+        return;
     }
     if (!live) return;
     if (whole) {
@@ -1676,21 +1834,7 @@ __global__ __launch_bounds__(256) void k_grad_mean(const double* f, u64 B, u64 P
 // ------------------------------------------------------------------------------------------
 // Reverse-mode (adjoint) gradient of <Z_obs>.  Rows come in pairs: 2r holds psi, 2r+1 holds lambda.
 
-// S[2r] = A[r], S[2r+1] = O A[r] for a diagonal observable O given by its weight w(k):
-//   kind 0: Z_q,             w = +1 / -1 by bit q
-//   kind 1: -P0(mask),       w = -1 where no bit of mask is set, else 0  (loss 1 - P0)
-//   kind 2: sum_q c[r][q] Z_q, w = sum_q c[r][q] (1 - 2 bit_q(k))        (chain rule of the squared error)
-struct AdjObs { int kind; int q; u64 mask; const double* coef; };
-
-__device__ __forceinline__ float adj_weight(const AdjObs& o, u64 r, u64 k, int n) {
-    if (o.kind == 0) return ((k >> o.q) & 1ull) ? -1.f : 1.f;
-    if (o.kind == 1) return (k & o.mask) ? 0.f : -1.f;
-    double w = 0.0;
-    const double* c = o.coef + r * n;
-    for (int q = 0; q < n; ++q) w += ((k >> q) & 1ull) ? -c[q] : c[q];
-    return (float)w;
-}
-
+// S[2r] = A[r], S[2r+1] = O A[r].
 __global__ __launch_bounds__(256) void k_adj_init(const float2* A, int n, AdjObs o, u64 total, float2* S,
                                                   int paired) {
     const u64 e2 = ((u64)blockIdx.x * 256 + threadIdx.x) * 2;
@@ -2073,6 +2217,19 @@ __global__ __launch_bounds__(256) void k_trans_finish(const double* partial, int
     }
 }
 
+__device__ __forceinline__ int axis_of(const CircDev& c, int sl) {
+    return c.reupload && sl == 0 ? (int)QSV_RX : c.rot[sl - c.reupload];
+}
+
+// The RZ rotations that end the last layer are followed by an entangler, which permutes or signs basis
+// states, and a diagonal observable: their derivative is exactly zero (what was summed is rounding, about
+// 1e-9 a sample, and an optimiser that divides by a gradient's size makes steps of it).
+__device__ __forceinline__ bool vanishing(const CircDev& c, int layer, int s) {
+    bool all = layer + 1 == c.n_layers;
+    for (int sl = s; sl < c.reupload + c.n_rot; ++sl) all = all && axis_of(c, sl) == QSV_RZ;
+    return all;
+}
+
 // Derivative with respect to the angle of slot s on qubit q of a layer, from the qubit's transition sums M at the
 // layer's start.  With U the qubit's unitary and V = R_last ... R_{s+1} its slots after s it is
 // 2 Re sum_ab Bt[a][b] M[a][b], Bt = U^dagger V (-i/2 P_s) V^dagger U.  U^dagger (ud) is taken from the
@@ -2082,10 +2239,9 @@ __device__ __forceinline__ double adj_derivative(const double (&M)[8], const M2&
                                                  const float* params) {
     const int slots = c.reupload + c.n_rot;
     M2 w = ud;                                       // then times V
-    auto axis_of = [&](int sl) { return c.reupload && sl == 0 ? (int)QSV_RX : c.rot[sl - c.reupload]; };
     for (int sl = slots - 1; sl > s; --sl)          // never the re-upload slot
-        w = mul_m(w, rot_m(axis_of(sl), (double)params[((u64)layer * slots + sl) * c.n + q]));
-    const int axis = axis_of(s);
+        w = mul_m(w, rot_m(axis_of(c, sl), (double)params[((u64)layer * slots + sl) * c.n + q]));
+    const int axis = axis_of(c, s);
     // G = -i/2 P for the axis of slot s
     M2 g;
     for (int k = 0; k < 4; ++k) { g.r[k] = 0.0; g.i[k] = 0.0; }
@@ -2098,12 +2254,7 @@ __device__ __forceinline__ double adj_derivative(const double (&M)[8], const M2&
     const M2 bt = mul_m(w, mul_m(g, wd));
     double acc = 0.0;
     for (int k = 0; k < 4; ++k) acc += bt.r[k] * M[2 * k] - bt.i[k] * M[2 * k + 1];
-    // The RZ rotations that end the last layer are followed by an entangler, which permutes or signs basis
-    // states, and a diagonal observable: their derivative is exactly zero (what was summed is rounding, about
-    // 1e-9 a sample, and an optimiser that divides by a gradient's size makes steps of it).
-    bool vanishes = layer + 1 == c.n_layers;
-    for (int sl = s; sl < slots; ++sl) vanishes = vanishes && axis_of(sl) == QSV_RZ;
-    if (vanishes) acc *= 0.0;
+    if (vanishing(c, layer, s)) acc *= 0.0;
     return 2.0 * acc;
 }
 
@@ -2154,6 +2305,47 @@ __global__ __launch_bounds__(256) void k_adj_all(const double* sums, int waves, 
     const double M[8] = {0.0, m00, kre, kim, 0.0, 0.0, 0.0, t - m00};
     const u64 entry = (c.reupload ? sample * (u64)c.n_layers * c.n : 0) + (u64)l * c.n + q;
     const double g = adj_derivative(M, entry_m(back + entry * 8, true, 0, 1), c, l, s, q, params);
+    double* fb = f + sample * (2 * P + 1);
+    fb[2 * p] = g;
+    fb[2 * p + 1] = -g;
+}
+
+// The same from the records of k_pair_pass: `lanes` lanes per (unitary by position, row) add its records up in a
+// fixed order, and lane s of them takes the derivative of slot s.  corr: the scale table of k_build_mats.
+__global__ __launch_bounds__(256) void k_pair_finish(const float4* sums, int waves, int lanes, CircDev c, const float* params,
+                                                     u64 rows, u64 sample0, u64 P, const int* order,
+                                                     const int* entry_of, const float* back, int n_mats,
+                                                     const double* corr, int seq0, int seq_stride, double* f) {
+    const u64 job = ((u64)blockIdx.x * 256 + threadIdx.x) / (unsigned)lanes;
+    const int lane = (int)(threadIdx.x & (unsigned)(lanes - 1));
+    const int per = c.n_layers * c.n, slots = c.reupload + c.n_rot;
+    const bool live = job < (u64)per * rows;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const u64 pos = live ? job / rows : 0, r = live ? job % rows : 0;
+    if (live) {
+        const float4* rec = sums + job * (u64)waves;
+        for (int i = lane; i < waves; i += lanes) {
+            const float4 v = rec[i];
+            acc[0] += (double)v.x; acc[1] += (double)v.y; acc[2] += (double)v.z; acc[3] += (double)v.w;
+        }
+    }
+    for (int d = lanes >> 1; d > 0; d >>= 1)
+        for (int j = 0; j < 4; ++j) acc[j] += __shfl_xor(acc[j], d, 64);
+    if (!live || lane >= slots) return;
+    const int lq = order[pos], layer = lq / c.n, q = lq % c.n, s = lane;
+    const u64 sample = sample0 + r, table = c.reupload ? sample : 0;
+    const double up = corr[(table * (u64)per + pos) * 2], up_before = corr[(table * (u64)per + pos) * 2 + 1];
+    double g;
+    if (slots >= 3) {
+        const double x = acc[0] * up, z = acc[1] * up, y = acc[2] * up;
+        const double M[8] = {0.0, 0.5 * z, -y, x, 0.0, 0.0, 0.0, -0.5 * z};
+        const float* entry = back + (table * (u64)n_mats + (u64)entry_of[pos]) * 8;
+        g = adj_derivative(M, entry_m(entry, false, seq0, seq_stride), c, layer, s, q, params);
+    } else {
+        g = s == 0 ? acc[0] * up : acc[2] * up_before;
+        if (vanishing(c, layer, s)) g *= 0.0;
+    }
+    const u64 p = ((u64)layer * slots + s) * c.n + q;
     double* fb = f + sample * (2 * P + 1);
     fb[2 * p] = g;
     fb[2 * p + 1] = -g;
@@ -2992,6 +3184,26 @@ hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles
     return hipGetLastError();
 }
 
+hipError_t launch_pair_pass(int tile, const PairArgs& a, hipStream_t st) {
+    if (tile < kMinTile || tile > kPairMaxTile || a.n < tile || a.n > kDirectMaxQubits || a.w + tile - a.c > a.n || a.s_in < 0 ||
+        a.s_out < 0 || a.s_in > tile - R || a.s_out > tile - R || a.rows < 1 || !a.psi || !a.sums ||
+        (a.imap && a.lam_in && a.lam_in == a.lam_out) || a.psi == a.lam_out)
+        return hipErrorInvalidValue;
+    const u64 tiles = (u64)a.rows << (a.n - tile);
+    if (tiles > 0x7fffffffull || ((u64)a.rows << (a.n - 10)) * 16 > 0xffffffffull) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)tiles), block(1u << (tile - R));
+    const size_t bytes = (size_t)direct_lds_bytes(tile);
+    switch (a.imap ? -tile : tile) {
+#define QSV_PAIR(T)                                                                         \
+    case T: hipLaunchKernelGGL((k_pair_pass<T, false>), grid, block, bytes, st, a); break;  \
+    case -T: hipLaunchKernelGGL((k_pair_pass<T, true>), grid, block, bytes, st, a); break;
+        QSV_PAIR(10) QSV_PAIR(11) QSV_PAIR(12) QSV_PAIR(13)
+#undef QSV_PAIR
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_naive_u(float2* state, int64_t rows, int n, int q, const float* mats,
                           const float* ovr, int mat_id, int n_mats, int rowdep, const RowMap& rm,
                           hipStream_t st) {
@@ -3016,19 +3228,26 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
 }
 
 // how a factored entry names its instruction sequence
-inline int seq_first(MatForm f) { return f == MatForm::direct ? (int)direct::kSeq0 : 0; }
-inline int seq_step(MatForm f) { return f == MatForm::direct ? (int)direct::kSeqStride : 16; }
+inline int seq_first(MatForm f) {
+    return f == MatForm::direct ? (int)direct::kSeq0 : f == MatForm::paired ? (int)paired::kSeq0 : 0;
+}
+inline int seq_step(MatForm f) {
+    return f == MatForm::direct ? (int)direct::kSeqStride : f == MatForm::paired ? (int)paired::kSeqStride : 16;
+}
 
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
-                             const int* order, int period, MatForm form, float* out, double* scale, hipStream_t st) {
-    if (period < 0 || (period > 0 && period != c.n)) return hipErrorInvalidValue;
+                             const int* order, int period, const int* starts, int n_starts, MatForm form, float* out,
+                             double* scale, hipStream_t st) {
+    if (period < 0 || (period > 0 && (period != c.n || starts)) || (starts && (n_starts < 1 || !order)) ||
+        (form == MatForm::paired && !(scale && starts)))
+        return hipErrorInvalidValue;
     const u64 tables = (u64)(c.reupload ? samples : 1);
     const u64 per = (u64)c.n_layers * c.n;
     if (tables * per == 0) return hipSuccess;
     const u64 seg = period > 0 ? (u64)period : per;
-    const u64 groups = tables * (per / seg) * ((seg + kMatGroup - 1) / kMatGroup);
+    const u64 groups = tables * (starts ? (u64)n_starts : (per / seg) * ((seg + kMatGroup - 1) / kMatGroup));
     hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(groups, 4)), dim3(256), 0, st, c, params, feats, groups, inverse,
-                       order, period, form, seq_first(form), seq_step(form), out, scale);
+                       order, period, starts, n_starts, form, seq_first(form), seq_step(form), out, scale);
     return hipGetLastError();
 }
 
@@ -3425,6 +3644,19 @@ hipError_t launch_adj_layers(double* partial, int64_t row_pairs, const CircDev& 
     hipLaunchKernelGGL(k_adj_layers, dim3(blocks_for(jobs, 256)), dim3(256), 0, st, sums, c, layer0, n_layers, params,
                        (u64)sample0, (u64)row_pairs, (u64)P, back, exec_of, form == MatForm::plain ? 1 : 0,
                        seq_first(form), seq_step(form), f);
+    return hipGetLastError();
+}
+
+hipError_t launch_pair_finish(const float* sums, int64_t rows, const CircDev& c, const float* params, int64_t sample0,
+                              int64_t P, const int* order, const int* entry_of, const float* back, int n_mats,
+                              const double* corr, double* f, hipStream_t st) {
+    const u64 jobs = (u64)rows * c.n_layers * c.n;
+    if (jobs == 0 || c.slots() < 1) return hipSuccess;
+    const int waves = 1 << (c.n - 10);
+    const int lanes = waves < 4 ? 4 : waves > 64 ? 64 : waves;     // a lane per slot at least
+    hipLaunchKernelGGL(k_pair_finish, dim3(blocks_for(jobs * lanes, 256)), dim3(256), 0, st,
+                       reinterpret_cast<const float4*>(sums), waves, lanes, c, params, (u64)rows, (u64)sample0, (u64)P,
+                       order, entry_of, back, n_mats, corr, seq_first(MatForm::paired), seq_step(MatForm::paired), f);
     return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "qsv_gate_asm.h"
@@ -10,7 +11,7 @@
 namespace qsv {
 
 struct DirectOp {
-    uint32_t code;   // byte offset of the operation's code in the interpreter
+    uint32_t code;   // byte offset of the operation's code in its interpreter
     uint32_t arg;    // unitaries: index in execution order; conditions: mask of index bits; lane exchange: mask of the
                      // lane number; transposes: offset / 64 of the target layout's code | flags << 16
 };
@@ -19,26 +20,47 @@ static_assert(sizeof(DirectOp) == sizeof(Op), "both forms take the same room");
 struct DirectPass {
     int begin;           // first operation
     int s_in, s_out;     // register layouts of the load and the store
-    int first_mat;       // index of the first unitary (0 if none)
+    int first_mat;       // table entry of the first unitary (0 if none)
+    int first_u;         // its index (0 if none)
 };
 
 struct DirectPlan {
-    std::vector<DirectOp> ops;   // never more than the plan has
+    std::vector<DirectOp> ops;   // never more than the plan has, but for the scalars of groups and the sums of pairs
     std::vector<DirectPass> passes;
 };
 
+// What the paired interpreter does around a unitary (see sum_handlers in the generator): the axes, 0..2 for X, Y, Z, of
+// the circuit's rotation slots; none: no sums.
+struct SumAxes {
+    int count = 0, axis[4] = {};
+};
+
+inline SumAxes sum_axes(const qsv_circuit& c) {
+    SumAxes a;
+    if (c.reupload) a.axis[a.count++] = QSV_RX - 1;
+    for (int r = 0; r < c.n_rot; ++r) a.axis[a.count++] = c.rot[r] - 1;
+    return a;
+}
+
 // Lowers one operation list (a pass: OP_LOAD ... OP_END) onto out; false if it holds something the direct
 // interpreter has no code for (never planned for tiles of one row).  shifts: some row may replace a matrix.
-inline bool lower_pass(const Op* ops, int count, bool shifts, DirectPlan* out) {
+// sums (the paired interpreter): the sums to be taken.  groups: Plan::groups, NULL or empty: the scalars are in the matrices.
+template <class Code>
+bool lower_pass_as(const Op* ops, int count, bool shifts, const SumAxes& sums, const std::vector<int32_t>* groups,
+                   DirectPlan* out) {
+    constexpr bool pair = std::is_same<Code, paired>::value;
+    const bool scaled = groups && !groups->empty();
+    // the group of unitary k: the last start that is not behind it
+    auto group_of = [&](int k) { return (int)(std::upper_bound(groups->begin(), groups->end(), k) - groups->begin()) - 1; };
     DirectPass dp;
     dp.begin = (int)out->ops.size();
     dp.s_in = dp.s_out = -1;
-    dp.first_mat = -1;
+    dp.first_mat = dp.first_u = -1;
     int s = -1;
     uint32_t rungs = 0;          // CZ rungs inside the run, collected: neighbouring ones go in one operation
     auto put = [&](uint32_t code, uint32_t arg) { out->ops.push_back({code, arg}); };
     auto flush = [&]() {
-        if (rungs) put(direct::kCz[rungs], 0);
+        if (rungs) put(Code::kCz[rungs], 0);
         rungs = 0;
     };
     for (int k = 0; k < count; ++k) {
@@ -57,62 +79,85 @@ inline bool lower_pass(const Op* ops, int count, bool shifts, DirectPlan* out) {
                 break;
             case OP_U:
                 if (o.a > 3) return false;
-                if (dp.first_mat < 0) dp.first_mat = o.arg;
-                put(o.c ? (shifts ? direct::kGShift[o.a] : direct::kG[o.a]) : (shifts ? direct::kUShift[o.a] : direct::kU[o.a]),
-                    (uint32_t)o.arg);
+                if (dp.first_u < 0) {
+                    dp.first_u = o.arg;
+                    dp.first_mat = o.arg + (scaled ? group_of(o.arg) : 0);
+                }
+                if (scaled && (o.c || shifts)) return false;
+                if constexpr (pair) {
+                    if (sums.count < 1 || shifts || o.c) return false;
+                    if (sums.count == 2) put(Code::kBefore[o.a][sums.axis[1]], 0);
+                    put(Code::kU[o.a], (uint32_t)o.arg);
+                    put(sums.count == 1   ? Code::kSum1[o.a][sums.axis[0]]
+                        : sums.count == 2 ? Code::kSum2[o.a][sums.axis[0]]
+                                          : Code::kSum3[o.a],
+                        0);
+                } else {
+                    put(o.c ? (shifts ? Code::kGShift[o.a] : Code::kG[o.a]) : (shifts ? Code::kUShift[o.a] : Code::kU[o.a]),
+                        (uint32_t)o.arg);
+                }
+                if (scaled && (*groups)[group_of(o.arg) + 1] == o.arg + 1) put(Code::kScale, 0);
                 break;
             case OP_CX_REG:
                 if (o.a > 3 || o.b > 3 || o.a == o.b) return false;
-                put(direct::kCx[o.a][o.b], 0);
+                put(Code::kCx[o.a][o.b], 0);
                 break;
             case OP_CX_CHAIN:
-                if (o.arg < 0 || o.arg >= (int)(sizeof direct::kChain / sizeof direct::kChain[0])) return false;
-                put(direct::kChain[o.arg], 0);
+                if (o.arg < 0 || o.arg >= (int)(sizeof Code::kChain / sizeof Code::kChain[0])) return false;
+                put(Code::kChain[o.arg], 0);
                 break;
             case OP_CX_DYN:
                 if (o.a > 3 || o.b > 31) return false;
-                put(direct::kCxBit[o.a], 1u << o.b);
+                put(Code::kCxBit[o.a], 1u << o.b);
                 break;
             case OP_CX_PAR:
                 if (o.a > 3) return false;
-                put(direct::kCxParity[o.a], (uint32_t)o.arg);
+                put(Code::kCxParity[o.a], (uint32_t)o.arg);
                 break;
             case OP_CX_LANE:
                 if (o.a > 3 || o.b > 5) return false;
-                if (o.b < 2) put(direct::kCxQuad[o.a][o.b], 0);
-                else put(direct::kCxLane[o.a], 1u << o.b);
+                if (o.b < 2) put(Code::kCxQuad[o.a][o.b], 0);
+                else put(Code::kCxLane[o.a], 1u << o.b);
                 break;
             case OP_CZ_MIX:
                 if (o.a > 3 || o.b > 31) return false;
-                put(direct::kCzMix[o.a], 1u << o.b);
+                put(Code::kCzMix[o.a], 1u << o.b);
                 break;
             case OP_CZ_LANE:
-                put(direct::kCzLane, (uint32_t)o.arg);
+                put(Code::kCzLane, (uint32_t)o.arg);
                 break;
             case OP_XPOSE:
                 if (s < 0 || s > 10 || o.a > 10) return false;
-                put(direct::kWrite[s], direct::kRead[o.a] / 64u | (o.b ? 1u << 16 : 0u) | (o.c ? 1u << 17 : 0u));
+                put(Code::kWrite[s], Code::kRead[o.a] / 64u | (o.b ? 1u << 16 : 0u) | (o.c ? 1u << 17 : 0u));
                 s = o.a;
                 break;
             case OP_END:
-                put(direct::kEnd, 0);
+                put(Code::kEnd, 0);
                 break;
             default:
                 return false;
         }
     }
     dp.s_out = s;
-    if (dp.first_mat < 0) dp.first_mat = 0;
+    if (dp.first_u < 0) dp.first_mat = dp.first_u = 0;
     out->passes.push_back(dp);
-    return s >= 0 && !out->ops.empty() && out->ops.back().code == direct::kEnd;
+    return s >= 0 && !out->ops.empty() && out->ops.back().code == Code::kEnd;
 }
 
-inline bool lower_plan(const Plan& p, bool shifts, DirectPlan* out) {
+inline bool lower_pass(const Op* ops, int count, bool shifts, DirectPlan* out) {
+    return lower_pass_as<direct>(ops, count, shifts, SumAxes(), nullptr, out);
+}
+
+// sums: a mirrored plan for the paired interpreter, which takes the transition sums of its unitaries on the way.
+inline bool lower_plan(const Plan& p, bool shifts, DirectPlan* out, const SumAxes* sums = nullptr) {
     for (const Pass& ps : p.passes) {
         if (ps.w + ps.t - ps.c > p.n) return false;
-        if (!lower_pass(p.ops.data() + ps.op_begin, ps.op_count, shifts, out)) return false;
+        const Op* ops = p.ops.data() + ps.op_begin;
+        if (!(sums ? lower_pass_as<paired>(ops, ps.op_count, shifts, *sums, &p.groups, out)
+                   : lower_pass_as<direct>(ops, ps.op_count, shifts, SumAxes(), &p.groups, out)))
+            return false;
         // the table is read front to back
-        int next = out->passes.back().first_mat;
+        int next = out->passes.back().first_u;
         for (int k = 0; k < ps.op_count; ++k) {
             const Op& o = p.ops[ps.op_begin + k];
             if (o.kind == OP_U && o.arg != next++) return false;

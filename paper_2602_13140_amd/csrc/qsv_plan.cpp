@@ -668,6 +668,23 @@ Plan mirror_plan(const Plan& f) {
     return p;
 }
 
+void group_by_passes(Plan* p) {
+    p->groups.clear();
+    int32_t at = 0;
+    for (const Pass& ps : p->passes) {
+        int32_t end = at;
+        for (int i = 0; i < ps.op_count; ++i) {
+            Op& o = p->ops[ps.op_begin + i];
+            if (o.kind != OP_U) continue;
+            o.c = 0;
+            ++end;
+        }
+        for (int32_t k = at; k < end; k += kMatGroup) p->groups.push_back(k);
+        at = end;
+    }
+    p->groups.push_back(at);
+}
+
 std::string describe_plan(const Plan& p) {
     std::string s;
     char buf[96];

@@ -97,6 +97,10 @@ struct Plan {
     // state row) always map to themselves.
     std::vector<uint32_t> maps;
     std::vector<Op> defers;      // the deferred CNOTs, pass by pass (description and tests only)
+    // Not empty: the first unitaries of the groups that share their scalars, and at the end the number of unitaries.  No
+    // unitary of a group holds its scalars then: they are an entry of the table and an operation of their own behind
+    // the group's last one (unitary k of group g has entry k + g), and no Op::c is set.
+    std::vector<int32_t> groups;
 };
 
 // Validates a circuit descriptor; returns false and fills why on failure.
@@ -114,6 +118,10 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
 // index map reads through the same map.  Backwards the chain of a CNOT ring defers badly (20 qubits, 20
 // layers: 31 passes planned directly against 21 forwards; 26 qubits, 30 layers: 52 against 50).
 Plan mirror_plan(const Plan& forward);
+
+// Groups (see Plan::groups) that end with their pass, so that the states between the passes lack no scalars: a reverse-mode
+// sweep keeps them.  It costs 64 vector instructions a wavefront and pass, beside about twenty unitaries of 60.
+void group_by_passes(Plan* p);
 
 std::string describe_plan(const Plan& p);
 

@@ -1296,3 +1296,114 @@ def test_rows_at_the_largest_offsets(n, L, ent):
         del res
     ctx.close()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n,B,L,rot,ent,reup,opts", [
+    (10, 3, 7, (RY, RZ), RING, 0, {"small_apply": 0}),          # a wavefront a tile, one pass, an odd number of rows
+    (10, 2, 8, (RX, RY, RZ), LADDER, 1, {"small_apply": 0}),    # 80 unitaries: two groups in a pass
+    (11, 5, 3, (RZ,), RING, 0, {}),                             # one rotation each: its axis commutes with the observable
+    (11, 4, 5, (RX,), LADDER, 1, {"split_streams": 1}),         # two axes, per-sample tables, halves on two streams
+    (12, 1, 4, (RY, RZ), NONE, 0, {}),                          # no entangler
+    (12, 3, 4, (RZ, RY), RING, 0, {"tile_log2": 10}),           # four passes and more, index maps, four tiles a row
+    (13, 2, 6, (RX, RY), RING, 0, {"tile_log2": 11, "defer_cnots": 0}),
+    (14, 5, 3, (RY, RY), RING, 0, {"split_streams": 1, "grad_chunk_rows": 2}),   # three chunks, the last of one row
+    (14, 2, 5, (RX, RY, RZ), RING, 0, {"tile_log2": 10}),       # tiles that share lines eight workgroups apart
+    (15, 1, 4, (RY, RZ), LADDER, 1, {"tile_log2": 13}),
+    (16, 2, 2, (RZ, RX), RING, 1, {"reverse_passes": 0, "nt_store": 1}),
+])
+def test_reverse_mode_in_the_passes_of_the_whole_circuit(oracle, n, B, L, rot, ent, reup, opts):
+    """The fused sweep for every kind of sums (one, two, three rotations a unitary) and all three observables, against the
+    sweep that goes layer by layer and, up to 12 qubits, against the oracle's shift rule.
+    A sum over 2^n products of amplitudes that carry the rounding of 2 L n gates, of a few 6e-8 each: as for the
+    one-launch sweep above."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, rot, ent, reup)
+    g = rng(131 * n + B)
+    P = spec.num_params(n)
+    x, p, f = (a.astype(np.float32) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P), g.standard_normal((B, n))))
+    y = g.uniform(-1, 1, (B, n)).astype(np.float32)
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
+    for k, v in opts.items():
+        ctx.qsv_set_option(k, v)
+    res = {}
+    for fused in (1, 0):
+        ctx.qsv_set_option("grad_layered", fused)
+        for kind in (0, 1, 2):
+            loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+            args = circ, gu.dev(x), gu.dev(p), gu.dev(f) if reup else None
+            for _ in range(2):                                  # the second time the plan is there
+                if kind == 0:
+                    ctx.qsv_adjoint_grad(*args, n - 1, loss, grad)
+                else:
+                    ctx.qsv_loss_grad(*args, kind, loss, grad, mask=1 << (n // 2) | 1, targets=gu.dev(y))
+            torch.cuda.synchronize()
+            res[fused, kind] = loss.cpu().numpy().astype(np.float64), grad.cpu().numpy().astype(np.float64)
+    ctx.close()
+    tol = 2e-7 * np.sqrt(L * n) * 4
+    for kind in (0, 1, 2):
+        (la, ga), (lb, gb) = res[1, kind], res[0, kind]
+        assert np.abs(la - lb).max() <= tol
+        assert np.abs(ga - gb).max() <= tol * max(1.0, np.abs(gb).max())
+    if n <= 12:
+        lref, gref = oracle.loss_grad(x, n, ocirc(oracle, spec), p, f if reup else None, kind=oracle.LOSS_MSE_Z, targets=y)
+        assert np.abs(res[1, 2][0] - lref).max() <= tol
+        assert np.abs(res[1, 2][1] - gref).max() <= tol * max(1.0, np.abs(gref).max())
+
+
+def test_reverse_mode_without_room_for_the_states_goes_another_way():
+    """The smallest workspace does not hold the states between the passes of this circuit (the plan is made, then dropped):
+    psi is taken back beside lambda as before, with the same result up to rounding (see above)."""
+    torch = gu.torch_cuda()
+    n, B, L = 16, 128, 12
+    spec = wl.CircuitSpec(L, (RY, RZ), RING, 0)
+    circ = qb.circuit_from_spec(spec)
+    g = rng(5)
+    x = gu.dev(g.standard_normal((B, 1 << n)).astype(np.float32))
+    p = gu.dev(g.uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32))
+    res = []
+    for size in (qb.qsv_workspace_bytes(n, B), qb.qsv_grad_workspace_bytes(n, B, circ)):
+        ctx = gu.make_ctx(n, B, ws_bytes=size)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, spec.num_params(n)), 9.0, device="cuda")
+        ctx.qsv_adjoint_grad(circ, x, p, None, 0, loss, grad)
+        torch.cuda.synchronize()
+        res.append((loss, grad))
+        ctx.close()
+    tol = 2e-7 * np.sqrt(L * n) * 4
+    assert (res[0][0] - res[1][0]).abs().max().item() <= tol
+    d = (res[0][1] - res[1][1]).abs().max().item()
+    assert 0.0 < d <= tol
+
+
+def test_reverse_mode_sweep_in_a_graph():
+    """Captured once, replayed with other inputs between eager calls: every replay equals the eager result."""
+    torch = gu.torch_cuda()
+    n, B, L = 13, 40, 4
+    spec = wl.CircuitSpec(L, (RY, RZ), RING, 1)
+    circ = qb.circuit_from_spec(spec)
+    P = spec.num_params(n)
+    g = rng(8)
+    x, p, f = (gu.dev(a.astype(np.float32)) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P), g.standard_normal((B, n))))
+    y = gu.dev(g.uniform(-1, 1, (B, n)).astype(np.float32))
+    loss, grad = torch.zeros(B, device="cuda"), torch.zeros((B, P), device="cuda")
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = qb.Context(n, B)
+        ctx.qsv_set_option("split_streams", 1)
+        run = lambda: ctx.qsv_loss_grad(circ, x, p, f, qb.QSV_LOSS_MSE_Z, loss, grad, targets=y)
+        run()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            run()
+        for _ in range(4):
+            p.uniform_(0, 6.0)
+            run()
+            torch.cuda.synchronize()
+            want = loss.clone(), grad.clone()
+            loss.zero_()
+            grad.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(loss, want[0]) and torch.equal(grad, want[1])
+        ctx.close()
