@@ -216,7 +216,8 @@ qsv_status qsv_pauli_expect(qsv_ctx* ctx, uint64_t xmask, uint64_t ymask, uint64
  * workspace for the shifted circuits' states; the context's state buffer is left untouched.
  * When the workspace has room for n_layers + 1 states per sample (qsv_grad_workspace_bytes), the
  * unshifted circuit's state before every layer is kept and a circuit that shifts a parameter of
- * layer l runs layers l..L-1 only, from that state: the same values with about half the gate
+ * layer l runs layers l..L-1 only, from that state, or, for larger batches, from the state behind that layer's
+ * rotations, on which it first turns the one qubit: the same values with about half the gate
  * applications (option grad_layered = 0 switches this off). */
 qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float* x_dev, int64_t dim,
                                 const float* params_dev, const float* feats_dev, int32_t obs_qubit,

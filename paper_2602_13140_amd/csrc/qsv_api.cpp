@@ -29,6 +29,11 @@ constexpr size_t kOpsRegion = 4u << 20;  // persistent: uploaded pass programs
 // (26 qubits) 3663 -> 3451 us; 2 x 128 MiB (24 qubits) 761 -> 849 us.
 constexpr uint64_t kNtStoreBytes = 384ull << 20;
 constexpr uint64_t kSplitBytes = 32ull << 20;    // see run_circuit
+// Amplitudes of a layer's shifted circuits from which the layer's rotations are applied to the start states first: that is one
+// more pass or two over the batch for every layer.  Measured without / with: 16 qubits x 256, 10 layers 98.4 / 91.3 ms
+// (2^30), 13 x 32, 3 layers 379 / 352 us (2^24.3), 16 x 4, 6 layers 971 / 944 (2^24), 12 x 64, 6 layers 603 / 587 (2^23.6);
+// 15 x 4, 5 layers 727 / 760 (2^22.9), 14 x 4, 3 layers 195 / 214 (2^21.8), 15 x 1, 1 layer 65 / 75 (2^20.9).
+constexpr uint64_t kAheadAmplitudes = 1ull << 23;
 constexpr int kChunkBits = 12;
 constexpr int kMaxBatch = 1 << 24;
 constexpr int64_t kMaxAmplitudes = (int64_t)1 << 36;
@@ -43,6 +48,11 @@ int ceil_log2_i64(int64_t v) {
     return b;
 }
 
+// kSweep: of a fused reverse-mode sweep: groups end with their passes, the inverse is the circuit's mirror image for the
+// paired interpreter.  kShifts: the first layer's unitaries are in the start states, gradient rows multiply one of
+// them by their shift.
+enum PlanForm { kPlain = 0, kSweep = 1, kShifts = 2 };
+
 // A plan the context has built.  Entries are never destroyed before qsv_destroy and never move (a
 // std::deque only grows at its end), so pointers to them, and the host arrays uploads read from,
 // stay valid for the life of the context: also for a HIP graph that recorded such an upload.
@@ -51,8 +61,7 @@ struct CachedPlan {
     int inverse, tile, grad, low;   // tile: the resolved tile size (the default depends on the rows)
     int defer = 0;                  // planned with deferred CNOTs (index maps)
     int direct = 0;                 // for the direct interpreter: `low_ops` is uploaded in place of plan.ops
-    int sweep = 0;                  // of a fused reverse-mode sweep: groups end with their passes, the inverse is the
-                                    // circuit's mirror image for the paired interpreter
+    int form = kPlain;
     DirectPlan low_ops;
     std::vector<unsigned> mates;   // of a mirrored plan's passes: PassArgs::mate
     size_t maps_off = 0;            // uint32[plan.maps.size()]: the index maps of its passes
@@ -60,7 +69,8 @@ struct CachedPlan {
     bool resident = false;          // its arrays are in the ops region right now
     size_t dev_off;     // byte offset of the ops inside the ops region
     size_t order_off;   // int32[n_mats]: execution order -> (layer*n + qubit)
-    size_t execof_off;  // int32[n_mats]: (layer*n + qubit) -> execution order; sweep: execution order -> table entry
+    size_t execof_off;  // int32[]: (layer*n + qubit) -> execution order; kSweep: execution order -> table entry;
+                        // kShifts: qubit -> what its OP_SHIFT is called by
     size_t groups_off = 0;          // int32[plan.groups.size()]
     std::vector<int32_t> exec_of;
 };
@@ -209,15 +219,20 @@ int tile_of(const qsv_ctx* ctx, int64_t rows, int layers, int defer) {
     return std::max(kMinTile, std::min(kMaxTile, tile));
 }
 
+// tiles of one row through one LDS plane (tiles of 2^14 have no other way): see kDirectMaxQubits
+bool is_direct(const qsv_ctx* ctx, int tile) {
+    return ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile);
+}
+
 qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad,
-                    const CachedPlan** out, int defer = 0, int sweep = 0) {
+                    const CachedPlan** out, int defer = 0, PlanForm form = kPlain) {
     const int tile = tile_of(ctx, rows, c.n_layers, defer);
-    // tiles of one row through one LDS plane (tiles of 2^14 have no other way): see kDirectMaxQubits
-    const int direct = ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile) ? 1 : 0;
+    const bool sweep = form == kSweep;
+    const int direct = is_direct(ctx, tile) ? 1 : 0;
     CachedPlan* hit = nullptr;
     for (CachedPlan& cp : ctx->cache)
         if (cp.inverse == inverse && cp.tile == tile && cp.grad == grad && cp.low == ctx->opt_low &&
-            cp.defer == defer && cp.direct == direct && cp.sweep == sweep && same_circuit(cp.c, c)) {
+            cp.defer == defer && cp.direct == direct && cp.form == form && same_circuit(cp.c, c)) {
             hit = &cp;
             break;
         }
@@ -234,7 +249,7 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         cp.low = ctx->opt_low;
         cp.defer = defer;
         cp.direct = direct;
-        cp.sweep = sweep;
+        cp.form = form;
         auto build = [&](bool inv) {
             return planned(c, ctx->n, rows, inv, tile, grad != 0, ctx->opt_low, defer != 0);
         };
@@ -255,14 +270,18 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
             cp.mates.assign(cp.plan.passes.size(), 0);
         if (!cp.plan.complete) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: pass planner failed");
         if (sweep) group_by_passes(&cp.plan);
+        if (form == kShifts) shift_first_layer(&cp.plan);
         const SumAxes axes = sum_axes(c);
-        if (direct && !lower_plan(cp.plan, grad != 0, &cp.low_ops, sweep && inverse ? &axes : nullptr))
+        if (direct && !lower_plan(cp.plan, grad != 0 && form != kShifts, &cp.low_ops, sweep && inverse ? &axes : nullptr))
             return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: lowering the pass plan failed");
         const size_t nm = cp.plan.mat_order.size();
         cp.exec_of.assign(nm, 0);
         if (sweep) {
             for (size_t g = 0; g + 1 < cp.plan.groups.size(); ++g)
                 for (int32_t k = cp.plan.groups[g]; k < cp.plan.groups[g + 1]; ++k) cp.exec_of[k] = k + (int32_t)g;
+        } else if (form == kShifts) {
+            cp.exec_of.resize(ctx->n);
+            for (int q = 0; q < ctx->n; ++q) cp.exec_of[q] = q;
         } else {
             for (size_t k = 0; k < nm; ++k) cp.exec_of[cp.plan.mat_order[k]] = (int32_t)k;
         }
@@ -272,7 +291,7 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
     CachedPlan& cp = *hit;
     const size_t nm = cp.plan.mat_order.size();
     const size_t ops_bytes = align_up(std::max(cp.plan.ops.size(), cp.low_ops.ops.size()) * sizeof(Op) + sizeof(Op));
-    const size_t tab_bytes = align_up(nm * sizeof(int32_t) + 4);
+    const size_t tab_bytes = align_up(std::max(nm, cp.exec_of.size()) * sizeof(int32_t) + 4);
     const size_t map_bytes = align_up(cp.plan.maps.size() * sizeof(uint32_t) + 4);
     const size_t group_bytes = align_up(cp.plan.groups.size() * sizeof(int32_t) + 4);
     const size_t bytes = ops_bytes + 2 * tab_bytes + map_bytes + group_bytes;
@@ -304,14 +323,14 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
                                     (cp.direct ? cp.low_ops.ops.size() : cp.plan.ops.size()) * sizeof(Op),
                                     hipMemcpyHostToDevice, ctx->stream),
                 "upload plan");
-    if (nm) {
+    if (nm)
         QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.order_off, cp.plan.mat_order.data(), nm * sizeof(int32_t),
                                     hipMemcpyHostToDevice, ctx->stream),
                 "upload matrix order");
-        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.execof_off, cp.exec_of.data(), nm * sizeof(int32_t),
+    if (!cp.exec_of.empty())
+        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.execof_off, cp.exec_of.data(), cp.exec_of.size() * sizeof(int32_t),
                                     hipMemcpyHostToDevice, ctx->stream),
                 "upload matrix order");
-    }
     ctx->ops_used += bytes;
     cp.resident = true;
     *out = &cp;
@@ -1125,16 +1144,29 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         RowMap rm_fwd;    // rows are the samples: the first pass of layer l reads state l and writes state l + 1
         rm_fwd.grad = 1; rm_fwd.two_p = 0; rm_fwd.per = 1; rm_fwd.row0 = 0;
         rm_fwd.slots_n = slots_n < 1 ? 1 : slots_n; rm_fwd.n = n;
+        Prepared all;
+        st = prepare_layers(ctx, *c, one, B, 0, params_dev, feats_dev, B, mats, &all);
+        if (st != QSV_OK) return st;
         for (int l = 0; l < L; ++l) {
-            Prepared pr;
-            st = prepare_circuit(ctx, one, B, 0, 0, params_dev + (size_t)l * slots_n, feats_dev, B, mats, &pr);
-            if (st != QSV_OK) return st;
-            st = run_circuit(ctx, one, pr, ck(l + 1), B, 0, nullptr, rm_fwd, ck(l));
+            st = run_circuit(ctx, one, layer_of(all, l, n), ck(l + 1), B, 0, nullptr, rm_fwd, ck(l));
             if (st != QSV_OK) return st;
         }
         QSV_HIP(ctx, launch_expz_block(ck(L), B, n, zpart, ctx->stream), "expz block");
         QSV_HIP(ctx, launch_expz_finish_scatter(zpart, B, n, obs_qubit, f, Scatter{0, 1, per, 2 * P}, ctx->stream),
                 "expz finish");
+        // A shifted unitary is a shift times the unshifted one, so a circuit that shifts an angle of layer l also shares that
+        // layer's rotations with the unshifted circuit: the states go through them once per sample, and a shifted circuit
+        // starts with one matrix on one qubit instead of n unitaries.  See kAheadAmplitudes for where that pays.
+        const bool ahead = !ctx->opt_naive && is_direct(ctx, tile_of(ctx, chunk, 1, 0)) &&
+                           ((uint64_t)(B * per_l) << n) >= kAheadAmplitudes;
+        if (ahead) {
+            qsv_circuit rot = one;
+            rot.entangler = QSV_ENT_NONE;
+            st = prepare_layers(ctx, *c, rot, B, 0, params_dev, feats_dev, B, mats, &all);
+            for (int l = 0; l < L && st == QSV_OK; ++l)
+                st = run_circuit(ctx, rot, layer_of(all, l, n), ck(l), B, 0, nullptr, rm_fwd);
+            if (st != QSV_OK) return st;
+        }
         // shifted circuits of layer l: start from ck(l), run layers l..L-1 with one matrix replaced
         const CircDev cd1 = to_dev(one, n);
         for (int l = 0; l < L; ++l) {
@@ -1142,9 +1174,24 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
             tail.n_layers = L - l;
             const float* p_l = params_dev + (size_t)l * slots_n;
             Prepared pr;
-            st = prepare_circuit(ctx, tail, chunk, 0, 1, p_l, feats_dev, B, mats, &pr);
-            if (st != QSV_OK) return st;
-            QSV_HIP(ctx, launch_build_shifted(cd1, p_l, feats_dev, B, pr.exec_of, pr.scale, tail.n_layers * n, ovr, ctx->stream), "build shifted");
+            if (ahead) {
+                st = get_plan(ctx, tail, chunk, 0, 1, &pr.cp, 0, kShifts);
+                if (st != QSV_OK) return st;
+                CircDev rest = to_dev(tail, n);
+                rest.n_layers -= 1;
+                pr.mats = mats;
+                pr.mat_stride = rest.n_layers * n;
+                pr.form = MatForm::direct;
+                QSV_HIP(ctx, launch_build_mats(rest, p_l + slots_n, feats_dev, B, 0,
+                                               reinterpret_cast<const int*>(ctx->ws + pr.cp->order_off), 0, nullptr, 0,
+                                               MatForm::direct, mats, nullptr, ctx->stream),
+                        "build matrices");
+                QSV_HIP(ctx, launch_build_shifts(cd1, p_l, B, ovr, ctx->stream), "build shifts");
+            } else {
+                st = prepare_circuit(ctx, tail, chunk, 0, 1, p_l, feats_dev, B, mats, &pr);
+                if (st != QSV_OK) return st;
+                QSV_HIP(ctx, launch_build_shifted(cd1, p_l, feats_dev, B, pr.exec_of, pr.scale, tail.n_layers * n, ovr, ctx->stream), "build shifted");
+            }
             const int64_t circuits_l = B * per_l;
             for (int64_t row0 = 0; row0 < circuits_l; row0 += chunk) {
                 const int64_t rows = (circuits_l - row0) < chunk ? (circuits_l - row0) : chunk;
@@ -1293,8 +1340,8 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
     if (ar.remaining() < fixed + (size_t)sets * half * sample_bytes(1)) return QSV_OK;     // without planning for it
     const CachedPlan *fp = nullptr, *bp = nullptr;
     for (int k = 0; k < 2; ++k) {      // twice: should the second plan recycle the plan buffer, the first comes back
-        qsv_status st = get_plan(ctx, c, B, 0, 0, &fp, defer, 1);
-        if (st == QSV_OK) st = get_plan(ctx, c, B, 1, 0, &bp, defer, 1);
+        qsv_status st = get_plan(ctx, c, B, 0, 0, &fp, defer, kSweep);
+        if (st == QSV_OK) st = get_plan(ctx, c, B, 1, 0, &bp, defer, kSweep);
         if (st != QSV_OK) return st;
     }
     const size_t passes = fp->plan.passes.size();

@@ -154,6 +154,8 @@ inline size_t mat_scale_bytes(const CircDev& c, int64_t samples) {
 // it of (layer*n + qubit)
 hipError_t launch_build_shifted(const CircDev& c, const float* params, const float* feats, int64_t samples,
                                 const int* exec_of, const double* scale, int per, float* out, hipStream_t st);
+// What multiplies a layer's unitary when one of its angles is shifted, for a one-layer circuit c: shifted matrix = out * matrix.
+hipError_t launch_build_shifts(const CircDev& c, const float* params, int64_t samples, float* out, hipStream_t st);
 
 // encoding
 hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* partial, int nblk,

@@ -792,6 +792,10 @@ __global__ __launch_bounds__(256) void k_naive_cz_ladder(float2* state, u64 tota
 // Fused per-(layer, qubit) matrices, computed in double and rounded once to float.
 struct M2 { double r[4], i[4]; };  // row-major 2x2: [0]=m00 [1]=m01 [2]=m10 [3]=m11
 
+__device__ __forceinline__ int axis_of(const CircDev& c, int sl) {
+    return c.reupload && sl == 0 ? (int)QSV_RX : c.rot[sl - c.reupload];
+}
+
 __device__ __forceinline__ M2 rot_m(int axis, double t) {
     double s, c;
     sincos(0.5 * t, &s, &c);
@@ -1096,6 +1100,20 @@ __global__ __launch_bounds__(256) void k_build_shifted(CircDev c, const float* p
         scale_m(u, {f[0], f[1]});
     }
     store_m(u, out + idx * 8);
+}
+
+// What a shifted unitary of the layer is more than the unshifted one: R_last .. R_s(t +- pi/2) .. R_0 = S U with
+// S = V R_s(+-pi/2) V^dagger, V the slots after s (never the re-upload slot: S is the same for every sample).
+__global__ __launch_bounds__(256) void k_build_shifts(CircDev c, const float* params, u64 count, float* out) {
+    const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= count) return;
+    const int slots = c.reupload + c.n_rot, v = (int)(idx % (2ull * slots * c.n)), p = v >> 1, q = p % c.n, s = p / c.n;
+    M2 m = rot_m(axis_of(c, s), (v & 1) ? -1.57079632679489661923 : 1.57079632679489661923);
+    for (int sl = s + 1; sl < slots; ++sl) {
+        const double t = (double)params[(u64)sl * c.n + q];
+        m = mul_m(mul_m(rot_m(axis_of(c, sl), t), m), rot_m(axis_of(c, sl), -t));
+    }
+    store_m(m, out + idx * 8);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2217,10 +2235,6 @@ __global__ __launch_bounds__(256) void k_trans_finish(const double* partial, int
     }
 }
 
-__device__ __forceinline__ int axis_of(const CircDev& c, int sl) {
-    return c.reupload && sl == 0 ? (int)QSV_RX : c.rot[sl - c.reupload];
-}
-
 // The RZ rotations that end the last layer are followed by an entangler, which permutes or signs basis
 // states, and a diagonal observable: their derivative is exactly zero (what was summed is rounding, about
 // 1e-9 a sample, and an optimiser that divides by a gradient's size makes steps of it).
@@ -3264,6 +3278,14 @@ hipError_t launch_build_shifted(const CircDev& c, const float* params, const flo
 
 // ||x_b|| of every sample: inv_norm [samples] (0 for a zero vector), norm_out optional.  One launch
 // when a sample fits one block, else block partials and a finishing launch.
+hipError_t launch_build_shifts(const CircDev& c, const float* params, int64_t samples, float* out, hipStream_t st) {
+    const u64 count = (u64)(c.reupload ? samples : 1) * 2ull * c.slots() * c.n;
+    if (c.n_layers != 1) return hipErrorInvalidValue;
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_build_shifts, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params, count, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* partial, int nblk,
                         double* inv_norm, float* norm_out, hipStream_t st) {
     const bool one = nblk == 1;

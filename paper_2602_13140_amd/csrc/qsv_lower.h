@@ -98,6 +98,11 @@ bool lower_pass_as(const Op* ops, int count, bool shifts, const SumAxes& sums, c
                 }
                 if (scaled && (*groups)[group_of(o.arg) + 1] == o.arg + 1) put(Code::kScale, 0);
                 break;
+            case OP_SHIFT:
+                if (o.a > 3 || shifts) return false;
+                if constexpr (pair) return false;
+                else put(Code::kShift[o.a], (uint32_t)o.arg);
+                break;
             case OP_CX_REG:
                 if (o.a > 3 || o.b > 3 || o.a == o.b) return false;
                 put(Code::kCx[o.a][o.b], 0);

@@ -1407,3 +1407,40 @@ def test_reverse_mode_sweep_in_a_graph():
             torch.cuda.synchronize()
             assert torch.equal(loss, want[0]) and torch.equal(grad, want[1])
         ctx.close()
+
+
+@pytest.mark.parametrize("n,B,L,rot,ent,reup,opts", [
+    (10, 220, 2, (RY, RZ), RING, 0, {}),                        # a wavefront a tile
+    (11, 70, 3, (RX, RY, RZ), LADDER, 0, {}),
+    (12, 33, 2, (RZ, RY), RING, 1, {"grad_chunk_rows": 700}),   # re-uploading; chunks that end inside a sample's rows
+    (13, 20, 3, (RX,), LADDER, 1, {}),
+    (14, 10, 2, (RY, RX), RING, 0, {"tile_log2": 10}),          # several passes, halves on two streams
+    (14, 6, 1, (RZ, RX, RY), NONE, 1, {}),                      # nothing but shifts is left of the circuit
+])
+def test_shift_rule_from_states_behind_the_layers_rotations(oracle, n, B, L, rot, ent, reup, opts):
+    """Batches large enough that the shifted circuits start behind their layer's rotations: against whole circuits and against
+    the oracle on the first sample.  A difference of two expectation values, each with the rounding of L (slots) n gates."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, rot, ent, reup)
+    g = rng(17 * n + B)
+    P = spec.num_params(n)
+    x, p, f = (a.astype(np.float32) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P), g.standard_normal((B, n))))
+    circ = qb.circuit_from_spec(spec)
+    assert (2 * P // L * B) << n >= 1 << 23
+    ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
+    for k, v in opts.items():
+        ctx.qsv_set_option(k, v)
+    res = []
+    for layered in (1, 0):
+        ctx.qsv_set_option("grad_layered", layered)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+        ctx.qsv_param_shift_grad(circ, gu.dev(x), gu.dev(p), gu.dev(f) if reup else None, n // 2, loss, grad)
+        torch.cuda.synchronize()
+        res.append((loss.cpu().numpy().astype(np.float64), grad.cpu().numpy().astype(np.float64)))
+    ctx.close()
+    scale = max(1.0, float(np.abs(f).max())) if reup else 1.0
+    tol = 2e-7 * np.sqrt(L * n) * 4 * scale
+    assert np.abs(res[0][0] - res[1][0]).max() <= tol and np.abs(res[0][1] - res[1][1]).max() <= tol
+    assert not np.array_equal(res[0][1], res[1][1])
+    lref, gref = oracle.param_shift_grad(x[:1], n, ocirc(oracle, spec), p, f[:1] if reup else None, n // 2)
+    assert np.abs(res[0][0][:1] - lref).max() <= tol and np.abs(res[0][1][:1] - gref).max() <= tol
