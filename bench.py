@@ -309,8 +309,10 @@ def bench_c2(torch, qb, wl, args):
     updates = wl.nominal_updates(w.circuit, n, circuits)
     L = w.circuit.n_layers
     layer_updates = wl.nominal_updates(w.circuit, n, 1) // L      # gate-amplitude updates of one layer
-    per_layer = 2 * P // L                                         # shifted circuits per sample and layer
-    executed = B * layer_updates * (L + sum(per_layer * (L - l) for l in range(L)))
+    # Both shifted states of a parameter are combinations of the unshifted one and of one whose angle is turned by pi, so
+    # one circuit per parameter is run, from the state behind the layer's rotations on.
+    per_layer = P // L                                             # turned circuits per sample and layer
+    executed = B * layer_updates * (2 * L + sum(per_layer * (L - 1 - l) for l in range(L)))
     ms, _ = run_steps(torch, step, steps, 1)
     ctx.qsv_set_option("grad_layered", 0)
     ms_whole, _ = run_steps(torch, step, steps, 1)
@@ -336,7 +338,8 @@ def bench_c2(torch, qb, wl, args):
     ctx3.close()
     updates3 = wl.nominal_updates(spec3, n, B * (2 * P3 + 1))
     return {"workload": "c2: 16 qubits, batch 256, 10 layers RY,RZ + CZ ladder, full parameter-shift gradient",
-            "method": "layer by layer from kept states: a circuit that shifts a parameter of layer l runs layers l..L-1",
+            "method": "layer by layer from kept states: one circuit per parameter of layer l, its angle turned by pi, runs "
+                      "layers l+1..L-1; both shifted states are combinations of its state and the unshifted one",
             "ms_per_step": ms, "steps": steps, "circuits": circuits, "params": P, "updates": updates,
             "updates_per_s": updates / (ms * 1e-3),
             "executed_updates": executed, "executed_updates_per_s": executed / (ms * 1e-3),

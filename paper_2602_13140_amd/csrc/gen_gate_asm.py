@@ -685,7 +685,7 @@ def _renumbered(line):
 #   s[38:39] operation list   s40 byte offset of the next word   s[42:43] the word (code, argument)
 #   s[44:45] matrix table     s41 byte offset of the next entry   s[48:55] the next entry
 #   s[56:63] shifted matrix of a gradient row
-#   s[64:65], s[66:67] jump targets   s[68:69] saved exec   s70 argument of a transpose or a shift
+#   s[64:65], s[66:67] jump targets   s[68:69] saved exec   s70 argument of a transpose or a turn
 #
 # The paired form (pair=True) is the same block for two states at once, psi in r, i and lambda in p, q: the reverse-mode
 # sweep takes both back through a pass and reads the transition sums off the registers between the gates (see
@@ -860,13 +860,17 @@ def direct_handlers(pair=False):
             H.append(("GS%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc0 L_dG%d_%%=" % j, "L_dovr%d_%%=:" % j,
                                "s_load_dwordx8 s[56:63], %[ovr], 0x0", "s_waitcnt lgkmcnt(0)"] +
                   ["v_mov_b32 %%[m%d], s%d" % (k, 56 + k) for k in range(8)] + ["s_branch L_dgj%d_%%=" % j]))
-    # what a gradient row shifts a qubit's angle by, as a matrix of its own: applied if the row shifts qubit s43, else nothing
+    # gradient rows that turn an angle by pi: the turn as a matrix before the unitary (UT), or by itself where the unitaries
+    # are in the start state (V), in the row that names it
     if not pair:
+        turn = lambda j: ["s_load_dwordx8 s[56:63], %[ovr], 0x0", "s_waitcnt lgkmcnt(0)"] + [
+            "v_mov_b32 %%[m%d], s%d" % (k, 56 + k) for k in range(8)] + [
+            ln for i in range(NR) if not i & (1 << j) for ln in u_pair(i, i | (1 << j))]
         for j in range(R):
-            body = [ln for i in range(NR) if not i & (1 << j) for ln in u_pair(i, i | (1 << j))]
+            H.append(("UT%d" % j, ["s_cmp_eq_u32 s43, %[ovrid]", "s_cbranch_scc0 L_dU%d_%%=" % j] + turn(j) +
+                      ["s_branch L_dU%d_%%=" % j]))
             H.append(("V%d" % j, ["s_mov_b32 s70, s43"] + NEXT_WORD +
-                      ["s_cmp_eq_u32 s70, %[ovrid]", "s_cbranch_scc0 L_dV%dx_%%=" % j, "s_load_dwordx8 s[56:63], %[ovr], 0x0",
-                       "s_waitcnt lgkmcnt(0)"] + ["v_mov_b32 %%[m%d], s%d" % (k, 56 + k) for k in range(8)] + body +
+                      ["s_cmp_eq_u32 s70, %[ovrid]", "s_cbranch_scc0 L_dV%dx_%%=" % j] + turn(j) +
                       ["L_dV%dx_%%=:" % j] + DISPATCH))
     # the scalar of a group by itself: 4 instructions an amplitude, as many as the whole matrix takes above the
     # cheapest form; it rounds all amplitudes alike, where a rounded matrix changes the lengths of its two columns by
@@ -1028,9 +1032,9 @@ def direct_constants(pair=False):
         "namespace qsv { struct %s {" % ("paired" if pair else "direct"),
         "// byte offsets of the code of each operation in the block (see gen_direct in the generator)",
         "static constexpr unsigned kU[4] = {%s};" % rows("U%d" % j for j in j4),
-        "static constexpr unsigned kG[4] = {%s}, kUShift[4] = {%s}, kGShift[4] = {%s}, kShift[4] = {%s};" % (
-            rows("G%d" % j for j in j4), rows("US%d" % j for j in j4), rows("GS%d" % j for j in j4),
-            rows("V%d" % j for j in j4)) if not pair else
+        "static constexpr unsigned kG[4] = {%s}, kUShift[4] = {%s}, kGShift[4] = {%s};\n"
+        "static constexpr unsigned kUTurn[4] = {%s}, kTurn[4] = {%s};" % tuple(
+            rows("%s%d" % (name, j) for j in j4) for name in ("G", "US", "GS", "UT", "V")) if not pair else
         "static constexpr unsigned kBefore[4][3] = {%s}, kSum1[4][3] = {%s}, kSum2[4][3] = {%s}, kSum3[4] = {%s};" % (
             *(", ".join("{%s}" % rows("%s%d%s" % (k, j, x) for x in AXES) for j in j4) for k in ("B", "S1", "S2")),
             rows("S3%d" % j for j in j4)),

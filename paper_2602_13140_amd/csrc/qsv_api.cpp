@@ -29,11 +29,16 @@ constexpr size_t kOpsRegion = 4u << 20;  // persistent: uploaded pass programs
 // (26 qubits) 3663 -> 3451 us; 2 x 128 MiB (24 qubits) 761 -> 849 us.
 constexpr uint64_t kNtStoreBytes = 384ull << 20;
 constexpr uint64_t kSplitBytes = 32ull << 20;    // see run_circuit
-// Amplitudes of a layer's shifted circuits from which the layer's rotations are applied to the start states first: that is one
-// more pass or two over the batch for every layer.  Measured without / with: 16 qubits x 256, 10 layers 98.4 / 91.3 ms
-// (2^30), 13 x 32, 3 layers 379 / 352 us (2^24.3), 16 x 4, 6 layers 971 / 944 (2^24), 12 x 64, 6 layers 603 / 587 (2^23.6);
-// 15 x 4, 5 layers 727 / 760 (2^22.9), 14 x 4, 3 layers 195 / 214 (2^21.8), 15 x 1, 1 layer 65 / 75 (2^20.9).
-constexpr uint64_t kAheadAmplitudes = 1ull << 23;
+// Amplitudes of a layer's gradient rows (B slots n 2^n) from which one circuit per parameter is run instead of two (see
+// qsv_param_shift_grad): reading the unshifted states at the end of the last pass takes 2 to 3 us.  Measured, two / one:
+// 10 qubits x 16, 2 layers 72 / 76 us (2^18.3), 12 x 4, 2 layers 77 / 77 (2^18.6), 15 x 1, 1 layer 65 / 60 (2^19.9), 14 x 4, 3
+// layers 193 / 163 (2^20.8), 16 x 256, 10 layers 98.4 / 52.7 ms (2^29).
+constexpr uint64_t kTurnAmplitudes = 1ull << 19;
+// ... and from which the layer's rotations are applied to the start states first: that is one more pass or two over the
+// batch for every layer.  Measured without / with: 15 x 4, 5 layers 502 / 549 us (2^21.9), 16 x 4, 6 layers 680 / 742 (2^23),
+// 14 x 64, 4 layers 1141 / 1137 (2^24.8), 16 x 16, 6 layers 1662 / 1579 (2^25), 12 x 1024, 4 layers 3019 / 2587 (2^27), 16 x 256,
+// 10 layers 52.7 / 49.7 ms.
+constexpr uint64_t kAheadAmplitudes = 1ull << 25;
 constexpr int kChunkBits = 12;
 constexpr int kMaxBatch = 1 << 24;
 constexpr int64_t kMaxAmplitudes = (int64_t)1 << 36;
@@ -49,9 +54,9 @@ int ceil_log2_i64(int64_t v) {
 }
 
 // kSweep: of a fused reverse-mode sweep: groups end with their passes, the inverse is the circuit's mirror image for the
-// paired interpreter.  kShifts: the first layer's unitaries are in the start states, gradient rows multiply one of
-// them by their shift.
-enum PlanForm { kPlain = 0, kSweep = 1, kShifts = 2 };
+// paired interpreter.  kTurned: gradient rows turn an angle of the first layer (see Rows); kTurnedAhead: and that layer's
+// unitaries are in the start states.  kGrouped: the circuit's plan as it is.  All but kPlain have Plan::groups.
+enum PlanForm { kPlain = 0, kSweep = 1, kTurned = 2, kTurnedAhead = 3, kGrouped = 4 };
 
 // A plan the context has built.  Entries are never destroyed before qsv_destroy and never move (a
 // std::deque only grows at its end), so pointers to them, and the host arrays uploads read from,
@@ -70,7 +75,7 @@ struct CachedPlan {
     size_t dev_off;     // byte offset of the ops inside the ops region
     size_t order_off;   // int32[n_mats]: execution order -> (layer*n + qubit)
     size_t execof_off;  // int32[]: (layer*n + qubit) -> execution order; kSweep: execution order -> table entry;
-                        // kShifts: qubit -> what its OP_SHIFT is called by
+                        // kTurnedAhead: qubit -> what its OP_TURN is called by
     size_t groups_off = 0;          // int32[plan.groups.size()]
     std::vector<int32_t> exec_of;
 };
@@ -269,17 +274,18 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         else
             cp.mates.assign(cp.plan.passes.size(), 0);
         if (!cp.plan.complete) return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: pass planner failed");
-        if (sweep) group_by_passes(&cp.plan);
-        if (form == kShifts) shift_first_layer(&cp.plan);
+        if (form == kTurnedAhead) turn_first_layer(&cp.plan);
+        if (form != kPlain) group_by_passes(&cp.plan);
         const SumAxes axes = sum_axes(c);
-        if (direct && !lower_plan(cp.plan, grad != 0 && form != kShifts, &cp.low_ops, sweep && inverse ? &axes : nullptr))
+        const Rows what = form == kTurned ? Rows::turn : form == kTurnedAhead || !grad ? Rows::none : Rows::replace;
+        if (direct && !lower_plan(cp.plan, what, &cp.low_ops, sweep && inverse ? &axes : nullptr))
             return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: lowering the pass plan failed");
         const size_t nm = cp.plan.mat_order.size();
         cp.exec_of.assign(nm, 0);
         if (sweep) {
             for (size_t g = 0; g + 1 < cp.plan.groups.size(); ++g)
                 for (int32_t k = cp.plan.groups[g]; k < cp.plan.groups[g + 1]; ++k) cp.exec_of[k] = k + (int32_t)g;
-        } else if (form == kShifts) {
+        } else if (form == kTurnedAhead) {
             cp.exec_of.resize(ctx->n);
             for (int q = 0; q < ctx->n; ++q) cp.exec_of[q] = q;
         } else {
@@ -348,7 +354,8 @@ RowMap plain_rows(int n) {
 struct Prepared {
     const CachedPlan* cp = nullptr;  // null: one-gate-per-launch path
     float* mats = nullptr;
-    int mat_stride = 0;              // matrices per sample in a per-sample table; 0: those of the circuit run
+    int mat_stride = 0;              // entries per sample in a per-sample table; 0: the matrices of the circuit run
+    int layer_entries = 0;           // entries per layer of a table of layers
     const int* exec_of = nullptr;    // gradient: for the shifted matrices
     const double* scale = nullptr;   // gradient: the table's scalars (null: a plain table)
     MatForm form = MatForm::plain;   // of the table
@@ -369,17 +376,18 @@ size_t mats_bytes(const qsv_circuit& c, int n, int64_t samples) {
 // that plan's order; layer l then runs with layer_of(prepared, l).  Otherwise run = c.
 qsv_status prepare(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& run, bool layered, int64_t rows, int inverse,
                    int grad, const float* params, const float* feats, int64_t samples, float* mats, Prepared* out,
-                   int defer) {
+                   int defer, PlanForm plan_form = kPlain, double* residues = nullptr) {
     const int n = ctx->n;
     const bool has_u = (c.reupload + c.n_rot) > 0 && c.n_layers > 0;
     out->mats = mats;
     out->cp = nullptr;
+    out->layer_entries = n;
     out->mat_stride = layered ? c.n_layers * n : 0;
     const int* order = nullptr;
     MatForm& form = out->form;
     form = MatForm::plain;
     if (!(ctx->opt_naive || n < kRegBits)) {
-        qsv_status st = get_plan(ctx, run, rows, inverse, grad, &out->cp, defer);
+        qsv_status st = get_plan(ctx, run, rows, inverse, grad, &out->cp, defer, plan_form);
         if (st != QSV_OK) return st;
         order = reinterpret_cast<const int*>(ctx->ws + out->cp->order_off);
         out->exec_of = reinterpret_cast<const int*>(ctx->ws + out->cp->execof_off);
@@ -388,11 +396,16 @@ qsv_status prepare(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& run, b
             form = out->cp->direct ? MatForm::direct : MatForm::factored;
     }
     if (!has_u) return QSV_OK;
-    double* scale = grad && form != MatForm::plain
+    // groups with their scalars as entries of their own: so many more entries a table or layer
+    const int n_groups = out->cp && !out->cp->plan.groups.empty() ? (int)out->cp->plan.groups.size() - 1 : 0;
+    out->layer_entries = n + n_groups;
+    out->mat_stride = layered ? c.n_layers * out->layer_entries : n_groups ? c.n_layers * n + n_groups : 0;
+    double* scale = n_groups ? residues : grad && form != MatForm::plain
         ? reinterpret_cast<double*>(reinterpret_cast<char*>(mats) + mats_table_bytes(c, n, samples)) : nullptr;
     out->scale = scale;
-    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0, nullptr, 0, form,
-                                   mats, scale, ctx->stream),
+    QSV_HIP(ctx, launch_build_mats(to_dev(c, n), params, feats, samples, inverse, order, layered && order ? n : 0,
+                                   n_groups ? reinterpret_cast<const int*>(ctx->ws + out->cp->groups_off) : nullptr, n_groups,
+                                   form, mats, scale, ctx->stream),
             "build matrices");
     return QSV_OK;
 }
@@ -404,13 +417,14 @@ qsv_status prepare_circuit(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int
 }
 
 qsv_status prepare_layers(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit& one, int64_t rows, int inverse,
-                          const float* params, const float* feats, int64_t samples, float* mats, Prepared* out) {
-    return prepare(ctx, c, one, true, rows, inverse, 0, params, feats, samples, mats, out, 0);
+                          const float* params, const float* feats, int64_t samples, float* mats, Prepared* out,
+                          PlanForm form = kPlain, double* residues = nullptr) {
+    return prepare(ctx, c, one, true, rows, inverse, 0, params, feats, samples, mats, out, 0, form, residues);
 }
 
-inline Prepared layer_of(const Prepared& all, int l, int n) {
+inline Prepared layer_of(const Prepared& all, int l) {
     Prepared pr = all;
-    pr.mats = all.mats + (size_t)l * n * 8;
+    pr.mats = all.mats + (size_t)l * all.layer_entries * 8;
     return pr;
 }
 
@@ -421,7 +435,11 @@ inline Prepared layer_of(const Prepared& all, int l, int n) {
 // zs (optional): what the gradient wants of the final states, <Z_q> per row scattered into out.
 // The fused path computes it in its last pass (which then stores nothing) when a tile never spans
 // two rows; otherwise the reduction kernels read the final states.  zpart: room for partials.
-struct ZSpec { int q; double* out; Scatter sc; double* zpart; };
+// unturned (optional, direct plans): see PassArgs; two results a row then, and what follows is for launch_turned_finish.
+struct ZSpec {
+    int q; double* out; Scatter sc; double* zpart;
+    const float2* unturned; int64_t unturned_at; Residues ra, rb1, rb2;
+};
 
 // pong (needed when the plan defers CNOTs): a second buffer of the state's shape.  A pass with an
 // index map reads one buffer and writes the other; the result always ends up in `state`.
@@ -473,6 +491,8 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
     const Plan& pl = cp->plan;
     const Op* dev_ops = reinterpret_cast<const Op*>(ctx->ws + cp->dev_off);
     const bool z_in_pass = zs && n >= pl.tile && !pl.passes.empty();
+    if (zs && zs->unturned && !(z_in_pass && cp->direct))
+        return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: turned rows need the direct kernel");
     // Two rows or more: the rows go through the passes as two halves on two streams.  The halves
     // never meet (a tile lies inside one row when n > tile, and the geometry of the passes does not
     // depend on the number of rows), and each one's launch gaps and tails are covered by the
@@ -530,6 +550,8 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         a.zout = (last && z_in_pass) ? zs->zpart : nullptr;
         a.zq = zs ? zs->q : 0;
         a.nostore = a.zout ? 1 : 0;
+        a.turns = zs && zs->unturned ? 1 : 0;
+        a.unturned = a.zout ? zs->unturned : nullptr;
         a.ops = dev_ops + (cp->direct ? cp->low_ops.passes[pi].begin : ps.op_begin);
         a.mats = mats;
         a.exec_of = reinterpret_cast<const int*>(ctx->ws + cp->execof_off);
@@ -579,7 +601,8 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
             if (b.src) b.src = b.src + ((uint64_t)rows_a << n);
             if (c.reupload && b.mats) b.mats = b.mats + (uint64_t)rows_a * (uint64_t)n_mats * 8;
         }
-        if (b.zout) b.zout = b.zout + (uint64_t)rows_a * ((uint64_t)1 << (n - pl.tile)) * (uint64_t)waves_per_group;
+        if (b.zout)
+            b.zout = b.zout + (b.unturned ? 3 : 1) * (uint64_t)rows_a * ((uint64_t)1 << (n - pl.tile)) * (uint64_t)waves_per_group;
         QSV_HIP(ctx, launch_pass(pl.tile, planes, b, tiles_of(rows_b), ctx->side), "fused pass");
     }
     if (split) {       // what follows on the caller's stream sees both halves
@@ -593,7 +616,12 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
         // partials per row: tiles of the row x wavefronts of a workgroup
         const int64_t per_row = ((int64_t)1 << (n - pl.tile)) * (((int64_t)1 << (pl.tile - kRegBits)) / 64 > 0
                                                                     ? ((int64_t)1 << (pl.tile - kRegBits)) / 64 : 1);
-        QSV_HIP(ctx, launch_zsum_finish(zs->zpart, rows, per_row, zs->out, zs->sc, ctx->stream), "z finish");
+        if (zs->unturned)
+            QSV_HIP(ctx, launch_turned_finish(zs->zpart, rows, per_row, zs->out, zs->sc, zs->unturned_at, zs->ra, zs->rb1,
+                                              zs->rb2, c.reupload, ctx->stream),
+                    "z finish");
+        else
+            QSV_HIP(ctx, launch_zsum_finish(zs->zpart, rows, per_row, zs->out, zs->sc, ctx->stream), "z finish");
         return QSV_OK;
     }
     return z_after();
@@ -1123,13 +1151,28 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     // ---- layer by layer: the circuits that shift a parameter of layer l share layers 0..l-1 with
     // the unshifted circuit, so its state before layer l is kept per sample and each shifted
     // circuit runs layers l..L-1 only.  Needs room for (L+1) states per sample; otherwise every
-    // shifted circuit is run whole (below).
+    // shifted circuit is run whole (below).  Where the direct kernel takes the rows, one circuit per parameter is run instead of
+    // two, with the angle turned by pi: R(t +- pi/2) = (R(t) +- R(t + pi)) / sqrt 2, so both shifted states are
+    // combinations of its state and the unshifted circuit's, and the last pass forms them and takes both expectation values.
+    // See kTurnAmplitudes for what it gives and where it pays.
     const int L = c->n_layers;
     const int slots_n = (c->reupload + c->n_rot) * n;
     const size_t ckpt_bytes = (size_t)B * (size_t)(L + 1) * state_bytes;
     if (ctx->opt_grad_layered && P > 0 && ar.remaining() >= align_up(ckpt_bytes) + row_bytes + 2 * kAlign) {
         float2* ckpt = (float2*)ar.take(ckpt_bytes);
-        const int64_t per_l = 2 * (int64_t)slots_n;          // shifted circuits per sample and layer
+        // rows per sample and layer; the tile of gradient rows does not depend on their number from 10 qubits on
+        bool turns = !ctx->opt_naive && n >= kMinTile && is_direct(ctx, tile_of(ctx, B, 1, 0)) &&
+                     ((uint64_t)(B * slots_n) << n) >= kTurnAmplitudes;
+        // what the scalars of the tables' groups lack, for at most kLayerGroups groups a layer (a pass of a layer is one; a
+        // tail has no more than its layers one by one, and one more for every 64 unitaries)
+        constexpr int kLayerGroups = 8;
+        const size_t res_count = msamples * (size_t)L * kLayerGroups;
+        double* residues = turns ? (double*)ar.take(3 * res_count * 16) : nullptr;
+        turns = turns && residues;
+        double *res_one = residues, *res_rot = residues + (turns ? 2 * res_count : 0),
+               *res_tail = residues + (turns ? 4 * res_count : 0);
+        int g_one = 0, g_rot = 0, g_tail = 0;
+        const int64_t per_l = (turns ? 1 : 2) * (int64_t)slots_n;
         const int64_t want = B * per_l > B ? B * per_l : B;
         const int64_t chunk = chunk_rows(want);
         float2* states = (float2*)ar.take((size_t)chunk * state_bytes);
@@ -1145,26 +1188,29 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         rm_fwd.grad = 1; rm_fwd.two_p = 0; rm_fwd.per = 1; rm_fwd.row0 = 0;
         rm_fwd.slots_n = slots_n < 1 ? 1 : slots_n; rm_fwd.n = n;
         Prepared all;
-        st = prepare_layers(ctx, *c, one, B, 0, params_dev, feats_dev, B, mats, &all);
+        // (with turned rows the states are combined with theirs: unitaries rounded alike)
+        const PlanForm unshifted = turns ? kGrouped : kPlain;
+        st = prepare_layers(ctx, *c, one, B, 0, params_dev, feats_dev, B, mats, &all, unshifted, res_one);
         if (st != QSV_OK) return st;
+        g_one = all.layer_entries - n;
         for (int l = 0; l < L; ++l) {
-            st = run_circuit(ctx, one, layer_of(all, l, n), ck(l + 1), B, 0, nullptr, rm_fwd, ck(l));
+            st = run_circuit(ctx, one, layer_of(all, l), ck(l + 1), B, 0, nullptr, rm_fwd, ck(l));
             if (st != QSV_OK) return st;
         }
         QSV_HIP(ctx, launch_expz_block(ck(L), B, n, zpart, ctx->stream), "expz block");
         QSV_HIP(ctx, launch_expz_finish_scatter(zpart, B, n, obs_qubit, f, Scatter{0, 1, per, 2 * P}, ctx->stream),
                 "expz finish");
-        // A shifted unitary is a shift times the unshifted one, so a circuit that shifts an angle of layer l also shares that
-        // layer's rotations with the unshifted circuit: the states go through them once per sample, and a shifted circuit
-        // starts with one matrix on one qubit instead of n unitaries.  See kAheadAmplitudes for where that pays.
-        const bool ahead = !ctx->opt_naive && is_direct(ctx, tile_of(ctx, chunk, 1, 0)) &&
-                           ((uint64_t)(B * per_l) << n) >= kAheadAmplitudes;
+        // A unitary with a turned angle is a turn times the unturned one, so the circuits of layer l also share that layer's
+        // rotations: the states go through them once per sample, and a circuit starts with one matrix on one qubit instead of n
+        // unitaries.  See kAheadAmplitudes for where that pays.
+        const bool ahead = turns && ((uint64_t)(B * per_l) << n) >= kAheadAmplitudes;
         if (ahead) {
             qsv_circuit rot = one;
             rot.entangler = QSV_ENT_NONE;
-            st = prepare_layers(ctx, *c, rot, B, 0, params_dev, feats_dev, B, mats, &all);
+            st = prepare_layers(ctx, *c, rot, B, 0, params_dev, feats_dev, B, mats, &all, unshifted, res_rot);
+            g_rot = all.layer_entries - n;
             for (int l = 0; l < L && st == QSV_OK; ++l)
-                st = run_circuit(ctx, rot, layer_of(all, l, n), ck(l), B, 0, nullptr, rm_fwd);
+                st = run_circuit(ctx, rot, layer_of(all, l), ck(l), B, 0, nullptr, rm_fwd);
             if (st != QSV_OK) return st;
         }
         // shifted circuits of layer l: start from ck(l), run layers l..L-1 with one matrix replaced
@@ -1174,19 +1220,24 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
             tail.n_layers = L - l;
             const float* p_l = params_dev + (size_t)l * slots_n;
             Prepared pr;
-            if (ahead) {
-                st = get_plan(ctx, tail, chunk, 0, 1, &pr.cp, 0, kShifts);
+            if (turns) {
+                st = get_plan(ctx, tail, chunk, 0, 1, &pr.cp, 0, ahead ? kTurnedAhead : kTurned);
                 if (st != QSV_OK) return st;
                 CircDev rest = to_dev(tail, n);
-                rest.n_layers -= 1;
+                if (ahead) rest.n_layers -= 1;
+                g_tail = (int)pr.cp->plan.groups.size() - 1;
                 pr.mats = mats;
-                pr.mat_stride = rest.n_layers * n;
+                pr.mat_stride = rest.n_layers * n + g_tail;
                 pr.form = MatForm::direct;
-                QSV_HIP(ctx, launch_build_mats(rest, p_l + slots_n, feats_dev, B, 0,
-                                               reinterpret_cast<const int*>(ctx->ws + pr.cp->order_off), 0, nullptr, 0,
-                                               MatForm::direct, mats, nullptr, ctx->stream),
-                        "build matrices");
-                QSV_HIP(ctx, launch_build_shifts(cd1, p_l, B, ovr, ctx->stream), "build shifts");
+                if (g_one > kLayerGroups || g_rot > kLayerGroups || g_tail > L * kLayerGroups)
+                    return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: more groups than expected");
+                if (g_tail > 0)
+                    QSV_HIP(ctx, launch_build_mats(rest, ahead ? p_l + slots_n : p_l, feats_dev, B, 0,
+                                                   reinterpret_cast<const int*>(ctx->ws + pr.cp->order_off), 0,
+                                                   reinterpret_cast<const int*>(ctx->ws + pr.cp->groups_off), g_tail,
+                                                   MatForm::direct, mats, res_tail, ctx->stream),
+                            "build matrices");
+                QSV_HIP(ctx, launch_build_turns(cd1, p_l, feats_dev, B, ahead ? 1 : 0, ovr, ctx->stream), "build turns");
             } else {
                 st = prepare_circuit(ctx, tail, chunk, 0, 1, p_l, feats_dev, B, mats, &pr);
                 if (st != QSV_OK) return st;
@@ -1202,7 +1253,9 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
                 rm.row0 = row0;
                 rm.slots_n = slots_n;
                 rm.n = n;
-                const ZSpec zs{obs_qubit, f, Scatter{row0, per_l, per, (int64_t)l * per_l}, zpart};
+                const ZSpec zs{obs_qubit, f, Scatter{row0, per_l, per, 2 * (int64_t)l * slots_n}, zpart, turns ? ck(L) : nullptr, 2 * P,
+                               Residues{res_one, l * g_one, (L - l) * g_one, L * g_one}, Residues{res_tail, 0, g_tail, g_tail},
+                               ahead ? Residues{res_rot, l * g_rot, g_rot, L * g_rot} : Residues{res_rot, 0, 0, 0}};
                 st = run_circuit(ctx, tail, pr, states, rows, 0, ovr, rm, ck(l), &zs);
                 if (st != QSV_OK) return st;
             }
@@ -1234,7 +1287,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         rm.slots_n = slots_n < 1 ? 1 : slots_n;
         rm.n = n;
         QSV_HIP(ctx, launch_encode_write(x_dev, dim, n, rows, inv, rm, states, ctx->stream), "encode rows");
-        const ZSpec zs{obs_qubit, f, Scatter{row0, 1, 1, 0}, zpart};
+        const ZSpec zs{obs_qubit, f, Scatter{row0, 1, 1, 0}, zpart, nullptr, 0, {}, {}, {}};
         st = run_circuit(ctx, *c, pr, states, rows, 0, ovr, rm, nullptr, &zs);
         if (st != QSV_OK) return st;
     }
@@ -1606,7 +1659,7 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
             if (st != QSV_OK) return st;
             for (int l = 0; l < L; ++l) {
                 // the start states are addressed by sample (ck(l, 0)), the rows written are the chunk's
-                st = run_circuit(ctx, one, layer_of(all, l, n), ck(l + 1, b0), bc, 0, nullptr, rm1, ck(l, 0));
+                st = run_circuit(ctx, one, layer_of(all, l), ck(l + 1, b0), bc, 0, nullptr, rm1, ck(l, 0));
                 if (st != QSV_OK) return st;
             }
         } else {
@@ -1633,7 +1686,7 @@ static qsv_status adjoint_impl(qsv_ctx* ctx, const qsv_circuit* c, const float* 
         st = prepare_layers(ctx, *c, one, back_rows, 1, params_dev, feats_dev, B, sc.mats, &back);
         if (st != QSV_OK) return st;
         for (int l = L - 1; l >= 0; --l) {
-            st = run_circuit(ctx, one, layer_of(back, l, n), sc.S, back_rows, 1, nullptr, rm2);
+            st = run_circuit(ctx, one, layer_of(back, l), sc.S, back_rows, 1, nullptr, rm2);
             if (st != QSV_OK) return st;
             const float2* psi0 = keep ? ck(l, b0) : sc.S;
             const float2* lam0 = keep ? sc.S : sc.S + amps;
@@ -1742,7 +1795,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     // a window over qubits alone goes through the kernel that the circuits use
     DirectPlan low;
     const bool direct = n >= tile && n <= kDirectMaxQubits && window_start + tile - low_bits <= n &&
-                        (ctx->opt_planes == 1 || tile == kMaxTile) && lower_pass(ops.data(), (int)ops.size(), false, &low);
+                        (ctx->opt_planes == 1 || tile == kMaxTile) && lower_pass(ops.data(), (int)ops.size(), &low);
     // a small synchronous upload: this is a measurement aid, not part of the hot path
     const void* list = direct ? (const void*)low.ops.data() : (const void*)ops.data();
     QSV_HIP(ctx, hipMemcpyAsync(dev, list, (direct ? low.ops.size() : ops.size()) * sizeof(Op), hipMemcpyHostToDevice,
@@ -1754,7 +1807,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
     a.in = ctx->state;
     a.imap = nullptr;
     a.src = nullptr;
-    a.zout = nullptr; a.zq = 0; a.nostore = 0;
+    a.zout = nullptr; a.unturned = nullptr; a.turns = 0; a.zq = 0; a.nostore = 0;
     a.nt_store = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : ((((uint64_t)ctx->batch << n) * 8) >= kNtStoreBytes ? 1 : 0);
     a.rev = ctx->opt_rev != 0 && (ctx->probe_count++ & 1) ? 2 : 0;      // as run_circuit's passes without a map
     a.ops = dev;

@@ -25,7 +25,8 @@ struct CircDev {
 // the matrix of parameter v/2 of the circuit being run by its +pi/2 (v even) or -pi/2 (v odd)
 // shifted version.  Whole-circuit gradients use per = 2P+1 (variant 2P is the unshifted circuit);
 // the layer-by-layer gradient runs the circuit's last layers only and shifts parameters of their
-// first layer: per = two_p = 2 * slots * n.
+// first layer: per = two_p = 2 * slots * n, or (PassArgs::turns) per = two_p = slots * n: R(t + pi) is what the two shifted
+// rotations are made of, R(t +- pi/2) = (R(t) +- R(t + pi)) / sqrt 2.
 struct RowMap {
     int grad;        // 0 plain, 1 gradient
     int two_p;       // variants that replace a matrix: v < two_p (also the row stride of the shifted table)
@@ -45,6 +46,9 @@ struct PassArgs {
     const float2* src;   // not NULL: tiles are read from src[sample of the row] instead of in (needs n >= tile)
     const void* ops;     // Op list of the pass (direct: DirectOp)
     double* zout;        // not NULL: the pass also writes <Z_zq> partials [tile][wavefront] (needs n >= tile)
+    const float2* unturned;  // not NULL (direct, with zout): states a [samples][2^n], and the partials are of three sums each: z |b|^2,
+                         // and the real and imaginary part of z conj(a) b, z = +-1 by bit zq, b the row's state
+    int turns;           // direct: variant v turns parameter v's angle by pi (rm.two_p of them a sample): see RowMap
     int zq;
     int nostore;         // with zout: the state is not written back
     int nt_store;        // nontemporal tile stores (states much larger than the last-level cache)
@@ -138,9 +142,10 @@ hipError_t launch_naive_cz_ladder(float2* state, int64_t rows, int n, hipStream_
 // interpreters of the fused pass read them.  scale (NULL: not wanted): [tables][n_layers*n] complex doubles.
 enum class MatForm { plain, factored, direct, paired, phaseless };   // direct, paired: factored, for those interpreters;
                                                              // phaseless: matrices up to a phase, which a group's last one has
-// groups (device, NULL: every kMatGroup entries): the n_groups groups of a table with their scalars as entries of their own
-// (see Plan::groups; period = 0, form = direct or paired); a table then has n_layers*n + n_groups entries.
-// form = paired: scale (then [tables][n_layers*n][2] doubles by position) receives what sums of products of two states that
+// groups (device, NULL: every kMatGroup entries): the n_groups groups of a table (of a layer, if period = n) with their
+// scalars as entries of their own (see Plan::groups; form = direct or paired): n_groups entries more a table or layer.
+// form = direct with groups: scale (may be NULL) receives what the rounded scalars lack, float / exact, [tables][groups of all
+// layers][2].  form = paired: scale (then [tables][n_layers*n][2] doubles by position) receives what sums of products of two states that
 // have come through the unitaries up to this one are to be multiplied by, and the same without this one.
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
                              const int* order, int period, const int* groups, int n_groups, MatForm form, float* out,
@@ -154,8 +159,10 @@ inline size_t mat_scale_bytes(const CircDev& c, int64_t samples) {
 // it of (layer*n + qubit)
 hipError_t launch_build_shifted(const CircDev& c, const float* params, const float* feats, int64_t samples,
                                 const int* exec_of, const double* scale, int per, float* out, hipStream_t st);
-// What multiplies a layer's unitary when one of its angles is shifted, for a one-layer circuit c: shifted matrix = out * matrix.
-hipError_t launch_build_shifts(const CircDev& c, const float* params, int64_t samples, float* out, hipStream_t st);
+// What a one-layer circuit's unitary is to be multiplied by for one of its angles to be turned by pi, from the right (behind =
+// 0) or from the left; [samples if reupload][P][8].
+hipError_t launch_build_turns(const CircDev& c, const float* params, const float* feats, int64_t samples, int behind,
+                              float* out, hipStream_t st);
 
 // encoding
 hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* partial, int nblk,
@@ -259,6 +266,16 @@ hipError_t launch_expz_finish_scatter(const double* partial, int64_t rows, int n
 // out[scatter(row)] = sum of the row's per_row partials written by a pass with zout
 hipError_t launch_zsum_finish(const double* partial, int64_t rows, int64_t per_row, double* out,
                               const Scatter& sc, hipStream_t st);
+// What the scalars of a table's groups lack of the exact ones, as launch_build_mats writes it: the product of the entries
+// first .. first + count - 1 of a sample's `stride`.
+struct Residues { const double* table; int first, count, stride; };
+// The two results of a turned row b from its three sums (PassArgs::unturned), <Z> of (a + b) / sqrt 2 and of (a - b) / sqrt 2, at
+// out[(gid / per) * stride + offset + 2 (gid % per)] and behind it; <Z> of a is out[(gid / per) * stride + unturned_at].
+// Without their scalars' rounding: what a has come through since the two parted is in ra, b's in rb1 and rb2; a phase of
+// a few 1e-8 between them would show in the results in full.  rowdep: a table per sample.
+hipError_t launch_turned_finish(const double* partial, int64_t rows, int64_t per_row, double* out, const Scatter& sc,
+                                int64_t unturned_at, const Residues& ra, const Residues& rb1, const Residues& rb2, int rowdep,
+                                hipStream_t st);
 // states[r] = src[sample of row r] for the rows of a gradient chunk (src: [samples][2^n])
 hipError_t launch_gather_rows(const float2* src, int n, int64_t rows, const RowMap& rm, float2* states,
                               hipStream_t st);

@@ -163,8 +163,9 @@ __device__ __forceinline__ u64 uni64(u64 v) {
 // from the previous one by adding or subtracting one of four strides, two scalar instructions
 // instead of the nine it takes to build it from k (scalar instructions compete with the vector
 // ones for issue slots).  The walk starts from "element 0 minus stride 0".
-#define QSV_16G(X) X(0, 0, +) X(1, 0, +) X(3, 1, +) X(2, 0, -) X(6, 2, +) X(7, 0, +) X(5, 1, -) X(4, 0, -) \
-                   X(12, 3, +) X(13, 0, +) X(15, 1, +) X(14, 0, -) X(10, 2, -) X(11, 0, +) X(9, 1, -) X(8, 0, -)
+#define QSV_8G(X) X(0, 0, +) X(1, 0, +) X(3, 1, +) X(2, 0, -) X(6, 2, +) X(7, 0, +) X(5, 1, -) X(4, 0, -)
+#define QSV_8G2(X) X(12, 3, +) X(13, 0, +) X(15, 1, +) X(14, 0, -) X(10, 2, -) X(11, 0, +) X(9, 1, -) X(8, 0, -)
+#define QSV_16G(X) QSV_8G(X) QSV_8G2(X)
 #define QSV_DECL(k) float vr##k, vi##k;
 #define QSV_RV(k) [r##k] "+v"(vr##k), [i##k] "+v"(vi##k),
 #define QSV_DECL2(k) float lr##k, li##k;
@@ -463,7 +464,8 @@ void k_pass(const PassArgs a) {
 // workgroups apart, that is on the same XCD and at nearly the same time, so that its L2 serves the second.
 // 20 qubits x 32, 20 layers and back: reads of the mirrored passes 1.31 -> 1.00 times their bytes (2.00 in the worst),
 // 4416 -> 4365 us.
-template <int T, bool GATHER>
+// TURNED: the variant for the last pass of turned gradient rows, which stores three sums and no state.
+template <int T, bool GATHER, bool TURNED = false>
 __global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(96), amdgpu_waves_per_eu(8, 8)))
 void k_pass_direct(const PassArgs a) {
     extern __shared__ float lds[];
@@ -486,7 +488,7 @@ void k_pass_direct(const PassArgs a) {
         sample = a.g_sample0 + local / (unsigned)a.rm.per;
         const unsigned v = local % (unsigned)a.rm.per;
         if (v < (unsigned)a.rm.two_p) {
-            const unsigned p = v >> 1;
+            const unsigned p = a.turns ? v : v >> 1;
             ovr_at = a.exec_of[p / (unsigned)a.rm.slots_n * (unsigned)a.n + p % (unsigned)a.n];
             ovr += ((a.rowdep ? (u64)sample * (unsigned)a.rm.two_p : 0) + v) * 8;
         }
@@ -544,7 +546,7 @@ void k_pass_direct(const PassArgs a) {
 #undef QSV_GET
     }
     if (a.prio) __builtin_amdgcn_s_setprio(0);
-    const bool scatter = !GATHER && a.imap;
+    const bool scatter = !GATHER && !TURNED && a.imap;
     if (scatter) follow_map(s_out);                  // while the tile is on its way
     {
         unsigned ldsb = (tau0 + 2u * (tau0 >> 5)) * 4u, ldsn;
@@ -561,17 +563,50 @@ void k_pass_direct(const PassArgs a) {
                      : QSV_GATE_DIRECT_CLOBBERS);
     }
     const unsigned lane_out = expand(lane_tau(s_out));
-    if (a.zout) {
+    if (TURNED || a.zout) {
         // last pass of a gradient row: see k_pass
         const int zq = a.zq;
-        float acc = 0.f;
+        const u64 at = (u64)tile * (blockDim.x >> 6) + (thr >> 6);
+        const bool flip = ((base | lane_out) >> zq) & 1u;
+        if constexpr (TURNED) {
+            // The row's angle is turned by pi: its state b and the unturned a make the two shifted ones.  a's amplitudes come
+            // eight at a time: what is free of 64 registers does not hold all 16.
+            const __amdgpu_buffer_rsrc_t ru =
+                __builtin_amdgcn_make_buffer_rsrc((void*)(a.unturned + ((u64)sample << a.n)), 0, row_bytes, 0x00020000);
+            float zb = 0.f, cr = 0.f, ci = 0.f;
+            unsigned off = lane_out * 8u;
+            // Gray-code walk over the register elements: strides of their bits, and the sign bit where bit zq is among them
+            const unsigned st0 = expand(1u << s_out), st1 = expand(2u << s_out), st2 = expand(4u << s_out), st3 = expand(8u << s_out);
+            const unsigned zm = 1u << zq, f0 = st0 & zm ? 1u << 31 : 0u, f1 = st1 & zm ? 1u << 31 : 0u, f2 = st2 & zm ? 1u << 31 : 0u,
+                           f3 = st3 & zm ? 1u << 31 : 0u;
+            unsigned so = base - st0, sg = f0;
+#define QSV_ZP(k, bit, sign) { so = so sign st##bit; sg ^= f##bit; \
+                    const u32x2v g = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(ru, (int)off, (int)(so * 8u), 0)); \
+                    const float ur = __uint_as_float(g.x), ui = __uint_as_float(g.y), pb = vr##k * vr##k + vi##k * vi##k, \
+                                pr = ur * vr##k + ui * vi##k, pi = ur * vi##k - ui * vr##k; \
+                    zb += __uint_as_float(__float_as_uint(pb) ^ sg); cr += __uint_as_float(__float_as_uint(pr) ^ sg); \
+                    ci += __uint_as_float(__float_as_uint(pi) ^ sg); }
+            QSV_8G(QSV_ZP)
+            asm volatile("" : "+v"(off), "+v"(zb), "+v"(cr), "+v"(ci));      // the second half's loads wait for these sums
+            QSV_8G2(QSV_ZP)
+#undef QSV_ZP
+            const double sign = flip ? -1.0 : 1.0;
+            const double tb = wave_sum(sign * zb), tr = wave_sum(sign * cr), ti = wave_sum(sign * ci);
+            if ((thr & 63u) == 0) {
+                a.zout[3 * at] = tb;
+                a.zout[3 * at + 1] = tr;
+                a.zout[3 * at + 2] = ti;
+            }
+            return;
+        } else {
+            float acc = 0.f;
 #define QSV_Z(k) { const float p = vr##k * vr##k + vi##k * vi##k; \
                    acc += (expand((unsigned)k << s_out) >> zq) & 1u ? -p : p; }
-        QSV_16(QSV_Z)
+            QSV_16(QSV_Z)
 #undef QSV_Z
-        if (((base | lane_out) >> zq) & 1u) acc = -acc;
-        const double tot = wave_sum((double)acc);
-        if ((thr & 63u) == 0) a.zout[(u64)tile * (blockDim.x >> 6) + (thr >> 6)] = tot;
+            const double tot = wave_sum((double)(flip ? -acc : acc));
+            if ((thr & 63u) == 0) a.zout[at] = tot;
+        }
         if (a.nostore) return;
     }
     if (a.prio) __builtin_amdgcn_s_setprio(3);
@@ -1012,12 +1047,13 @@ __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* para
     if (gi >= groups) return;
     const int lane = threadIdx.x & 63;
     const int per = c.n_layers * c.n, seg = period > 0 ? period : per;
-    const int per_seg = (seg + kMatGroup - 1) / kMatGroup, per_table = starts ? n_starts : per_seg * (per / seg);
+    const int per_seg = starts ? n_starts : (seg + kMatGroup - 1) / kMatGroup, per_table = per_seg * (per / seg);
     const u64 sample = gi / (u64)per_table;
     const int gt = (int)(gi % (u64)per_table);
-    const int in_seg = (gt % per_seg) * kMatGroup + lane;
-    const int pos = starts ? starts[gt] + lane : (gt / per_seg) * seg + in_seg;
-    const bool live = starts ? pos < starts[gt + 1] : in_seg < seg;
+    const int in_seg = (starts ? starts[gt % per_seg] : (gt % per_seg) * kMatGroup) + lane;
+    const int seg_end = starts ? starts[gt % per_seg + 1] : seg;
+    const int pos = (gt / per_seg) * seg + in_seg;
+    const bool live = in_seg < seg_end;
     const int lq = !live ? -1 : order ? ordered(order, period, pos) : pos;
     int top = lq;
 #pragma unroll
@@ -1025,7 +1061,7 @@ __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* para
     const bool whole = !starts && (kind == MatForm::plain || lq == top), matrix = whole || kind == MatForm::phaseless;
     Cx g = {1.0, 0.0};
     M2 u;
-    float* o = out + (sample * (u64)(per + (starts ? n_starts : 0)) + (u64)(pos + (starts ? gt : 0))) * 8;
+    float* o = out + (sample * (u64)(per + (starts ? per_table : 0)) + (u64)(pos + (starts ? gt : 0))) * 8;
     if (live) {
         u = fused_raw(c, params, feats, sample, lq / c.n, lq % c.n, -1, 0.0, matrix ? inverse : 0);
         if (!matrix) g = factor_m(u, inverse, seq0, seq_stride, o);
@@ -1045,10 +1081,17 @@ __global__ __launch_bounds__(256) void k_build_mats(CircDev c, const float* para
         f = (lane & d) ? mul_c(other, f) : mul_c(f, other);   // the same product in every lane
     }
     if (starts) {
-        if (live && pos + 1 == starts[gt + 1]) {
+        if (live && in_seg + 1 == seg_end) {
             float4* own = reinterpret_cast<float4*>(o + 8);
             own[0] = make_float4((float)f.r, (float)f.i, 0.f, 0.f);
             own[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (scale && kind == MatForm::direct) {      // what rounding the scalar has changed it by
+                const double m2 = f.r * f.r + f.i * f.i;
+                const Cx x = mul_c({(double)(float)f.r, (double)(float)f.i}, {f.r / m2, -f.i / m2});
+                double* to = scale + (sample * (u64)per_table + (u64)gt) * 2;
+                to[0] = x.r;
+                to[1] = x.i;
+            }
         }
         if (kind != MatForm::paired) return;
         const double own = g.r * g.r + g.i * g.i;
@@ -1102,18 +1145,29 @@ __global__ __launch_bounds__(256) void k_build_shifted(CircDev c, const float* p
     store_m(u, out + idx * 8);
 }
 
-// What a shifted unitary of the layer is more than the unshifted one: R_last .. R_s(t +- pi/2) .. R_0 = S U with
-// S = V R_s(+-pi/2) V^dagger, V the slots after s (never the re-upload slot: S is the same for every sample).
-__global__ __launch_bounds__(256) void k_build_shifts(CircDev c, const float* params, u64 count, float* out) {
+// Turns of a layer's angles by pi: R_last .. R_s(t + pi) .. R_0 = U S with S = W^dagger R_s(pi) W, W the slots before s, or
+// (behind) S U with S = V R_s(pi) V^dagger, V the slots after s.  S = -i (x X + y Y + z Z), whose float32 numbers have
+// columns of exactly equal length at right angles.
+__global__ __launch_bounds__(256) void k_build_turns(CircDev c, const float* params, const float* feats, u64 count, int behind,
+                                                     float* out) {
     const u64 idx = (u64)blockIdx.x * 256 + threadIdx.x;
     if (idx >= count) return;
-    const int slots = c.reupload + c.n_rot, v = (int)(idx % (2ull * slots * c.n)), p = v >> 1, q = p % c.n, s = p / c.n;
-    M2 m = rot_m(axis_of(c, s), (v & 1) ? -1.57079632679489661923 : 1.57079632679489661923);
-    for (int sl = s + 1; sl < slots; ++sl) {
-        const double t = (double)params[(u64)sl * c.n + q];
-        m = mul_m(mul_m(rot_m(axis_of(c, sl), t), m), rot_m(axis_of(c, sl), -t));
-    }
-    store_m(m, out + idx * 8);
+    const int slots = c.reupload + c.n_rot, per = slots * c.n, p = (int)(idx % (u64)per), q = p % c.n, s = p / c.n;
+    auto rot = [&](int sl, double sign) {
+        double t = (double)params[(u64)sl * c.n + q];
+        if (c.reupload && sl == 0) t *= (double)feats[idx / (u64)per * c.n + q];
+        return rot_m(axis_of(c, sl), sign * t);
+    };
+    M2 m = rot_m(axis_of(c, s), 3.14159265358979323846);
+    if (behind)
+        for (int sl = s + 1; sl < slots; ++sl) m = mul_m(mul_m(rot(sl, 1.0), m), rot(sl, -1.0));
+    else
+        for (int sl = s - 1; sl >= 0; --sl) m = mul_m(mul_m(rot(sl, -1.0), m), rot(sl, 1.0));
+    M2 o;                                            // equal and vanishing entries exactly so
+    const double x = -m.i[1], y = m.r[2], z = m.i[3];
+    o.r[0] = 0.0; o.i[0] = -z; o.r[1] = -y; o.i[1] = -x;
+    o.r[2] = y; o.i[2] = -x; o.r[3] = 0.0; o.i[3] = z;
+    store_m(o, out + idx * 8);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1399,6 +1453,39 @@ __global__ __launch_bounds__(256) void k_zsum_finish(const double* partial, u64 
     for (u64 i = 0; i < per_row; ++i) acc += p[i];
     const u64 gid = (u64)sc.row0 + r;
     out[(gid / (u64)sc.per) * (u64)sc.stride + (u64)sc.offset + gid % (u64)sc.per] = acc;
+}
+
+// ... of turned rows (see launch_turned_finish), two results a row: a wavefront per row.
+struct TurnedArgs { Scatter sc; u64 unturned_at; Residues ra, rb1, rb2; int rowdep; };
+
+__global__ __launch_bounds__(256) void k_turned_finish(const double* partial, u64 rows, u64 per_row, double* out, TurnedArgs t) {
+    const u64 r = (u64)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= rows) return;
+    const double* p = partial + r * per_row * 3;
+    double zb = 0.0, cr = 0.0, ci = 0.0;
+    for (u64 i = threadIdx.x & 63u; i < per_row; i += 64) { zb += p[3 * i]; cr += p[3 * i + 1]; ci += p[3 * i + 2]; }
+    zb = wave_sum(zb);
+    cr = wave_sum(cr);
+    ci = wave_sum(ci);
+    const u64 gid = (u64)t.sc.row0 + r, sample = gid / (u64)t.sc.per;
+    // conj(a) b of the exact states is c / d, d = conj(ra) rb: a lane multiplies every 64th entry
+    Cx d = {1.0, 0.0};
+    auto take = [&](const Residues& res, double sign) {
+        const double* e = res.table + ((t.rowdep ? sample * (u64)res.stride : 0) + (u64)res.first) * 2;
+        for (int k = (int)(threadIdx.x & 63u); k < res.count; k += 64) d = mul_c(d, {e[2 * k], sign * e[2 * k + 1]});
+    };
+    take(t.ra, -1.0);
+    take(t.rb1, 1.0);
+    take(t.rb2, 1.0);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) d = mul_c(d, {__shfl_xor(d.r, o, 64), __shfl_xor(d.i, o, 64)});
+    if (threadIdx.x & 63u) return;
+    const double cross = (cr * d.r + ci * d.i) / (d.r * d.r + d.i * d.i);
+    double* o = out + sample * (u64)t.sc.stride;
+    const double half = 0.5 * (o[t.unturned_at] + zb);
+    o += (u64)t.sc.offset + gid % (u64)t.sc.per * 2;
+    o[0] = half + cross;
+    o[1] = half - cross;
 }
 
 // Copies each row's starting state from the per-sample source (16 bytes per lane and step).
@@ -3148,6 +3235,9 @@ hipError_t set_pass_attributes(int device) {
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14, false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, direct_lds_bytes(14));
     if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14, false, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, direct_lds_bytes(14));
+    if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pass_direct<14, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, direct_lds_bytes(14));
     if (e == hipSuccess && device >= 0 && device < 64) done[device] = true;
@@ -3166,7 +3256,8 @@ hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles
     if (planes != 1 && planes != 2) return hipErrorInvalidValue;
     if (tile == 14) planes = 1;   // the largest tile exists with one plane only
     const dim3 grid((unsigned)n_tiles);
-    if (!a.direct && a.gather) return hipErrorInvalidValue;
+    if (!a.direct && (a.gather || a.unturned || a.turns)) return hipErrorInvalidValue;
+    if (a.unturned && (!a.zout || !a.nostore || a.imap)) return hipErrorInvalidValue;
     if (a.direct) {
         if (a.n < tile || a.n > kDirectMaxQubits || planes != 1 || a.w + tile - a.c > a.n || a.s_in < 0 || a.s_out < 0 ||
             a.s_in > tile - R || a.s_out > tile - R)
@@ -3175,7 +3266,9 @@ hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles
         const size_t bytes = (size_t)direct_lds_bytes(tile);
         switch (a.imap && a.gather ? -tile : tile) {
 #define QSV_DIRECT(T)                                                                         \
-    case T: hipLaunchKernelGGL((k_pass_direct<T, false>), grid, block, bytes, st, a); break;  \
+    case T: if (a.unturned) hipLaunchKernelGGL((k_pass_direct<T, false, true>), grid, block, bytes, st, a);  \
+            else hipLaunchKernelGGL((k_pass_direct<T, false>), grid, block, bytes, st, a);               \
+            break;                                                                                       \
     case -T: hipLaunchKernelGGL((k_pass_direct<T, true>), grid, block, bytes, st, a); break;
             QSV_DIRECT(10) QSV_DIRECT(11) QSV_DIRECT(12) QSV_DIRECT(13) QSV_DIRECT(14)
 #undef QSV_DIRECT
@@ -3252,14 +3345,14 @@ inline int seq_step(MatForm f) {
 hipError_t launch_build_mats(const CircDev& c, const float* params, const float* feats, int64_t samples, int inverse,
                              const int* order, int period, const int* starts, int n_starts, MatForm form, float* out,
                              double* scale, hipStream_t st) {
-    if (period < 0 || (period > 0 && (period != c.n || starts)) || (starts && (n_starts < 1 || !order)) ||
+    if (period < 0 || (period > 0 && period != c.n) || (starts && (n_starts < 1 || !order)) ||
         (form == MatForm::paired && !(scale && starts)))
         return hipErrorInvalidValue;
     const u64 tables = (u64)(c.reupload ? samples : 1);
     const u64 per = (u64)c.n_layers * c.n;
     if (tables * per == 0) return hipSuccess;
     const u64 seg = period > 0 ? (u64)period : per;
-    const u64 groups = tables * (starts ? (u64)n_starts : (per / seg) * ((seg + kMatGroup - 1) / kMatGroup));
+    const u64 groups = tables * (per / seg) * (starts ? (u64)n_starts : (seg + kMatGroup - 1) / kMatGroup);
     hipLaunchKernelGGL(k_build_mats, dim3(blocks_for(groups, 4)), dim3(256), 0, st, c, params, feats, groups, inverse,
                        order, period, starts, n_starts, form, seq_first(form), seq_step(form), out, scale);
     return hipGetLastError();
@@ -3270,19 +3363,17 @@ hipError_t launch_build_shifted(const CircDev& c, const float* params, const flo
     const u64 two_p = 2ull * c.n_layers * c.slots() * c.n;
     const u64 count = (u64)(c.reupload ? samples : 1) * two_p;
     if (count == 0) return hipSuccess;
-    if (scale && !exec_of) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_build_shifted, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params,
-                       feats, count, exec_of, scale, per, out);
+    hipLaunchKernelGGL(k_build_shifted, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params, feats, count,
+                       exec_of, scale, per, out);
     return hipGetLastError();
 }
 
-// ||x_b|| of every sample: inv_norm [samples] (0 for a zero vector), norm_out optional.  One launch
-// when a sample fits one block, else block partials and a finishing launch.
-hipError_t launch_build_shifts(const CircDev& c, const float* params, int64_t samples, float* out, hipStream_t st) {
-    const u64 count = (u64)(c.reupload ? samples : 1) * 2ull * c.slots() * c.n;
+hipError_t launch_build_turns(const CircDev& c, const float* params, const float* feats, int64_t samples, int behind,
+                              float* out, hipStream_t st) {
+    const u64 count = (u64)(c.reupload ? samples : 1) * c.slots() * c.n;
     if (c.n_layers != 1) return hipErrorInvalidValue;
     if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_build_shifts, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params, count, out);
+    hipLaunchKernelGGL(k_build_turns, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params, feats, count, behind, out);
     return hipGetLastError();
 }
 
@@ -3440,6 +3531,16 @@ hipError_t launch_zsum_finish(const double* partial, int64_t rows, int64_t per_r
     if (rows < 1 || per_row < 1 || sc.per < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_zsum_finish, dim3(blocks_for((u64)rows, 256)), dim3(256), 0, st, partial, (u64)rows,
                        (u64)per_row, out, sc);
+    return hipGetLastError();
+}
+
+hipError_t launch_turned_finish(const double* partial, int64_t rows, int64_t per_row, double* out, const Scatter& sc,
+                                int64_t unturned_at, const Residues& ra, const Residues& rb1, const Residues& rb2, int rowdep,
+                                hipStream_t st) {
+    if (rows < 1 || per_row < 1 || sc.per < 1) return hipErrorInvalidValue;
+    const TurnedArgs t{sc, (u64)unturned_at, ra, rb1, rb2, rowdep};
+    hipLaunchKernelGGL(k_turned_finish, dim3(blocks_for((u64)rows, 4)), dim3(256), 0, st, partial, (u64)rows,
+                       (u64)per_row, out, t);
     return hipGetLastError();
 }
 

@@ -43,10 +43,12 @@ inline SumAxes sum_axes(const qsv_circuit& c) {
 }
 
 // Lowers one operation list (a pass: OP_LOAD ... OP_END) onto out; false if it holds something the direct
-// interpreter has no code for (never planned for tiles of one row).  shifts: some row may replace a matrix.
+// interpreter has no code for (never planned for tiles of one row).  rows: what gradient rows may do to a unitary.
 // sums (the paired interpreter): the sums to be taken.  groups: Plan::groups, NULL or empty: the scalars are in the matrices.
+enum class Rows { none, replace, turn };   // replace its matrix, or multiply by another before it
+
 template <class Code>
-bool lower_pass_as(const Op* ops, int count, bool shifts, const SumAxes& sums, const std::vector<int32_t>* groups,
+bool lower_pass_as(const Op* ops, int count, Rows rows, const SumAxes& sums, const std::vector<int32_t>* groups,
                    DirectPlan* out) {
     constexpr bool pair = std::is_same<Code, paired>::value;
     const bool scaled = groups && !groups->empty();
@@ -83,9 +85,9 @@ bool lower_pass_as(const Op* ops, int count, bool shifts, const SumAxes& sums, c
                     dp.first_u = o.arg;
                     dp.first_mat = o.arg + (scaled ? group_of(o.arg) : 0);
                 }
-                if (scaled && (o.c || shifts)) return false;
+                if (scaled ? o.c || rows == Rows::replace : rows == Rows::turn) return false;
                 if constexpr (pair) {
-                    if (sums.count < 1 || shifts || o.c) return false;
+                    if (sums.count < 1 || o.c) return false;
                     if (sums.count == 2) put(Code::kBefore[o.a][sums.axis[1]], 0);
                     put(Code::kU[o.a], (uint32_t)o.arg);
                     put(sums.count == 1   ? Code::kSum1[o.a][sums.axis[0]]
@@ -93,15 +95,17 @@ bool lower_pass_as(const Op* ops, int count, bool shifts, const SumAxes& sums, c
                                           : Code::kSum3[o.a],
                         0);
                 } else {
-                    put(o.c ? (shifts ? Code::kGShift[o.a] : Code::kG[o.a]) : (shifts ? Code::kUShift[o.a] : Code::kU[o.a]),
+                    put(rows == Rows::replace ? (o.c ? Code::kGShift : Code::kUShift)[o.a]
+                        : rows == Rows::turn  ? Code::kUTurn[o.a]
+                                              : (o.c ? Code::kG : Code::kU)[o.a],
                         (uint32_t)o.arg);
                 }
                 if (scaled && (*groups)[group_of(o.arg) + 1] == o.arg + 1) put(Code::kScale, 0);
                 break;
-            case OP_SHIFT:
-                if (o.a > 3 || shifts) return false;
+            case OP_TURN:
+                if (o.a > 3) return false;
                 if constexpr (pair) return false;
-                else put(Code::kShift[o.a], (uint32_t)o.arg);
+                else put(Code::kTurn[o.a], (uint32_t)o.arg);
                 break;
             case OP_CX_REG:
                 if (o.a > 3 || o.b > 3 || o.a == o.b) return false;
@@ -149,17 +153,17 @@ bool lower_pass_as(const Op* ops, int count, bool shifts, const SumAxes& sums, c
     return s >= 0 && !out->ops.empty() && out->ops.back().code == Code::kEnd;
 }
 
-inline bool lower_pass(const Op* ops, int count, bool shifts, DirectPlan* out) {
-    return lower_pass_as<direct>(ops, count, shifts, SumAxes(), nullptr, out);
+inline bool lower_pass(const Op* ops, int count, DirectPlan* out) {
+    return lower_pass_as<direct>(ops, count, Rows::none, SumAxes(), nullptr, out);
 }
 
 // sums: a mirrored plan for the paired interpreter, which takes the transition sums of its unitaries on the way.
-inline bool lower_plan(const Plan& p, bool shifts, DirectPlan* out, const SumAxes* sums = nullptr) {
+inline bool lower_plan(const Plan& p, Rows rows, DirectPlan* out, const SumAxes* sums = nullptr) {
     for (const Pass& ps : p.passes) {
         if (ps.w + ps.t - ps.c > p.n) return false;
         const Op* ops = p.ops.data() + ps.op_begin;
-        if (!(sums ? lower_pass_as<paired>(ops, ps.op_count, shifts, *sums, &p.groups, out)
-                   : lower_pass_as<direct>(ops, ps.op_count, shifts, SumAxes(), &p.groups, out)))
+        if (!(sums ? lower_pass_as<paired>(ops, ps.op_count, Rows::none, *sums, &p.groups, out)
+                   : lower_pass_as<direct>(ops, ps.op_count, rows, SumAxes(), &p.groups, out)))
             return false;
         // the table is read front to back
         int next = out->passes.back().first_u;

@@ -685,14 +685,13 @@ void group_by_passes(Plan* p) {
     p->groups.push_back(at);
 }
 
-void shift_first_layer(Plan* p) {
+void turn_first_layer(Plan* p) {
     std::vector<int32_t> order;
     for (Op& o : p->ops) {
         if (o.kind != OP_U) continue;
         const int32_t id = p->mat_order[o.arg];
-        o.c = 0;
         if (id < p->n) {
-            o.kind = OP_SHIFT;
+            o.kind = OP_TURN;
             o.arg = id;
         } else {
             o.arg = (int32_t)order.size();
@@ -701,7 +700,6 @@ void shift_first_layer(Plan* p) {
     }
     p->mat_order.swap(order);
     p->n_mats -= p->n;
-    mark_groups(*p);
 }
 
 std::string describe_plan(const Plan& p) {
@@ -728,7 +726,7 @@ std::string describe_plan(const Plan& p) {
                 case OP_CX_CHAIN: snprintf(buf, sizeof buf, " C%c%d:%d", o.c ? 'd' : 'u', o.a, o.b); break;
                 case OP_CX_PAR: snprintf(buf, sizeof buf, " Q%d:%d:%x", o.a, o.b, (unsigned)o.arg); break;
                 case OP_CX_LANE: snprintf(buf, sizeof buf, " N%d:%d:%d", o.a, o.b, o.c); break;
-                case OP_SHIFT: snprintf(buf, sizeof buf, " S%d:%d", o.a, o.arg); break;
+                case OP_TURN: snprintf(buf, sizeof buf, " S%d:%d", o.a, o.arg); break;
                 default: snprintf(buf, sizeof buf, " ?"); break;
             }
             s += buf;

@@ -48,8 +48,8 @@ enum OpKind : uint8_t {
                     // lane number: the eight amplitudes with the control set are exchanged with the
                     // partner lane's (DPP for b < 2, ds_bpermute above); c = the target qubit (for the
                     // description only)
-    OP_SHIFT = 13,  // a = register bit j, arg = qubit behind it: the matrix that a gradient row which shifts this qubit
-                    // multiplies by, nothing in other rows (see shift_first_layer)
+    OP_TURN = 13,   // a = register bit j, arg = qubit behind it: the matrix that a gradient row which turns an angle of
+                    // this qubit multiplies by, nothing in other rows (see turn_first_layer)
     OP_CX_DEFER = 11 // never part of an operation list: a CNOT that the pass's index map carries (see
                     // Plan::defers); a = target qubit, b = control qubit, arg = the control's bit set
 };
@@ -121,13 +121,14 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
 // layers: 31 passes planned directly against 21 forwards; 26 qubits, 30 layers: 52 against 50).
 Plan mirror_plan(const Plan& forward);
 
-// Groups (see Plan::groups) that end with their pass, so that the states between the passes lack no scalars: a reverse-mode
-// sweep keeps them.  It costs 64 vector instructions a wavefront and pass, beside about twenty unitaries of 60.
+// Groups (see Plan::groups) that end with their pass, so that the states between the passes lack no scalars (a reverse-mode
+// sweep keeps them), and that round no matrix (whose columns then differ in length by about 3e-8, which shows where states
+// of different plans are combined).  It costs 64 vector instructions a wavefront and pass, beside about twenty unitaries of 60.
 void group_by_passes(Plan* p);
 
-// Turns the first layer's unitaries into OP_SHIFT: the plan then starts from states that have the layer's rotations
+// Replaces the first layer's unitaries by OP_TURN: the plan then starts from states that have the layer's rotations
 // behind them.  The unitaries that are left are numbered anew, and mat_order counts layers from the second one on.
-void shift_first_layer(Plan* p);
+void turn_first_layer(Plan* p);
 
 std::string describe_plan(const Plan& p);
 

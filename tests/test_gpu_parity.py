@@ -1409,24 +1409,30 @@ def test_reverse_mode_sweep_in_a_graph():
         ctx.close()
 
 
-@pytest.mark.parametrize("n,B,L,rot,ent,reup,opts", [
-    (10, 220, 2, (RY, RZ), RING, 0, {}),                        # a wavefront a tile
-    (11, 70, 3, (RX, RY, RZ), LADDER, 0, {}),
-    (12, 33, 2, (RZ, RY), RING, 1, {"grad_chunk_rows": 700}),   # re-uploading; chunks that end inside a sample's rows
-    (13, 20, 3, (RX,), LADDER, 1, {}),
-    (14, 10, 2, (RY, RX), RING, 0, {"tile_log2": 10}),          # several passes, halves on two streams
-    (14, 6, 1, (RZ, RX, RY), NONE, 1, {}),                      # nothing but shifts is left of the circuit
+@pytest.mark.parametrize("ahead,n,B,L,rot,ent,reup,opts", [
+    (1, 10, 1640, 2, (RY, RZ), RING, 0, {}),                    # a wavefront a tile
+    (1, 11, 500, 2, (RX, RY, RZ), LADDER, 0, {}),
+    (1, 12, 230, 2, (RZ, RY), RING, 1, {"grad_chunk_rows": 700}),   # re-uploading; chunks that end inside a sample's rows
+    (1, 13, 158, 2, (RX,), LADDER, 1, {}),
+    (1, 14, 74, 2, (RY, RX), RING, 0, {"tile_log2": 10}),       # several passes, halves on two streams
+    (1, 14, 37, 1, (RZ, RX, RY), NONE, 1, {}),                  # nothing but turns is left of the circuit
+    (0, 10, 30, 3, (RY, RZ), RING, 0, {}),
+    (0, 11, 9, 9, (RX, RY, RZ), LADDER, 1, {}),                 # 99 unitaries: two groups in a pass
+    (0, 12, 6, 2, (RZ, RX), RING, 0, {"grad_chunk_rows": 7}),
+    (0, 14, 3, 3, (RY,), LADDER, 1, {"tile_log2": 11, "split_streams": 1}),
+    (0, 16, 2, 2, (RX, RZ), RING, 0, {}),
 ])
-def test_shift_rule_from_states_behind_the_layers_rotations(oracle, n, B, L, rot, ent, reup, opts):
-    """Batches large enough that the shifted circuits start behind their layer's rotations: against whole circuits and against
-    the oracle on the first sample.  A difference of two expectation values, each with the rounding of L (slots) n gates."""
+def test_shift_rule_from_one_circuit_per_parameter(oracle, ahead, n, B, L, rot, ent, reup, opts):
+    """Batches large enough for one circuit per parameter (2^19 amplitudes a layer), and for starting behind its layer's
+    rotations (ahead: 2^25): against whole circuits, two per parameter, and against the oracle on the first sample.  A
+    difference of two expectation values, each with the rounding of L (slots) n gates."""
     torch = gu.torch_cuda()
     spec = wl.CircuitSpec(L, rot, ent, reup)
     g = rng(17 * n + B)
     P = spec.num_params(n)
     x, p, f = (a.astype(np.float32) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P), g.standard_normal((B, n))))
     circ = qb.circuit_from_spec(spec)
-    assert (2 * P // L * B) << n >= 1 << 23
+    assert ((P // L * B) << n >= 1 << 25) == bool(ahead) and (P // L * B) << n >= 1 << 19
     ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
     for k, v in opts.items():
         ctx.qsv_set_option(k, v)
