@@ -815,15 +815,7 @@ qsv_status qsv_amp_encode(qsv_ctx* ctx, const float* x_dev, int64_t dim, float* 
     double* partial = (double*)ar.take((size_t)ctx->batch * nblk * 8);
     double* inv = (double*)ar.take((size_t)ctx->batch * 8);
     if (!partial || !inv) return ws_fail(ctx, ar, "qsv_amp_encode");
-    if (dim <= 4096 && ctx->n <= 12) {     // a block covers a sample: one launch
-        QSV_HIP(ctx, launch_encode_small(x_dev, ctx->batch, dim, ctx->n, inv, norm_out_dev, ctx->state, ctx->stream),
-                "encode");
-        return QSV_OK;
-    }
-    QSV_HIP(ctx, launch_norms(x_dev, ctx->batch, dim, partial, nblk, inv, norm_out_dev, ctx->stream), "norms");
-    QSV_HIP(ctx, launch_encode_write(x_dev, dim, ctx->n, ctx->batch, inv, plain_rows(ctx->n), ctx->state,
-                                     ctx->stream),
-            "encode");
+    QSV_HIP(ctx, launch_encode(x_dev, ctx->batch, dim, ctx->n, partial, nblk, inv, norm_out_dev, ctx->state, ctx->stream), "encode");
     return QSV_OK;
 }
 
@@ -897,12 +889,12 @@ static qsv_status measure_impl(qsv_ctx* ctx, const qsv_measure_req* req, Arena& 
             if (req->kind == QSV_M_EXPZ_ONE && (q < 0 || q >= n))
                 return fail(ctx, QSV_ERR_INVALID_ARG, "qubit out of range");
             if ((st = bind_device(ctx)) != QSV_OK) return st;
-            if (chunk_blocks(n) == 1) {           // a row is one chunk: no partial sums to combine
+            double* partial = n > 12 ? (double*)ar.take((size_t)B * chunk_blocks(n) * 13 * 8) : nullptr;
+            if (n > 12 && !partial) return ws_fail(ctx, ar, "qsv_measure(EXPZ)");
+            if (expz_in_one_launch(n, B)) {       // a block has a row: no partial sums to combine
                 QSV_HIP(ctx, launch_expz_small(ctx->state, B, n, q, (float*)req->out_dev, ctx->stream), "expz");
                 return QSV_OK;
             }
-            double* partial = (double*)ar.take((size_t)B * chunk_blocks(n) * 13 * 8);
-            if (!partial) return ws_fail(ctx, ar, "qsv_measure(EXPZ)");
             QSV_HIP(ctx, launch_expz_block(ctx->state, B, n, partial, ctx->stream), "expz block");
             QSV_HIP(ctx, launch_expz_finish(partial, B, n, q, (float*)req->out_dev, nullptr, ctx->stream),
                     "expz finish");
@@ -1134,7 +1126,6 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     float* ovr = (float*)ar.take(msamples * (size_t)(2 * P) * 32);
     double* f = (double*)ar.take((size_t)circuits * 8);
     if (!npart || !inv || !mats || !ovr || !f) return ws_fail(ctx, ar, "qsv_param_shift_grad");
-    QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
 
     // a chunk of circuit states plus their reduction partials, sized to what is left of the workspace
     const size_t row_bytes = state_bytes + (size_t)chunk_blocks(n) * 13 * 8 + 2 * kAlign;
@@ -1183,7 +1174,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         qsv_circuit one = *c;
         one.n_layers = 1;
         // unshifted circuit, one layer at a time: ck(l) = state of every sample before layer l
-        QSV_HIP(ctx, launch_encode_write(x_dev, dim, n, B, inv, plain_rows(n), ck(0), ctx->stream), "encode");
+        QSV_HIP(ctx, launch_encode(x_dev, B, dim, n, npart, nblk, inv, nullptr, ck(0), ctx->stream), "encode");
         RowMap rm_fwd;    // rows are the samples: the first pass of layer l reads state l and writes state l + 1
         rm_fwd.grad = 1; rm_fwd.two_p = 0; rm_fwd.per = 1; rm_fwd.row0 = 0;
         rm_fwd.slots_n = slots_n < 1 ? 1 : slots_n; rm_fwd.n = n;
@@ -1267,6 +1258,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     }
 
     // ---- every shifted circuit whole
+    QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
     const int64_t chunk = chunk_rows(circuits);
     if (chunk < 1) { ar.need = ar.off + row_bytes; return ws_fail(ctx, ar, "qsv_param_shift_grad"); }
     float2* states = (float2*)ar.take((size_t)chunk * state_bytes);
@@ -1425,7 +1417,6 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
                 "build matrices");
         return QSV_OK;
     };
-    QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
     qsv_status st = table(fp, 0, MatForm::direct, fmats, nullptr);
     if (st == QSV_OK) st = table(bp, 1, MatForm::paired, bmats, corr);
     if (st != QSV_OK) return st;
@@ -1436,7 +1427,9 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
         auto state = [&](size_t k) { return sc.psi + k * (size_t)chunk * amps; };   // 0: encoded; k: after pass k - 1
         RowMap rm;
         rm.grad = 1; rm.two_p = 0; rm.per = 1; rm.row0 = b0; rm.slots_n = 1; rm.n = n;
-        QSV_HIP(ctx, launch_encode_write(x_dev, dim, n, rows, inv, rm, state(0), ctx->stream), "encode rows");
+        QSV_HIP(ctx, launch_encode(x_dev + (size_t)b0 * dim, rows, dim, n, npart + (size_t)b0 * nblk, nblk, inv + b0, nullptr,
+                                   state(0), ctx->stream),
+                "encode rows");
         const uint64_t touched = ((uint64_t)rows << n) * 16;
         const int nt = ctx->opt_nt_store >= 0 ? ctx->opt_nt_store : (touched >= kNtStoreBytes ? 1 : 0);
         for (size_t k = 0; k < passes; ++k) {

@@ -167,9 +167,11 @@ hipError_t launch_build_turns(const CircDev& c, const float* params, const float
 // encoding
 hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* partial, int nblk,
                         double* inv_norm, float* norm_out, hipStream_t st);
-// norm and state rows of small samples (dim <= 4096, n <= 12) in one launch; inv_norm receives 1/||x_b||
-hipError_t launch_encode_small(const float* x, int64_t samples, int64_t dim, int n, double* inv_norm, float* norm_out,
-                               float2* state, hipStream_t st);
+// Norms and state rows: inv_norm receives 1/||x_b||, norm_out (may be NULL) ||x_b||; partial: samples * nblk doubles.
+// k_norm_finish goes where a state has at most so many amplitudes (k_encode_write has both sides)
+constexpr uint64_t kEncodeFolded = 1ull << 20;
+hipError_t launch_encode(const float* x, int64_t samples, int64_t dim, int n, double* partial, int nblk, double* inv_norm,
+                         float* norm_out, float2* state, hipStream_t st);
 // A whole small workload in one launch: encoding, circuit (decode = 1: followed by its inverse), final
 // state, and the measurement `kind` (QSV_M_PROBS or QSV_M_EXPZ_ALL).  A thread keeps 2^regs amplitudes
 // (regs = 2, 3 or 4), the other index bits are bits of the thread number (at most 8: 256 threads); with
@@ -254,7 +256,8 @@ hipError_t launch_encode_write(const float* x, int64_t dim, int n, int64_t rows,
 hipError_t launch_probs(const float2* state, uint64_t total, float* out, hipStream_t st);
 // partial: rows * max(1, 2^n / 4096) * 13 doubles or fewer; the finishing kernels take the same rows and n
 hipError_t launch_expz_block(const float2* state, int64_t rows, int n, double* partial, hipStream_t st);
-// rows of at most 4096 amplitudes: <Z_q> of every qubit (q_only < 0) or of q_only in one launch
+// <Z_q> of every qubit (q_only < 0) or of q_only in one launch, where a row is a block's work
+bool expz_in_one_launch(int n, int64_t rows);
 hipError_t launch_expz_small(const float2* state, int64_t rows, int n, int q_only, float* out_f, hipStream_t st);
 hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,
                               double* out_d, hipStream_t st);

@@ -1230,14 +1230,34 @@ __global__ __launch_bounds__(256) void k_norm_finish(const double* partial, int 
     }
 }
 
-__global__ __launch_bounds__(256) void k_encode_write(const float* x, u64 dim, int n, u64 total,
-                                                      const double* inv_norm, RowMap rm,
-                                                      float2* state) {
+// FOLDED: every block adds up the sums of k_sumsq ([samples][nblk]) of its row again, in one order, and the row's first
+// block writes the norm.  It saves k_norm_finish, a launch between two that wait for it: 19 qubits 7.2 -> 6.5 us, 16 x 4
+// 7.1 -> 6.1, 20 qubits 8.5 -> 7.9.  From 2^22 amplitudes the wait in every block costs more than the launch (16 x 64
+// 17.5 -> 17.9, 16 x 1024 224 -> 272): inv_norm is then read.
+template <bool FOLDED>
+__global__ __launch_bounds__(256) void k_encode_write(const float* x, u64 dim, int n, u64 total, const double* partial,
+                                                      int nblk, double* inv_norm, float* norm_out, RowMap rm, float2* state) {
+    __shared__ double sm[4];
     const u64 e2 = ((u64)blockIdx.x * 256 + threadIdx.x) * 2;
+    if constexpr (FOLDED) {                                 // rows of 512 amplitudes and more: a block lies in one row
+        const u64 first = (u64)blockIdx.x * 512, sample = row_ctx(rm, first >> n).sample;
+        double acc = 0.0;
+        for (int i = threadIdx.x; i < nblk; i += 256) acc += partial[sample * (u64)nblk + i];
+        const double nrm = sqrt(block_sum256(acc, sm)), inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            sm[0] = inv;
+            if ((first & ((1ull << n) - 1)) == 0) {
+                inv_norm[sample] = inv;
+                if (norm_out) norm_out[sample] = (float)nrm;
+            }
+        }
+        __syncthreads();
+    }
     if (e2 >= total) return;
     const u64 row = e2 >> n;
     const u64 sample = row_ctx(rm, row).sample;
-    const double inv = inv_norm[sample];
+    const double inv = FOLDED ? sm[0] : inv_norm[sample];
     const u64 k = e2 & ((1ull << n) - 1);
     const float* xb = x + sample * dim;
     float4 o;
@@ -1248,8 +1268,7 @@ __global__ __launch_bounds__(256) void k_encode_write(const float* x, u64 dim, i
     *reinterpret_cast<float4*>(state + e2) = o;
 }
 
-// Small samples (one block covers a sample): norm and state row in one launch.  Same arithmetic as
-// k_sumsq + k_encode_write, so the bits are the same.
+// Samples of up to 2^7 entries: norm and state row in one launch.
 __global__ __launch_bounds__(256) void k_encode_small(const float* x, u64 rows, u64 dim, int n, double* inv_norm,
                                                       float* norm_out, float2* state) {
     __shared__ double sm[4];
@@ -1268,6 +1287,63 @@ __global__ __launch_bounds__(256) void k_encode_small(const float* x, u64 rows, 
     float2* row = state + (b << n);
     for (u64 k = threadIdx.x; k < (1ull << n); k += 256)
         row[k] = make_float2(k < dim ? (float)((double)xb[k] * inv) : 0.f, 0.f);
+}
+
+// A workgroup per sample of 4 THREADS V = 2^n entries, which stay in registers between the sum of their squares and the
+// state row: one read of x and one launch instead of two or three.  Bound by the latency of a load, a reduction and a store
+// where samples are few, by memory where they are many (15 x 4096: 310 us, 5.2 TB/s).  Before and after: 12 qubits 6.2 -> 2.9
+// us, 12 x 4096 41.7 -> 33.0, 13 6.1 -> 3.5, 13 x 256 11.0 -> 6.9, 14 6.2 -> 4.6, 14 x 1024 47 -> 34.  15 qubits: 32
+// samples 8.8 -> 8.3, 256 27 -> 19, but 1 sample 6.2 -> 7.1, so few samples are spread over more blocks.  A form for 16
+// qubits gained at 256 samples (46 -> 41) and lost at 512 (93 -> 100).
+template <int THREADS, int V>
+__global__ __launch_bounds__(THREADS) void k_encode_row(const float* x, u64 rows, u64 dim, int n, double* inv_norm,
+                                                        float* norm_out, float2* state) {
+    __shared__ double sm[THREADS / 64];
+    const u64 b = grid_row();
+    if (b >= rows) return;
+    const float* xb = x + b * dim;
+    const unsigned t = threadIdx.x;
+    float4 v[V];
+    if ((dim & 3) == 0 && ((uintptr_t)x & 15) == 0) {
+        const float4* xv = reinterpret_cast<const float4*>(xb);
+        const u64 dimv = dim >> 2;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const u64 k = (u64)i * THREADS + t;
+            v[i] = k < dimv ? xv[k] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const u64 k = ((u64)i * THREADS + t) * 4;
+            v[i] = make_float4(k < dim ? xb[k] : 0.f, k + 1 < dim ? xb[k + 1] : 0.f, k + 2 < dim ? xb[k + 2] : 0.f,
+                               k + 3 < dim ? xb[k + 3] : 0.f);
+        }
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        acc += (double)v[i].x * v[i].x + (double)v[i].y * v[i].y + (double)v[i].z * v[i].z + (double)v[i].w * v[i].w;
+    double tot = wave_sum(acc);
+    if constexpr (THREADS > 64) {
+        if ((t & 63u) == 0) sm[t >> 6] = tot;
+        __syncthreads();
+        tot = 0.0;
+#pragma unroll
+        for (int w = 0; w < THREADS / 64; ++w) tot += sm[w];
+    }
+    const double nrm = sqrt(tot), inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+    if (t == 0) {
+        inv_norm[b] = inv;
+        if (norm_out) norm_out[b] = (float)nrm;
+    }
+    float4* row = reinterpret_cast<float4*>(state + (b << n));
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const u64 k = ((u64)i * THREADS + t) * 2;
+        row[k] = make_float4((float)((double)v[i].x * inv), 0.f, (float)((double)v[i].y * inv), 0.f);
+        row[k + 1] = make_float4((float)((double)v[i].z * inv), 0.f, (float)((double)v[i].w * inv), 0.f);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1327,8 +1403,12 @@ __device__ __forceinline__ void expz_tree(const double (&p)[16], double& T, doub
 // are signs of the chunks' totals.  partial: [row][13 + g][nblk] doubles: T, index bits 0..11, then those.
 // One chunk per block and one reduction per chunk: 40 us on 24 qubits and 21 us for the finishing kernel,
 // which walked over 104-byte records; with 2048 blocks left and the entries side by side 24 + 10 us.
+// out (NULL: partials): the block has the whole row (nblk = 1) and writes <Z_q> itself, of every qubit or of q_only.  Rows
+// of 13 and 14 qubits, one launch instead of two: 13 qubits 6.0 -> 4.1 us, 13 x 256 8.6 -> 4.9, 14 6.0 -> 4.7, 14 x 1024
+// 28.7 -> 22.9.  15 and 16 qubits from 64 rows: 15 x 64 8.4 -> 6.4, 15 x 256 19.7 -> 13.0, 16 x 64 11.9 -> 9.8; with fewer
+// rows too few blocks work (16 x 16: 6.6 -> 8.9, 15 qubits 6.1 -> 6.2).
 __global__ __launch_bounds__(256) void k_expz_block(const float2* state, u64 rows, int n, int g, int nblk,
-                                                    double* partial) {
+                                                    double* partial, float* out, int q_only) {
     __shared__ double sm[4][15];
     const u64 row = grid_row();
     if (row >= rows) return;
@@ -1371,7 +1451,8 @@ __global__ __launch_bounds__(256) void k_expz_block(const float2* state, u64 row
     else if (e >= 13) from = 5 + e - 13;
     const double w0 = sm[0][from], w1 = sm[1][from], w2 = sm[2][from], w3 = sm[3][from];
     const double tot = sign == 1 ? (w0 - w1) + (w2 - w3) : sign == 2 ? (w0 + w1) - (w2 + w3) : (w0 + w1) + (w2 + w3);
-    partial[(row * (u64)(13 + g) + e) * (u64)nblk + blockIdx.x] = tot;
+    if (!out) partial[(row * (u64)(13 + g) + e) * (u64)nblk + blockIdx.x] = tot;
+    else if (e > 0 && (q_only < 0 || e - 1 == q_only)) out[q_only < 0 ? row * (u64)n + (e - 1) : row] = (float)tot;
 }
 
 // Rows of at most 4096 amplitudes: a wavefront per row, index = step * 128 + lane * 2 + {0, 1}, which writes the
@@ -3389,11 +3470,38 @@ hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* pa
     return hipGetLastError();
 }
 
-hipError_t launch_encode_small(const float* x, int64_t samples, int64_t dim, int n, double* inv_norm, float* norm_out,
-                               float2* state, hipStream_t st) {
-    if (dim > 4096 || n > 12) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_encode_small, rows_grid(1, (u64)samples), dim3(256), 0, st, x, (u64)samples, (u64)dim, n,
-                       inv_norm, norm_out, state);
+hipError_t launch_encode(const float* x, int64_t samples, int64_t dim, int n, double* partial, int nblk, double* inv_norm,
+                         float* norm_out, float2* state, hipStream_t st) {
+    const dim3 grid = rows_grid(1, (u64)samples);
+    switch (n) {
+#define QSV_ROW(THREADS, V) { hipLaunchKernelGGL((k_encode_row<THREADS, V>), grid, dim3(THREADS), 0, st, x, (u64)samples, (u64)dim, n, inv_norm, norm_out, state); return hipGetLastError(); }
+        case 8: QSV_ROW(64, 1);
+        case 9: QSV_ROW(128, 1);
+        case 10: QSV_ROW(256, 1);
+        case 11: QSV_ROW(256, 2);
+        case 12: QSV_ROW(256, 4);
+        case 13: QSV_ROW(1024, 2);
+        case 14: QSV_ROW(1024, 4);
+        case 15: if (samples >= 32) QSV_ROW(1024, 8); break;
+#undef QSV_ROW
+        default: break;
+    }
+    if (n < 8) {
+        hipLaunchKernelGGL(k_encode_small, grid, dim3(256), 0, st, x, (u64)samples, (u64)dim, n, inv_norm, norm_out, state);
+        return hipGetLastError();
+    }
+    const RowMap rm{0, 0, 1, 0, 1, n};
+    if (nblk == 1 || (u64)samples << n > kEncodeFolded) {
+        hipError_t e = launch_norms(x, samples, dim, partial, nblk, inv_norm, norm_out, st);
+        return e != hipSuccess ? e : launch_encode_write(x, dim, n, samples, inv_norm, rm, state, st);
+    }
+    hipLaunchKernelGGL(k_sumsq, rows_grid(nblk, (u64)samples), dim3(256), 0, st, x, (u64)samples, (u64)dim, partial, nblk,
+                       (double*)nullptr, (float*)nullptr);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const u64 total = (u64)samples << n;
+    hipLaunchKernelGGL((k_encode_write<true>), dim3(blocks_for(total / 2, 256)), dim3(256), 0, st, x, (u64)dim, n, total, partial, nblk,
+                       inv_norm, norm_out, rm, state);
     return hipGetLastError();
 }
 
@@ -3470,8 +3578,8 @@ hipError_t launch_sweep_small(const float* x, int64_t dim, int64_t batch, const 
 hipError_t launch_encode_write(const float* x, int64_t dim, int n, int64_t rows, const double* inv_norm,
                                const RowMap& rm, float2* state, hipStream_t st) {
     const u64 total = (u64)rows << n;
-    hipLaunchKernelGGL(k_encode_write, dim3(blocks_for(total / 2, 256)), dim3(256), 0, st, x, (u64)dim,
-                       n, total, inv_norm, rm, state);
+    hipLaunchKernelGGL((k_encode_write<false>), dim3(blocks_for(total / 2, 256)), dim3(256), 0, st, x, (u64)dim, n, total,
+                       (const double*)nullptr, 0, const_cast<double*>(inv_norm), (float*)nullptr, rm, state);
     return hipGetLastError();
 }
 
@@ -3503,11 +3611,18 @@ static hipError_t launch_expz_row(const float2* state, int64_t rows, int n, int 
 hipError_t launch_expz_block(const float2* state, int64_t rows, int n, double* partial, hipStream_t st) {
     if (n < CHUNK_BITS) return launch_expz_row(state, rows, n, -1, nullptr, partial, st);
     const int g = expz_group(n, rows), nblk = chunk_blocks(n) >> g;
-    hipLaunchKernelGGL(k_expz_block, rows_grid(nblk, (u64)rows), dim3(256), 0, st, state, (u64)rows, n, g, nblk, partial);
+    hipLaunchKernelGGL(k_expz_block, rows_grid(nblk, (u64)rows), dim3(256), 0, st, state, (u64)rows, n, g, nblk, partial,
+                       (float*)nullptr, -1);
     return hipGetLastError();
 }
+bool expz_in_one_launch(int n, int64_t rows) { return n <= 14 || (n <= 16 && rows >= 64); }
 hipError_t launch_expz_small(const float2* state, int64_t rows, int n, int q_only, float* out_f, hipStream_t st) {
-    if (chunk_blocks(n) != 1 || !out_f || q_only >= n) return hipErrorInvalidValue;
+    if (!expz_in_one_launch(n, rows) || !out_f || q_only >= n) return hipErrorInvalidValue;
+    if (n > CHUNK_BITS) {
+        hipLaunchKernelGGL(k_expz_block, rows_grid(1, (u64)rows), dim3(256), 0, st, state, (u64)rows, n, n - CHUNK_BITS, 1,
+                           (double*)nullptr, out_f, q_only);
+        return hipGetLastError();
+    }
     return launch_expz_row(state, rows, n, q_only, out_f, nullptr, st);
 }
 hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,

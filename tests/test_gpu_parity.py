@@ -1011,6 +1011,40 @@ def test_expz_at_every_grouping(n, B):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,B", [(13, 1), (14, 65), (15, 63), (15, 64), (16, 63), (16, 64)])
+def test_expz_of_rows_that_are_a_blocks_work(n, B):
+    test_expz_at_every_grouping(n, B)
+
+
+@pytest.mark.parametrize("n,B,dim,shift", [
+    (7, 3, 128, 0), (8, 2, 255, 1), (8, 5, 256, 0), (9, 3, 512, 1), (10, 3, 1021, 0), (11, 2, 2048, 0), (11, 2, 4, 0),
+    (12, 3, 4096, 2), (13, 2, 8192, 0), (13, 2, 5003, 0), (14, 2, 16384, 3), (14, 3, 9000, 0), (15, 31, 32768, 0),
+    (15, 32, 32768, 0), (15, 33, 32763, 0), (15, 2, 4000, 0), (16, 16, 65536, 0), (16, 17, 65536, 1), (17, 3, 70001, 0),
+    (20, 1, (1 << 20) - 4, 0), (20, 2, 1 << 20, 0), (14, 1, 1, 0)])
+def test_amp_encode_at_every_split(n, B, dim, shift):
+    """Samples of a wavefront, of a block and of several, of which each block or a launch of its own combines the sums;
+    samples that start anywhere.  An amplitude is a double rounded once: half a unit in the last place, 2^-24."""
+    torch = gu.torch_cuda()
+    gen = torch.Generator(device="cuda").manual_seed(n + dim)
+    flat = torch.randn(B * dim + shift, device="cuda", generator=gen)
+    x = flat[shift:].view(B, dim)
+    x[0].mul_(1e-3)
+    x[B - 1, dim - 1] = 0.0 if dim > 1 else 1.0
+    ctx = gu.make_ctx(n, B)
+    ctx.state.fill_(9.0)
+    norm = torch.zeros(B, device="cuda")
+    ctx.qsv_amp_encode(x, norm)
+    want = x.double().norm(dim=1)
+    assert ((norm.double() - want).abs() <= 2 ** -24 * 1.001 * want).all()
+    amps = x.double() / want[:, None]
+    assert ((ctx.state[:, :dim, 0].double() - amps).abs() <= 2 ** -24 * 1.001 * amps.abs() + 1e-44).all()
+    assert not ctx.state[:, dim:].any() and not ctx.state[:, :, 1].any()
+    x.zero_()
+    ctx.qsv_amp_encode(x, norm)
+    assert not ctx.state.any() and not norm.any()
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,B,shots", [(1, 3, 5), (5, 2, 64), (7, 3, 100), (8, 3, 100), (12, 2, 129), (13, 3, 600), (14, 1, 5000), (18, 2, 1000)])
 def test_sampling_and_shot_means_by_size(n, B, shots):
     """Draws against the integer rule in Python, one shot in 37; shot means against whole-number sums."""
