@@ -30,10 +30,11 @@ constexpr size_t kOpsRegion = 4u << 20;  // persistent: uploaded pass programs
 constexpr uint64_t kNtStoreBytes = 384ull << 20;
 constexpr uint64_t kSplitBytes = 32ull << 20;    // see run_circuit
 // Amplitudes of a layer's gradient rows (B slots n 2^n) from which one circuit per parameter is run instead of two (see
-// qsv_param_shift_grad): reading the unshifted states at the end of the last pass takes 2 to 3 us.  Measured, two / one:
-// 10 qubits x 16, 2 layers 72 / 76 us (2^18.3), 12 x 4, 2 layers 77 / 77 (2^18.6), 15 x 1, 1 layer 65 / 60 (2^19.9), 14 x 4, 3
-// layers 193 / 163 (2^20.8), 16 x 256, 10 layers 98.4 / 52.7 ms (2^29).
-constexpr uint64_t kTurnAmplitudes = 1ull << 19;
+// qsv_param_shift_grad): reading the unshifted states at the end of the last pass takes 2 to 3 us, and up to 13 qubits, where a
+// row is one or two tiles, little else is saved.  Measured, two / one: 12 qubits x 7, 2 layers 75.8 / 82.2 us (2^19.4), 13 x 4
+// 79.4 / 87.6 (2^19.7), 12 x 14 82.5 / 82.8 (2^20.4), 11 x 30 81.5 / 79.2 (2^20.4), 13 x 8 92.2 / 89.8 (2^20.7), 14 x 2 116.6 /
+// 110.3 (2^19.8), 16 x 1 187.5 / 135.9 (2^21), 16 x 256, 10 layers 98.4 / 52.7 ms (2^29).
+constexpr uint64_t turn_amplitudes(int n) { return n <= 13 ? 1ull << 20 : 1ull << 19; }
 // ... and from which the layer's rotations are applied to the start states first: that is one more pass or two over the
 // batch for every layer.  Measured without / with: 15 x 4, 5 layers 502 / 549 us (2^21.9), 16 x 4, 6 layers 680 / 742 (2^23),
 // 14 x 64, 4 layers 1141 / 1137 (2^24.8), 16 x 16, 6 layers 1662 / 1579 (2^25), 12 x 1024, 4 layers 3019 / 2587 (2^27), 16 x 256,
@@ -422,6 +423,18 @@ qsv_status prepare_layers(qsv_ctx* ctx, const qsv_circuit& c, const qsv_circuit&
     return prepare(ctx, c, one, true, rows, inverse, 0, params, feats, samples, mats, out, 0, form, residues);
 }
 
+// What the wavefronts of a pass fetch ahead (see warm_scalar_cache), where all its tiles run at once and find the caches cold:
+// with more of them, later ones find what earlier ones have fetched.  Without / with, 8 layers of a ladder: 16 qubits 67 -> 59
+// us, 19 qubits 86 -> 77, 18 x 8 111 -> 105, 16 x 64 (1024 tiles) 127 -> 123.5, 16 x 128 (2048) 174 / 173, 16 x 256 295 /
+// 296; 26 qubits, 30 layers 10.94 / 11.02 ms, 22 qubits (1024) 165.5 / 167.2 us.  Rows that have matrices of their own: 13
+// x 128 53.3 -> 52.3, 13 x 512 79.3 / 80.2.  Reverse mode: 18 x 8 264 -> 256, 16 x 64 305 -> 299, re-uploading 469 / 477.
+template <class Args>
+void warm(Args* a, const DirectPass& low, uint64_t tiles) {
+    if (a->n > 20 || tiles > (a->rowdep ? 256u : 1024u)) return;
+    a->warm_ops = low.n_ops * (int)sizeof(DirectOp);
+    a->warm_mats = low.n_mats * 32;
+}
+
 inline Prepared layer_of(const Prepared& all, int l) {
     Prepared pr = all;
     pr.mats = all.mats + (size_t)l * all.layer_entries * 8;
@@ -537,7 +550,7 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
     bool first = true;
     for (size_t pi = 0; pi < pl.passes.size(); ++pi) {
         const Pass& ps = pl.passes[pi];
-        PassArgs a;
+        PassArgs a{};
         const bool switches = ps.map_begin >= 0 || pi == extra_switch;
         float2* const dst = switches ? (cur == state ? pong : state) : cur;
         a.state = dst;
@@ -583,6 +596,7 @@ qsv_status run_circuit(qsv_ctx* ctx, const qsv_circuit& c, const Prepared& pr, f
             a.s_in = cp->low_ops.passes[pi].s_in;
             a.s_out = cp->low_ops.passes[pi].s_out;
             a.first_mat = cp->low_ops.passes[pi].first_mat;
+            warm(&a, cp->low_ops.passes[pi], tiles_of(rows));
         }
         QSV_HIP(ctx, launch_pass(pl.tile, planes, a, tiles_of(rows_a), ctx->stream), "fused pass");
         if (!split) continue;
@@ -1145,7 +1159,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     // shifted circuit is run whole (below).  Where the direct kernel takes the rows, one circuit per parameter is run instead of
     // two, with the angle turned by pi: R(t +- pi/2) = (R(t) +- R(t + pi)) / sqrt 2, so both shifted states are
     // combinations of its state and the unshifted circuit's, and the last pass forms them and takes both expectation values.
-    // See kTurnAmplitudes for what it gives and where it pays.
+    // See turn_amplitudes for what it gives and where it pays.
     const int L = c->n_layers;
     const int slots_n = (c->reupload + c->n_rot) * n;
     const size_t ckpt_bytes = (size_t)B * (size_t)(L + 1) * state_bytes;
@@ -1153,7 +1167,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         float2* ckpt = (float2*)ar.take(ckpt_bytes);
         // rows per sample and layer; the tile of gradient rows does not depend on their number from 10 qubits on
         bool turns = !ctx->opt_naive && n >= kMinTile && is_direct(ctx, tile_of(ctx, B, 1, 0)) &&
-                     ((uint64_t)(B * slots_n) << n) >= kTurnAmplitudes;
+                     ((uint64_t)(B * slots_n) << n) >= turn_amplitudes(n);
         // what the scalars of the tables' groups lack, for at most kLayerGroups groups a layer (a pass of a layer is one; a
         // tail has no more than its layers one by one, and one more for every 64 unitaries)
         constexpr int kLayerGroups = 8;
@@ -1452,6 +1466,7 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
             a.direct = 1;
             a.s_in = low.s_in; a.s_out = low.s_out; a.first_mat = low.first_mat;
             a.g_sample0 = (unsigned)b0;
+            warm(&a, low, (uint64_t)rows << (n - tile));
             QSV_HIP(ctx, launch_pass(tile, 1, a, (uint64_t)rows << (n - tile), ctx->stream), "fused pass");
         }
         qsv_status s = losses(ctx, ob, state(passes), rows, b0, P, sc.zpart, sc.zall, sc.coef, f);
@@ -1477,6 +1492,7 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
             a.rowdep = c.reupload;
             a.s_in = low.s_in; a.s_out = low.s_out; a.first_mat = low.first_mat; a.first_u = low.first_u;
             a.mate = ps.map_begin >= 0 ? bp->mates[k] : 0;
+            warm(&a, low, (uint64_t)rows << (n - tile));
             // the forward run's last pass was number passes - 1: go on in turns
             a.rev = ctx->opt_rev != 0 && ((passes + k) & 1) ? (ps.map_begin < 0 ? 2 : 1) : 0;
             a.nt_store = nt;
@@ -1795,7 +1811,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
                                 ctx->stream),
             "upload probe");
     QSV_HIP(ctx, hipStreamSynchronize(ctx->stream), "upload probe");
-    PassArgs a;
+    PassArgs a{};
     a.state = ctx->state;
     a.in = ctx->state;
     a.imap = nullptr;

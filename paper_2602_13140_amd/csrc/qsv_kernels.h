@@ -71,6 +71,7 @@ struct PassArgs {
     unsigned mate;       // gather: the tile of a row that has the other halves of tile t's lines is t ^ mate (0: t itself)
     int s_in, s_out;     // register layouts in which the tile is loaded and stored
     int first_mat;       // index of the pass's first unitary
+    int warm_ops, warm_mats;   // bytes of the operation list and of the table to fetch ahead (0: none)
     unsigned g_sample0, g_rem0;   // gradient rows: rm.row0 / rm.per and rm.row0 % rm.per
 };
 
@@ -104,7 +105,7 @@ struct PairArgs {
     float* sums;           // [unitaries][rows][2^(n - 10)][4]: a record per unitary (execution order) and wavefront
     int64_t sample0;       // row r belongs to sample sample0 + r
     int64_t rows;
-    int n, c, w, n_mats, rowdep, s_in, s_out, first_mat, first_u;
+    int n, c, w, n_mats, rowdep, s_in, s_out, first_mat, first_u, warm_ops, warm_mats;
     unsigned mate;
     int rev, nt_store;
     int kind, q;           // observable, as launch_adj_init's

@@ -448,6 +448,25 @@ void k_pass(const PassArgs a) {
     }
 }
 
+// Fetches what the interpreter will read, `bytes` from p on, into the scalar cache, every wavefront its share of the lines, all
+// at once.  The interpreter itself looks one operation ahead, and a line that it finds missing costs it an L2's latency: on
+// one 19-qubit state a pass of 80 operations found 46 lines missing, one after the other, in the 15 us that it took (58 % of
+// the wavefronts' cycles were waits); 8 layers and back 84.6 -> 75.6 us.  The caller's rule has both sides.
+__device__ __forceinline__ void warm_scalar_cache(u64 p, unsigned bytes) {
+    unsigned at = to_sgpr(threadIdx.x >> 6) * 64u;
+    const unsigned step = to_sgpr(blockDim.x >> 6) * 64u;
+    if (at >= bytes) return;
+    asm volatile("L_warm_%=:\n\t"
+                 "s_load_dword s36, %[p], %[at]\n\t"
+                 "s_add_u32 %[at], %[at], %[step]\n\t"
+                 "s_cmp_lt_u32 %[at], %[n]\n\t"
+                 "s_cbranch_scc1 L_warm_%=\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : [at] "+s"(at)
+                 : [p] "s"(uni64(p)), [step] "s"(step), [n] "s"(to_sgpr(bytes))
+                 : "s36", "scc", "memory");
+}
+
 // ------------------------------------------------------------------------------------------
 // The same pass for tiles of one state row (n >= T, n <= 28): the form that almost every launch takes.
 // What a row's tiles have in common (register layouts of the load and the store, the row's sample, the
@@ -465,7 +484,8 @@ void k_pass(const PassArgs a) {
 // 20 qubits x 32, 20 layers and back: reads of the mirrored passes 1.31 -> 1.00 times their bytes (2.00 in the worst),
 // 4416 -> 4365 us.
 // TURNED: the variant for the last pass of turned gradient rows, which stores three sums and no state.
-template <int T, bool GATHER, bool TURNED = false>
+// WARM: the variant that fetches ahead (see warm_scalar_cache): as a branch it costs launches that don't 0.5 % (26 qubits).
+template <int T, bool GATHER, bool TURNED = false, bool WARM = false>
 __global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(96), amdgpu_waves_per_eu(8, 8)))
 void k_pass_direct(const PassArgs a) {
     extern __shared__ float lds[];
@@ -546,6 +566,10 @@ void k_pass_direct(const PassArgs a) {
 #undef QSV_GET
     }
     if (a.prio) __builtin_amdgcn_s_setprio(0);
+    if constexpr (WARM) {                            // while the tile is on its way
+        warm_scalar_cache((u64)(uintptr_t)a.ops, (unsigned)a.warm_ops);
+        warm_scalar_cache((u64)(uintptr_t)(mats + (u64)a.first_mat * 8), (unsigned)a.warm_mats);
+    }
     const bool scatter = !GATHER && !TURNED && a.imap;
     if (scatter) follow_map(s_out);                  // while the tile is on its way
     {
@@ -672,7 +696,8 @@ __device__ __forceinline__ float adj_weight(const AdjObs& o, u64 r, u64 k, int n
 // Against layer by layer (psi of every layer kept, lambda taken back by k_pass_direct, the sums by two or three launches
 // that read both): 11.8 -> 7.1 ms and 2.83 -> 1.05 ms; 13 x 37, 5 re-uploading layers 500 -> 160 us, 18 x 4, 6 layers 584 ->
 // 300, 22 x 2, 6 layers 1428 -> 840.
-template <int T, bool GATHER>
+// WARM: as in k_pass_direct.
+template <int T, bool GATHER, bool WARM>
 __global__ __launch_bounds__(1 << (T - R)) __attribute__((amdgpu_num_sgpr(100), amdgpu_waves_per_eu(6, 6)))
 void k_pair_pass(const PairArgs a) {
     extern __shared__ float lds[];
@@ -732,6 +757,10 @@ void k_pair_pass(const PairArgs a) {
         map_off = voff | base * 8u;
     }
 #undef QSV_GETV
+    if constexpr (WARM) {                            // while the tiles are on their way
+        warm_scalar_cache((u64)(uintptr_t)a.ops, (unsigned)a.warm_ops);
+        warm_scalar_cache((u64)(uintptr_t)(mats + (u64)a.first_mat * 8), (unsigned)a.warm_mats);
+    }
     if (!a.lam_in) {                                 // lambda = O psi, at the indices the amplitudes were read from
         const AdjObs o{a.kind, a.q, a.mask, a.coef};
         unsigned off = map_off ^ x0;
@@ -3347,10 +3376,13 @@ hipError_t launch_pass(int tile, int planes, const PassArgs& a, uint64_t n_tiles
         const size_t bytes = (size_t)direct_lds_bytes(tile);
         switch (a.imap && a.gather ? -tile : tile) {
 #define QSV_DIRECT(T)                                                                         \
-    case T: if (a.unturned) hipLaunchKernelGGL((k_pass_direct<T, false, true>), grid, block, bytes, st, a);  \
-            else hipLaunchKernelGGL((k_pass_direct<T, false>), grid, block, bytes, st, a);               \
-            break;                                                                                       \
-    case -T: hipLaunchKernelGGL((k_pass_direct<T, true>), grid, block, bytes, st, a); break;
+    case T: if (a.unturned) hipLaunchKernelGGL((k_pass_direct<T, false, true>), grid, block, bytes, st, a);             \
+            else if (a.warm_ops) hipLaunchKernelGGL((k_pass_direct<T, false, false, (T < 14)>), grid, block, bytes, st, a); \
+            else hipLaunchKernelGGL((k_pass_direct<T, false>), grid, block, bytes, st, a);                          \
+            break;                                                                                                  \
+    case -T: if (a.warm_ops) hipLaunchKernelGGL((k_pass_direct<T, true, false, (T < 14)>), grid, block, bytes, st, a);   \
+             else hipLaunchKernelGGL((k_pass_direct<T, true>), grid, block, bytes, st, a);                           \
+             break;
             QSV_DIRECT(10) QSV_DIRECT(11) QSV_DIRECT(12) QSV_DIRECT(13) QSV_DIRECT(14)
 #undef QSV_DIRECT
             default: return hipErrorInvalidValue;
@@ -3383,8 +3415,12 @@ hipError_t launch_pair_pass(int tile, const PairArgs& a, hipStream_t st) {
     const size_t bytes = (size_t)direct_lds_bytes(tile);
     switch (a.imap ? -tile : tile) {
 #define QSV_PAIR(T)                                                                         \
-    case T: hipLaunchKernelGGL((k_pair_pass<T, false>), grid, block, bytes, st, a); break;  \
-    case -T: hipLaunchKernelGGL((k_pair_pass<T, true>), grid, block, bytes, st, a); break;
+    case T: if (a.warm_ops) hipLaunchKernelGGL((k_pair_pass<T, false, true>), grid, block, bytes, st, a);  \
+            else hipLaunchKernelGGL((k_pair_pass<T, false, false>), grid, block, bytes, st, a);           \
+            break;                                                                                    \
+    case -T: if (a.warm_ops) hipLaunchKernelGGL((k_pair_pass<T, true, true>), grid, block, bytes, st, a);  \
+             else hipLaunchKernelGGL((k_pair_pass<T, true, false>), grid, block, bytes, st, a);           \
+             break;
         QSV_PAIR(10) QSV_PAIR(11) QSV_PAIR(12) QSV_PAIR(13)
 #undef QSV_PAIR
         default: return hipErrorInvalidValue;

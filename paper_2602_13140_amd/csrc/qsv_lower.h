@@ -22,6 +22,7 @@ struct DirectPass {
     int s_in, s_out;     // register layouts of the load and the store
     int first_mat;       // table entry of the first unitary (0 if none)
     int first_u;         // its index (0 if none)
+    int n_ops, n_mats;   // operations and table entries of the pass
 };
 
 struct DirectPlan {
@@ -58,6 +59,7 @@ bool lower_pass_as(const Op* ops, int count, Rows rows, const SumAxes& sums, con
     dp.begin = (int)out->ops.size();
     dp.s_in = dp.s_out = -1;
     dp.first_mat = dp.first_u = -1;
+    dp.n_mats = 0;
     int s = -1;
     uint32_t rungs = 0;          // CZ rungs inside the run, collected: neighbouring ones go in one operation
     auto put = [&](uint32_t code, uint32_t arg) { out->ops.push_back({code, arg}); };
@@ -85,6 +87,7 @@ bool lower_pass_as(const Op* ops, int count, Rows rows, const SumAxes& sums, con
                     dp.first_u = o.arg;
                     dp.first_mat = o.arg + (scaled ? group_of(o.arg) : 0);
                 }
+                ++dp.n_mats;
                 if (scaled ? o.c || rows == Rows::replace : rows == Rows::turn) return false;
                 if constexpr (pair) {
                     if (sums.count < 1 || o.c) return false;
@@ -100,7 +103,10 @@ bool lower_pass_as(const Op* ops, int count, Rows rows, const SumAxes& sums, con
                                               : (o.c ? Code::kG : Code::kU)[o.a],
                         (uint32_t)o.arg);
                 }
-                if (scaled && (*groups)[group_of(o.arg) + 1] == o.arg + 1) put(Code::kScale, 0);
+                if (scaled && (*groups)[group_of(o.arg) + 1] == o.arg + 1) {
+                    put(Code::kScale, 0);
+                    ++dp.n_mats;
+                }
                 break;
             case OP_TURN:
                 if (o.a > 3) return false;
@@ -149,6 +155,7 @@ bool lower_pass_as(const Op* ops, int count, Rows rows, const SumAxes& sums, con
     }
     dp.s_out = s;
     if (dp.first_u < 0) dp.first_mat = dp.first_u = 0;
+    dp.n_ops = (int)out->ops.size() - dp.begin;
     out->passes.push_back(dp);
     return s >= 0 && !out->ops.empty() && out->ops.back().code == Code::kEnd;
 }

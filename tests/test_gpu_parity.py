@@ -968,6 +968,31 @@ def test_ring_circuit_and_its_inverse_at_the_bounds_of_the_tile_rule(n, B, L):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,B,rot,ent,reup", [
+    (12, 1024, (RY, RZ), LADDER, 0), (12, 1025, (RY, RZ), RING, 0), (11, 256, (RX,), RING, 1), (11, 257, (RX,), RING, 1),
+    (13, 3, (), RING, 0), (20, 3, (RY,), RING, 0), (21, 1, (RY,), RING, 0)])
+def test_passes_at_the_bounds_of_what_they_fetch_ahead(n, B, rot, ent, reup):
+    """Against one gate per launch: 3 n L gates of a few roundings of 6e-8 each."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(2, rot, ent, reup)
+    g = rng(n + B)
+    p = gu.dev(g.uniform(0, 2 * np.pi, spec.num_params(n)).astype(np.float32)) if rot else None
+    fd = gu.dev(g.standard_normal((B, n)).astype(np.float32)) if reup else None
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, B)
+    ctx.qsv_set_option("small_apply", 0)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    start = torch.randn(ctx.state.shape, generator=gen, device="cuda") * 2.0 ** (-n / 2)
+    res = []
+    for naive in (1, 0):
+        ctx.qsv_set_option("naive", naive)
+        ctx.state.copy_(start)
+        ctx.qsv_apply_layers(circ, p, fd, 0)
+        res.append(ctx.state.double())
+    assert ((res[1] - res[0]).norm() / res[0].norm()).item() <= 6e-8 * 3 * np.sqrt(2 * n * 4)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,rot,ent", [(5, (RY, RZ), RING), (11, (RX, RZ), LADDER), (13, (RX, RY, RZ), RING)])
 def test_reverse_mode_gradient_of_the_last_phases_is_zero(oracle, n, rot, ent):
     """RZ rotations that end the last layer commute with the entangler's effect on a diagonal observable."""
@@ -1450,14 +1475,14 @@ def test_reverse_mode_sweep_in_a_graph():
     (1, 13, 158, 2, (RX,), LADDER, 1, {}),
     (1, 14, 74, 2, (RY, RX), RING, 0, {"tile_log2": 10}),       # several passes, halves on two streams
     (1, 14, 37, 1, (RZ, RX, RY), NONE, 1, {}),                  # nothing but turns is left of the circuit
-    (0, 10, 30, 3, (RY, RZ), RING, 0, {}),
-    (0, 11, 9, 9, (RX, RY, RZ), LADDER, 1, {}),                 # 99 unitaries: two groups in a pass
-    (0, 12, 6, 2, (RZ, RX), RING, 0, {"grad_chunk_rows": 7}),
+    (0, 10, 60, 3, (RY, RZ), RING, 0, {}),
+    (0, 11, 18, 9, (RX, RY, RZ), LADDER, 1, {}),                 # 99 unitaries: two groups in a pass
+    (0, 12, 13, 2, (RZ, RX), RING, 0, {"grad_chunk_rows": 7}),
     (0, 14, 3, 3, (RY,), LADDER, 1, {"tile_log2": 11, "split_streams": 1}),
     (0, 16, 2, 2, (RX, RZ), RING, 0, {}),
 ])
 def test_shift_rule_from_one_circuit_per_parameter(oracle, ahead, n, B, L, rot, ent, reup, opts):
-    """Batches large enough for one circuit per parameter (2^19 amplitudes a layer), and for starting behind its layer's
+    """Batches large enough for one circuit per parameter (2^20 amplitudes a layer, 2^19 from 14 qubits on), and for starting behind its layer's
     rotations (ahead: 2^25): against whole circuits, two per parameter, and against the oracle on the first sample.  A
     difference of two expectation values, each with the rounding of L (slots) n gates."""
     torch = gu.torch_cuda()
