@@ -346,7 +346,7 @@ def bench_c2(torch, qb, wl, args):
             "whole_circuits": {"ms_per_step": ms_whole, "executed_updates": updates,
                                "executed_updates_per_s": updates / (ms_whole * 1e-3)},
             "adjoint": {"method": "qsv_adjoint_grad: same loss and gradient in reverse mode (one forward run, "
-                                  "psi and lambda taken back layer by layer, 2x2 transition sums per qubit)",
+                                  "psi kept after every pass, lambda taken back beside it, sums per unitary)",
                         "ms_per_step": ms_adj, "speedup_over_shift_rule": ms / ms_adj},
             "three_rotations": {"workload": "same with RX,RY,RZ per layer: 480 parameters", "params": P3,
                                 "circuits": B * (2 * P3 + 1), "updates": updates3, "ms_per_step": ms3,
