@@ -317,6 +317,8 @@ def bench_c2(torch, qb, wl, args):
     ctx.qsv_set_option("grad_layered", 0)
     ms_whole, _ = run_steps(torch, step, steps, 1)
 
+    ctx.qsv_set_option("grad_layered", 1)
+
     def step_adj(tm):
         ctx.qsv_adjoint_grad(circ, xd, pd, None, 0, loss, grad, None, mg)
 

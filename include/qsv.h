@@ -293,7 +293,7 @@ qsv_status qsv_probe_pass(qsv_ctx* ctx, int low_bits, int window_start, int tran
  * qubits than the tile has index bits, at most 28 of them, and the workspace has room for a copy of
  * the state; the result is the same up to rounding order); load_store_priority = 1 (default) / 0 lets
  * the pass kernel's wavefronts raise their issue priority while they issue a tile's loads and stores (the
- * two-stream reverse-mode sweep does so below 18 qubits only);
+ * layer-by-layer reverse-mode sweep on two streams does so below 18 qubits only, the one in whole passes never);
  * small_apply = 1 (default) / 0 lets qsv_apply_layers run states of at most 10 qubits and 2^21 amplitudes in
  * all (10 qubits: 2^20) in one launch with the gates in registers and lane exchanges (the kernel of qsv_forward_small, started
  * from the state; measured 1.6 to 4 times faster there than the fused passes, whose launches cost more than
