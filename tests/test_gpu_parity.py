@@ -1036,7 +1036,8 @@ def test_expz_at_every_grouping(n, B):
     ctx.close()
 
 
-@pytest.mark.parametrize("n,B", [(13, 1), (14, 65), (15, 63), (15, 64), (16, 63), (16, 64)])
+@pytest.mark.parametrize("n,B", [(13, 1), (14, 65), (15, 63), (15, 64), (16, 63), (16, 64), (21, 1), (22, 1), (22, 3),
+                                 (23, 1), (24, 1)])
 def test_expz_of_rows_that_are_a_blocks_work(n, B):
     test_expz_at_every_grouping(n, B)
 
