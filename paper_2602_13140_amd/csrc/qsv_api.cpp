@@ -215,11 +215,6 @@ std::shared_ptr<const Plan> planned(const qsv_circuit& c, int n, int64_t rows, b
     return plan;
 }
 
-// Finds or builds the plan and makes sure its arrays are resident in the ops region.  Uploads are
-// asynchronous copies on the context's stream from host arrays that live as long as the context.
-// When the region is full, every plan in it is dropped from the region (not from the host) and the
-// region is filled again from its start: the copies that overwrite it are ordered, on the stream,
-// behind every kernel that read the old contents, so nothing waits on the host.
 int tile_of(const qsv_ctx* ctx, int64_t rows, int layers, int defer) {
     const int tile = ctx->opt_tile > 0 ? ctx->opt_tile : defer ? defer_tile(ctx->n, rows, layers) : default_tile(ctx->n, rows);
     return std::max(kMinTile, std::min(kMaxTile, tile));
@@ -230,8 +225,9 @@ bool is_direct(const qsv_ctx* ctx, int tile) {
     return ctx->n >= tile && ctx->n <= kDirectMaxQubits && (ctx->opt_planes == 1 || tile == kMaxTile);
 }
 
-qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad,
-                    const CachedPlan** out, int defer = 0, PlanForm form = kPlain) {
+// The context's plan for a circuit, built if it has none yet: host memory only.
+qsv_status find_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad, CachedPlan** out, int defer = 0,
+                     PlanForm form = kPlain) {
     const int tile = tile_of(ctx, rows, c.n_layers, defer);
     const bool sweep = form == kSweep;
     const int direct = is_direct(ctx, tile) ? 1 : 0;
@@ -242,10 +238,6 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
             hit = &cp;
             break;
         }
-    if (hit && hit->resident) {
-        *out = hit;
-        return QSV_OK;
-    }
     if (!hit) {
         CachedPlan cp;
         cp.c = c;
@@ -295,13 +287,30 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         ctx->cache.push_back(std::move(cp));
         hit = &ctx->cache.back();
     }
-    CachedPlan& cp = *hit;
-    const size_t nm = cp.plan.mat_order.size();
-    const size_t ops_bytes = align_up(std::max(cp.plan.ops.size(), cp.low_ops.ops.size()) * sizeof(Op) + sizeof(Op));
-    const size_t tab_bytes = align_up(std::max(nm, cp.exec_of.size()) * sizeof(int32_t) + 4);
-    const size_t map_bytes = align_up(cp.plan.maps.size() * sizeof(uint32_t) + 4);
-    const size_t group_bytes = align_up(cp.plan.groups.size() * sizeof(int32_t) + 4);
-    const size_t bytes = ops_bytes + 2 * tab_bytes + map_bytes + group_bytes;
+    *out = hit;
+    return QSV_OK;
+}
+
+// What a plan's arrays take of the ops region.
+struct PlanRoom {
+    size_t ops, table, maps, groups;
+    explicit PlanRoom(const CachedPlan& cp)
+        : ops(align_up(std::max(cp.plan.ops.size(), cp.low_ops.ops.size()) * sizeof(Op) + sizeof(Op))),
+          table(align_up(std::max(cp.plan.mat_order.size(), cp.exec_of.size()) * sizeof(int32_t) + 4)),
+          maps(align_up(cp.plan.maps.size() * sizeof(uint32_t) + 4)),
+          groups(align_up(cp.plan.groups.size() * sizeof(int32_t) + 4)) {}
+    size_t bytes() const { return ops + 2 * table + maps + groups; }
+};
+
+// Makes sure the plan's arrays are resident in the ops region.  Uploads are
+// asynchronous copies on the context's stream from host arrays that live as long as the context.
+// When the region is full, every plan in it is dropped from the region (not from the host) and the
+// region is filled again from its start: the copies that overwrite it are ordered, on the stream,
+// behind every kernel that read the old contents, so nothing waits on the host.
+qsv_status upload_plan(qsv_ctx* ctx, CachedPlan& cp) {
+    if (cp.resident) return QSV_OK;
+    const PlanRoom room(cp);
+    const size_t bytes = room.bytes();
     if (bytes > kOpsRegion) return fail(ctx, QSV_ERR_UNSUPPORTED, "circuit too long for the plan buffer");
     if (ctx->ops_used + bytes > kOpsRegion) {
         // While a call has work on the second stream, kernels there may still read the region, and
@@ -312,10 +321,10 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
         ctx->ops_used = 0;
     }
     cp.dev_off = ctx->ops_used;
-    cp.order_off = cp.dev_off + ops_bytes;
-    cp.execof_off = cp.order_off + tab_bytes;
-    cp.maps_off = cp.execof_off + tab_bytes;
-    cp.groups_off = cp.maps_off + map_bytes;
+    cp.order_off = cp.dev_off + room.ops;
+    cp.execof_off = cp.order_off + room.table;
+    cp.maps_off = cp.execof_off + room.table;
+    cp.groups_off = cp.maps_off + room.maps;
     if (!cp.plan.groups.empty())
         QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.groups_off, cp.plan.groups.data(), cp.plan.groups.size() * sizeof(int32_t),
                                     hipMemcpyHostToDevice, ctx->stream),
@@ -330,8 +339,8 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
                                     (cp.direct ? cp.low_ops.ops.size() : cp.plan.ops.size()) * sizeof(Op),
                                     hipMemcpyHostToDevice, ctx->stream),
                 "upload plan");
-    if (nm)
-        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.order_off, cp.plan.mat_order.data(), nm * sizeof(int32_t),
+    if (!cp.plan.mat_order.empty())
+        QSV_HIP(ctx, hipMemcpyAsync(ctx->ws + cp.order_off, cp.plan.mat_order.data(), cp.plan.mat_order.size() * sizeof(int32_t),
                                     hipMemcpyHostToDevice, ctx->stream),
                 "upload matrix order");
     if (!cp.exec_of.empty())
@@ -340,8 +349,17 @@ qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int invers
                 "upload matrix order");
     ctx->ops_used += bytes;
     cp.resident = true;
-    *out = &cp;
     return QSV_OK;
+}
+
+// Both: the plan, in the ops region.
+qsv_status get_plan(qsv_ctx* ctx, const qsv_circuit& c, int64_t rows, int inverse, int grad, const CachedPlan** out,
+                    int defer = 0, PlanForm form = kPlain) {
+    CachedPlan* cp = nullptr;
+    qsv_status st = find_plan(ctx, c, rows, inverse, grad, &cp, defer, form);
+    if (st == QSV_OK) st = upload_plan(ctx, *cp);
+    *out = cp;
+    return st;
 }
 
 RowMap plain_rows(int n) {
@@ -1165,18 +1183,54 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     const size_t ckpt_bytes = (size_t)B * (size_t)(L + 1) * state_bytes;
     if (ctx->opt_grad_layered && P > 0 && ar.remaining() >= align_up(ckpt_bytes) + row_bytes + 2 * kAlign) {
         float2* ckpt = (float2*)ar.take(ckpt_bytes);
-        // rows per sample and layer; the tile of gradient rows does not depend on their number from 10 qubits on
+        qsv_circuit one = *c;
+        one.n_layers = 1;
+        qsv_circuit rot = one;
+        rot.entangler = QSV_ENT_NONE;
+        // the tile of gradient rows does not depend on their number from 10 qubits on
         bool turns = !ctx->opt_naive && n >= kMinTile && is_direct(ctx, tile_of(ctx, B, 1, 0)) &&
                      ((uint64_t)(B * slots_n) << n) >= turn_amplitudes(n);
-        // what the scalars of the tables' groups lack, for at most kLayerGroups groups a layer (a pass of a layer is one; a
-        // tail has no more than its layers one by one, and one more for every 64 unitaries)
-        constexpr int kLayerGroups = 8;
-        const size_t res_count = msamples * (size_t)L * kLayerGroups;
-        double* residues = turns ? (double*)ar.take(3 * res_count * 16) : nullptr;
-        turns = turns && residues;
-        double *res_one = residues, *res_rot = residues + (turns ? 2 * res_count : 0),
-               *res_tail = residues + (turns ? 4 * res_count : 0);
+        // A unitary with a turned angle is a turn times the unturned one, so the circuits of layer l also share that layer's
+        // rotations: the states go through them once per sample, and a circuit starts with one matrix on one qubit instead of n
+        // unitaries.  See kAheadAmplitudes for where that pays.
+        bool ahead = turns && ((uint64_t)(B * slots_n) << n) >= kAheadAmplitudes;
+        // The groups of a layer, of its rotations and of every tail: their scalars are entries of the tables, beside which the
+        // region for matrices has room for L n / 2 others (tables with groups have no scale table), and what these lack is kept per group.
+        // Options that leave a tile few qubits to choose (tile_log2, low_bits) make more passes, and with them groups, than
+        // that: two circuits per parameter then, as where a tail's plan is too long for the ops region.
         int g_one = 0, g_rot = 0, g_tail = 0;
+        std::vector<CachedPlan*> tails;
+        if (turns) {
+            auto groups_of = [&](const qsv_circuit& k, int grad, PlanForm form, CachedPlan** cp, int* groups) -> qsv_status {
+                const qsv_status s = find_plan(ctx, k, B, 0, grad, cp, 0, form);
+                if (s == QSV_OK) *groups = (int)(*cp)->plan.groups.size() - 1;
+                return s;
+            };
+            const size_t entries = mats_bytes(*c, n, B) / 32 - 1;      // one is only prefetched
+            auto fits = [&](int64_t per_sample) { return msamples * (size_t)per_sample <= entries; };
+            CachedPlan* cp = nullptr;
+            st = groups_of(one, 0, kGrouped, &cp, &g_one);
+            if (st == QSV_OK && ahead) st = groups_of(rot, 0, kGrouped, &cp, &g_rot);
+            turns = fits((int64_t)L * (n + std::max(g_one, g_rot)));
+            for (int l = 0; l < L && turns && st == QSV_OK; ++l) {
+                qsv_circuit tail = *c;
+                tail.n_layers = L - l;
+                int g = 0;
+                st = groups_of(tail, 1, ahead ? kTurnedAhead : kTurned, &cp, &g);
+                if (st != QSV_OK) break;
+                turns = fits((int64_t)(L - l) * n + g) && PlanRoom(*cp).bytes() <= kOpsRegion;
+                g_tail = std::max(g_tail, g);
+                tails.push_back(cp);
+            }
+            if (st != QSV_OK) return st;
+            ahead = ahead && turns;
+        }
+        const size_t res_one_count = msamples * (size_t)L * g_one, res_rot_count = msamples * (size_t)L * g_rot;
+        double* residues = turns ? (double*)ar.take((res_one_count + res_rot_count + msamples * (size_t)g_tail) * 16) : nullptr;
+        turns = turns && residues;
+        ahead = ahead && turns;
+        double *res_one = residues, *res_rot = turns ? res_one + 2 * res_one_count : nullptr,
+               *res_tail = turns ? res_rot + 2 * res_rot_count : nullptr;
         const int64_t per_l = (turns ? 1 : 2) * (int64_t)slots_n;
         const int64_t want = B * per_l > B ? B * per_l : B;
         const int64_t chunk = chunk_rows(want);
@@ -1185,8 +1239,6 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         if (!ckpt || chunk < 1 || !states || !zpart) return ws_fail(ctx, ar, "qsv_param_shift_grad");
         const size_t sample_stride = (size_t)1 << n;          // amplitudes per state
         auto ck = [&](int l) { return ckpt + (size_t)l * (size_t)B * sample_stride; };
-        qsv_circuit one = *c;
-        one.n_layers = 1;
         // unshifted circuit, one layer at a time: ck(l) = state of every sample before layer l
         QSV_HIP(ctx, launch_encode(x_dev, B, dim, n, npart, nblk, inv, nullptr, ck(0), ctx->stream), "encode");
         RowMap rm_fwd;    // rows are the samples: the first pass of layer l reads state l and writes state l + 1
@@ -1197,7 +1249,6 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         const PlanForm unshifted = turns ? kGrouped : kPlain;
         st = prepare_layers(ctx, *c, one, B, 0, params_dev, feats_dev, B, mats, &all, unshifted, res_one);
         if (st != QSV_OK) return st;
-        g_one = all.layer_entries - n;
         for (int l = 0; l < L; ++l) {
             st = run_circuit(ctx, one, layer_of(all, l), ck(l + 1), B, 0, nullptr, rm_fwd, ck(l));
             if (st != QSV_OK) return st;
@@ -1205,15 +1256,8 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         QSV_HIP(ctx, launch_expz_block(ck(L), B, n, zpart, ctx->stream), "expz block");
         QSV_HIP(ctx, launch_expz_finish_scatter(zpart, B, n, obs_qubit, f, Scatter{0, 1, per, 2 * P}, ctx->stream),
                 "expz finish");
-        // A unitary with a turned angle is a turn times the unturned one, so the circuits of layer l also share that layer's
-        // rotations: the states go through them once per sample, and a circuit starts with one matrix on one qubit instead of n
-        // unitaries.  See kAheadAmplitudes for where that pays.
-        const bool ahead = turns && ((uint64_t)(B * per_l) << n) >= kAheadAmplitudes;
         if (ahead) {
-            qsv_circuit rot = one;
-            rot.entangler = QSV_ENT_NONE;
             st = prepare_layers(ctx, *c, rot, B, 0, params_dev, feats_dev, B, mats, &all, unshifted, res_rot);
-            g_rot = all.layer_entries - n;
             for (int l = 0; l < L && st == QSV_OK; ++l)
                 st = run_circuit(ctx, rot, layer_of(all, l), ck(l), B, 0, nullptr, rm_fwd);
             if (st != QSV_OK) return st;
@@ -1225,21 +1269,21 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
             tail.n_layers = L - l;
             const float* p_l = params_dev + (size_t)l * slots_n;
             Prepared pr;
+            int groups = 0;
             if (turns) {
-                st = get_plan(ctx, tail, chunk, 0, 1, &pr.cp, 0, ahead ? kTurnedAhead : kTurned);
+                st = upload_plan(ctx, *tails[l]);
                 if (st != QSV_OK) return st;
+                pr.cp = tails[l];
                 CircDev rest = to_dev(tail, n);
                 if (ahead) rest.n_layers -= 1;
-                g_tail = (int)pr.cp->plan.groups.size() - 1;
+                groups = (int)pr.cp->plan.groups.size() - 1;
                 pr.mats = mats;
-                pr.mat_stride = rest.n_layers * n + g_tail;
+                pr.mat_stride = rest.n_layers * n + groups;
                 pr.form = MatForm::direct;
-                if (g_one > kLayerGroups || g_rot > kLayerGroups || g_tail > L * kLayerGroups)
-                    return fail(ctx, QSV_ERR_UNSUPPORTED, "internal: more groups than expected");
-                if (g_tail > 0)
+                if (groups > 0)
                     QSV_HIP(ctx, launch_build_mats(rest, ahead ? p_l + slots_n : p_l, feats_dev, B, 0,
                                                    reinterpret_cast<const int*>(ctx->ws + pr.cp->order_off), 0,
-                                                   reinterpret_cast<const int*>(ctx->ws + pr.cp->groups_off), g_tail,
+                                                   reinterpret_cast<const int*>(ctx->ws + pr.cp->groups_off), groups,
                                                    MatForm::direct, mats, res_tail, ctx->stream),
                             "build matrices");
                 QSV_HIP(ctx, launch_build_turns(cd1, p_l, feats_dev, B, ahead ? 1 : 0, ovr, ctx->stream), "build turns");
@@ -1259,7 +1303,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
                 rm.slots_n = slots_n;
                 rm.n = n;
                 const ZSpec zs{obs_qubit, f, Scatter{row0, per_l, per, 2 * (int64_t)l * slots_n}, zpart, turns ? ck(L) : nullptr, 2 * P,
-                               Residues{res_one, l * g_one, (L - l) * g_one, L * g_one}, Residues{res_tail, 0, g_tail, g_tail},
+                               Residues{res_one, l * g_one, (L - l) * g_one, L * g_one}, Residues{res_tail, 0, groups, groups},
                                ahead ? Residues{res_rot, l * g_rot, g_rot, L * g_rot} : Residues{res_rot, 0, 0, 0}};
                 st = run_circuit(ctx, tail, pr, states, rows, 0, ovr, rm, ck(l), &zs);
                 if (st != QSV_OK) return st;

@@ -1510,3 +1510,34 @@ def test_shift_rule_from_one_circuit_per_parameter(oracle, ahead, n, B, L, rot, 
     assert not np.array_equal(res[0][1], res[1][1])
     lref, gref = oracle.param_shift_grad(x[:1], n, ocirc(oracle, spec), p, f[:1] if reup else None, n // 2)
     assert np.abs(res[0][0][:1] - lref).max() <= tol and np.abs(res[0][1][:1] - gref).max() <= tol
+
+
+@pytest.mark.parametrize("n,B,rot,ent,reup,opts", [
+    (19, 1, (RY, RZ), LADDER, 0, {"tile_log2": 10, "low_bits": 9}),     # 10 groups a layer: more than the tables have room for
+    (20, 1, (RY,), RING, 1, {"tile_log2": 10, "low_bits": 9}),          # 11, behind the layer's rotations
+    (19, 1, (RX, RY), RING, 0, {"tile_log2": 11, "low_bits": 10}),      # 9: room for as many
+    (19, 2, (RZ, RX), NONE, 1, {"tile_log2": 11, "low_bits": 10}),      # 9, behind the layer's rotations
+])
+def test_shift_rule_of_tiles_that_leave_a_pass_few_qubits(n, B, rot, ent, reup, opts):
+    """A group of unitaries ends with its pass, and such tiles make a pass for every qubit or two.  Against whole circuits,
+    two per parameter, with the bound of the test above."""
+    torch = gu.torch_cuda()
+    L = 2
+    spec = wl.CircuitSpec(L, rot, ent, reup)
+    g = rng(n + B)
+    P = spec.num_params(n)
+    x, p, f = (a.astype(np.float32) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P), g.standard_normal((B, n))))
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
+    for k, v in opts.items():
+        ctx.qsv_set_option(k, v)
+    res = []
+    for layered in (1, 0):
+        ctx.qsv_set_option("grad_layered", layered)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+        ctx.qsv_param_shift_grad(circ, gu.dev(x), gu.dev(p), gu.dev(f) if reup else None, 1, loss, grad)
+        torch.cuda.synchronize()
+        res.append((loss.cpu().numpy().astype(np.float64), grad.cpu().numpy().astype(np.float64)))
+    ctx.close()
+    tol = 2e-7 * np.sqrt(L * n) * 4 * (max(1.0, float(np.abs(f).max())) if reup else 1.0)
+    assert np.abs(res[0][0] - res[1][0]).max() <= tol and np.abs(res[0][1] - res[1][1]).max() <= tol
