@@ -1159,10 +1159,13 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     double* f = (double*)ar.take((size_t)circuits * 8);
     if (!npart || !inv || !mats || !ovr || !f) return ws_fail(ctx, ar, "qsv_param_shift_grad");
 
-    // a chunk of circuit states plus their reduction partials, sized to what is left of the workspace
-    const size_t row_bytes = state_bytes + (size_t)chunk_blocks(n) * 13 * 8 + 2 * kAlign;
-    auto chunk_rows = [&](int64_t want) -> int64_t {
-        int64_t chunk = (int64_t)(ar.remaining() / row_bytes);
+    // rows of a chunk, at most `want`: their circuit states and the reduction partials of as many rows, or of `least` if those are
+    // more, sized to what is left of the workspace
+    const size_t zbytes = (size_t)chunk_blocks(n) * 13 * 8, row_bytes = state_bytes + zbytes + 2 * kAlign;
+    auto chunk_rows = [&](const Arena& left, int64_t want, int64_t least) -> int64_t {
+        const size_t room = left.remaining(), least_bytes = align_up((size_t)least * zbytes);
+        int64_t chunk = (int64_t)(room / row_bytes);
+        if (chunk < least) chunk = room > least_bytes ? (int64_t)((room - least_bytes) / kAlign * kAlign / state_bytes) : 0;
         if (chunk > want) chunk = want;
         if (chunk > 32768) chunk = 32768;  // rows index a grid dimension
         if (ctx->opt_grad_chunk > 0 && chunk > ctx->opt_grad_chunk) chunk = ctx->opt_grad_chunk;
@@ -1180,9 +1183,20 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
     // See turn_amplitudes for what it gives and where it pays.
     const int L = c->n_layers;
     const int slots_n = (c->reupload + c->n_rot) * n;
-    const size_t ckpt_bytes = (size_t)B * (size_t)(L + 1) * state_bytes;
-    if (ctx->opt_grad_layered && P > 0 && ar.remaining() >= align_up(ckpt_bytes) + row_bytes + 2 * kAlign) {
-        float2* ckpt = (float2*)ar.take(ckpt_bytes);
+    struct Layered { float2 *ckpt, *states; double *residues, *zpart; int64_t chunk; } lay{};
+    // what is taken of the workspace for per_l rows per sample and layer; false: it has no room for that
+    auto carve = [&](int64_t per_l, size_t residue_count) -> bool {
+        Arena a = ar;
+        lay.ckpt = (float2*)a.take((size_t)B * (size_t)(L + 1) * state_bytes);
+        lay.residues = residue_count ? (double*)a.take(residue_count * 16) : nullptr;
+        if (!lay.ckpt || (residue_count && !lay.residues)) return false;
+        lay.chunk = chunk_rows(a, std::max(B * per_l, B), B);
+        if (lay.chunk < 1) return false;
+        lay.states = (float2*)a.take((size_t)lay.chunk * state_bytes);
+        lay.zpart = (double*)a.take((size_t)std::max(lay.chunk, B) * zbytes);
+        return lay.states && lay.zpart;
+    };
+    if (ctx->opt_grad_layered && P > 0 && carve(2 * (int64_t)slots_n, 0)) {
         qsv_circuit one = *c;
         one.n_layers = 1;
         qsv_circuit rot = one;
@@ -1226,17 +1240,16 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
             ahead = ahead && turns;
         }
         const size_t res_one_count = msamples * (size_t)L * g_one, res_rot_count = msamples * (size_t)L * g_rot;
-        double* residues = turns ? (double*)ar.take((res_one_count + res_rot_count + msamples * (size_t)g_tail) * 16) : nullptr;
-        turns = turns && residues;
-        ahead = ahead && turns;
-        double *res_one = residues, *res_rot = turns ? res_one + 2 * res_one_count : nullptr,
+        // (rows half as many make another chunk)
+        if (turns && !carve(slots_n, res_one_count + res_rot_count + msamples * (size_t)g_tail)) {
+            turns = ahead = false;
+            carve(2 * (int64_t)slots_n, 0);
+        }
+        double *res_one = lay.residues, *res_rot = turns ? res_one + 2 * res_one_count : nullptr,
                *res_tail = turns ? res_rot + 2 * res_rot_count : nullptr;
-        const int64_t per_l = (turns ? 1 : 2) * (int64_t)slots_n;
-        const int64_t want = B * per_l > B ? B * per_l : B;
-        const int64_t chunk = chunk_rows(want);
-        float2* states = (float2*)ar.take((size_t)chunk * state_bytes);
-        double* zpart = (double*)ar.take((size_t)(chunk > B ? chunk : B) * chunk_blocks(n) * 13 * 8);
-        if (!ckpt || chunk < 1 || !states || !zpart) return ws_fail(ctx, ar, "qsv_param_shift_grad");
+        const int64_t per_l = (turns ? 1 : 2) * (int64_t)slots_n, chunk = lay.chunk;
+        float2 *const ckpt = lay.ckpt, *const states = lay.states;
+        double* const zpart = lay.zpart;
         const size_t sample_stride = (size_t)1 << n;          // amplitudes per state
         auto ck = [&](int l) { return ckpt + (size_t)l * (size_t)B * sample_stride; };
         // unshifted circuit, one layer at a time: ck(l) = state of every sample before layer l
@@ -1317,7 +1330,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
 
     // ---- every shifted circuit whole
     QSV_HIP(ctx, launch_norms(x_dev, B, dim, npart, nblk, inv, nullptr, ctx->stream), "norms");
-    const int64_t chunk = chunk_rows(circuits);
+    const int64_t chunk = chunk_rows(ar, circuits, 0);
     if (chunk < 1) { ar.need = ar.off + row_bytes; return ws_fail(ctx, ar, "qsv_param_shift_grad"); }
     float2* states = (float2*)ar.take((size_t)chunk * state_bytes);
     double* zpart = (double*)ar.take((size_t)chunk * chunk_blocks(n) * 13 * 8);

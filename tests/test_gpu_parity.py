@@ -1541,3 +1541,28 @@ def test_shift_rule_of_tiles_that_leave_a_pass_few_qubits(n, B, rot, ent, reup, 
     ctx.close()
     tol = 2e-7 * np.sqrt(L * n) * 4 * (max(1.0, float(np.abs(f).max())) if reup else 1.0)
     assert np.abs(res[0][0] - res[1][0]).max() <= tol and np.abs(res[0][1] - res[1][1]).max() <= tol
+
+
+@pytest.mark.parametrize("n,B,L,rot,reup", [(10, 1068, 30, (RX, RY, RZ), 1), (10, 2026, 23, (RY,), 1), (14, 1992, 1, (RX, RY, RZ), 1),
+                                            (14, 2032, 1, (RZ,), 1), (15, 767, 1, (RY,), 0), (15, 760, 1, (RY,), 1)])
+def test_shift_rule_where_the_kept_states_nearly_fill_the_workspace(n, B, L, rot, reup):
+    """The smallest workspace, which the states between the layers leave room in for few rows at a time: what the gradient
+    keeps beside them must not make the call fail.  Against whole circuits, with the bound of the tests above."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, rot, LADDER, reup)
+    P = spec.num_params(n)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x, f = torch.randn((B, 1 << n), device="cuda", generator=gen), torch.randn((B, n), device="cuda", generator=gen)
+    p = torch.rand(P, device="cuda", generator=gen) * 6.0
+    circ = qb.circuit_from_spec(spec)
+    ctx = gu.make_ctx(n, B)
+    res = []
+    for layered in (1, 0):
+        ctx.qsv_set_option("grad_layered", layered)
+        loss, grad = torch.full((B,), 9.0, device="cuda"), torch.full((B, P), 9.0, device="cuda")
+        ctx.qsv_param_shift_grad(circ, x, p, f if reup else None, 1, loss, grad)
+        torch.cuda.synchronize()
+        res.append((loss, grad))
+    ctx.close()
+    tol = 2e-7 * np.sqrt(L * n) * 4 * (max(1.0, float(f.abs().max())) if reup else 1.0)
+    assert (res[0][0] - res[1][0]).abs().max().item() <= tol and (res[0][1] - res[1][1]).abs().max().item() <= tol
