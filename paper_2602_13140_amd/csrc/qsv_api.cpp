@@ -1424,7 +1424,8 @@ static qsv_status losses(qsv_ctx* ctx, const Objective& ob, const float2* A, int
 // every unitary off the registers where it is undone.  So a sweep moves five states a pass (two there; psi and lambda in,
 // lambda out on the way back) of a plan with deferral, where the layers one by one move twelve each: 20 qubits x 32, 20
 // layers 18 passes, 24 GB instead of 64; a 16-qubit ladder of 10 layers 3 passes, 2 GB instead of 16.
-// *done = false: nothing was launched, the scratch has no room (or the options ask for another way).
+// *done = false: nothing was launched: the scratch has no room, the plans are too long for the ops region, or the options ask
+// for another way.
 // f: [batch][2P+1]; inv: room for the norms; what is taken of ar is taken for good.
 static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objective& ob, const float* x_dev, int64_t dim,
                               const float* params, const float* feats, double* npart, int nblk, double* inv, double* f,
@@ -1454,15 +1455,19 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
     const int sets = two ? 2 : 1;
     const int64_t half = std::min(most, two ? (B + 1) / 2 : B);
     if (ar.remaining() < fixed + (size_t)sets * half * sample_bytes(1)) return QSV_OK;     // without planning for it
-    const CachedPlan *fp = nullptr, *bp = nullptr;
-    for (int k = 0; k < 2; ++k) {      // twice: should the second plan recycle the plan buffer, the first comes back
-        qsv_status st = get_plan(ctx, c, B, 0, 0, &fp, defer, kSweep);
-        if (st == QSV_OK) st = get_plan(ctx, c, B, 1, 0, &bp, defer, kSweep);
-        if (st != QSV_OK) return st;
-    }
+    CachedPlan *fp = nullptr, *bp = nullptr;
+    qsv_status st = find_plan(ctx, c, B, 0, 0, &fp, defer, kSweep);
+    if (st == QSV_OK) st = find_plan(ctx, c, B, 1, 0, &bp, defer, kSweep);
+    if (st != QSV_OK) return st;
+    // (the other way needs no more than one layer's plans in the ops region)
     const size_t passes = fp->plan.passes.size();
-    if (!fp->resident || !bp->resident || passes == 0 || ar.remaining() < fixed + (size_t)sets * half * sample_bytes(passes))
+    if (PlanRoom(*fp).bytes() + PlanRoom(*bp).bytes() > kOpsRegion || passes == 0 ||
+        ar.remaining() < fixed + (size_t)sets * half * sample_bytes(passes))
         return QSV_OK;
+    st = upload_plan(ctx, *fp);
+    if (st == QSV_OK) st = upload_plan(ctx, *bp);
+    if (st == QSV_OK) st = upload_plan(ctx, *fp);      // should the second one have recycled the region
+    if (st != QSV_OK) return st;
     int64_t chunk = std::min<int64_t>(half, 32768);
     // the records of a unitary are at most 4 GiB
     while (chunk > 1 && ((uint64_t)chunk << (n - 10)) * 16 > 0xffffffffull) chunk = (chunk + 1) / 2;
@@ -1488,7 +1493,7 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
                 "build matrices");
         return QSV_OK;
     };
-    qsv_status st = table(fp, 0, MatForm::direct, fmats, nullptr);
+    st = table(fp, 0, MatForm::direct, fmats, nullptr);
     if (st == QSV_OK) st = table(bp, 1, MatForm::paired, bmats, corr);
     if (st != QSV_OK) return st;
 

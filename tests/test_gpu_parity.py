@@ -1566,3 +1566,31 @@ def test_shift_rule_where_the_kept_states_nearly_fill_the_workspace(n, B, L, rot
     ctx.close()
     tol = 2e-7 * np.sqrt(L * n) * 4 * (max(1.0, float(f.abs().max())) if reup else 1.0)
     assert (res[0][0] - res[1][0]).abs().max().item() <= tol and (res[0][1] - res[1][1]).abs().max().item() <= tol
+
+
+def test_reverse_mode_of_plans_too_long_for_their_buffer():
+    """4096 layers in tiles that make eleven passes a layer: the list of the sweep in whole passes takes 4.03 MiB and the buffer
+    holds 4, but one layer's plan is short.  Against one gate per launch: L n gates of a few roundings of 6e-8."""
+    torch = gu.torch_cuda()
+    n, L = 20, 4096
+    spec = wl.CircuitSpec(L, (RY, RZ), RING, 0)
+    circ = qb.circuit_from_spec(spec)
+    P = spec.num_params(n)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((1, 1 << n), device="cuda", generator=gen)
+    p = torch.rand(P, device="cuda", generator=gen) * 6.0
+    res = []
+    for opts in ({"tile_log2": 10, "low_bits": 9, "defer_cnots": 0}, {"naive": 1}):
+        ctx = gu.make_ctx(n, 1, ws_bytes=qb.qsv_grad_workspace_bytes(n, 1, circ))
+        for k, v in opts.items():
+            ctx.qsv_set_option(k, v)
+        loss, grad = torch.full((1,), 9.0, device="cuda"), torch.full((1, P), 9.0, device="cuda")
+        ctx.qsv_adjoint_grad(circ, x, p, None, 0, loss, grad)
+        torch.cuda.synchronize()
+        print("[%s done]" % opts, flush=True)
+        res.append((loss, grad))
+        ctx.close()
+        del ctx
+        torch.cuda.empty_cache()
+    tol = 2e-7 * np.sqrt(L * n) * 4
+    assert (res[0][0] - res[1][0]).abs().max().item() <= tol and (res[0][1] - res[1][1]).abs().max().item() <= tol
