@@ -1454,7 +1454,8 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
                      (ctx->opt_split >= 0 ? ctx->opt_split == 1 : (uint64_t)B * state_bytes >= kSplitBytes);
     const int sets = two ? 2 : 1;
     const int64_t half = std::min(most, two ? (B + 1) / 2 : B);
-    if (ar.remaining() < fixed + (size_t)sets * half * sample_bytes(1)) return QSV_OK;     // without planning for it
+    // without planning for it: a deep circuit's plan takes longer than the call (20 qubits, 1024 layers of a ring 2.9 s)
+    if (ar.remaining() < fixed + (size_t)sets * half * sample_bytes((size_t)fewest_passes(c, n, tile))) return QSV_OK;
     CachedPlan *fp = nullptr, *bp = nullptr;
     qsv_status st = find_plan(ctx, c, B, 0, 0, &fp, defer, kSweep);
     if (st == QSV_OK) st = find_plan(ctx, c, B, 1, 0, &bp, defer, kSweep);

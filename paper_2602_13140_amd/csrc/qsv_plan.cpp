@@ -668,6 +668,12 @@ Plan mirror_plan(const Plan& f) {
     return p;
 }
 
+int fewest_passes(const qsv_circuit& c, int n, int tile) {
+    if (n <= tile) return 1;
+    const int ahead = c.entangler == QSV_ENT_CNOT_RING ? 2 : c.entangler == QSV_ENT_CZ_LADDER ? tile : c.n_layers + 1;
+    return std::max(1, (c.n_layers + ahead - 1) / ahead);
+}
+
 void group_by_passes(Plan* p) {
     p->groups.clear();
     int32_t at = 0;

@@ -121,6 +121,11 @@ Plan build_plan(const qsv_circuit& c, int n, int64_t batch, bool inverse, int ti
 // layers: 31 passes planned directly against 21 forwards; 26 qubits, 30 layers: 52 against 50).
 Plan mirror_plan(const Plan& forward);
 
+// A number of passes that no plan of the circuit has fewer of.  With qubits outside the tile, a pass takes those no further.
+// The ring closes in every layer, so all others get at most two layers ahead of them: L / 2.  The ladder's light cone
+// grows by a qubit a layer: at most as many layers as the tile has bits.
+int fewest_passes(const qsv_circuit& c, int n, int tile);
+
 // Groups (see Plan::groups) that end with their pass, so that the states between the passes lack no scalars (a reverse-mode
 // sweep keeps them), and that round no matrix (whose columns then differ in length by about 3e-8, which shows where states
 // of different plans are combined).  It costs 64 vector instructions a wavefront and pass, beside about twenty unitaries of 60.

@@ -2,6 +2,8 @@
 interpreter that follows the documented meaning of each operation, must reproduce the oracle's
 circuit.  This checks the lowering, the commutation rules and the tile/run bookkeeping before any
 kernel runs."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -399,3 +401,21 @@ def test_default_tile_never_costs_a_pass(n):
             assert got <= p12, (L, batch)
             if n >= 26:
                 assert got <= p13, (L, batch)
+
+
+@pytest.mark.parametrize("ent,flag", [(RING, DEFER), (RING, 0), (LADDER, 0), (NONE, 0)])
+def test_no_plan_has_fewer_passes_than_the_reverse_mode_sweep_expects(ent, flag):
+    """The bound by which a circuit whose states cannot fit the workspace is not planned at all."""
+    fewest = qb.load()["_ZN3qsv13fewest_passesERK11qsv_circuitii"]
+    grows = 0
+    for n in (10, 11, 13, 14, 16, 19, 20, 23):
+        for tile in (10, 12, 13):
+            for L in (1, 2, 3, 5, 8, 21):
+                if n < tile:
+                    continue
+                circ = qb.make_circuit(L, [RY, RZ], ent)
+                passes = sum(ln.startswith("P ") for ln in qb.qsv_plan_describe(circ, n, 1, 0, tile | flag).split("\n"))
+                bound = fewest(ctypes.byref(circ), n, tile)
+                assert 1 <= bound <= passes, (n, tile, L)
+                grows = max(grows, bound)
+    assert grows == {RING: 11, LADDER: 3, NONE: 1}[ent]
