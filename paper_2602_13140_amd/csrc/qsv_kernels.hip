@@ -3498,6 +3498,7 @@ hipError_t launch_build_shifted(const CircDev& c, const float* params, const flo
     const u64 two_p = 2ull * c.n_layers * c.slots() * c.n;
     const u64 count = (u64)(c.reupload ? samples : 1) * two_p;
     if (count == 0) return hipSuccess;
+    if (scale && !exec_of) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_build_shifted, dim3(blocks_for(count, 256)), dim3(256), 0, st, c, params, feats, count,
                        exec_of, scale, per, out);
     return hipGetLastError();
@@ -3512,6 +3513,8 @@ hipError_t launch_build_turns(const CircDev& c, const float* params, const float
     return hipGetLastError();
 }
 
+// ||x_b|| of every sample: inv_norm [samples] (0 for a zero vector), norm_out optional.  One launch
+// when a sample fits one block, else block partials and a finishing launch.
 hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* partial, int nblk,
                         double* inv_norm, float* norm_out, hipStream_t st) {
     const bool one = nblk == 1;
@@ -3526,6 +3529,7 @@ hipError_t launch_norms(const float* x, int64_t samples, int64_t dim, double* pa
 
 hipError_t launch_encode(const float* x, int64_t samples, int64_t dim, int n, double* partial, int nblk, double* inv_norm,
                          float* norm_out, float2* state, hipStream_t st) {
+    if (dim < 1 || dim > (int64_t)1 << n) return hipErrorInvalidValue;
     const dim3 grid = rows_grid(1, (u64)samples);
     switch (n) {
 #define QSV_ROW(THREADS, V) { hipLaunchKernelGGL((k_encode_row<THREADS, V>), grid, dim3(THREADS), 0, st, x, (u64)samples, (u64)dim, n, inv_norm, norm_out, state); return hipGetLastError(); }

@@ -1,11 +1,15 @@
 """Host arithmetic of launches (no GPU): what a workgroup of the one-launch kernel writes into LDS stays inside what its
 launch asks for; workgroups of a pass that goes downwards take every tile once."""
+import ctypes
 import os
 import shutil
 import subprocess
 
 import pytest
 
+from paper_2602_13140_amd import binding as qb
+
+HIP_ERROR_INVALID_VALUE = 1
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
@@ -93,3 +97,17 @@ def test_lds_of_the_one_launch_kernel_holds_all_it_writes(tmp_path):
 
 def test_a_pass_that_goes_downwards_takes_every_tile_once(tmp_path):
     run(tmp_path, ORDER)
+
+
+def test_launches_that_would_read_beyond_a_table_are_refused():
+    """A table of scalars is read through the execution order, and a sample has at most as many entries as its state.  The
+    arguments are looked at before anything is launched, so no device is needed to be refused."""
+    lib = qb.load()
+    circ = (ctypes.c_int * 7)(3, 1, 0, 1, 2, 0, 0)                # CircDev: 3 qubits, 1 layer, 1 rotation
+    some = ctypes.c_void_p(256)
+    shifted = lib["_ZN3qsv20launch_build_shiftedERKNS_7CircDevEPKfS4_lPKiPKdiPfP12ihipStream_t"]
+    assert shifted(circ, some, None, ctypes.c_long(1), None, some, 3, some, None) == HIP_ERROR_INVALID_VALUE
+    encode = lib["_ZN3qsv13launch_encodeEPKflliPdiS2_PfP15HIP_vector_typeIfLj2EEP12ihipStream_t"]
+    for n in (3, 8, 13, 16):
+        for dim in (0, (1 << n) + 1):
+            assert encode(some, ctypes.c_long(1), ctypes.c_long(dim), n, some, 1, some, None, some, None) == HIP_ERROR_INVALID_VALUE
