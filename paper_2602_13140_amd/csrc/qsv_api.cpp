@@ -1267,7 +1267,9 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
             if (st != QSV_OK) return st;
         }
         QSV_HIP(ctx, launch_expz_block(ck(L), B, n, zpart, ctx->stream), "expz block");
-        QSV_HIP(ctx, launch_expz_finish_scatter(zpart, B, n, obs_qubit, f, Scatter{0, 1, per, 2 * P}, ctx->stream),
+        const Residues through{res_one, 0, L * g_one, L * g_one};
+        QSV_HIP(ctx, launch_expz_finish_scatter(zpart, B, n, obs_qubit, f, Scatter{0, 1, per, 2 * P}, ctx->stream,
+                                                turns ? &through : nullptr, c->reupload),
                 "expz finish");
         if (ahead) {
             st = prepare_layers(ctx, *c, rot, B, 0, params_dev, feats_dev, B, mats, &all, unshifted, res_rot);

@@ -265,14 +265,15 @@ hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_
 // Where one-qubit results of gradient rows go: circuit gid = row0 + r lands at
 // out[(gid / per) * stride + offset + gid % per].
 struct Scatter { int64_t row0, per, stride, offset; };
-hipError_t launch_expz_finish_scatter(const double* partial, int64_t rows, int n, int q, double* out,
-                                      const Scatter& sc, hipStream_t st);
-// out[scatter(row)] = sum of the row's per_row partials written by a pass with zout
-hipError_t launch_zsum_finish(const double* partial, int64_t rows, int64_t per_row, double* out,
-                              const Scatter& sc, hipStream_t st);
 // What the scalars of a table's groups lack of the exact ones, as launch_build_mats writes it: the product of the entries
 // first .. first + count - 1 of a sample's `stride`.
 struct Residues { const double* table; int first, count, stride; };
+// res (NULL: none): of the tables that the rows, which are samples then, have come through; rowdep: a table per sample
+hipError_t launch_expz_finish_scatter(const double* partial, int64_t rows, int n, int q, double* out,
+                                      const Scatter& sc, hipStream_t st, const Residues* res = nullptr, int rowdep = 0);
+// out[scatter(row)] = sum of the row's per_row partials written by a pass with zout
+hipError_t launch_zsum_finish(const double* partial, int64_t rows, int64_t per_row, double* out,
+                              const Scatter& sc, hipStream_t st);
 // The two results of a turned row b from its three sums (PassArgs::unturned), <Z> of (a + b) / sqrt 2 and of (a - b) / sqrt 2, at
 // out[(gid / per) * stride + offset + 2 (gid % per)] and behind it; <Z> of a is out[(gid / per) * stride + unturned_at].
 // Without their scalars' rounding: what a has come through since the two parted is in ra, b's in rb1 and rb2; a phase of

@@ -1526,10 +1526,13 @@ __global__ __launch_bounds__(256) void k_expz_row(const float2* state, u64 rows,
 // sums; higher bits are constant inside a block, so they sign the block totals.
 // WHOLE: a workgroup per (row, qubit), four loads of a thread in flight.  From 1024 partials on, of which there are few sums
 // (a wavefront takes 32 of them one after the other, latencies that nothing covers): 24 qubits 9.9 -> 4.6 us.
-template <bool WHOLE>
+// SCALED: rows that have come through tables with groups, whose rounded scalars make a row longer or shorter by what res has of
+// its sample: that is divided out.  Left in, it makes every <Z> of a row wrong by the same 3e-8 a group (16
+// qubits x 16, 10 layers in two passes each, 60 seeds: losses 8.7e-7 from 64 bits, without it 8.5e-7).
+template <bool WHOLE, bool SCALED = false>
 __global__ __launch_bounds__(256) void k_expz_finish(const double* partial, u64 rows, int n, int g, int nblk,
                                                      int q_only, float* out_f, double* out_d,
-                                                     Scatter sc) {
+                                                     Scatter sc, Residues res, int rowdep) {
     __shared__ double sm[WHOLE ? 4 : 1];
     const int lane = WHOLE ? threadIdx.x : threadIdx.x & 63;
     const u64 job = WHOLE ? (u64)blockIdx.x : (u64)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1562,6 +1565,14 @@ __global__ __launch_bounds__(256) void k_expz_finish(const double* partial, u64 
             }
         }
         acc = wave_sum(acc);
+    }
+    if constexpr (SCALED) {
+        const double* e = res.table + ((rowdep ? row * (u64)res.stride : 0) + (u64)res.first) * 2;
+        double m = 1.0;
+        for (int k = (int)(threadIdx.x & 63u); k < res.count; k += 64) m *= e[2 * k] * e[2 * k] + e[2 * k + 1] * e[2 * k + 1];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) m *= __shfl_xor(m, d, 64);
+        acc /= m;
     }
     if (lane == 0) {
         u64 o = job;
@@ -3686,28 +3697,25 @@ hipError_t launch_expz_small(const float2* state, int64_t rows, int n, int q_onl
     }
     return launch_expz_row(state, rows, n, q_only, out_f, nullptr, st);
 }
-static hipError_t expz_finish(const double* partial, int64_t rows, int n, int g, u64 jobs, int q_only, float* out_f, double* out_d,
-                              const Scatter& sc, hipStream_t st) {
-    const int nblk = chunk_blocks(n) >> g;
-    if (nblk >= 1024 && jobs <= 4096)
-        hipLaunchKernelGGL((k_expz_finish<true>), dim3((unsigned)jobs), dim3(256), 0, st, partial, (u64)rows, n, g, nblk, q_only,
-                           out_f, out_d, sc);
-    else
-        hipLaunchKernelGGL((k_expz_finish<false>), dim3(blocks_for(jobs, 4)), dim3(256), 0, st, partial, (u64)rows, n, g, nblk,
-                           q_only, out_f, out_d, sc);
+static hipError_t expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f, double* out_d,
+                              const Scatter& sc, const Residues* res, int rowdep, hipStream_t st) {
+    const u64 jobs = (u64)rows * (q_only >= 0 ? 1 : n);
+    const int g = expz_group(n, rows), nblk = chunk_blocks(n) >> g;
+    const bool whole = nblk >= 1024 && jobs <= 4096;
+    const auto kernel = whole ? (res ? k_expz_finish<true, true> : k_expz_finish<true>)
+                              : (res ? k_expz_finish<false, true> : k_expz_finish<false>);
+    hipLaunchKernelGGL(kernel, dim3(whole ? (unsigned)jobs : blocks_for(jobs, 4)), dim3(256), 0, st, partial, (u64)rows, n, g, nblk,
+                       q_only, out_f, out_d, sc, res ? *res : Residues{nullptr, 0, 0, 0}, rowdep);
     return hipGetLastError();
 }
 hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,
                               double* out_d, hipStream_t st) {
-    const u64 jobs = (u64)rows * (q_only >= 0 ? 1 : n);
-    const int g = expz_group(n, rows);
-    return expz_finish(partial, rows, n, g, jobs, q_only, out_f, out_d, Scatter{0, 0, 0, 0}, st);
+    return expz_finish(partial, rows, n, q_only, out_f, out_d, Scatter{0, 0, 0, 0}, nullptr, 0, st);
 }
 hipError_t launch_expz_finish_scatter(const double* partial, int64_t rows, int n, int q, double* out,
-                                      const Scatter& sc, hipStream_t st) {
-    if (q < 0 || sc.per < 1) return hipErrorInvalidValue;
-    const int g = expz_group(n, rows);
-    return expz_finish(partial, rows, n, g, (u64)rows, q, nullptr, out, sc, st);
+                                      const Scatter& sc, hipStream_t st, const Residues* res, int rowdep) {
+    if (q < 0 || sc.per < 1 || (res && !res->table)) return hipErrorInvalidValue;
+    return expz_finish(partial, rows, n, q, nullptr, out, sc, res, rowdep, st);
 }
 hipError_t launch_zsum_finish(const double* partial, int64_t rows, int64_t per_row, double* out,
                               const Scatter& sc, hipStream_t st) {

@@ -1594,3 +1594,27 @@ def test_reverse_mode_of_plans_too_long_for_their_buffer():
         torch.cuda.empty_cache()
     tol = 2e-7 * np.sqrt(L * n) * 4
     assert (res[0][0] - res[1][0]).abs().max().item() <= tol and (res[0][1] - res[1][1]).abs().max().item() <= tol
+
+
+@pytest.mark.parametrize("n,B,L,opts", [(14, 4, 40, {}), (13, 12, 60, {}), (16, 3, 40, {"tile_log2": 10}), (22, 1, 8, {"tile_log2": 10})])
+def test_shift_rule_loss_without_the_rounding_of_its_scalars(n, B, L, opts):
+    """RY on all qubits but 0, no entangler, and no amplitude where bit 0 is set: <Z_0> = 1.  Every operation rounds an
+    amplitude up or down as it comes, which sums over 2^n of them lose, but the scalar that a group of unitaries shares makes
+    all of them longer or shorter, by 3e-8 a group: 1e-7 is less than what a dozen groups would leave, and two units of the result."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, (RY,), NONE, 0)
+    circ = qb.circuit_from_spec(spec)
+    P = spec.num_params(n)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((B, 1 << n), device="cuda", generator=gen)
+    x[:, 1::2] = 0.0
+    p = torch.rand((L, n), device="cuda", generator=gen) * 6.0
+    p[:, 0] = 0.0
+    ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
+    for k, v in opts.items():
+        ctx.qsv_set_option(k, v)
+    loss, grad = torch.zeros(B, device="cuda"), torch.zeros((B, P), device="cuda")
+    ctx.qsv_param_shift_grad(circ, x, p.reshape(-1), None, 0, loss, grad)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert (loss.double() - 1.0).abs().max().item() <= 1e-7, loss
