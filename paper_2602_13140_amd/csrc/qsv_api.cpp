@@ -30,11 +30,21 @@ constexpr size_t kOpsRegion = 4u << 20;  // persistent: uploaded pass programs
 constexpr uint64_t kNtStoreBytes = 384ull << 20;
 constexpr uint64_t kSplitBytes = 32ull << 20;    // see run_circuit
 // Amplitudes of a layer's gradient rows (B slots n 2^n) from which one circuit per parameter is run instead of two (see
-// qsv_param_shift_grad): reading the unshifted states at the end of the last pass takes 2 to 3 us, and up to 13 qubits, where a
-// row is one or two tiles, little else is saved.  Measured, two / one: 12 qubits x 7, 2 layers 75.8 / 82.2 us (2^19.4), 13 x 4
-// 79.4 / 87.6 (2^19.7), 12 x 14 82.5 / 82.8 (2^20.4), 11 x 30 81.5 / 79.2 (2^20.4), 13 x 8 92.2 / 89.8 (2^20.7), 14 x 2 116.6 /
-// 110.3 (2^19.8), 16 x 1 187.5 / 135.9 (2^21), 16 x 256, 10 layers 98.4 / 52.7 ms (2^29).
-constexpr uint64_t turn_amplitudes(int n) { return n <= 13 ? 1ull << 20 : 1ull << 19; }
+// qsv_param_shift_grad).  Its tables, and reading the unshifted states at the end of the last pass, take some 4 us a layer; up to 13
+// qubits, where a row is one or two tiles, little else than rows is saved, and of a single layer least.  Measured in turn, two / one:
+//   10 qubits  1 layer x 118 55.4 / 56.4 us (2^21.2); 2 x 63 74.6 / 76.8 (2^20.3), x 78 78.4 / 77.4 (2^20.6); 5 x 126 167 / 176
+//              (2^20.3), x 52 206 / 194 (2^20.6)
+//   11         1 x 29 49.4 / 50.4 (2^20.9), x 53 47.9 / 48.1 (2^21.2); 2 x 29 75.0 / 77.6 (2^20.3), x 71 82.2 / 81.4 (2^20.6);
+//              5 x 23 162 / 178 (2^20.0), x 19 198 / 195 (2^20.3)
+//   12         1 x 32 46.4 / 47.2 (2^20.6), x 16 54.5 / 54.3 (2^21.2); 2 x 13 81.1 / 83.2 (2^20.3), x 32 82.1 / 81.4 (2^20.6)
+//   13         1 x 6 56.4 / 57.6 (2^20.9); 2 x 8 78.9 / 83.8 (2^19.7), x 5 90.9 / 88.8 (2^20.0); 5 x 4 240 / 256 (2^19.7)
+//   14         1 x 1 60.6 / 62.8 (2^19.4), x 2 60.8 / 61.1 (2^19.8); 2 x 2 102.3 / 104.8 (2^18.8), x 1 126.6 / 121.5 (2^19.4)
+//   15         1 x 1 65.6 / 64.2 (2^19.9); 16 x 256, 10 layers 98.4 / 52.7 ms (2^29).
+constexpr uint64_t turn_amplitudes(int n, int layers) {
+    const int single = n <= 14 && layers == 1 ? 1 : 0;
+    if (n <= 12) return n == 10 || layers <= 2 ? 3ull << (19 + single) : 5ull << 18;
+    return 1ull << ((n == 13 ? 20 : 19) + single);
+}
 // ... and from which the layer's rotations are applied to the start states first: that is one more pass or two over the
 // batch for every layer.  Measured without / with: 15 x 4, 5 layers 502 / 549 us (2^21.9), 16 x 4, 6 layers 680 / 742 (2^23),
 // 14 x 64, 4 layers 1141 / 1137 (2^24.8), 16 x 16, 6 layers 1662 / 1579 (2^25), 12 x 1024, 4 layers 3019 / 2587 (2^27), 16 x 256,
@@ -1203,7 +1213,7 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
         rot.entangler = QSV_ENT_NONE;
         // the tile of gradient rows does not depend on their number from 10 qubits on
         bool turns = !ctx->opt_naive && n >= kMinTile && is_direct(ctx, tile_of(ctx, B, 1, 0)) &&
-                     ((uint64_t)(B * slots_n) << n) >= turn_amplitudes(n);
+                     ((uint64_t)(B * slots_n) << n) >= turn_amplitudes(n, L);
         // A unitary with a turned angle is a turn times the unturned one, so the circuits of layer l also share that layer's
         // rotations: the states go through them once per sample, and a circuit starts with one matrix on one qubit instead of n
         // unitaries.  See kAheadAmplitudes for where that pays.

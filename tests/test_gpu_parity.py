@@ -1476,14 +1476,15 @@ def test_reverse_mode_sweep_in_a_graph():
     (1, 13, 158, 2, (RX,), LADDER, 1, {}),
     (1, 14, 74, 2, (RY, RX), RING, 0, {"tile_log2": 10}),       # several passes, halves on two streams
     (1, 14, 37, 1, (RZ, RX, RY), NONE, 1, {}),                  # nothing but turns is left of the circuit
-    (0, 10, 60, 3, (RY, RZ), RING, 0, {}),
-    (0, 11, 18, 9, (RX, RY, RZ), LADDER, 1, {}),                 # 99 unitaries: two groups in a pass
-    (0, 12, 13, 2, (RZ, RX), RING, 0, {"grad_chunk_rows": 7}),
+    (0, 10, 120, 3, (RY, RZ), RING, 0, {}),
+    (0, 11, 36, 9, (RX, RY, RZ), LADDER, 1, {}),                 # 99 unitaries: two groups in a pass
+    (0, 12, 26, 2, (RZ, RX), RING, 0, {"grad_chunk_rows": 7}),
     (0, 14, 3, 3, (RY,), LADDER, 1, {"tile_log2": 11, "split_streams": 1}),
     (0, 16, 2, 2, (RX, RZ), RING, 0, {}),
 ])
 def test_shift_rule_from_one_circuit_per_parameter(oracle, ahead, n, B, L, rot, ent, reup, opts):
-    """Batches large enough for one circuit per parameter (2^20 amplitudes a layer, 2^19 from 14 qubits on), and for starting behind its layer's
+    """Batches large enough for one circuit per parameter (2^20.3 to 2^20.6 amplitudes a layer up to 12 qubits, 2^20 at 13, 2^19 from 14 on,
+    a single layer twice that), and for starting behind its layer's
     rotations (ahead: 2^25): against whole circuits, two per parameter, and against the oracle on the first sample.  A
     difference of two expectation values, each with the rounding of L (slots) n gates."""
     torch = gu.torch_cuda()
@@ -1492,7 +1493,7 @@ def test_shift_rule_from_one_circuit_per_parameter(oracle, ahead, n, B, L, rot, 
     P = spec.num_params(n)
     x, p, f = (a.astype(np.float32) for a in (g.standard_normal((B, 1 << n)), g.uniform(0, 2 * np.pi, P), g.standard_normal((B, n))))
     circ = qb.circuit_from_spec(spec)
-    assert ((P // L * B) << n >= 1 << 25) == bool(ahead) and (P // L * B) << n >= 1 << 19
+    assert ((P // L * B) << n >= 1 << 25) == bool(ahead) and (P // L * B) << n >= 1 << max(19, min(21, 33 - n))
     ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
     for k, v in opts.items():
         ctx.qsv_set_option(k, v)
