@@ -1413,20 +1413,23 @@ struct Fork {
 struct Objective { int kind, q; uint64_t mask; const float* targets; };
 
 // The losses of rows 0 .. rows - 1 of A (samples sample0 + row) into f[sample][2P]; kind 2 also the coefficients of lambda.
+// res, rowdep: see launch_expz_finish; of row 0's sample on.
 static qsv_status losses(qsv_ctx* ctx, const Objective& ob, const float2* A, int64_t rows, int64_t sample0, int64_t P,
-                         double* zpart, double* zall, double* coef, double* f) {
+                         double* zpart, double* zall, double* coef, double* f, const Residues* res = nullptr,
+                         int rowdep = 0) {
     const int n = ctx->n;
     if (ob.kind == 1) {
-        QSV_HIP(ctx, launch_trash_loss(A, n, ob.mask, rows, sample0, P, zpart, f, ctx->stream), "trash loss");
+        QSV_HIP(ctx, launch_trash_loss(A, n, ob.mask, rows, sample0, P, zpart, f, ctx->stream, res, rowdep), "trash loss");
         return QSV_OK;
     }
     QSV_HIP(ctx, launch_expz_block(A, rows, n, zpart, ctx->stream), "expz block");
     if (ob.kind == 0) {
-        QSV_HIP(ctx, launch_expz_finish_scatter(zpart, rows, n, ob.q, f, Scatter{sample0, 1, 2 * P + 1, 2 * P}, ctx->stream),
+        QSV_HIP(ctx, launch_expz_finish_scatter(zpart, rows, n, ob.q, f, Scatter{sample0, 1, 2 * P + 1, 2 * P}, ctx->stream,
+                                                res, rowdep),
                 "expz finish");
         return QSV_OK;
     }
-    QSV_HIP(ctx, launch_expz_finish(zpart, rows, n, -1, nullptr, zall, ctx->stream), "expz finish");
+    QSV_HIP(ctx, launch_expz_finish(zpart, rows, n, -1, nullptr, zall, ctx->stream, res, rowdep), "expz finish");
     QSV_HIP(ctx, launch_mse_coef(zall, ob.targets, n, rows, sample0, P, coef, f, ctx->stream), "mse loss");
     return QSV_OK;
 }
@@ -1459,7 +1462,8 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
     };
     // a table: the unitaries and at most as many groups' scalars, and one entry that is only prefetched
     const size_t table_bytes = 2 * mats_table_bytes(c, n, B), corr_bytes = mat_scale_bytes(to_dev(c, n), B);
-    const size_t fixed = 2 * table_bytes + corr_bytes + 16 * kAlign;
+    // (a group's residue for every unitary at most)
+    const size_t fixed = 2 * table_bytes + 2 * corr_bytes + 16 * kAlign;
     // Two halves on two streams pay as in run_circuit: 20 qubits x 32, 20 layers 8.66 -> 8.24 ms, 16 x 256 1.25 -> 1.17, 22 x 2,
     // 6 layers 0.98 -> 0.88; 18 x 4 296 -> 312 us, 16 x 16 357 -> 374, 13 x 37 163 -> 210, 11 x 64 135 -> 168.
     const bool two = B >= 2 && !ctx->forked &&
@@ -1488,6 +1492,7 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
     float* fmats = (float*)ar.take(table_bytes);
     float* bmats = (float*)ar.take(table_bytes);
     double* corr = (double*)ar.take(corr_bytes);
+    double* residues = (double*)ar.take(corr_bytes);
     struct Scratch { float2* psi; float* sums; double *zpart, *zall, *coef; } scr[2];
     for (int i = 0; i < sets; ++i) {
         scr[i].psi = (float2*)ar.take((passes + 1) * (size_t)chunk * state_bytes);
@@ -1506,7 +1511,7 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
                 "build matrices");
         return QSV_OK;
     };
-    st = table(fp, 0, MatForm::direct, fmats, nullptr);
+    st = table(fp, 0, MatForm::direct, fmats, residues);
     if (st == QSV_OK) st = table(bp, 1, MatForm::paired, bmats, corr);
     if (st != QSV_OK) return st;
 
@@ -1544,7 +1549,8 @@ static qsv_status fused_sweep(qsv_ctx* ctx, const qsv_circuit& c, const Objectiv
             warm(&a, low, (uint64_t)rows << (n - tile));
             QSV_HIP(ctx, launch_pass(tile, 1, a, (uint64_t)rows << (n - tile), ctx->stream), "fused pass");
         }
-        qsv_status s = losses(ctx, ob, state(passes), rows, b0, P, sc.zpart, sc.zall, sc.coef, f);
+        const Residues through{residues + (c.reupload ? (size_t)b0 * groups * 2 : 0), 0, groups, groups};
+        qsv_status s = losses(ctx, ob, state(passes), rows, b0, P, sc.zpart, sc.zall, sc.coef, f, &through, c.reupload);
         if (s != QSV_OK) return s;
         // backwards: lambda changes between the encoded states' buffer and the last states', whose pass comes first
         const float2* lam = nullptr;

@@ -260,15 +260,15 @@ hipError_t launch_expz_block(const float2* state, int64_t rows, int n, double* p
 // <Z_q> of every qubit (q_only < 0) or of q_only in one launch, where a row is a block's work
 bool expz_in_one_launch(int n, int64_t rows);
 hipError_t launch_expz_small(const float2* state, int64_t rows, int n, int q_only, float* out_f, hipStream_t st);
-hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,
-                              double* out_d, hipStream_t st);
-// Where one-qubit results of gradient rows go: circuit gid = row0 + r lands at
-// out[(gid / per) * stride + offset + gid % per].
-struct Scatter { int64_t row0, per, stride, offset; };
 // What the scalars of a table's groups lack of the exact ones, as launch_build_mats writes it: the product of the entries
 // first .. first + count - 1 of a sample's `stride`.
 struct Residues { const double* table; int first, count, stride; };
 // res (NULL: none): of the tables that the rows, which are samples then, have come through; rowdep: a table per sample
+hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,
+                              double* out_d, hipStream_t st, const Residues* res = nullptr, int rowdep = 0);
+// Where one-qubit results of gradient rows go: circuit gid = row0 + r lands at
+// out[(gid / per) * stride + offset + gid % per].
+struct Scatter { int64_t row0, per, stride, offset; };
 hipError_t launch_expz_finish_scatter(const double* partial, int64_t rows, int n, int q, double* out,
                                       const Scatter& sc, hipStream_t st, const Residues* res = nullptr, int rowdep = 0);
 // out[scatter(row)] = sum of the row's per_row partials written by a pass with zout
@@ -328,7 +328,7 @@ hipError_t launch_pauli(const float2* state, int64_t rows, int n, uint64_t xmask
 hipError_t launch_adj_init(const float2* A, int n, int kind, int q, uint64_t mask, const double* coef,
                            int64_t rows, float2* S, int paired, hipStream_t st);
 hipError_t launch_trash_loss(const float2* A, int n, uint64_t mask, int64_t rows, int64_t sample0, int64_t P,
-                             double* partial, double* f, hipStream_t st);
+                             double* partial, double* f, hipStream_t st, const Residues* res = nullptr, int rowdep = 0);
 hipError_t launch_mse_coef(const double* z, const float* y, int n, int64_t rows, int64_t sample0, int64_t P,
                            double* coef, double* f, hipStream_t st);
 // optimiser steps in double on float storage; t is the 1-based step count of Adam

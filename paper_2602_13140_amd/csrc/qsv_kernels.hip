@@ -1522,13 +1522,19 @@ __global__ __launch_bounds__(256) void k_expz_row(const float2* state, u64 rows,
     }
 }
 
+// The first of a sample's entries.
+__device__ __forceinline__ const double* residues_of(const Residues& res, int rowdep, u64 sample) {
+    return res.table + ((rowdep ? sample * (u64)res.stride : 0) + (u64)res.first) * 2;
+}
+
 // One wavefront per (row, qubit): combine block partials.  Bits up to 12 + g - 1 use the blocks' signed
 // sums; higher bits are constant inside a block, so they sign the block totals.
 // WHOLE: a workgroup per (row, qubit), four loads of a thread in flight.  From 1024 partials on, of which there are few sums
 // (a wavefront takes 32 of them one after the other, latencies that nothing covers): 24 qubits 9.9 -> 4.6 us.
 // SCALED: rows that have come through tables with groups, whose rounded scalars make a row longer or shorter by what res has of
-// its sample: that is divided out.  Left in, it makes every <Z> of a row wrong by the same 3e-8 a group (16
-// qubits x 16, 10 layers in two passes each, 60 seeds: losses 8.7e-7 from 64 bits, without it 8.5e-7).
+// its sample: that is divided out.  Left in, it makes every <Z> of a row wrong by the same 3e-8 a group (shift rule, 16
+// qubits x 16, 10 layers in two passes each, 60 seeds: losses 8.7e-7 from 64 bits, without it 8.5e-7; reverse mode,
+// forty shapes, 16 seeds: trash losses 1.03 times as far as layer by layer with it, 0.69 times without, losses of <Z> 1.01 and 1.00).
 template <bool WHOLE, bool SCALED = false>
 __global__ __launch_bounds__(256) void k_expz_finish(const double* partial, u64 rows, int n, int g, int nblk,
                                                      int q_only, float* out_f, double* out_d,
@@ -1567,7 +1573,7 @@ __global__ __launch_bounds__(256) void k_expz_finish(const double* partial, u64 
         acc = wave_sum(acc);
     }
     if constexpr (SCALED) {
-        const double* e = res.table + ((rowdep ? row * (u64)res.stride : 0) + (u64)res.first) * 2;
+        const double* e = residues_of(res, rowdep, row);
         double m = 1.0;
         for (int k = (int)(threadIdx.x & 63u); k < res.count; k += 64) m *= e[2 * k] * e[2 * k] + e[2 * k + 1] * e[2 * k + 1];
 #pragma unroll
@@ -1613,7 +1619,7 @@ __global__ __launch_bounds__(256) void k_turned_finish(const double* partial, u6
     // conj(a) b of the exact states is c / d, d = conj(ra) rb: a lane multiplies every 64th entry
     Cx d = {1.0, 0.0};
     auto take = [&](const Residues& res, double sign) {
-        const double* e = res.table + ((t.rowdep ? sample * (u64)res.stride : 0) + (u64)res.first) * 2;
+        const double* e = residues_of(res, t.rowdep, sample);
         for (int k = (int)(threadIdx.x & 63u); k < res.count; k += 64) d = mul_c(d, {e[2 * k], sign * e[2 * k + 1]});
     };
     take(t.ra, -1.0);
@@ -2115,12 +2121,20 @@ __global__ __launch_bounds__(256) void k_p0_block(const float2* A, u64 rows, int
     if (threadIdx.x == 0) partial[r * nblk + blockIdx.x] = t;
 }
 
+// SCALED: see k_expz_finish.
+template <bool SCALED>
 __global__ __launch_bounds__(256) void k_trash_loss(const double* partial, int nblk, u64 rows, u64 sample0,
-                                                    u64 P, double* f) {
+                                                    u64 P, double* f, Residues res, int rowdep) {
     const u64 r = (u64)blockIdx.x * 256 + threadIdx.x;
     if (r >= rows) return;
     double acc = 0.0;
     for (int b = 0; b < nblk; ++b) acc += partial[r * nblk + b];
+    if constexpr (SCALED) {
+        const double* e = residues_of(res, rowdep, r);
+        double m = 1.0;
+        for (int k = 0; k < res.count; ++k) m *= e[2 * k] * e[2 * k] + e[2 * k + 1] * e[2 * k + 1];
+        acc /= m;
+    }
     f[(sample0 + r) * (2 * P + 1) + 2 * P] = 1.0 - acc;
 }
 
@@ -3709,8 +3723,9 @@ static hipError_t expz_finish(const double* partial, int64_t rows, int n, int q_
     return hipGetLastError();
 }
 hipError_t launch_expz_finish(const double* partial, int64_t rows, int n, int q_only, float* out_f,
-                              double* out_d, hipStream_t st) {
-    return expz_finish(partial, rows, n, q_only, out_f, out_d, Scatter{0, 0, 0, 0}, nullptr, 0, st);
+                              double* out_d, hipStream_t st, const Residues* res, int rowdep) {
+    if (res && !res->table) return hipErrorInvalidValue;
+    return expz_finish(partial, rows, n, q_only, out_f, out_d, Scatter{0, 0, 0, 0}, res, rowdep, st);
 }
 hipError_t launch_expz_finish_scatter(const double* partial, int64_t rows, int n, int q, double* out,
                                       const Scatter& sc, hipStream_t st, const Residues* res, int rowdep) {
@@ -3845,14 +3860,14 @@ hipError_t launch_adj_init(const float2* A, int n, int kind, int q, uint64_t mas
 }
 
 hipError_t launch_trash_loss(const float2* A, int n, uint64_t mask, int64_t rows, int64_t sample0, int64_t P,
-                             double* partial, double* f, hipStream_t st) {
-    if (rows < 1) return hipErrorInvalidValue;
+                             double* partial, double* f, hipStream_t st, const Residues* res, int rowdep) {
+    if (rows < 1 || (res && !res->table)) return hipErrorInvalidValue;
     const int nblk = chunk_blocks(n);
     hipLaunchKernelGGL(k_p0_block, rows_grid(nblk, (u64)rows), dim3(256), 0, st, A, (u64)rows, n, (u64)mask, nblk, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_trash_loss, dim3(blocks_for((u64)rows, 256)), dim3(256), 0, st, partial, nblk,
-                       (u64)rows, (u64)sample0, (u64)P, f);
+    hipLaunchKernelGGL(res ? k_trash_loss<true> : k_trash_loss<false>, dim3(blocks_for((u64)rows, 256)), dim3(256), 0, st, partial,
+                       nblk, (u64)rows, (u64)sample0, (u64)P, f, res ? *res : Residues{nullptr, 0, 0, 0}, rowdep);
     return hipGetLastError();
 }
 

@@ -1619,3 +1619,46 @@ def test_shift_rule_loss_without_the_rounding_of_its_scalars(n, B, L, opts):
     torch.cuda.synchronize()
     ctx.close()
     assert (loss.double() - 1.0).abs().max().item() <= 1e-7, loss
+
+
+@pytest.mark.parametrize("n,B,L,opts", [(14, 4, 40, {}), (13, 12, 60, {"grad_chunk_rows": 5}), (16, 3, 40, {"tile_log2": 10}), (20, 1, 20, {})])
+@pytest.mark.parametrize("reup", [0, 1])
+def test_reverse_mode_losses_without_the_rounding_of_their_scalars(n, B, L, opts, reup):
+    """The states of the test above in reverse mode: <Z_0> = 1, no weight where bit 0 is set, and a squared error of
+    (1 + sum of the other qubits' <Z>^2) / n against targets of 0, whose relative error is twice that of <Z_0>.  One rotation a
+    unitary: with two, it has phases, whose lengths are rounded numbers too."""
+    torch = gu.torch_cuda()
+    spec = wl.CircuitSpec(L, () if reup else (RY,), NONE, reup)
+    circ = qb.circuit_from_spec(spec)
+    P = spec.num_params(n)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((B, 1 << n), device="cuda", generator=gen)
+    x[:, 1::2] = 0.0
+    f = torch.randn((B, n), device="cuda", generator=gen)
+    p = torch.rand((L, n), device="cuda", generator=gen) * 6.0
+    p[:, 0] = 0.0
+    p = p.reshape(-1)
+    ctx = gu.make_ctx(n, B, ws_bytes=qb.qsv_grad_workspace_bytes(n, B, circ))
+    for k, v in opts.items():
+        ctx.qsv_set_option(k, v)
+    loss, grad, z = torch.zeros(B, device="cuda"), torch.zeros((B, P), device="cuda"), torch.zeros((B, n), device="cuda")
+    feats = f if reup else None
+    got = []
+    for objective in ("z", "trash", "mse"):
+        if objective == "z":
+            ctx.qsv_adjoint_grad(circ, x, p, feats, 0, loss, grad)
+        elif objective == "trash":
+            ctx.qsv_loss_grad(circ, x, p, feats, qb.QSV_LOSS_TRASH, loss, grad, mask=1)
+        else:
+            ctx.qsv_loss_grad(circ, x, p, feats, qb.QSV_LOSS_MSE_Z, loss, grad, targets=torch.zeros((B, n), device="cuda"))
+        torch.cuda.synchronize()
+        got.append(loss.double().clone())
+    ctx.qsv_amp_encode(x)
+    ctx.qsv_apply_layers(circ, p, feats, 0)
+    ctx.qsv_measure(qb.QSV_M_EXPZ_ALL, z)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert (got[0] - 1.0).abs().max().item() <= 1e-7, got[0]
+    assert got[1].abs().max().item() <= 1e-7, got[1]
+    want = (1.0 + z[:, 1:].double().square().sum(1)) / n
+    assert (got[2] / want - 1.0).abs().max().item() <= 2e-7, got[2] / want
