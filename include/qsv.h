@@ -217,7 +217,7 @@ qsv_status qsv_pauli_expect(qsv_ctx* ctx, uint64_t xmask, uint64_t ymask, uint64
  * When the workspace has room for n_layers + 1 states per sample (qsv_grad_workspace_bytes), the
  * unshifted circuit's state before every layer is kept and a circuit that shifts a parameter of
  * layer l runs layers l..L-1 only, from that state: the same values with about half the gate
- * applications (option grad_layered = 0 switches this off).  From 10 qubits on, unless the batch is tiny, the two
+ * applications (option grad_layered = 0 switches this off).  From 10 qubits on, unless the batch is small, the two
  * shifted states of a parameter are then formed from one run instead of two, with the angle turned by
  * pi: R(t +- pi/2) = (R(t) +- R(t + pi)) / sqrt 2, so they are (unshifted +- turned) / sqrt 2, and both expectation values are
  * taken of them; larger batches start such runs behind the layer's rotations. */
@@ -235,8 +235,8 @@ qsv_status qsv_param_shift_grad(qsv_ctx* ctx, const qsv_circuit* c, const float*
  * read off the 2x2 sums  M_q[a][b] = sum_rest conj(lambda[a, rest]) psi[b, rest].
  * Work: about 3 L layers and L n reductions per sample instead of 2 P circuits.  Uses the workspace (at
  * least three states per sample of a chunk; with room for the states between the passes of the circuit, which
- * qsv_grad_workspace_bytes mostly has, the way back reads them and takes the sums as it goes, in a third to two thirds of the
- * time); the context's state buffer is left untouched. */
+ * qsv_grad_workspace_bytes nearly always has up to 20 qubits and beyond for few samples of few layers, the way back reads them
+ * and takes the sums as it goes, in a third to two thirds of the time); the context's state buffer is left untouched. */
 qsv_status qsv_adjoint_grad(qsv_ctx* ctx, const qsv_circuit* c, const float* x_dev, int64_t dim,
                             const float* params_dev, const float* feats_dev, int32_t obs_qubit,
                             float* loss_dev, float* grad_dev, float* mean_loss_dev,
